@@ -233,6 +233,16 @@ template <typename HT>
 void launch_decode_attention_h16(const HT *qkv, HT *kcache, HT *vcache, HT *o, const int32_t *t_dev, int B, int T, int H,
                                  bool frag, hipStream_t s);
 
+// The float32 counterparts (decode_f32.hip), everything row-major.  Projection C[M,N] = epi(LN?(A)[M,K] * Wm[K,N] + bias),
+// K % 16 == 0; with g != nullptr the rows of A are normalised first (gain g, shift be; skinny_f32_ln_ok(K)).
+bool skinny_f32_ln_ok(int K);
+void launch_skinny_f32(const float *A, const float *g, const float *be, const float *Wm, const float *bias,
+                       const float *resid, float *C, int M, int N, int K, Epi epi, hipStream_t s);
+// qkv [B, 3W], caches [B, T, W], o [B, W], position *t_dev; decode_attention_f32_ok(dh)
+bool decode_attention_f32_ok(int dh);
+void launch_decode_attention_f32(const float *qkv, float *kcache, float *vcache, float *o, const int32_t *t_dev, int B, int T,
+                                 int H, int dh, hipStream_t s);
+
 // Step boundary of the sequential inverse: x_{t+1} from the head row of position t (eq. 5), its
 // embedding into h, and t <- t+1 (device counter).  first != 0: x_0 = z_0, embedding of position 0, t <- 0.
 void launch_decode_advance(const float *p, const float *z, float *x, const float *w_in, const float *b_in,

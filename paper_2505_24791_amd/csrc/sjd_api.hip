@@ -512,9 +512,12 @@ int run_jacobi(sjd_flow *f, int j, const float *z, float *x, int batch, const sj
     return SJD_OK;
 }
 
-// ---- sequential fast path (16-bit modes, head size 64) ------------------------------------------
+// ---- sequential fast path (16-bit modes with head size 64; float32) ------------------------------
 bool fast_decode_ok(const sjd_flow *f) {
     return f->cfg.dtype != SJD_DTYPE_F32 && f->cfg.width / f->cfg.n_heads == 64 && f->cfg.max_batch <= 256;
+}
+bool fast_decode_f32_ok(const sjd_flow *f) {
+    return f->cfg.dtype == SJD_DTYPE_F32 && f->cfg.width % 16 == 0 && decode_attention_f32_ok(f->cfg.width / f->cfg.n_heads);
 }
 // Fragment-major operands: a width the fused LayerNorm projection covers.
 bool frag_ok(const sjd_flow *f, int batch) {
@@ -577,8 +580,47 @@ void fast_step(sjd_flow *f, int j, const float *z, float *x, int B, bool frag, h
     }
 }
 
+// The same step in float32 (decode_f32.hip): LayerNorm inside the projections where the width is covered.
+void fast_step_f32(sjd_flow *f, int j, const float *z, float *x, int B, hipStream_t s) {
+    const sjd_config &c = f->cfg;
+    const int T = c.seq_len, W = c.width, D = c.token_dim, H = c.n_heads, RW = c.mlp_ratio * c.width;
+    const int rev = (c.reverse_mask >> j) & 1;
+    const BlockW &bw = f->block[j];
+    float *a = (float *)f->a, *qkv = (float *)f->qkv, *o = (float *)f->o, *ff = (float *)f->f;
+    const bool ln_in = skinny_f32_ln_ok(W);
+    auto bytes = [&](int N, int K, double outs) { return 4.0 * ((double)K * N + (double)B * K + outs * B * N); };
+    auto ln_project = [&](int fam, const float *g, const float *be, const float *w, const float *bias, float *out, int N, Epi epi) {
+        ProfScope ps(f, fam, 2.0 * B * (double)N * W, bytes(N, W, 1), s);
+        if (!ln_in) launch_layernorm<float>(f->h, g, be, a, B, W, s);
+        launch_skinny_f32(ln_in ? f->h : a, ln_in ? g : nullptr, be, w, bias, nullptr, out, B, N, W, epi, s);
+    };
+    auto resid_project = [&](const float *in, const float *w, const float *bias, int K) {
+        ProfScope ps(f, SJD_PROF_DECODE_RESID, 2.0 * B * (double)K * W, bytes(W, K, 2), s);
+        launch_skinny_f32(in, nullptr, nullptr, w, bias, f->h, f->h, B, W, K, EPI_BIAS_RESIDUAL, s);
+    };
+    for (int l = 0; l < c.n_layers; ++l) {
+        const LayerW &lw = bw.layer[l];
+        const size_t layer_off = (size_t)l * c.max_batch * T * W;
+        ln_project(SJD_PROF_DECODE_GEMM, lw.ln1_g, lw.ln1_b, lw.w_qkv, lw.b_qkv, qkv, 3 * W, EPI_BIAS);
+        {
+            ProfScope ps(f, SJD_PROF_DECODE_ATTN, 4.0 * B * (T / 2.0) * W, 4.0 * B * (2.0 * (T / 2.0) * W + 4.0 * W), s);
+            launch_decode_attention_f32(qkv, (float *)f->kcache + layer_off, (float *)f->vcache + layer_off, o, f->t_dev, B, T,
+                                        H, W / H, s);
+        }
+        resid_project(o, lw.w_o, lw.b_o, W);
+        ln_project(SJD_PROF_DECODE_FC1, lw.ln2_g, lw.ln2_b, lw.w_fc1, lw.b_fc1, ff, RW, EPI_BIAS_GELU);
+        resid_project(ff, lw.w_fc2, lw.b_fc2, RW);
+    }
+    ln_project(SJD_PROF_DECODE_HEAD, bw.lnf_g, bw.lnf_b, bw.w_head, bw.b_head, f->p, 2 * D, EPI_BIAS);
+    {
+        ProfScope ps(f, SJD_PROF_EPILOGUE, 0.0, (double)B * (D * 16.0 + W * 4.0), s);
+        launch_decode_advance(f->p, z, x, bw.w_in, bw.b_in, bw.pos, f->h, f->t_dev, f->ticket, B, T, D, W, rev, 0, false, s);
+    }
+}
+
 void fast_step_any(sjd_flow *f, int j, const float *z, float *x, int B, bool frag, hipStream_t s) {
-    if (f->cfg.dtype == SJD_DTYPE_BF16) fast_step<bf16>(f, j, z, x, B, frag, s);
+    if (f->cfg.dtype == SJD_DTYPE_F32) fast_step_f32(f, j, z, x, B, s);
+    else if (f->cfg.dtype == SJD_DTYPE_BF16) fast_step<bf16>(f, j, z, x, B, frag, s);
     else fast_step<f16>(f, j, z, x, B, frag, s);
 }
 
@@ -695,7 +737,7 @@ int run_sequential(sjd_flow *f, int j, const float *z, float *x, int batch, hipS
             if (rc != SJD_ELAUNCH_RETRY) return rc;
             if (f->seq_path != 0) return SJD_EHIP;      // the persistent kernel was asked for explicitly
         }
-        if (fast_decode_ok(f)) return run_sequential_fast(f, j, z, x, batch, s);
+        if (fast_decode_ok(f) || fast_decode_f32_ok(f)) return run_sequential_fast(f, j, z, x, batch, s);
     }
     launch_decode_epilogue(f->p, z, x, batch, T, D, -1, rev, s);  // x_1 = y_1
     for (int t = 0; t + 1 < T; ++t) decode_step(f, j, z, x, batch, t, s);

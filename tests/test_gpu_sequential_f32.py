@@ -1,0 +1,43 @@
+"""Single-token steps of float32 flows against the CPU oracle: every width whose LayerNorm is part of a projection and
+one whose is not, every head size of the attention kernel, row counts around the 16-row blocks, head columns that no
+tile divides.  Needs an MI355X.  Tolerance: 1e-4 on the block's output (the float32 bound of this build)."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # width, heads, layers, tokens, token size, batch
+    (64, 2, 2, 12, 3, 6),          # LayerNorm as a launch of its own
+    (128, 4, 2, 49, 16, 1),
+    (128, 8, 1, 35, 5, 17),        # head size 16, second row block with one row
+    (256, 4, 2, 70, 7, 16),
+    (512, 4, 1, 20, 12, 33),       # head size 128
+    (768, 12, 1, 9, 11, 40),
+    (1024, 16, 1, 7, 48, 3),
+    (48, 4, 1, 10, 4, 5),          # head size 12: the plain path
+]
+
+
+@pytest.mark.parametrize("W,H,N,T,D,B", CASES, ids=[f"w{c[0]}_dh{c[0] // c[1]}_b{c[5]}" for c in CASES])
+def test_float32_steps_match_oracle(orc32, W, H, N, T, D, B):
+    import torch
+    import paper_2505_24791_amd as sjd
+    cfg = wl.FlowConfig("seq_f32", n_blocks=2, n_layers=N, width=W, n_heads=H, seq_len=T, token_dim=D, batch=B, bf16=False)
+    print(cfg, flush=True)
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    z = wl.make_latent(cfg, seed=17)
+    zd = torch.from_numpy(z).cuda()
+    f = sjd.Flow(cfg)
+    f.load_weights(blob)
+    for j in range(2):                                     # block 1 works on the reversed token order
+        x = f.sequential_inverse_block(j, zd)
+        assert torch.equal(f.sequential_inverse_block(j, zd), x)
+        one = f.sequential_inverse_block(j, zd[-1:].contiguous())       # a row does not depend on the rows beside it
+        assert torch.equal(one[0], x[-1])
+        pick = sorted({0, B // 2, B - 1})
+        ref = np.stack([orc32.sequential_inverse_block(cfg, blob, j, z[b]) for b in pick])
+        assert np.abs(x.cpu().numpy()[pick] - ref).max() <= 1e-4
+    f.close()
