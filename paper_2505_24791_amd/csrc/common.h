@@ -148,8 +148,8 @@ void launch_embed(const float *x, const float *w_in, const float *b_in, const fl
 template <typename OutT>
 void launch_layernorm(const float *x, const float *g, const float *b, OutT *y, int n_rows, int W, hipStream_t s);
 
-// float32 projection: C[M,N] = epi(A[M,K] * B[K,N] + bias)
-void launch_gemm_f32(const float *A, const float *B, const float *bias, const float *resid, float *C, int M, int N,
+// float32 projection: C[M,N] = epi(A[M,K] * B[K,N] + bias), rows of B ldb floats apart; A and B 16-byte aligned
+void launch_gemm_f32(const float *A, const float *B, int ldb, const float *bias, const float *resid, float *C, int M, int N,
                      int K, Epi epi, hipStream_t s);
 
 // 16-bit MFMA projection (HT = bf16 or f16): C[M,N] = epi(A[M,K] * Bt[N,K]^T + bias); Bt holds the

@@ -46,6 +46,7 @@ struct LayerW {
 };
 struct BlockW {
     const float *w_in, *b_in, *pos, *lnf_g, *lnf_b, *w_head, *b_head;
+    const float *w_head4;        // w_head with rows padded to a multiple of four floats (w_head itself where they are)
     void *t_head, *f_head;
     std::vector<LayerW> layer;
 };
@@ -62,7 +63,8 @@ struct sjd_flow {
     bool loaded = false;
     size_t bytes = 0;
     std::vector<void *> allocs;
-    float *blob = nullptr;       // whole float32 blob on the device
+    float *blob = nullptr;       // whole float32 blob on the device, every block starting on a 256-byte boundary
+    float *head4 = nullptr;      // padded head matrices (token sizes that are odd)
     void *arena = nullptr;       // transposed 16-bit matrices
     void *arena_frag = nullptr;  // the same matrices in fragment-major order (sequential fast path)
     void *arena_panel = nullptr; // QKV, attention-output and MLP-input matrices in the panel kernels' order
@@ -121,6 +123,10 @@ size_t block_floats(const sjd_config &c) {
     size_t per_layer = 2 * W + W * 3 * W + 3 * W + W * W + W + 2 * W + W * R * W + R * W + R * W * W + W;
     return D * W + W + T * W + N * per_layer + 2 * W + W * 2 * D + 2 * D;
 }
+
+// floats per block as it lies on the device: tensors of a block then start on 16-byte boundaries (widths are multiples of 4)
+size_t block_stride(const sjd_config &c) { return round_up(block_floats(c), 64); }
+int head_ld(const sjd_config &c) { return (int)round_up(2 * (size_t)c.token_dim, 4); }
 
 constexpr size_t kNPad = 256;  // transposed weights are padded to this many rows per matrix
 
@@ -243,14 +249,14 @@ void project16(const void *A, const void *wt, const float *bias, void *C, int M,
 
 // in: A [M, K]; out: C [M, N]; residual variant accumulates into the float32 stream h in place.
 void project(sjd_flow *f, int fam, const void *A, const float *w32, const void *wt, const float *bias, void *C, int M,
-             int N, int K, Epi epi, bool out_f32, hipStream_t s) {
+             int N, int K, Epi epi, bool out_f32, hipStream_t s, int ldb = 0) {
     const int dt = f->cfg.dtype;
     const double in_b = dt == SJD_DTYPE_F32 ? 4.0 : 2.0, out_b = (dt != SJD_DTYPE_F32 && !out_f32) ? 2.0 : 4.0;
     double bytes = (double)M * K * in_b + (double)K * N * in_b + (double)M * N * out_b + (double)N * 4;
     if (epi == EPI_BIAS_RESIDUAL) bytes += (double)M * N * 4;
     ProfScope ps(f, fam, 2.0 * M * (double)N * K, bytes, s);
     if (dt == SJD_DTYPE_F32)
-        launch_gemm_f32((const float *)A, w32, bias, epi == EPI_BIAS_RESIDUAL ? (const float *)C : nullptr, (float *)C,
+        launch_gemm_f32((const float *)A, w32, ldb ? ldb : N, bias, epi == EPI_BIAS_RESIDUAL ? (const float *)C : nullptr, (float *)C,
                         M, N, K, epi, s);
     else if (dt == SJD_DTYPE_BF16) project16<bf16>(A, wt, bias, C, M, N, K, epi, out_f32, s);
     else project16<f16>(A, wt, bias, C, M, N, K, epi, out_f32, s);
@@ -352,7 +358,7 @@ void conditioner_pass(sjd_flow *f, int j, const float *x, int n, const int32_t *
         } else project(f, SJD_PROF_GEMM_RESID, f->f, lw.w_fc2, lw.t_fc2, lw.b_fc2, f->h, M, W, RW, EPI_BIAS_RESIDUAL, true, s);
     }
     layernorm(f, f->h, bw.lnf_g, bw.lnf_b, f->a, M, s);
-    project(f, SJD_PROF_GEMM_HEAD, f->a, bw.w_head, bw.t_head, bw.b_head, f->p, M, 2 * D, W, EPI_BIAS, true, s);
+    project(f, SJD_PROF_GEMM_HEAD, f->a, bw.w_head4, bw.t_head, bw.b_head, f->p, M, 2 * D, W, EPI_BIAS, true, s, head_ld(c));
 }
 
 // One single-token step of the sequential inverse: position t of every sample goes through all
@@ -384,7 +390,7 @@ void decode_step(sjd_flow *f, int j, const float *z, float *x, int B, int t, hip
         project(f, SJD_PROF_DECODE_GEMM, f->f, lw.w_fc2, lw.t_fc2, lw.b_fc2, f->h, B, W, RW, EPI_BIAS_RESIDUAL, true, s);
     }
     layernorm(f, f->h, bw.lnf_g, bw.lnf_b, f->a, B, s);
-    project(f, SJD_PROF_DECODE_GEMM, f->a, bw.w_head, bw.t_head, bw.b_head, f->p, B, 2 * D, W, EPI_BIAS, true, s);
+    project(f, SJD_PROF_DECODE_GEMM, f->a, bw.w_head4, bw.t_head, bw.b_head, f->p, B, 2 * D, W, EPI_BIAS, true, s, head_ld(c));
     {
         ProfScope ps(f, SJD_PROF_EPILOGUE, 0.0, (double)B * D * 16.0, s);
         launch_decode_epilogue(f->p, z, x, B, T, D, t, rev, s);
@@ -786,7 +792,8 @@ int sjd_flow_create(const sjd_config *cfg, sjd_flow **out) {
     const size_t M = B * T > 512 ? B * T : 512, ab = act_bytes(f);  // the single-token paths work on up to 8 x 32 rows; the persistent kernel keeps two copies of its residual stream
     int rc = SJD_OK;
     auto A = [&](void **p, size_t n) { if (rc == SJD_OK) rc = dev_alloc(f, p, n); };
-    A((void **)&f->blob, (size_t)c.n_blocks * block_floats(c) * sizeof(float));
+    A((void **)&f->blob, (size_t)c.n_blocks * block_stride(c) * sizeof(float));
+    if (c.token_dim % 2) A((void **)&f->head4, (size_t)c.n_blocks * W * head_ld(c) * sizeof(float));
     if (c.dtype != SJD_DTYPE_F32) A(&f->arena, (size_t)c.n_blocks * arena_elems_per_block(c) * 2);
     if (fast_decode_ok(f)) A(&f->arena_frag, (size_t)c.n_blocks * arena_elems_per_block(c) * 2);
     if (panel_ok(c)) A(&f->arena_panel, (size_t)c.n_blocks * c.n_layers * (3 * W + W + 2 * R * W) * W * 2);
@@ -853,7 +860,9 @@ int sjd_flow_load_weights(sjd_flow *f, const void *host_blob, size_t nbytes) {
     const size_t bf = block_floats(c);
     const size_t want = (size_t)c.n_blocks * bf * sizeof(float);
     if (nbytes != want) return fail(SJD_EINVAL, "weight blob has %zu bytes, the configuration implies %zu", nbytes, want);
-    HIP_TRY(hipMemcpy(f->blob, host_blob, nbytes, hipMemcpyHostToDevice));
+    for (int j = 0; j < c.n_blocks; ++j)
+        HIP_TRY(hipMemcpy(f->blob + (size_t)j * block_stride(c), (const float *)host_blob + (size_t)j * bf, bf * sizeof(float),
+                          hipMemcpyHostToDevice));
     const size_t D = c.token_dim, W = c.width, T = c.seq_len, R = c.mlp_ratio;
     const int dt = c.dtype;
     f->block.assign(c.n_blocks, BlockW());
@@ -887,7 +896,7 @@ int sjd_flow_load_weights(sjd_flow *f, const void *host_blob, size_t nbytes) {
         return dst;
     };
     for (int j = 0; j < c.n_blocks; ++j) {
-        const float *p = f->blob + (size_t)j * bf;
+        const float *p = f->blob + (size_t)j * block_stride(c);
         BlockW &bw = f->block[j];
         bw.w_in = p; p += D * W;
         bw.b_in = p; p += W;
@@ -929,6 +938,13 @@ int sjd_flow_load_weights(sjd_flow *f, const void *host_blob, size_t nbytes) {
         bw.lnf_b = p; p += W;
         bw.w_head = p; p += W * 2 * D;
         bw.b_head = p;
+        bw.w_head4 = bw.w_head;
+        if (f->head4) {
+            float *h4 = f->head4 + (size_t)j * W * head_ld(c);
+            HIP_TRY(hipMemcpy2D(h4, (size_t)head_ld(c) * sizeof(float), bw.w_head, 2 * D * sizeof(float), 2 * D * sizeof(float), W,
+                                hipMemcpyDeviceToDevice));
+            bw.w_head4 = h4;
+        }
         bw.t_head = prep(bw.w_head, W, 2 * D);
         bw.f_head = prep_frag(bw.w_head, W, 2 * D);
     }

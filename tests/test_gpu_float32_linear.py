@@ -1,0 +1,43 @@
+"""Float32 projections of whole-sequence passes through the conditioner, against the CPU oracle: row counts that give
+every tile size of the matrix kernel and its edges, token sizes that pad the head matrix, a width off the matrix kernel.
+Needs an MI355X.  Tolerance: 1e-4 (the float32 bound of this build; values are of order 0.1 to 1)."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # width, heads, tokens, token size, batch: rows 1, 63, 65, 1000, 8192, 9000
+    (128, 4, 1, 3, 1),
+    (128, 4, 63, 5, 1),
+    (256, 4, 13, 16, 5),
+    (64, 2, 100, 7, 10),
+    (128, 2, 256, 12, 32),
+    (512, 8, 250, 33, 36),
+    (72, 2, 50, 4, 3),             # 72 = 8 mod 16: the plain kernel
+]
+
+
+@pytest.mark.parametrize("W,H,T,D,B", CASES, ids=[f"w{c[0]}_rows{c[2] * c[4]}_d{c[3]}" for c in CASES])
+def test_float32_conditioner_matches_oracle(orc32, W, H, T, D, B):
+    import torch
+    import paper_2505_24791_amd as sjd
+    cfg = wl.FlowConfig("lin_f32", n_blocks=2, n_layers=1, width=W, n_heads=H, seq_len=T, token_dim=D, batch=B, bf16=False)
+    print(cfg, flush=True)
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    x = wl.make_latent(cfg, seed=23)
+    f = sjd.Flow(cfg)
+    f.load_weights(blob)
+    for j in range(2):
+        mu, al = f.conditioner(j, torch.from_numpy(x).cuda())
+        one_mu, one_al = f.conditioner(j, torch.from_numpy(x[-1:].copy()).cuda())     # same bits in any tile size
+        assert torch.equal(one_mu[0], mu[-1]) and torch.equal(one_al[0], al[-1])
+        for b in sorted({0, B // 2, B - 1}):
+            rmu, ral = orc32.cond(cfg, blob, j, x[b][::-1] if j else x[b])             # the oracle works in processing order
+            if j:
+                rmu, ral = rmu[::-1], ral[::-1]
+            assert np.abs(mu[b].cpu().numpy() - rmu).max() <= 1e-4
+            assert np.abs(al[b].cpu().numpy() - ral).max() <= 1e-4
+    f.close()
