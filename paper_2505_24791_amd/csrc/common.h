@@ -163,7 +163,7 @@ void launch_gemm_h16(const HT *A, const HT *Bt, const float *bias, const float *
                      Epi epi, hipStream_t s, int kernel = 0);
 
 // Persistent eight-wave projection (gemm_p8.hip): the same contract as launch_gemm_h16 (resid, when given, is C
-// itself: the float32 stream is updated in place) for K % 128 == 0 and N % 256 == 0; bit-identical to the tile kernels.
+// itself: the float32 stream is updated in place) for K % 64 == 0, K >= 128 and N % 256 == 0; bit-identical to the tile kernels.
 bool gemm_p8_applicable(int M, int N, int K);
 template <typename HT, typename OutT>
 void launch_gemm_p8(const HT *A, const HT *Bt, const float *bias, OutT *C, int M, int N, int K, Epi epi, hipStream_t s);

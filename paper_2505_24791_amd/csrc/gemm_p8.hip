@@ -3,22 +3,28 @@
 // The tile kernels of gemm_h16.hip run one tile per workgroup: every tile pays its first loads and the
 // drain of its epilogue's stores in full, because the next workgroup cannot start on the CU before this
 // one has gone (128 KB of LDS each).  Here one workgroup per CU stays resident and walks over its tiles:
-//   * 256 x 256 output tile; k-tiles of 32 in four 32 KB LDS stages filled by LDS-direct loads
-//     (no staging registers), requested three k-tiles ahead;
+//   * 256 x 256 output tile; k-tiles of 64, so that a row's piece of a k-tile is a whole 128-byte cache line: with
+//     k-tiles of 32 every line was asked of L2 twice, half a line at a time (34 M requests per launch at M = 32768,
+//     N = 1024, K = 4096 against 17 M now, for the same bytes), and L2 requests were what the kernel waited for;
+//   * one operand of one k-tile is a unit of 32 KB; five units form a ring in LDS, filled by LDS-direct loads
+//     (no staging registers): while k-tile t is multiplied (two units), k-tile t + 1 and the A operand of
+//     t + 2 land, so a load has one to two k-tiles to arrive and the requests are spread over the k-tile;
 //   * eight waves, two per SIMD, each owning 128 x 64 of the tile (128 accumulator registers);
-//   * the request stream runs on across tiles: the first three k-tiles of the NEXT tile are requested during
+//   * the request stream runs on across tiles: the first k-tiles of the NEXT tile are requested during
 //     the last ones of this tile and the first has landed before the epilogue starts, so a tile begins with
 //     operands already in LDS;
-//   * the epilogue parks accumulators in LDS of its own (32 KB beyond the stages), so the stages keep
+//   * the epilogue parks accumulators in the one unit that is free at that time, so the others keep
 //     filling meanwhile, and its stores drain while the next tile multiplies.
 // k is walked in index order with the 32x32x16 instruction, an output row depends on its own row of A
 // only: results are bit-identical to the tile kernels and independent of the batch.
-// Covers K % 128 == 0 and N % 256 == 0 (every projection of the workloads but the head).
-// What bounds it (timing probes on M = 32768, N = 1024, K = 4096; 1.05 PFLOP/s as is): the same loop
-// without its global loads runs at 1.49 PFLOP/s, with loads that land in registers instead of LDS at 1.13,
-// without its LDS fragment reads (loads kept) at 1.00, without the barrier at 1.05; k-tiles of 64 in two
-// stages, one wave per SIMD, or padded row strides change nothing.  It is the operand traffic from L2
-// (64 KB per CU per 8.4 MFLOP, about 8 TB/s in all) that costs the difference, not latency, LDS or the barrier.
+// Covers K % 64 == 0, K >= 128 and N % 256 == 0 (every projection of the workloads but the head).
+// Measured (us per launch, k-tiles of 32 in four stages -> this; IEEE half, bias / GELU / float32 residual epilogue):
+//   32768 x 3072 x 1024 bias 197 -> 178, 32768 x 4096 x 1024 GELU 300 -> 278, 32768 x 1024 x 1024 residual 101 -> 85,
+//   32768 x 1024 x 4096 residual 281 -> 246, 65536 x 768 x 3072 residual 337 -> 297.
+// What bounds it: power.  The matrix pipe is busy 71 % of the cycles of the K = 4096 launch at a clock of 1.55 GHz; a
+// loop of nothing but these instructions on random operands runs at 1.64 GHz (1.72 PFLOP/s).  Taking out the waits
+// and the barrier gains 4 %, and four waves of 128 x 128 (a third fewer LDS reads) take as long with more idle cycles
+// at a higher clock.
 #include "common.h"
 #include <atomic>
 
@@ -28,11 +34,10 @@ namespace {
 
 constexpr int Q_BM = 256, Q_BN = 256;
 constexpr int Q_CB = 4;                     // column tiles per column block of the tile order
-constexpr int D_BK = 32, D_KSUB = D_BK / 16, D_NS = 4;   // k-tile, k-steps per k-tile, LDS stages
-constexpr int D_OPB = 16 * 1024;            // bytes of one operand in one stage: 256 rows x 64 B
-constexpr int D_STB = 2 * D_OPB;            // bytes per stage
-constexpr int D_PARK = D_NS * D_STB;        // offset of the epilogue parking space: 8 waves x 16 rows x 64 floats
-constexpr int D_LDS = D_PARK + 8 * 4096;    // 160 KB
+constexpr int D_BK = 64, D_KSUB = D_BK / 16;  // k-tile, k-steps per k-tile
+constexpr int D_UNITS = 5;                  // units of the LDS ring
+constexpr int D_OPB = 32 * 1024;            // bytes of a unit: one operand of one k-tile, 256 rows x 128 B
+constexpr int D_LDS = D_UNITS * D_OPB;      // 160 KB
 constexpr int kOutside = 0x7FFFFFF0;        // a lane offset past any buffer range this kernel declares
 
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
@@ -81,36 +86,36 @@ __global__ __launch_bounds__(512) void gemm_h16_p8_kernel(const HT *__restrict__
     const int wm = wave >> 2, wn = wave & 3;                     // this wave's 128 x 64 part of the tile
     const int KT = K / D_BK;
 
-    // Loads.  A stage holds a k-tile of 32: rows of 64 bytes (four 16-byte chunks), A then B, 16 KB each.  Per
-    // k-tile a wave brings the 16-row blocks 2 wave + i (i = 0, 1) of A and of B, 1 KB each: lane 4 r + c delivers
-    // the chunk that belongs in slot c of row r.  Row r of a 32-row fragment group keeps chunk c in slot
-    // c ^ swz(r), swz(r) = bits 2 and 4 of r: a 16-byte LDS read of a wave is served in four passes of 16 lanes
-    // (rows {0-7, 16-23} or {8-15, 24-31} of the group, one chunk) over 64 banks; with rows 64 bytes apart the
-    // bank group of a read is 4 (r mod 4) + slot, which this makes distinct over the sixteen rows of a pass.
+    // Loads.  A unit holds 256 rows of 128 bytes (eight 16-byte chunks).  Per unit a wave brings the 8-row blocks
+    // 4 wave + q (q = 0..3), 1 KB each: lane 8 r + c delivers the chunk that belongs in slot c of row r.  Row r of
+    // a 32-row fragment group keeps chunk c in slot c ^ swz(r), swz(r) = bits 1, 2 and 4 of r: a 16-byte LDS read of
+    // a wave is served in four passes of 16 lanes (rows {0-7, 16-23} or {8-15, 24-31} of the group, one chunk) over
+    // 64 banks; with rows 128 bytes apart the bank group of a read is 8 (r mod 2) + slot, which this makes distinct
+    // over the sixteen rows of a pass.
     // Addresses are a wave-uniform 64-bit base (the tile's first row, advanced by the k-tile) plus a
     // per-lane 32-bit byte offset inside the tile: few registers, and no 32-bit overflow however large M is.
-    const int lr = lane >> 2;                                    // row within the 16-row block
-    const int lc0 = (lane & 3) ^ ((lr >> 2) & 1);                // chunk fetched for blocks with bit 4 of the row clear
+    const int lr = lane >> 3;                                    // row within the 8-row block
+    const int lc0 = (lane & 7) ^ ((lr >> 1) & 3);                // chunk fetched for blocks with bit 4 of the row clear
     const uint32_t row_bytes = (uint32_t)K * 2u;
-    struct Src { uint32_t a_off[2]; const char *a_base, *b_base; };
+    struct Src { uint32_t a_off[4]; const char *a_base, *b_base; };
     auto make_src = [&](int t) {
         Src s;
         const int tm = t / tiles_n, tn = t - tm * tiles_n;
         const int last = M - 1 - tm * Q_BM;                      // last valid row of this tile (tile-relative, >= 0)
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            int row = (wave * 2 + i) * 16 + lr;
+        for (int i = 0; i < 4; ++i) {
+            int row = (wave * 4 + i) * 8 + lr;
             row = row < last ? row : last;                       // rows past the end: re-read the last row, never stored
-            s.a_off[i] = (uint32_t)row * row_bytes + (uint32_t)((lc0 ^ (i << 1)) * 16);
+            s.a_off[i] = (uint32_t)row * row_bytes + (uint32_t)((lc0 ^ (((i >> 1) & 1) << 2)) * 16);
         }
         s.a_base = reinterpret_cast<const char *>(A + (size_t)tm * Q_BM * K);
         s.b_base = reinterpret_cast<const char *>(Bt + (size_t)tn * Q_BN * K);   // Bt rows are padded to the tile
         return s;
     };
-    uint32_t b_off[2];
+    uint32_t b_off[4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-        b_off[i] = (uint32_t)((wave * 2 + i) * 16 + lr) * row_bytes + (uint32_t)((lc0 ^ (i << 1)) * 16);
+    for (int i = 0; i < 4; ++i)
+        b_off[i] = (uint32_t)((wave * 4 + i) * 8 + lr) * row_bytes + (uint32_t)((lc0 ^ (((i >> 1) & 1) << 2)) * 16);
     // An LDS-direct load: 64 lanes x 16 bytes from (wave-uniform base) + (per-lane 32-bit offset) to 1 KB of LDS
     // at the wave-uniform byte address lds_addr (through M0).  Written out so that the address stays split
     // into a scalar base and a 32-bit lane offset (two registers per lane per load otherwise).  M0 is set
@@ -121,26 +126,26 @@ __global__ __launch_bounds__(512) void gemm_h16_p8_kernel(const HT *__restrict__
                      :: "s"(lds_addr), "v"(off), "s"(base) : "memory");
     };
     const uint32_t lds0 = (uint32_t)(uintptr_t)SJD_Q_LPTR(lds);
-    auto issue_load = [&](const Src &s, int kt, int stage, int q) {   // q = 0..3: this wave's four blocks
-        const uint32_t st = lds0 + (uint32_t)(stage * D_STB);
-        if (q < 2) dma(s.a_base + (size_t)kt * (D_BK * 2), s.a_off[q], st + (uint32_t)((wave * 2 + q) * 1024));
-        else dma(s.b_base + (size_t)kt * (D_BK * 2), b_off[q - 2], st + (uint32_t)(D_OPB + (wave * 2 + q - 2) * 1024));
+    auto issue_a = [&](const Src &s, int kt, int unit, int q) {
+        dma(s.a_base + (size_t)kt * (D_BK * 2), s.a_off[q], lds0 + (uint32_t)(unit * D_OPB + (wave * 4 + q) * 1024));
     };
-
-    // Fragments: row l32 of a 32-row group, chunk 2 ks + g, found in slot (2 ks + g) ^ swz(l32); rows are 64 B
+    auto issue_b = [&](const Src &s, int kt, int unit, int q) {
+        dma(s.b_base + (size_t)kt * (D_BK * 2), b_off[q], lds0 + (uint32_t)(unit * D_OPB + (wave * 4 + q) * 1024));
+    };
+    // Fragments: row l32 of a 32-row group, chunk 2 ks + g, found in slot (2 ks + g) ^ swz(l32); rows are 128 B
     // apart.  A fragments are refreshed in place right after their last use in a k-step, B fragments
     // (used by all four row groups) alternate between two sets.
-    const int swz = ((l32 >> 2) & 1) | (((l32 >> 4) & 1) << 1);
+    const int swz = ((l32 >> 1) & 3) | (((l32 >> 4) & 1) << 2);
     int fk[D_KSUB];
 #pragma unroll
-    for (int ks = 0; ks < D_KSUB; ++ks) fk[ks] = l32 * 64 + (((2 * ks + g) ^ swz) << 4);
-    const int a_lds = wm * (128 * 64), b_lds = D_OPB + wn * (64 * 64);
+    for (int ks = 0; ks < D_KSUB; ++ks) fk[ks] = l32 * 128 + (((2 * ks + g) ^ swz) << 4);
+    const int a_lds = wm * (128 * 128), b_lds = wn * (64 * 128);
     v8 fa[4], fb[2][2];
-    auto read_a = [&](int stage, int ks, int i) {
-        fa[i] = *reinterpret_cast<const v8 *>(lds + (stage * D_STB + a_lds + 32 * i * 64) + fk[ks]);
+    auto read_a = [&](int unit, int ks, int i) {
+        fa[i] = *reinterpret_cast<const v8 *>(lds + (unit * D_OPB + a_lds) + 32 * i * 128 + fk[ks]);
     };
-    auto read_b = [&](int stage, int ks, int buf, int j) {
-        fb[buf][j] = *reinterpret_cast<const v8 *>(lds + (stage * D_STB + b_lds + 32 * j * 64) + fk[ks]);
+    auto read_b = [&](int unit, int ks, int buf, int j) {
+        fb[buf][j] = *reinterpret_cast<const v8 *>(lds + (unit * D_OPB + b_lds) + 32 * j * 128 + fk[ks]);
     };
 
     f32x16 acc[4][2];
@@ -151,32 +156,35 @@ __global__ __launch_bounds__(512) void gemm_h16_p8_kernel(const HT *__restrict__
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    // One k-tile: 16 matrix instructions of this wave, each a slot with its LDS reads and loads pinned.
-    // `next` / `next_kt`: the k-tile requested during this one - three k-tiles ahead, into the stage that the
-    // previous k-tile used (released by the barrier that ended it).  After the second slot of the last k-step:
-    // wait until this wave's loads of the NEXT k-tile have landed (the eight younger ones, of the two k-tiles
-    // after it, may stay in flight: loads complete in order) and its LDS reads are done, then the barrier;
-    // the rest of the k-step reads the next k-tile's first fragments.
-    auto ktile = [&](int stage, const Src &next, int next_kt) {
+    // One k-tile t: 32 matrix instructions of this wave, each a slot with its LDS reads and loads pinned.  Its operands
+    // are units ra and ra + 1 (mod 5), those of t + 1 are ra + 2 and ra + 3.  The A operand of t + 2 (`next` / `next_kt`)
+    // goes to unit ra + 4 during the first two k-steps.  After the second slot of the last k-step, when all of this
+    // k-tile's fragments are in registers: wait until this wave's loads of k-tile t + 1 have landed (the four
+    // younger ones may stay in flight: loads complete in order), then the barrier; the rest of the k-step reads the
+    // next k-tile's first fragments and requests the B operand of t + 2 into unit ra.
+    auto up = [](int u, int d) { u += d; return u >= D_UNITS ? u - D_UNITS : u; };
+    auto ktile = [&](int ra, const Src &next, int next_kt) {
+        const int rb = up(ra, 1), ra1 = up(ra, 2), rb1 = up(ra, 3), ra2 = up(ra, 4);
 #pragma unroll
         for (int ks = 0; ks < D_KSUB; ++ks) {
             const int b = ks & 1;
             const bool last = ks + 1 == D_KSUB;
-            const int rs = last ? (stage + 1) % D_NS : stage, rk = last ? 0 : ks + 1;   // where the next k-step's fragments are
+            const int ua = last ? ra1 : ra, ub = last ? rb1 : rb, rk = last ? 0 : ks + 1;
 #pragma unroll
             for (int m = 0; m < 8; ++m) {
                 const int i = m >> 1, j = m & 1;
-                if (ks == 0 && j == 1) issue_load(next, next_kt, (stage + 3) % D_NS, i);
-                if (!last && m == 0) { read_b(rs, rk, b ^ 1, 0); read_b(rs, rk, b ^ 1, 1); }
+                if (!last && m == 0) { read_b(ub, rk, b ^ 1, 0); read_b(ub, rk, b ^ 1, 1); }
                 acc[i][j] = Half16<HT>::mfma(fa[i], fb[b][j], acc[i][j]);
                 __builtin_amdgcn_sched_barrier(0);
                 if (last && m == 1) {
-                    __builtin_amdgcn_s_waitcnt(0x0078);   // vmcnt(8) lgkmcnt(0)
+                    __builtin_amdgcn_s_waitcnt(0x0074);   // vmcnt(4) lgkmcnt(0)
                     __builtin_amdgcn_s_barrier();
-                    read_b(rs, rk, b ^ 1, 0);
-                    read_b(rs, rk, b ^ 1, 1);
+                    read_b(ub, rk, b ^ 1, 0);
+                    read_b(ub, rk, b ^ 1, 1);
                 }
-                if (j == 1) read_a(rs, rk, i);           // row group i is done for this k-step: fetch the next one's
+                if (last && m >= 2 && m < 6) issue_b(next, next_kt, ra, m - 2);
+                if (ks < 2 && (m == 2 || m == 6)) issue_a(next, next_kt, ra2, 2 * ks + (m >> 2));
+                if (j == 1) read_a(ua, rk, i);           // row group i is done for this k-step: fetch the next one's
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -184,17 +192,20 @@ __global__ __launch_bounds__(512) void gemm_h16_p8_kernel(const HT *__restrict__
 
     Src cur = make_src(tile);
 #pragma unroll
-    for (int t = 0; t < 3; ++t)
+    for (int t = 0; t < 2; ++t) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) issue_load(cur, t, t, q);
+        for (int q = 0; q < 4; ++q) issue_a(cur, t, 2 * t, q);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) issue_b(cur, t, 2 * t + 1, q);
+    }
     __builtin_amdgcn_s_waitcnt(0x0F78);       // vmcnt(8): the first k-tile has landed
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int i = 0; i < 4; ++i) read_a(0, 0, i);
-    read_b(0, 0, 0, 0);
-    read_b(0, 0, 0, 1);
+    read_b(1, 0, 0, 0);
+    read_b(1, 0, 0, 1);
+    int ra = 0;
 
-    float *ep = reinterpret_cast<float *>(lds + D_PARK) + wave * 1024;
     const int rl = lane >> 4, cl = (lane & 15) * 4;
 
     while (true) {
@@ -204,22 +215,22 @@ __global__ __launch_bounds__(512) void gemm_h16_p8_kernel(const HT *__restrict__
         // no next tile: request this tile's first k-tile again (in bounds, never used)
         const Src nxt = make_src(tile_next >= 0 ? tile_next : tile);
 
-        // four k-tiles per trip (stages 0..3); in the last trip the requests run over into the next tile's first
-        // three k-tiles - by selecting the source, not by branching: one straight-line loop body
-        for (int kt = 0; kt < KT; kt += 4) {
-            ktile(0, cur, kt + 3);
-            const bool wrap = kt + 4 >= KT;
+        for (int kt = 0; kt < KT; ++kt) {
+            // the last two k-tiles of a tile request the next tile's first two - by selecting the source, not by
+            // branching: one straight-line loop body
+            const bool wrap = kt + 2 >= KT;
             Src sel;
 #pragma unroll
-            for (int i = 0; i < 2; ++i) sel.a_off[i] = wrap ? nxt.a_off[i] : cur.a_off[i];
+            for (int i = 0; i < 4; ++i) sel.a_off[i] = wrap ? nxt.a_off[i] : cur.a_off[i];
             sel.a_base = wrap ? nxt.a_base : cur.a_base;
             sel.b_base = wrap ? nxt.b_base : cur.b_base;
-            const int k0 = wrap ? 0 : kt + 4;
-            ktile(1, sel, k0);
-            ktile(2, sel, k0 + 1);
-            ktile(3, sel, k0 + 2);
+            ktile(ra, sel, wrap ? kt + 2 - KT : kt + 2);
+            ra = up(ra, 2);
         }
-        // here: stage 0 holds the next tile's first k-tile (two more are on their way), fa / fb[0] its first fragments
+        // here: the next tile's first k-tile is in LDS, the second on its way, fa / fb[0] hold the first fragments.  The unit
+        // of this tile's last B operand stays free until the next tile's first k-tile refills it; each wave parks in the
+        // part of it that it refills itself.
+        float *ep = reinterpret_cast<float *>(lds + up(ra, 4) * D_OPB) + wave * 1024;
 
         // ---- epilogue.  In the accumulators a lane owns one column and sixteen rows of a 32x32 block
         // (register v: row 8 (v / 4) + 4 g + v % 4).  Sixteen rows x 64 columns at a time go through the
@@ -287,6 +298,7 @@ __global__ __launch_bounds__(512) void gemm_h16_p8_kernel(const HT *__restrict__
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave has read back what it parked
         if (tile_next < 0) break;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
@@ -316,7 +328,7 @@ int p8_cus() {
 }  // namespace
 
 bool gemm_p8_applicable(int M, int N, int K) {
-    return M >= 1 && N >= 256 && N % 256 == 0 && K >= 128 && K % 128 == 0 && (long long)N * 4 * 128 < (1ll << 31) &&
+    return M >= 1 && N >= 256 && N % 256 == 0 && K >= 128 && K % 64 == 0 && (long long)N * 4 * 128 < (1ll << 31) &&
            (long long)((M + 255) / 256) * (N / 256) < (1ll << 30);
 }
 

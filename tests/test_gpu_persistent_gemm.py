@@ -10,9 +10,9 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-# (M, N, K); N % 256 == 0, K % 128 == 0
+# (M, N, K); N % 256 == 0, K % 64 == 0
 SHAPES = [(256, 256, 128), (77, 256, 256), (700, 512, 384), (1300, 768, 1024), (16640, 1536, 512), (300, 1024, 4096),
-          (40000, 768, 256)]
+          (40000, 768, 256), (17000, 256, 192), (300, 512, 320)]
 
 
 @pytest.fixture(scope="module")
