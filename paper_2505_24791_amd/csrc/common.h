@@ -55,6 +55,13 @@ template <> struct Half16<bf16> {
         c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(p, p, 4, 5), one, c, false);
         return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(p, p, 6, 7), one, c, false);
     }
+    // the dot product of eight pairs, exact products summed in float32
+    static __device__ __forceinline__ float dot(v8 a, v8 b) {
+        float c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 0, 1), __builtin_shufflevector(b, b, 0, 1), 0.f, false);
+        c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 2, 3), __builtin_shufflevector(b, b, 2, 3), c, false);
+        c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 4, 5), __builtin_shufflevector(b, b, 4, 5), c, false);
+        return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(a, a, 6, 7), __builtin_shufflevector(b, b, 6, 7), c, false);
+    }
 };
 template <> struct Half16<f16> {
     typedef f16x4 v4;
@@ -69,6 +76,13 @@ template <> struct Half16<f16> {
         c = __builtin_amdgcn_fdot2(__builtin_shufflevector(p, p, 2, 3), one, c, false);
         c = __builtin_amdgcn_fdot2(__builtin_shufflevector(p, p, 4, 5), one, c, false);
         return __builtin_amdgcn_fdot2(__builtin_shufflevector(p, p, 6, 7), one, c, false);
+    }
+    // the dot product of eight pairs, exact products summed in float32
+    static __device__ __forceinline__ float dot(v8 a, v8 b) {
+        float c = __builtin_amdgcn_fdot2(__builtin_shufflevector(a, a, 0, 1), __builtin_shufflevector(b, b, 0, 1), 0.f, false);
+        c = __builtin_amdgcn_fdot2(__builtin_shufflevector(a, a, 2, 3), __builtin_shufflevector(b, b, 2, 3), c, false);
+        c = __builtin_amdgcn_fdot2(__builtin_shufflevector(a, a, 4, 5), __builtin_shufflevector(b, b, 4, 5), c, false);
+        return __builtin_amdgcn_fdot2(__builtin_shufflevector(a, a, 6, 7), __builtin_shufflevector(b, b, 6, 7), c, false);
     }
 };
 
@@ -298,16 +312,19 @@ struct SeqArgs {
     const float *w_in, *b_in, *pos;
     const float *z;
     float *x;
-    float *hs;             // float32 residual stream, fragment-major, 8 groups x 16*MB rows
-    void *qkv, *o, *ff;    // 16-bit activations, fragment-major, same rows
-    float *p;              // head output, row-major [rows, 2D]
+    void *ws;              // activations of a step, all buffers with their slots (see decode_persistent.hip)
     void *kcache, *vcache; // [layer][max_batch][T][W] 16-bit
     size_t kv_layer_stride;  // elements between layers
     int B, T, D, reversed;
-    int *sync;             // [0..7] members per XCD, [8] arrivals, [9] status, [64*(g+1)] barrier counter of XCD g
+    int xpg;               // XCDs per group (1, 2, 4 or 8)
+    int *sync;             // [0..7] members per XCD, [8] arrivals, [9] status
     int spin_max;
 };
-size_t seq_persistent_lds_bytes(int MB, int T, int D);
+// Bytes per (row, column of width W) of the workspace: stream 4 + 3 slots of float32, qkv, attention output and MLP hidden
+// (3 + 1 + 4 widths) 3 slots of 16 bits; rows for 8 groups of 16 MB.
+constexpr uint32_t kSeqWsBytesPerElem = 4 * 4 + 3 * 4 + 3 * 2 * (3 + 1 + 4);
+inline size_t seq_persistent_ws_bytes(int MB, int W) { return (size_t)8 * 16 * MB * W * kSeqWsBytesPerElem; }
+size_t seq_persistent_lds_bytes(int MB, int D);
 // One workgroup of 512 threads per CU (grid = number of CUs), as a cooperative launch or a plain one.  W = 256 S.
 hipError_t launch_seq_persistent(bool is_bf16, const SeqArgs &args, int MB, int S, int grid, bool cooperative,
                                  hipStream_t s);

@@ -1,29 +1,34 @@
 // Sequential inverse of one block (eq. 5 with the key/value cache of Sec. 3.5) as ONE persistent
 // kernel, for the 16-bit modes with head size 64.
 //
-// A step of the sequential inverse is a chain of ~5 N dependent skinny projections on a handful
-// of rows; launched one by one every link costs a kernel boundary (about 2 us) plus a cold start.
-// Here the chain runs inside one cooperative launch of one workgroup per CU.  The workgroups
-// that share an XCD (they share its L2) form a group; each group takes an equal share of the
-// samples and carries them through the whole block on its own, so groups never talk to each other
-// and the only synchronisation is a barrier among the ~32 workgroups of a group.  Inside a group
-// every projection is split by output columns over the members; what one member writes
-// (activations, a few KB per stage) the others read back through the shared L2:
-//   * the writer's stores are write-through; it waits for their acknowledgement (vmcnt) before it
-//     arrives at the barrier with a relaxed device-scope atomic add on the group's counter;
-//   * readers poll that counter with relaxed loads, then read the activations with loads that
-//     carry the sc1 scope bit, which never hit in the CU's own vector cache;
-//   * no L2 write-back or invalidate is needed, because writer and reader use the same L2.  (A
-//     barrier with release/acquire fences at device scope costs ~7 us for 32 members here, this
-//     one ~1 us.)
-// Weights are read-only and come through the normal cached path.  Every spin is bounded: if a
-// barrier does not complete within the spin limit the workgroup records an error and leaves, the
-// others of its group follow at their next barrier, and the host reports the failure.
+// A step of the sequential inverse is a chain of 5 N dependent skinny products on a handful of rows; launched
+// one by one every link costs a kernel boundary plus a cold start.  Here the chain runs inside one cooperative
+// launch of one workgroup per CU.  The workgroups of `xpg` neighbouring XCDs (1, 2, 4 or 8) form a group; each
+// group takes an equal share of the samples and carries them through the whole block on its own.  Inside a group
+// every product is split by output columns over the members, attention by (sample, head) pairs.
 //
-// The arithmetic per row is that of the step kernels in decode.hip: LayerNorm statistics in two
-// passes over a row held in registers, 16x16x32 MFMA with K split over the 8 waves of a
-// workgroup and partial sums added in wave order, float32 residual stream.  A row's result does
-// not depend on which group or member computes it.
+// What bounds it is the latency of a link: what one member writes all others need next.  There is no barrier: a
+// buffer is filled with a word that no result has (kEmpty, a NaN pattern) before it is used, and a reader simply
+// loads its operands again until no word of them is empty.  Every 32-bit word is its own flag, so the order in
+// which words arrive does not matter; stores and loads carry the sc1 scope bit (agent scope), which is coherent
+// between XCDs as well.  All-gather of 16 to 64 KB among 256 workgroups that way: 2.4 to 2.7 us, against a counter barrier
+// (0.9 to 2 us inside one XCD) followed by the loads (another 1 to 2 us); and as a group may span XCDs, few samples
+// still use the whole chip and the block's weights are read from memory once per group instead of once per XCD.
+//
+// Life of a buffer.  Results rotate through three slots (the residual stream after the MLP and the embedding: four).
+// A member that has written slot q of a buffer empties what it had written in slot q-1 (stream: q-2), and every
+// store is acknowledged before the member's next write.  That is safe because a member writes use q of a stage only
+// after the complete input of that use has arrived, which depends on every member that read use q-1 having finished
+// (all of a stage's outputs are needed by the next, and so on round the chain); and because a reader gets to use
+// q+2 (whose slot was emptied at q) only after it has seen, directly or through others, use q+1, which was written
+// after the emptying had been acknowledged.  The last stream of a step is read by every member (the head), which is
+// why the stream keeps one slot more: use q is written by the next step's MLP output at the earliest, when all
+// members have shown results that come after their head.  Every wait is bounded: after spin_max attempts a workgroup
+// records an error, stops waiting and leaves at the end of the step, so do the others in turn, and the host reports the failure.
+//
+// The arithmetic per row: LayerNorm statistics per slice of 1/8 of a row (mean, then centred sum of squares), slices
+// combined by the parallel formula for variances; 16x16x32 MFMA with K split over the 8 waves of a workgroup and partial sums
+// added in wave order; float32 residual stream.  A row's result does not depend on which group or member computes it.
 #include "common.h"
 
 namespace sjd {
@@ -32,49 +37,76 @@ namespace {
 
 constexpr int P_NW = 8;  // waves per workgroup
 constexpr int P_THREADS = 64 * P_NW;
-constexpr int P_CB = 4;  // 16-column blocks per round of a LayerNorm-fused projection
-constexpr int P_EB = 2;  // embedding column blocks of a member whose w_in slice is kept in LDS
+constexpr int P_EB = 2;  // embedding units of a member whose w_in slice is kept in LDS
+constexpr uint32_t kEmpty = 0xFFFFFFFFu;
+constexpr uint32_t kNowhere = 0xFFFFFFF0u;   // beyond every buffer: a load there returns zeros without any traffic
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 
 __device__ __forceinline__ rsrc_t make_rsrc(const void *p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
 }
-// 16-byte / 4-byte loads with the sc1 scope bit: served by L2, never by this CU's vector cache
-__device__ __forceinline__ i32x4 ld16_l2(rsrc_t rs, uint32_t byte_off) {
+// 16-byte loads with the sc1 scope bit: never served by this CU's vector cache
+__device__ __forceinline__ i32x4 ld16(rsrc_t rs, uint32_t byte_off) {
     return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, 16));
 }
 // the same for rows of the key/value cache, with the streaming hint on top: a row is read once per step and
 // the cache is far larger than any cache level, so it should not displace the weights, which every step reads again
-__device__ __forceinline__ i32x4 ld16_l2_stream(rsrc_t rs, uint32_t byte_off) {
+__device__ __forceinline__ i32x4 ld16_stream(rsrc_t rs, uint32_t byte_off) {
     return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, 16 | 2));
 }
-__device__ __forceinline__ float ld4_l2(rsrc_t rs, uint32_t byte_off) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, (int)byte_off, 0, 16));
+// `off` where the lane has something to read, else kNowhere: a select that the compiler must not turn into a branch with a
+// load (and a wait) on either side
+__device__ __forceinline__ uint32_t where(bool live, uint32_t off) {
+    uint32_t r = live ? off : kNowhere;
+    asm("" : "+v"(r));
+    return r;
 }
+// Sums over lanes without the LDS unit: within a row of sixteen lanes by DPP, across rows by the swap instructions.
+template <int CTRL> __device__ __forceinline__ float dpp(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float sum8(float x) {       // lanes that agree in bits 3..5
+    x += dpp<0xB1>(x);                                  // lane ^ 1
+    x += dpp<0x4E>(x);                                  // lane ^ 2
+    return x + dpp<0x141>(x);                           // mirrored within eight: the other half of them
+}
+__device__ __forceinline__ float sum_rows(float x) {   // lanes that agree in bits 0..3
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+__device__ __forceinline__ float max_rows(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+// A result must not look empty: the one NaN pattern becomes another NaN.
+__device__ __forceinline__ int flagged(float v) {
+    const uint32_t w = __float_as_uint(v);
+    return (int)(w == kEmpty ? 0x7FC00000u : w);
+}
+__device__ __forceinline__ int flagged(int two_halves) { return two_halves == -1 ? 0x7FFF7FFF : two_halves; }
+__device__ __forceinline__ void st16(rsrc_t rs, uint32_t byte_off, i32x4 v) { __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)byte_off, 0, 16); }
+__device__ __forceinline__ void st8(rsrc_t rs, uint32_t byte_off, i32x2 v) { __builtin_amdgcn_raw_buffer_store_b64(v, rs, (int)byte_off, 0, 16); }
+__device__ __forceinline__ void st4(rsrc_t rs, uint32_t byte_off, int v) { __builtin_amdgcn_raw_buffer_store_b32(v, rs, (int)byte_off, 0, 16); }
+
+typedef __attribute__((address_space(3))) int LdsInt;   // LDS, not the generic address space: no flat accesses
 
 struct Ctx {
     int tid, lane, wave, r, kg;
     int slot, n;        // this workgroup's index in its group, members of the group
     int rb0;            // first 16-row block of the group in the workspaces
     int row0, nrows;    // first sample of the group, samples of the group
-    int epoch;
-    int *cnt, *status;
+    int cw;             // columns of a unit of the residual projections (4, 8 or 16)
     int spin_max;
-#ifdef SJD_SEQ_TIMELINE
-    int *tl; int *tl_k; bool tl_on; long long tl_t0;   // tl_k: counter in LDS
-#endif
+    int *status;
+    LdsInt *bad;        // a wait of this workgroup gave up
 };
-
-// Development aid, compiled in only with -DSJD_SEQ_TIMELINE: member 0 of group 0 records the 100 MHz
-// clock at stage boundaries (and a few points inside stages) of one step into the tail of the
-// synchronisation words.
-#ifdef SJD_SEQ_TIMELINE
-#define SJD_TLC(cc_) do { if ((cc_).tl_on && (cc_).tid == 0) { const int k_ = (*(cc_).tl_k)++; if (k_ < 300) (cc_).tl[k_] = (int)(wall_clock64() - (cc_).tl_t0); } } while (0)
-#else
-#define SJD_TLC(c) do { } while (0)
-#endif
 
 // A copy of the per-thread indices that the optimiser cannot see through: addresses derived from it
 // are recomputed where they are used instead of being hoisted out of the step loop and kept in
@@ -89,74 +121,62 @@ __device__ __forceinline__ Ctx local_ctx(const Ctx &c) {
     return d;
 }
 
-// Barrier among the workgroups of one group (see the header).  Returns false after a time-out.
-__device__ __forceinline__ bool group_barrier(Ctx &c, volatile int *sh_ok) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's stores have been acknowledged by L2
-    __syncthreads();
-    ++c.epoch;
-    if (c.tid == 0) {
-        __hip_atomic_fetch_add(c.cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int target = c.epoch * c.n;
-        int it = 0, ok = 1;
-        while (__hip_atomic_load(c.cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            if (++it > c.spin_max) { ok = 0; break; }
-            __builtin_amdgcn_s_sleep(1);
+// Load N pieces of 16 bytes until no word of them is empty.  Afterwards everything this wave has stored or requested so
+// far is complete (the wait is free: the operands requested before the poll are needed next).  Reloading only the pieces that
+// were missing, or pausing between attempts, was slower or made no difference.
+template <int N, class OFF>
+__device__ __forceinline__ void poll16(const Ctx &c, rsrc_t rs, OFF off, i32x4 (&v)[N]) {
+    int it = 0;
+    while (true) {
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int u = 0; u < N; ++u) v[u] = ld16(rs, off(u));
+        uint32_t m = 0;
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            m = max(m, max(max((uint32_t)v[u].x, (uint32_t)v[u].y), max((uint32_t)v[u].z, (uint32_t)v[u].w)));
+        if (__builtin_amdgcn_ballot_w64(m == kEmpty) == 0) break;
+        if (++it > c.spin_max || ((it & 63) == 0 && *c.bad)) {   // after one wait of the workgroup gave up the others do not start
+            if (c.lane == 0) {
+                *c.bad = 1;
+                __hip_atomic_store(c.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            break;
         }
-        if (!ok) __hip_atomic_store(c.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        *sh_ok = ok;
     }
-    __syncthreads();
-    return *sh_ok != 0;
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
 }
 
-// Weight fragments of a stage, fetched ahead of the barrier that precedes the stage (weights do
-// not depend on what the other members are still computing).
-template <typename HT, int S> struct LnPre { typename Half16<HT>::v8 f[P_CB][S]; };
-template <typename HT, int S, int KMUL> struct ResPre { typename Half16<HT>::v8 f[KMUL * S]; };
-struct NoPrefetch { __device__ __forceinline__ void operator()() const {} };
-
-// first-round weights of a LayerNorm-fused projection: column blocks slot, slot+n, ... (clamped, so
-// that the loads are unconditional; blocks past the end are never used)
-template <typename HT, int S>
-__device__ __forceinline__ void ln_prefetch(const Ctx &c, const HT *__restrict__ Wt, int N, int cb0, LnPre<HT, S> &w) {
-    typedef typename Half16<HT>::v8 v8;
-    constexpr int KS = 8 * S;
-    const int nbt = (N + 15) >> 4;
-#pragma unroll
-    for (int cc = 0; cc < P_CB; ++cc) {
-        int cb = cb0 + cc * c.n;
-        cb = cb < nbt ? cb : nbt - 1;
-#pragma unroll
-        for (int s = 0; s < S; ++s)
-            w.f[cc][s] = *reinterpret_cast<const v8 *>(Wt + (((size_t)cb * KS + c.wave * S + s) * 64 + c.lane) * 8);
-    }
-}
-
-// C[:, cols of this member] = epi(LayerNorm(Hs) * Wt^T + bias) for the group's 16*MB workspace rows,
-// K = W = 256 S.  Hs float32 fragment-major (read through L2), Wt fragment-major, C fragment-major
-// when 16-bit, row-major [row, N] when float.  Column block cb belongs to member cb % n.
-// pre: the weights of the first round; pf(): issues the next stage's weight loads (called once the
-// activation loads of this stage are under way).  LOCAL: C holds the group's rows only (row 0 = the
-// group's first row), e.g. a buffer in LDS.
-template <typename HT, int MB, int S, int EPI, typename OutT, class PF, bool LOCAL = false>
-__device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t hs_rs, const float *__restrict__ g,
+// C[:, blocks of this member] = epi(LayerNorm(stream) * Wt^T + bias) for the group's rows, K = W = 256 S.  The stream
+// (at in_off) is float32 fragment-major, Wt fragment-major; 16-column block cb belongs to member cb % n, CB blocks a round.  Weights are the first
+// matrix operand and rows the second, so a lane ends up with four consecutive columns of one row.
+// 16-bit results go to out_off (fragment-major; the member's part at empty_off is emptied); with LOCAL the float32
+// result goes to the workgroup's own buffer (row-major [16 MB][N], row 0 = the group's first row) and the member takes every block.
+template <typename HT, int MB, int S, int CB, int EPI, bool LOCAL>
+__device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t ws, uint32_t in_off, const float *__restrict__ g,
                                               const float *__restrict__ be, const HT *__restrict__ Wt,
-                                              const float *__restrict__ bias, OutT *C, int N, f32x4v *red,
-                                              float *stat, LnPre<HT, S> &pre, PF pf) {
+                                              const float *__restrict__ bias, uint32_t out_off, uint32_t empty_off,
+                                              float *local, int N, f32x4v *red, float2 *stat) {
     typedef typename Half16<HT>::v8 v8;
-    constexpr int W = 256 * S;
+    typedef typename Half16<HT>::v4 v4;
+    constexpr int W = 256 * S, KS = 8 * S;
+    const int nbt = (N + 15) >> 4;
+    const int slot = LOCAL ? 0 : c_in.slot, n = LOCAL ? 1 : c_in.n;
+    if (slot >= nbt) return;
     const Ctx c = local_ctx(c_in);
     const int k0 = c.wave * 32 * S + c.kg * 8;
-    f32x4 xr[MB][S][2];
+    v8 w[CB][S];
+    auto fetch = [&](int cb0) {     // clamped, so that the loads are unconditional; blocks past the end are never used
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+        for (int cc = 0; cc < CB; ++cc) {
+            int cb = cb0 + cc * n;
+            cb = cb < nbt ? cb : nbt - 1;
 #pragma unroll
-        for (int s = 0; s < S; ++s) {
-            const uint32_t off = (uint32_t)((((c.rb0 + i) * (8 * S) + c.wave * S + s) * 64 + c.lane) * 8) * 4u;
-            xr[i][s][0] = __builtin_bit_cast(f32x4, ld16_l2(hs_rs, off));
-            xr[i][s][1] = __builtin_bit_cast(f32x4, ld16_l2(hs_rs, off + 16u));
+            for (int s = 0; s < S; ++s)
+                w[cc][s] = *reinterpret_cast<const v8 *>(Wt + (((size_t)cb * KS + c.wave * S + s) * 64 + c.lane) * 8);
         }
+    };
+    fetch(slot);
     f32x4 gr[S][2], br[S][2];
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -165,387 +185,335 @@ __device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t hs_rs, con
         br[s][0] = *reinterpret_cast<const f32x4 *>(be + k0 + 32 * s);
         br[s][1] = *reinterpret_cast<const f32x4 *>(be + k0 + 32 * s + 4);
     }
-    // bias of the output blocks this wave will finish in the first round (q = wave, wave + 8, ...)
-    const int nbt = (N + 15) >> 4;
-    constexpr int NQ = (P_CB * MB + P_NW - 1) / P_NW;
-    float bv0[NQ];
+    constexpr int NQ = (CB * MB + P_NW - 1) / P_NW;   // output blocks a wave finishes in a round (q = wave, wave + 8, ...)
+    float bv[NQ][4];
+    const rsrc_t bias_rs = make_rsrc(bias, (uint32_t)N * 4u);
+    auto fetch_bias = [&](int cb0) {
 #pragma unroll
-    for (int qi = 0; qi < NQ; ++qi) {
-        const int q = c.wave + qi * P_NW;
-        const int col = (c.slot + (q / MB) * c.n) * 16 + c.r;
-        bv0[qi] = (q < P_CB * MB && col < N) ? bias[col] : 0.f;
-    }
-    pf();
-    // row statistics: mean, then centred sum of squares; partial sums of the 8 waves meet in LDS
-    float mean[MB], rstd[MB];
+        for (int qi = 0; qi < NQ; ++qi) {
+            const int q = c.wave + qi * P_NW;
+            const int col = (cb0 + (q / MB) * n) * 16 + 4 * c.kg;
+#pragma unroll
+            for (int v = 0; v < 4; ++v)     // zeros past the end
+                bv[qi][v] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(bias_rs, (int)(col + v) * 4, 0, 0));
+        }
+    };
+    fetch_bias(slot);
+    __builtin_amdgcn_sched_barrier(0);
+    i32x4 raw[MB * S * 2];
+    poll16(c, ws, [&](int u) {
+        const int i = u / (2 * S), s = (u >> 1) % S;
+        const uint32_t off = in_off + (uint32_t)((((c.rb0 + i) * KS + c.wave * S + s) * 64 + c.lane) * 8) * 4u + (u & 1) * 16u;
+        return where(i * 16 + c.r < c.nrows, off);
+    }, raw);
+    auto x = [&](int i, int s, int h2, int e) { return __int_as_float(raw[(i * S + s) * 2 + h2][e]); };
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
         float sum = 0.f;
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) sum += xr[i][s][0][e] + xr[i][s][1][e];
-        sum += __shfl_xor(sum, 16, 64);
-        sum += __shfl_xor(sum, 32, 64);
-        if (c.kg == 0) stat[c.wave * (MB * 16) + i * 16 + c.r] = sum;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < MB; ++i) {
-        float t = stat[i * 16 + c.r];
-#pragma unroll
-        for (int w = 1; w < P_NW; ++w) t += stat[w * (MB * 16) + i * 16 + c.r];
-        mean[i] = t * (1.0f / (float)W);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < MB; ++i) {
+            for (int e = 0; e < 4; ++e) sum += x(i, s, 0, e) + x(i, s, 1, e);
+        sum = sum_rows(sum);
+        const float mw = sum * (1.0f / (32.f * S));
         float m2 = 0.f;
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
             for (int h2 = 0; h2 < 2; ++h2)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) { const float d = xr[i][s][h2][e] - mean[i]; m2 = fmaf(d, d, m2); }
-        m2 += __shfl_xor(m2, 16, 64);
-        m2 += __shfl_xor(m2, 32, 64);
-        if (c.kg == 0) stat[c.wave * (MB * 16) + i * 16 + c.r] = m2;
+                for (int e = 0; e < 4; ++e) { const float d = x(i, s, h2, e) - mw; m2 = fmaf(d, d, m2); }
+        m2 = sum_rows(m2);
+        if (c.kg == 0) stat[c.wave * (MB * 16) + i * 16 + c.r] = float2{mw, m2};
     }
     __syncthreads();
-#pragma unroll
-    for (int i = 0; i < MB; ++i) {
-        float t = stat[i * 16 + c.r];
-#pragma unroll
-        for (int w = 1; w < P_NW; ++w) t += stat[w * (MB * 16) + i * 16 + c.r];
-        rstd[i] = 1.0f / sqrtf(t * (1.0f / (float)W) + 1e-5f);
-    }
-    SJD_TLC(c);   // statistics done (activations have arrived)
     v8 fa[MB][S];
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+    for (int i = 0; i < MB; ++i) {
+        float2 st[P_NW];
+        float mean = 0.f;
+#pragma unroll
+        for (int q = 0; q < P_NW; ++q) { st[q] = stat[q * (MB * 16) + i * 16 + c.r]; mean += st[q].x; }
+        mean *= 1.0f / P_NW;
+        float between = 0.f, within = 0.f;
+#pragma unroll
+        for (int q = 0; q < P_NW; ++q) { const float d = st[q].x - mean; between = fmaf(d, d, between); within += st[q].y; }
+        const float rstd = 1.0f / sqrtf(fmaf(32.f * S, between, within) * (1.0f / (float)W) + 1e-5f);
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
             for (int h2 = 0; h2 < 2; ++h2)
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    fa[i][s][4 * h2 + e] =
-                        from_f32<HT>((xr[i][s][h2][e] - mean[i]) * rstd[i] * gr[s][h2][e] + br[s][h2][e]);
-
-    // One round: the member's next (up to) P_CB column blocks.  The first round is straight-line code
-    // (its weights and biases were requested earlier), so that the waits in front of its matrix
-    // instructions cover exactly the loads they need and not the prefetches issued behind them.
-    auto round = [&](int cb0, bool first) {
-        f32x4v acc[P_CB][MB];
+                    fa[i][s][4 * h2 + e] = from_f32<HT>((x(i, s, h2, e) - mean) * rstd * gr[s][h2][e] + br[s][h2][e]);
+    }
+    for (int cb0 = slot; cb0 < nbt; cb0 += CB * n) {
+        if (cb0 != slot) {
+            __syncthreads();   // the previous round's partial sums have been read
+            fetch(cb0);
+            fetch_bias(cb0);
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // they are needed next; and no load is left under way behind the results' stores
+        }
 #pragma unroll
-        for (int cc = 0; cc < P_CB; ++cc)
+        for (int cc = 0; cc < CB; ++cc)
 #pragma unroll
             for (int i = 0; i < MB; ++i) {
-                acc[cc][i] = f32x4v{0.f, 0.f, 0.f, 0.f};
+                f32x4v acc = f32x4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int s = 0; s < S; ++s) acc[cc][i] = Mfma16<HT>::run(fa[i][s], pre.f[cc][s], acc[cc][i]);
-                red[(c.wave * (P_CB * MB) + cc * MB + i) * 64 + c.lane] = acc[cc][i];
+                for (int s = 0; s < S; ++s) acc = Mfma16<HT>::run(w[cc][s], fa[i][s], acc);
+                red[(c.wave * (CB * MB) + cc * MB + i) * 64 + c.lane] = acc;
             }
         __syncthreads();
-        SJD_TLC(c);   // partial sums in LDS
         // output block q = (cc, i) is summed in wave order and finished by wave q % 8
 #pragma unroll
         for (int qi = 0; qi < NQ; ++qi) {
             const int q = c.wave + qi * P_NW;
-            if (q >= P_CB * MB) break;
+            if (q >= CB * MB) break;
             const int cc = q / MB, i = q % MB;
-            const int cb = cb0 + cc * c.n;
-            const int col = cb * 16 + c.r;
-            if (cb < nbt && col < N) {
-                f32x4v t = red[q * 64 + c.lane];
+            const int cb = cb0 + cc * n;
+            if (cb >= nbt) continue;
+            f32x4v t = red[q * 64 + c.lane];
 #pragma unroll
-                for (int w = 1; w < P_NW; ++w) t += red[(w * (P_CB * MB) + q) * 64 + c.lane];
-                const float bv = first ? bv0[qi] : bias[col];
+            for (int p = 1; p < P_NW; ++p) t += red[(p * (CB * MB) + q) * 64 + c.lane];
+            const int row = i * 16 + c.r, col = cb * 16 + 4 * c.kg;
+            if constexpr (LOCAL) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (col + v < N) local[row * N + col + v] = t[v] + bv[qi][v];
+            } else {
+                v4 h;
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int row = ((LOCAL ? 0 : c.rb0) + i) * 16 + 4 * c.kg + v;   // LOCAL: C is the workgroup's own buffer
-                    float val = t[v] + bv;
+                    float val = t[v] + bv[qi][v];
                     if (EPI == EPI_BIAS_GELU) val = gelu_erf_h16(val);
-                    if constexpr (sizeof(OutT) == 2) C[frag_off(row, col, N >> 5)] = from_f32<OutT>(val);
-                    else C[(size_t)row * N + col] = val;
+                    h[v] = from_f32<HT>(val);
+                }
+                if (row < c.nrows) {
+                    const i32x2 two = __builtin_bit_cast(i32x2, h);
+                    const uint32_t eo = (uint32_t)frag_off(c.rb0 * 16 + row, col, N >> 5) * 2u;
+                    st8(ws, out_off + eo, i32x2{flagged(two.x), flagged(two.y)});
+                    st8(ws, empty_off + eo, i32x2{-1, -1});
                 }
             }
         }
-        __syncthreads();
-    };
-    round(c.slot, true);
-    for (int cb0 = c.slot + P_CB * c.n; cb0 < nbt; cb0 += P_CB * c.n) {
-        ln_prefetch<HT, S>(c, Wt, N, cb0, pre);
-        round(cb0, false);
     }
 }
 
-// weights of one column block of a residual projection: the KMUL*S k-steps of this wave
-template <typename HT, int S, int KMUL>
-__device__ __forceinline__ void res_prefetch(const Ctx &c, const HT *__restrict__ Wt, int cb, ResPre<HT, S, KMUL> &w) {
+// stream_out[:, units of this member] = stream_in + A * Wt^T + bias for the group's rows; N = W = 256 S, K = KMUL * W.
+// A (at a_off) 16-bit fragment-major, the streams float32 fragment-major.  A unit is cw columns: with many members a 16-column
+// block is shared out among two or four of them (the lanes of the other columns repeat theirs), so that every
+// member pulls an equal, small piece of the weights; unit u belongs to member u % n.
+template <typename HT, int MB, int S, int KMUL>
+__device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t ws, uint32_t a_off, const HT *__restrict__ Wt,
+                                                 const float *__restrict__ bias, uint32_t in_off, uint32_t out_off,
+                                                 uint32_t empty_off, f32x4v *red) {
     typedef typename Half16<HT>::v8 v8;
-    constexpr int nbt = 16 * S, KSA = 8 * S * KMUL, KSW = S * KMUL;
-    cb = cb < nbt ? cb : nbt - 1;
-#pragma unroll
-    for (int u = 0; u < KSW; ++u)
-        w.f[u] = *reinterpret_cast<const v8 *>(Wt + (((size_t)cb * KSA + c.wave * KSW + u) * 64 + c.lane) * 8);
-}
-
-// Hs[:, cols of this member] += A * Wt^T + bias for the group's rows; N = W = 256 S, K = KMUL * W.
-// A 16-bit fragment-major (read through L2), Hs float32 fragment-major (read through L2, written).
-template <typename HT, int MB, int S, int KMUL, class PF>
-__device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t a_rs, const HT *__restrict__ Wt,
-                                                 const float *__restrict__ bias, rsrc_t hs_rs, float *hs,
-                                                 f32x4v *red, ResPre<HT, S, KMUL> &pre, PF pf) {
-    typedef typename Half16<HT>::v8 v8;
-    constexpr int W = 256 * S, KSN = W / 32, nbt = W / 16, KSA = 8 * S * KMUL, KSW = S * KMUL;
+    constexpr int W = 256 * S, KSN = W / 32, KSA = 8 * S * KMUL, KSW = S * KMUL;
+    const int nu = W / c_in.cw;
+    if (c_in.slot >= nu) return;
     const Ctx c = local_ctx(c_in);
-    v8 fa[MB][KSW];
+    const int cmask = c.cw - 1;
+    v8 w[KSW];
+    float bv[4];
+    uint32_t eo;                                // this lane's four columns of a stream row (wave i < MB: row block i)
+    auto fetch = [&](int u) {
+        const int col0 = u * c.cw, cb = col0 >> 4, cl = (col0 & 15) + (c.r & cmask);
 #pragma unroll
-    for (int i = 0; i < MB; ++i)
+        for (int k = 0; k < KSW; ++k)
+            w[k] = *reinterpret_cast<const v8 *>(Wt + (((size_t)cb * KSA + c.wave * KSW + k) * 64 + c.kg * 16 + cl) * 8);
+        const int col = col0 + ((4 * c.kg) & cmask);
 #pragma unroll
-        for (int u = 0; u < KSW; ++u) {
-            const uint32_t off = (uint32_t)((((c.rb0 + i) * KSA + c.wave * KSW + u) * 64 + c.lane) * 8) * 2u;
-            fa[i][u] = __builtin_bit_cast(v8, ld16_l2(a_rs, off));
-        }
-    // every wave fetches residual values and bias of the block (only waves < MB use them: no branch
-    // between the loads and the matrix instructions; rows past the workspace read as zero)
-    float rv[4], bv;
-    uint32_t eo[4];
-    auto fetch_resid = [&](int cb) {
-        const int cbc = cb < nbt ? cb : nbt - 1;
-        const int col = cbc * 16 + c.r;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            eo[v] = (uint32_t)frag_off((c.rb0 + c.wave) * 16 + 4 * c.kg + v, col, KSN);
-            rv[v] = ld4_l2(hs_rs, eo[v] * 4u);
-        }
-        bv = bias[col];
+        for (int v = 0; v < 4; ++v) bv[v] = bias[col + v];
+        eo = (uint32_t)frag_off((c.rb0 + c.wave) * 16 + c.r, col, KSN) * 4u;
     };
-    auto block = [&](int cb) {
+    const bool finish = c.wave < MB && c.wave * 16 + c.r < c.nrows && 4 * c.kg < c.cw;
+    fetch(c.slot);
+    __builtin_amdgcn_sched_barrier(0);
+    i32x4 raw[MB * KSW + 1];                    // the activation, and the stream values of the first unit
+    poll16(c, ws, [&](int u) {
+        if (u == MB * KSW) return where(finish, in_off + eo);
+        const int i = u / KSW, k = u % KSW;
+        const uint32_t off = a_off + (uint32_t)((((c.rb0 + i) * KSA + c.wave * KSW + k) * 64 + c.lane) * 8) * 2u;
+        return where(i * 16 + c.r < c.nrows, off);
+    }, raw);
+    i32x4 rv[1] = {raw[MB * KSW]};
+    for (int u = c.slot; u < nu; u += c.n) {
+        if (u != c.slot) {
+            __syncthreads();                    // the previous unit's partial sums have been read
+            fetch(u);
+            poll16(c, ws, [&](int) { return where(finish, in_off + eo); }, rv);
+        }
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
             f32x4v acc = f32x4v{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int u = 0; u < KSW; ++u) acc = Mfma16<HT>::run(fa[i][u], pre.f[u], acc);
+            for (int k = 0; k < KSW; ++k) acc = Mfma16<HT>::run(w[k], __builtin_bit_cast(v8, raw[i * KSW + k]), acc);
             red[(c.wave * MB + i) * 64 + c.lane] = acc;
         }
-        SJD_TLC(c);   // operands have arrived, products done
         __syncthreads();
-        SJD_TLC(c);
-        if (c.wave < MB && cb < nbt) {
+        if (finish) {
             f32x4v t = red[c.wave * 64 + c.lane];
 #pragma unroll
-            for (int w = 1; w < P_NW; ++w) t += red[(w * MB + c.wave) * 64 + c.lane];
+            for (int p = 1; p < P_NW; ++p) t += red[(p * MB + c.wave) * 64 + c.lane];
+            i32x4 out;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) hs[eo[v]] = (t[v] + bv) + rv[v];
+            for (int v = 0; v < 4; ++v) out[v] = flagged((t[v] + bv[v]) + __int_as_float(rv[0][v]));
+            st16(ws, out_off + eo, out);
+            st16(ws, empty_off + eo, i32x4{-1, -1, -1, -1});
         }
-        __syncthreads();
-    };
-    fetch_resid(c.slot);
-    pf();
-    block(c.slot);                                          // straight-line first block (see ln_gemm_stage)
-    for (int cb = c.slot + c.n; cb < nbt; cb += c.n) {
-        res_prefetch<HT, S, KMUL>(c, Wt, cb, pre);
-        fetch_resid(cb);
-        block(cb);
     }
 }
 
-// Single-token attention of the group's (sample, head) pairs against the cache at position t:
-// pair (row, h) belongs to member (row * H + h) % n.  A pair is handled by four waves (32 key
-// groups x 8 sixteen-byte chunks of the head), two pairs at a time per workgroup; the partition
-// of the keys and the order of the partial sums are the same for every batch size.  This step's k
-// and v are appended to the cache.  Cached rows do not depend on the current step, so the first
-// P_AU rows of every thread (keys and values) are requested before the barrier that precedes
-// the stage (att_prefetch) and only q and the fresh row are waited for afterwards.
+// Single-token attention of the group's (sample, head) pairs against the cache at position t: pair (row, h) belongs to
+// member (row * H + h) % n, which also appends this step's k and v to the cache.  A pair is handled by four waves: 32
+// key groups x 8 sixteen-byte chunks of the head, two pairs at a time per workgroup.  A key group walks its keys in
+// batches of P_AU with an online softmax of its own; the groups meet once, at the end (the wave's eight by lane
+// exchange, the four waves through LDS).  The partition of the keys and the order of the sums depend on t only.
+// Cached rows do not depend on the current step: the first batch is requested before the poll for q, k, v, and each
+// next batch (of this pair or the next) as soon as the registers of the current one have been used.
 constexpr int P_NSUB = 2;
 constexpr int P_AU = 8;  // cache rows per thread and batch
-template <typename HT> struct AttPre { typename Half16<HT>::v8 k[P_AU], v[P_AU]; };
 
-template <typename HT, int S>
-__device__ __forceinline__ void att_fetch(const Ctx &c, rsrc_t kc_rs, rsrc_t vc_rs, int k0, int j0, int t, int T,
-                                          AttPre<HT> &w) {
-    typedef typename Half16<HT>::v8 v8;
-    constexpr int W = 256 * S, H = W / 64;
-    const int sub = c.tid >> 8, stid = c.tid & 255, dc = stid & 7, sg = stid >> 3;
-    const int npairs = c.nrows * H;
-    int pi = c.slot + (k0 + sub) * c.n;
-    pi = pi < npairs ? pi : 0;
-    const int row = pi / H, h = pi - row * H;
-    const size_t cbase = ((size_t)(c.row0 + row) * T) * W + h * 64;
-#pragma unroll
-    for (int u = 0; u < P_AU; ++u) {
-        const int s = sg + 32 * (j0 + u);
-        const int sr = s < t ? s : 0;                      // rows at or past t: any cached row, value not used
-        const uint32_t off = (uint32_t)(cbase + (size_t)sr * W + dc * 8) * 2u;
-        w.k[u] = __builtin_bit_cast(v8, ld16_l2_stream(kc_rs, off));
-        w.v[u] = __builtin_bit_cast(v8, ld16_l2_stream(vc_rs, off));
-    }
-}
-
-template <typename HT, int S>
-__device__ __forceinline__ void attention_stage(const Ctx &c_in, rsrc_t qkv_rs, HT *kc, HT *vc, rsrc_t kc_rs, rsrc_t vc_rs,
-                                                HT *o, int t, int T, float *sc_all, float *opart, float *wred) {
+template <typename HT, int MB, int S>
+__device__ __forceinline__ void attention_stage(const Ctx &c_in, rsrc_t ws, uint32_t qkv_off, HT *kc, HT *vc, rsrc_t kc_rs,
+                                                rsrc_t vc_rs, uint32_t out_off, uint32_t empty_off, int t, int T,
+                                                float *opart, float2 *wst, int &par) {
     typedef typename Half16<HT>::v8 v8;
     constexpr int W = 256 * S, H = W / 64, KS3 = 3 * W / 32;
+    const int npairs = c_in.nrows * H;
+    if (c_in.slot >= npairs) return;
     const Ctx c = local_ctx(c_in);
     const int sub = c.tid >> 8, stid = c.tid & 255;
     const int dc = stid & 7, sg = stid >> 3;               // chunk of the head, key group (0..31)
-    float *sc = sc_all + (size_t)sub * T;
-    const int npairs = c.nrows * H;
-    const int mine = npairs > c.slot ? (npairs - c.slot + c.n - 1) / c.n : 0;   // pairs of this member
-    const int nk = t + 1;
-    const int nbatch = (nk + 32 * P_AU - 1) / (32 * P_AU);  // batches of P_AU rows per thread
+    const int mine = (npairs - c.slot + c.n - 1) / c.n;    // pairs of this member
+    const int nb = (t + 32 * P_AU - 1) / (32 * P_AU);      // batches of cached keys
+    auto pair_of = [&](int k0) { return c.slot + (k0 + sub) * c.n; };
+    auto rows = [&](rsrc_t rs, int k0, int jb, i32x4 (&v)[P_AU]) {
+        const bool valid = k0 + sub < mine;
+        const int pi = valid ? pair_of(k0) : 0, row = pi / H, h = pi - row * H;
+        const uint32_t base = (uint32_t)(((size_t)(c.row0 + row) * T) * W + h * 64 + dc * 8) * 2u;
+#pragma unroll
+        for (int u = 0; u < P_AU; ++u) {
+            const int s = sg + 32 * (jb * P_AU + u);
+            v[u] = ld16_stream(rs, where(valid && s < t, base + (uint32_t)s * (W * 2u)));
+        }
+    };
+    i32x4 kk[P_AU], vv[P_AU];
+    if (nb > 0) { rows(kc_rs, 0, 0, kk); rows(vc_rs, 0, 0, vv); }
+    __builtin_amdgcn_sched_barrier(0);
     for (int k0 = 0; k0 < mine; k0 += P_NSUB) {
-        const int pi = c.slot + (k0 + sub) * c.n;
         const bool valid = (k0 + sub) < mine;
-        const int row = valid ? pi / H : 0, h = valid ? pi - row * H : 0;
-        const int b = c.row0 + row, wsrow = c.rb0 * 16 + row;
-        auto chunk = [&](int part, int ci) -> v8 {
-            return __builtin_bit_cast(v8, ld16_l2(qkv_rs, (uint32_t)frag_off(wsrow, part * W + h * 64 + ci * 8, KS3) * 2u));
-        };
-        const v8 kfresh = chunk(1, dc), vfresh = chunk(2, dc), q8 = chunk(0, dc);
-        const size_t cbase = ((size_t)b * T) * W + h * 64;
+        const int pi = valid ? pair_of(k0) : 0;
+        const int row = pi / H, h = pi - row * H;
+        const int wsrow = c.rb0 * 16 + row;
+        i32x4 fresh[3];
+        poll16(c, ws, [&](int part) {
+            return where(valid, qkv_off + (uint32_t)frag_off(wsrow, part * W + h * 64 + dc * 8, KS3) * 2u);
+        }, fresh);
+        const v8 q8 = __builtin_bit_cast(v8, fresh[0]), kf = __builtin_bit_cast(v8, fresh[1]), vf = __builtin_bit_cast(v8, fresh[2]);
         if (valid && stid < 16) {   // threads 0..7 hold the fresh k chunks, 8..15 the fresh v chunks (dc = stid & 7)
-            HT *dst = (stid < 8 ? kc : vc) + cbase + (size_t)t * W + dc * 8;
-            *reinterpret_cast<v8 *>(dst) = stid < 8 ? kfresh : vfresh;
+            HT *dst = (stid < 8 ? kc : vc) + ((size_t)(c.row0 + row) * T + t) * W + h * 64 + dc * 8;
+            *reinterpret_cast<v8 *>(dst) = stid < 8 ? kf : vf;
         }
-        float qf[8];
+        // softmax scale 1/sqrt(64) and log2(e) in one factor: the probabilities are powers of two
+        auto score = [&](v8 k8) { return sum8(Half16<HT>::dot(q8, k8)) * (0.125f * 1.44269504088896340736f); };
+        // the fresh key belongs to key group 0
+        const float df = score(kf);
+        float m = sg == 0 ? df : -INFINITY, l = sg == 0 ? 1.f : 0.f, acc[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) qf[e] = (float)q8[e] * 0.125f;  // 1/sqrt(64)
-        AttPre<HT> pre;
-        att_fetch<HT, S>(c, kc_rs, vc_rs, k0, 0, t, T, pre);   // first batch of cached keys and values, in one go
-        // scores of batch 0 (values stay in registers), further batches fetch keys only
-        float mx = -INFINITY;
-        float d0[P_AU];
-#pragma unroll
-        for (int u = 0; u < P_AU; ++u) {
-            const int s = sg + 32 * u;
-            const v8 k8 = s < t ? pre.k[u] : kfresh;
-            float d = 0.f;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) d = fmaf(qf[e], (float)k8[e], d);
-            d += __shfl_xor(d, 1, 64);
-            d += __shfl_xor(d, 2, 64);
-            d += __shfl_xor(d, 4, 64);
-            d0[u] = d;
-            if (s < nk) mx = fmaxf(mx, d);
-        }
-        for (int jb = 1; jb < nbatch; ++jb) {
-            v8 kk[P_AU];
+        for (int e = 0; e < 8; ++e) acc[e] = sg == 0 ? (float)vf[e] : 0.f;
+        for (int jb = 0; jb < nb; ++jb) {
+            const bool more = jb + 1 < nb;
+            const int nk0 = more ? k0 : k0 + P_NSUB, njb = more ? jb + 1 : 0;
+            const bool next = more || nk0 < mine;
+            float d[P_AU], mn = m;
 #pragma unroll
             for (int u = 0; u < P_AU; ++u) {
-                const int s = sg + 32 * (jb * P_AU + u);
-                const int sr = s < t ? s : 0;
-                kk[u] = __builtin_bit_cast(v8, ld16_l2_stream(kc_rs, (uint32_t)(cbase + (size_t)sr * W + dc * 8) * 2u));
+                d[u] = score(__builtin_bit_cast(v8, kk[u]));
+                if (sg + 32 * (jb * P_AU + u) >= t) d[u] = -INFINITY;
+                mn = fmaxf(mn, d[u]);
             }
+            if (next) rows(kc_rs, nk0, njb, kk);
+            const float mu = mn == -INFINITY ? 0.f : mn;       // a key group may not have any key yet
+            const float corr = __builtin_amdgcn_exp2f(m - mu);
+            m = mn;
+            l *= corr;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] *= corr;
 #pragma unroll
             for (int u = 0; u < P_AU; ++u) {
-                const int s = sg + 32 * (jb * P_AU + u);
-                const v8 k8 = s < t ? kk[u] : kfresh;
-                float d = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) d = fmaf(qf[e], (float)k8[e], d);
-                d += __shfl_xor(d, 1, 64);
-                d += __shfl_xor(d, 2, 64);
-                d += __shfl_xor(d, 4, 64);
-                if (s < nk) {
-                    if (dc == 0) sc[s] = d;
-                    mx = fmaxf(mx, d);
-                }
-            }
-        }
-        mx = wave_max(mx);
-        SJD_TLC(c);   // scores done (q, fresh row and cached keys have arrived)
-        if (c.lane == 0) wred[c.wave] = mx;
-        __syncthreads();
-        SJD_TLC(c);
-        mx = fmaxf(fmaxf(wred[4 * sub], wred[4 * sub + 1]), fmaxf(wred[4 * sub + 2], wred[4 * sub + 3]));
-        float acc[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = 0.f;
-        float psum = 0.f;
-#pragma unroll
-        for (int u = 0; u < P_AU; ++u) {
-            const int s = sg + 32 * u;
-            if (s < nk) {
-                const float p = expf(d0[u] - mx);
-                const v8 v8v = s < t ? pre.v[u] : vfresh;
+                const float p = __builtin_amdgcn_exp2f(d[u] - mu);
+                const v8 v8v = __builtin_bit_cast(v8, vv[u]);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) acc[e] = fmaf(p, (float)v8v[e], acc[e]);
-                psum += p;
+                l += p;
             }
-        }
-        for (int jb = 1; jb < nbatch; ++jb) {
-            v8 vv[P_AU];
-#pragma unroll
-            for (int u = 0; u < P_AU; ++u) {
-                const int s = sg + 32 * (jb * P_AU + u);
-                const int sr = s < t ? s : 0;
-                vv[u] = __builtin_bit_cast(v8, ld16_l2_stream(vc_rs, (uint32_t)(cbase + (size_t)sr * W + dc * 8) * 2u));
-            }
-#pragma unroll
-            for (int u = 0; u < P_AU; ++u) {
-                const int s = sg + 32 * (jb * P_AU + u);
-                if (s < nk) {
-                    const float p = expf(sc[s] - mx);
-                    const v8 v8v = s < t ? vv[u] : vfresh;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[e] = fmaf(p, (float)v8v[e], acc[e]);
-                    psum += p;
-                }
-            }
+            if (next) rows(vc_rs, nk0, njb, vv);
         }
         // the 8 key groups of a wave (lanes differing in bits 3..5), then the pair's four waves in order
+        const float mw = max_rows(fmaxf(m, dpp<0x128>(m)));    // 0x128: rotated by eight within sixteen lanes
+        const float f = __builtin_amdgcn_exp2f(m - (mw == -INFINITY ? 0.f : mw));
+        auto over_groups = [&](float x) { x *= f; return sum_rows(x + dpp<0x128>(x)); };
+        l = over_groups(l);
 #pragma unroll
-        for (int off = 8; off < 64; off <<= 1) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], off, 64);
-            psum += __shfl_xor(psum, off, 64);
-        }
-        SJD_TLC(c);   // weighted values summed within the wave
+        for (int e = 0; e < 8; ++e) acc[e] = over_groups(acc[e]);
+        // With few pairs per member there is hardly ever a next one under way here, and the compiler should know: it would
+        // wait at the start of the next stage, behind the stores of this one.
+        if (MB == 1) __builtin_amdgcn_s_waitcnt(0x0F70);
+        float *op = opart + par * (P_NW * 64);
+        float2 *wp = wst + par * P_NW;
+        par ^= 1;                                  // the other half may still be read by a slower wave
         if (c.lane < 8) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) opart[c.wave * 64 + c.lane * 8 + e] = acc[e];
-            if (c.lane == 0) wred[P_NW + c.wave] = psum;
+            for (int e = 0; e < 8; ++e) op[c.wave * 64 + c.lane * 8 + e] = acc[e];
+            if (c.lane == 0) wp[c.wave] = float2{mw, l};
         }
         __syncthreads();
         if (valid && stid < 8) {
             const int w0 = 4 * sub;
-            const float den = ((wred[P_NW + w0] + wred[P_NW + w0 + 1]) + wred[P_NW + w0 + 2]) + wred[P_NW + w0 + 3];
+            const float mm = fmaxf(fmaxf(wp[w0].x, wp[w0 + 1].x), fmaxf(wp[w0 + 2].x, wp[w0 + 3].x));
+            float fw[4], den = 0.f;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { fw[q] = __builtin_amdgcn_exp2f(wp[w0 + q].x - mm); den += wp[w0 + q].y * fw[q]; }
             v8 ov;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int d = stid * 8 + e;
-                ov[e] = from_f32<HT>((((opart[w0 * 64 + d] + opart[(w0 + 1) * 64 + d]) + opart[(w0 + 2) * 64 + d]) +
-                                      opart[(w0 + 3) * 64 + d]) / den);
+                float s = 0.f;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) s += op[(w0 + q) * 64 + d] * fw[q];
+                ov[e] = from_f32<HT>(s / den);
             }
-            *reinterpret_cast<v8 *>(o + frag_off(wsrow, h * 64 + stid * 8, W / 32)) = ov;
+            i32x4 four = __builtin_bit_cast(i32x4, ov);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) four[v] = flagged(four[v]);
+            const uint32_t eo = (uint32_t)frag_off(wsrow, h * 64 + stid * 8, W / 32) * 2u;
+            st16(ws, out_off + eo, four);
+            st16(ws, empty_off + eo, i32x4{-1, -1, -1, -1});
         }
-        __syncthreads();  // sc, opart and wred are reused by the next round
     }
 }
 
-template <typename HT, int MB, int S>
+template <typename HT, int MB, int S, int CB>
 __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
-    constexpr int W = 256 * S, RW_ROWS = 16 * MB;
+    constexpr int W = 256 * S, RW_ROWS = 16 * MB, CBH = S <= 2 ? 2 : 4;
+    constexpr int CBM = CB > CBH ? CB : CBH;
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     __shared__ int sh[8];
-    f32x4v *red = reinterpret_cast<f32x4v *>(lds_raw);                       // [8][P_CB*MB][64]
-    float *stat = reinterpret_cast<float *>(lds_raw + (size_t)P_NW * P_CB * MB * 64 * 16);  // [8][MB*16]
-    float *xs = stat + P_NW * MB * 16;                                        // [16*MB][D]
-    float *opart = xs + RW_ROWS * a.D;                                        // [8][64]
-    float *wred = opart + P_NW * 64;                                          // [16]
-    float *sc = wred + 16;                                                    // [2][T]
-    float *wemb = sc + 2 * a.T;                                               // [P_EB][D + 1][16]: w_in slice, then b_in
+    f32x4v *red = reinterpret_cast<f32x4v *>(lds_raw);                        // [8][CBM*MB][64]: LayerNorm-fused projections
+    f32x4v *red2 = red + P_NW * CBM * MB * 64;                                // [8][MB][64]: residual projections
+    float2 *stat = reinterpret_cast<float2 *>(red2 + P_NW * MB * 64);         // [8][MB*16]
+    float2 *wst = stat + P_NW * MB * 16;                                      // [2][8]
+    float *opart = reinterpret_cast<float *>(wst + 2 * P_NW);                 // [2][8][64]
+    float *xs = opart + 2 * P_NW * 64;                                        // [16*MB][D]
+    float *wemb = xs + RW_ROWS * a.D;                                         // [P_EB][D + 1][16]: w_in slice, then b_in
     float *pl = wemb + (size_t)P_EB * (a.D + 1) * 16;                         // [16*MB][2D]: this step's [mu | alpha] of the group's rows
 
     Ctx c;
     c.tid = threadIdx.x; c.lane = c.tid & 63; c.wave = c.tid >> 6; c.r = c.lane & 15; c.kg = c.lane >> 4;
-    c.epoch = 0; c.status = a.sync + 9; c.spin_max = a.spin_max;
+    c.status = a.sync + 9; c.spin_max = a.spin_max; c.bad = (LdsInt *)&sh[7];
 
-    // ---- groups: the workgroups of one XCD, found from the hardware's XCC id
+    // ---- groups: the workgroups of xpg XCDs, found from the hardware's XCC id
     if (c.tid == 0) {
         const int xcc = __builtin_amdgcn_s_getreg(20 | (3 << 11)) & 7;  // HW_REG_XCC_ID, bits 3:0
         const int slot = atomicAdd(&a.sync[xcc], 1);
@@ -557,20 +525,27 @@ __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
             if (++it > a.spin_max) { ok = 0; break; }
             __builtin_amdgcn_s_sleep(2);
         }
-        int n = 0, groups = 0, gidx = 0;
+        int count[8], present = 0, rank = 0;
         for (int g = 0; g < 8; ++g) {
-            const int m = __hip_atomic_load(&a.sync[g], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-            if (m > 0) { if (g < xcc) ++gidx; ++groups; }
-            if (g == xcc) n = m;
+            count[g] = __hip_atomic_load(&a.sync[g], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+            if (g == xcc) rank = present;
+            present += count[g] > 0 ? 1 : 0;
+        }
+        const int gidx = rank / a.xpg;
+        int n = 0, before = 0, seen = 0;             // members of the group; those on its lower XCDs
+        for (int g = 0; g < 8; ++g) {
+            if (count[g] > 0) {
+                if (seen / a.xpg == gidx) { n += count[g]; if (g < xcc) before += count[g]; }
+                ++seen;
+            }
         }
         if (!ok) __hip_atomic_store(c.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sh[0] = ok; sh[1] = slot; sh[2] = n; sh[3] = groups; sh[4] = gidx; sh[5] = xcc;
+        sh[0] = ok; sh[1] = before + slot; sh[2] = n; sh[3] = (present + a.xpg - 1) / a.xpg; sh[4] = gidx; sh[7] = 0;
     }
     __syncthreads();
     if (!sh[0]) return;
     c.slot = sh[1]; c.n = sh[2];
     const int groups = sh[3], gidx = sh[4];
-    c.cnt = a.sync + 64 * (sh[5] + 1);
     const int per = (a.B + groups - 1) / groups;  // samples per group
     if (per > RW_ROWS) {                           // fewer groups than the host planned for
         if (c.tid == 0) __hip_atomic_store(c.status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -579,22 +554,28 @@ __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
     c.row0 = gidx * per;
     c.nrows = a.B - c.row0 < per ? a.B - c.row0 : per;
     c.rb0 = gidx * MB;
+    c.cw = W / 4 <= c.n ? 4 : (W / 8 <= c.n ? 8 : 16);
     if (c.nrows <= 0) return;                      // groups are independent: an idle one just leaves
+    // a member without a share of any stage leaves as well: nobody reads anything of it
+    // (the MLP input has the most column blocks, W / 4; a unit of the residual projections has at least four columns)
+    if (c.slot >= W / 4 && c.slot >= c.nrows * (W / 64)) return;
 
     const int T = a.T, D = a.D;
-    HT *qkv = reinterpret_cast<HT *>(a.qkv), *o = reinterpret_cast<HT *>(a.o), *ff = reinterpret_cast<HT *>(a.ff);
-    const uint32_t ws_rows = 8u * RW_ROWS;
-    const rsrc_t qkv_rs = make_rsrc(qkv, ws_rows * 3u * W * 2u);
-    const rsrc_t o_rs = make_rsrc(o, ws_rows * W * 2u);
-    const rsrc_t ff_rs = make_rsrc(ff, ws_rows * (uint32_t)a.ratio * W * 2u);
-    volatile int *sh_ok = &sh[6];
+    constexpr uint32_t UW = 8u * RW_ROWS * W;      // elements of one slot of a buffer of width W
+    const rsrc_t ws = make_rsrc(a.ws, UW * kSeqWsBytesPerElem);
+    auto off_h = [&](int s) { return (uint32_t)(s & 3) * (4u * UW); };                  // stream: embedding, MLP output
+    auto off_a = [&](int s) { return (16u + (uint32_t)s * 4u) * UW; };                  // stream: attention output
+    auto off_q = [&](int s) { return (28u + (uint32_t)s * 6u) * UW; };
+    auto off_o = [&](int s) { return (46u + (uint32_t)s * 2u) * UW; };
+    auto off_f = [&](int s) { return (52u + (uint32_t)s * 8u) * UW; };
+    const int cw = c.cw, nu = W / cw;
     // this member's slices of the embedding matrix and bias stay in LDS for the whole block
-    for (int bi = 0, cb = c.slot; bi < P_EB && cb < W / 16; ++bi, cb += c.n)
-        for (int e = c.tid; e < (D + 1) * 16; e += P_THREADS) {
-            const int d = e >> 4, cl = e & 15;
-            wemb[(size_t)bi * (D + 1) * 16 + e] = d < D ? a.w_in[(size_t)d * W + cb * 16 + cl] : a.b_in[cb * 16 + cl];
+    for (int bi = 0, u = c.slot; bi < P_EB && u < nu; ++bi, u += c.n)
+        for (int e = c.tid; e < (D + 1) * cw; e += P_THREADS) {
+            const int d = e / cw, cl = e - d * cw;
+            wemb[bi * (D + 1) * 16 + e] = d < D ? a.w_in[(size_t)d * W + u * cw + cl] : a.b_in[u * cw + cl];
         }
-    // latent values of position 0 (each thread keeps the ones it will turn into x)
+    // latent values of position 0 (each thread keeps the ones it will turn into x), position embedding likewise
     constexpr int ZPT = (RW_ROWS * 64 + P_THREADS - 1) / P_THREADS;   // token sizes up to 64
     float zreg[ZPT];
 #pragma unroll
@@ -606,24 +587,16 @@ __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
             if (row < c.nrows) zreg[q] = a.z[((size_t)(c.row0 + row) * T + (a.reversed ? T - 1 : 0)) * D + d];
         }
     }
+    const int er = c.tid / cw, ec = c.tid - er * cw;     // embedding: row and column of a unit (512 threads: 32 x 16 at most)
+    float pos0 = c.slot < nu ? a.pos[c.slot * cw + ec] : 0.f;
     __syncthreads();
-    Ctx ch = c;      // the head projection: every member takes every column block
-    ch.slot = 0; ch.n = 1;
 
+    int s3 = 0, hq = 0, par = 0;
     for (int l = 0; l < T; ++l) {
-#ifdef SJD_SEQ_TIMELINE
-        Ctx &cm = const_cast<Ctx &>(c);
-        cm.tl_on = gidx == 0 && c.slot == 0 && l == T / 2;
-        cm.tl = a.sync + 640; cm.tl_t0 = wall_clock64(); cm.tl_k = &sh[7]; if (c.tid == 0) sh[7] = 0;
-#endif
         // ---- x_l of the group's samples (eq. 5; x_0 = z_0), kept in LDS for the embedding; the latent
         // values were requested one step ahead
         const int tok = a.reversed ? T - 1 - l : l;
         const int tok_next = a.reversed ? T - 2 - l : l + 1;
-        // The residual stream lives in two copies that alternate with the step: the embedding of step l+1
-        // is written while slower members may still read the stream of step l for their head projection.
-        float *hs = a.hs + (size_t)(l & 1) * ws_rows * W;
-        const rsrc_t hs_rs = make_rsrc(hs, ws_rows * W * 4u);
 #pragma unroll
         for (int q = 0; q < ZPT; ++q) {
             const int e = c.tid + q * P_THREADS;
@@ -642,114 +615,95 @@ __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
         }
         if (l == T - 1) break;
         __syncthreads();
-        // ---- embedding of this member's column blocks: hs = x_l * w_in + b_in + pos[l]
+        // ---- embedding of this member's units: stream = x_l * w_in + b_in + pos[l]
         {
             int bi = 0;
-            for (int cb = c.slot; cb < W / 16; cb += c.n, ++bi) {
-                for (int e = c.tid; e < RW_ROWS * 16; e += P_THREADS) {
-                    const int row = e >> 4, cl = e & 15, col = cb * 16 + cl;
-                    float acc = a.pos[(size_t)l * W + col];
+            for (int u = c.slot; u < nu; u += c.n, ++bi) {
+                const int col = u * cw + ec;
+                if (er < c.nrows) {
+                    float acc = bi == 0 ? pos0 : a.pos[(size_t)l * W + col];
                     if (bi < P_EB) {
-                        const float *we = wemb + (size_t)bi * (D + 1) * 16;
-                        acc += we[D * 16 + cl];
-                        for (int d = 0; d < D; ++d) acc = fmaf(xs[row * D + d], we[d * 16 + cl], acc);
+                        const float *we = wemb + bi * (D + 1) * 16;
+                        acc += we[D * cw + ec];
+                        for (int d = 0; d < D; ++d) acc = fmaf(xs[er * D + d], we[d * cw + ec], acc);
                     } else {
                         acc += a.b_in[col];
-                        for (int d = 0; d < D; ++d) acc = fmaf(xs[row * D + d], a.w_in[(size_t)d * W + col], acc);
+                        for (int d = 0; d < D; ++d) acc = fmaf(xs[er * D + d], a.w_in[(size_t)d * W + col], acc);
                     }
-                    hs[frag_off(c.rb0 * 16 + row, col, W / 32)] = acc;
+                    const uint32_t eo = (uint32_t)frag_off(c.rb0 * 16 + er, col, W / 32) * 4u;
+                    st4(ws, off_h(hq) + eo, flagged(acc));
+                    st4(ws, off_h(hq + 2) + eo, -1);            // slot of use hq - 2
+                    if (bi == 0 && l + 1 < T) pos0 = a.pos[(size_t)(l + 1) * W + col];
                 }
             }
         }
-        // Weights of a stage are requested one stage ahead where the registers allow it (W <= 512),
-        // else at the start of the stage itself.
-        constexpr bool AHEAD = S <= 2;
-        LnPre<HT, S> wln;
-        ResPre<HT, S, 1> wo;
-        ResPre<HT, S, 4> wf2;
-        if (AHEAD) ln_prefetch<HT, S>(c, (const HT *)a.layers[0].f_qkv, 3 * W, c.slot, wln);
-        SJD_TLC(c);
-        if (!group_barrier(c, sh_ok)) return;
-        SJD_TLC(c);
-
         for (int ly = 0; ly < a.n_layers; ++ly) {
             const SeqLayer &lw = a.layers[ly];
             HT *kc = reinterpret_cast<HT *>(a.kcache) + (size_t)ly * a.kv_layer_stride;
             HT *vc = reinterpret_cast<HT *>(a.vcache) + (size_t)ly * a.kv_layer_stride;
             const rsrc_t kc_rs = make_rsrc(kc, (uint32_t)(a.kv_layer_stride * 2u));
             const rsrc_t vc_rs = make_rsrc(vc, (uint32_t)(a.kv_layer_stride * 2u));
-            if (!AHEAD) ln_prefetch<HT, S>(c, (const HT *)lw.f_qkv, 3 * W, c.slot, wln);
-            ln_gemm_stage<HT, MB, S, EPI_BIAS, HT>(c, hs_rs, lw.ln1_g, lw.ln1_b, (const HT *)lw.f_qkv, lw.b_qkv, qkv,
-                                                  3 * W, red, stat, wln, NoPrefetch());
-            SJD_TLC(c);
-            if (!group_barrier(c, sh_ok)) return;
-            SJD_TLC(c);
-            if (AHEAD) res_prefetch<HT, S, 1>(c, (const HT *)lw.f_o, c.slot, wo);
-            attention_stage<HT, S>(c, qkv_rs, kc, vc, kc_rs, vc_rs, o, l, T, sc, opart, wred);
-            SJD_TLC(c);
-            if (!group_barrier(c, sh_ok)) return;
-            SJD_TLC(c);
-            if (!AHEAD) res_prefetch<HT, S, 1>(c, (const HT *)lw.f_o, c.slot, wo);
-            gemm_resid_stage<HT, MB, S, 1>(c, o_rs, (const HT *)lw.f_o, lw.b_o, hs_rs, hs, red, wo, [&]() {
-                if (AHEAD) ln_prefetch<HT, S>(c, (const HT *)lw.f_fc1, 4 * W, c.slot, wln);
-            });
-            SJD_TLC(c);
-            if (!group_barrier(c, sh_ok)) return;
-            SJD_TLC(c);
-            if (!AHEAD) ln_prefetch<HT, S>(c, (const HT *)lw.f_fc1, 4 * W, c.slot, wln);
-            ln_gemm_stage<HT, MB, S, EPI_BIAS_GELU, HT>(c, hs_rs, lw.ln2_g, lw.ln2_b, (const HT *)lw.f_fc1, lw.b_fc1, ff,
-                                                       4 * W, red, stat, wln, [&]() {
-                if (AHEAD) res_prefetch<HT, S, 4>(c, (const HT *)lw.f_fc2, c.slot, wf2);
-            });
-            SJD_TLC(c);
-            if (!group_barrier(c, sh_ok)) return;
-            SJD_TLC(c);
-            const bool last = ly + 1 == a.n_layers;
-            const HT *next_w = (const HT *)(last ? a.f_head : a.layers[last ? ly : ly + 1].f_qkv);
-            const int next_n = last ? 2 * D : 3 * W;
-            if (!AHEAD) res_prefetch<HT, S, 4>(c, (const HT *)lw.f_fc2, c.slot, wf2);
-            gemm_resid_stage<HT, MB, S, 4>(c, ff_rs, (const HT *)lw.f_fc2, lw.b_fc2, hs_rs, hs, red, wf2, [&]() {
-                if (AHEAD) { if (last) ln_prefetch<HT, S>(ch, next_w, next_n, 0, wln); else ln_prefetch<HT, S>(c, next_w, next_n, c.slot, wln); }
-            });
-            SJD_TLC(c);
-            if (!group_barrier(c, sh_ok)) return;
-            SJD_TLC(c);
+            const int e3 = s3 == 0 ? 2 : s3 - 1;                // slot of the use before this one
+            ln_gemm_stage<HT, MB, S, CB, EPI_BIAS, false>(c, ws, off_h(hq), lw.ln1_g, lw.ln1_b, (const HT *)lw.f_qkv, lw.b_qkv,
+                                                               off_q(s3), off_q(e3), nullptr, 3 * W, red, stat);
+            attention_stage<HT, MB, S>(c, ws, off_q(s3), kc, vc, kc_rs, vc_rs, off_o(s3), off_o(e3), l, T, opart, wst, par);
+            gemm_resid_stage<HT, MB, S, 1>(c, ws, off_o(s3), (const HT *)lw.f_o, lw.b_o, off_h(hq), off_a(s3), off_a(e3), red2);
+            ln_gemm_stage<HT, MB, S, CB, EPI_BIAS_GELU, false>(c, ws, off_a(s3), lw.ln2_g, lw.ln2_b, (const HT *)lw.f_fc1, lw.b_fc1,
+                                                                    off_f(s3), off_f(e3), nullptr, 4 * W, red, stat);
+            gemm_resid_stage<HT, MB, S, 4>(c, ws, off_f(s3), (const HT *)lw.f_fc2, lw.b_fc2, off_a(s3), off_h(hq + 1), off_h(hq + 3), red2);
+            ++hq;
+            s3 = s3 == 2 ? 0 : s3 + 1;
         }
         // ---- head: every member computes all of [mu | alpha] for the group's rows (a few column blocks)
-        // into its own LDS, so that x_l and the next embedding follow without another group barrier
-        if (!AHEAD) ln_prefetch<HT, S>(ch, (const HT *)a.f_head, 2 * D, 0, wln);
-        ln_gemm_stage<HT, MB, S, EPI_BIAS, float, NoPrefetch, true>(ch, hs_rs, a.lnf_g, a.lnf_b, (const HT *)a.f_head, a.b_head,
-                                                                   pl, 2 * D, red, stat, wln, NoPrefetch());
-        SJD_TLC(c);
-        SJD_TLC(c);
+        // into its own LDS, so that x_l and the next embedding follow without another exchange
+        ln_gemm_stage<HT, MB, S, CBH, EPI_BIAS, true>(c, ws, off_h(hq), a.lnf_g, a.lnf_b, (const HT *)a.f_head, a.b_head, 0, 0,
+                                                           pl, 2 * D, red, stat);
+        ++hq;
+        __syncthreads();
+        if (*c.bad) return;
     }
+}
+
+// Every buffer empty, the synchronisation words zero (a kernel: memory operations of the runtime stay out of the path).
+__global__ __launch_bounds__(256) void seq_reset_kernel(uint4 *ws, size_t n16, int *sync) {
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (size_t)gridDim.x * 256)
+        ws[i] = uint4{kEmpty, kEmpty, kEmpty, kEmpty};
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < 1024; i += 256) sync[i] = 0;
 }
 
 }  // namespace
 
-size_t seq_persistent_lds_bytes(int MB, int T, int D) {
-    size_t need = (size_t)P_NW * P_CB * MB * 64 * 16 + (size_t)P_NW * MB * 16 * 4 + (size_t)16 * MB * D * 4 +
-                  (size_t)P_NW * 64 * 4 + 16 * 4 + (size_t)2 * T * 4 + (size_t)P_EB * (D + 1) * 16 * 4 + (size_t)16 * MB * 2 * D * 4;
+size_t seq_persistent_lds_bytes(int MB, int D) {
+    const size_t need = (size_t)P_NW * 4 * MB * 64 * 16 + (size_t)P_NW * MB * 64 * 16 + (size_t)P_NW * MB * 16 * 8 + 2 * P_NW * 8 +
+                        (size_t)2 * P_NW * 64 * 4 + (size_t)16 * MB * D * 4 + (size_t)P_EB * (D + 1) * 16 * 4 + (size_t)16 * MB * 2 * D * 4;
     const size_t one_per_cu = 84 * 1024;  // more than half of a CU's LDS: exactly one workgroup per CU
-    if (need < one_per_cu) need = one_per_cu;
-    return (need + 255) & ~(size_t)255;
+    return ((need < one_per_cu ? one_per_cu : need) + 255) & ~(size_t)255;
 }
 
 template <typename HT>
-static const void *pick_kernel(int MB, int S) {
-#define SJD_PK(MBv, Sv) if (MB == MBv && S == Sv) return reinterpret_cast<const void *>(&seq_persistent_kernel<HT, MBv, Sv>);
-    SJD_PK(1, 1) SJD_PK(1, 2) SJD_PK(1, 3) SJD_PK(1, 4) SJD_PK(2, 1) SJD_PK(2, 2) SJD_PK(2, 3) SJD_PK(2, 4)
+static const void *pick_kernel(int MB, int S, int CB) {
+#define SJD_PK(MBv, Sv, CBv) if (MB == MBv && S == Sv && CB == CBv) return reinterpret_cast<const void *>(&seq_persistent_kernel<HT, MBv, Sv, CBv>);
+#define SJD_PS(Sv) SJD_PK(1, Sv, 1) SJD_PK(1, Sv, 2) SJD_PK(1, Sv, 4) SJD_PK(2, Sv, 4)
+    SJD_PS(1) SJD_PS(2) SJD_PS(3) SJD_PS(4)
+#undef SJD_PS
 #undef SJD_PK
     return nullptr;
 }
 
 hipError_t launch_seq_persistent(bool is_bf16, const SeqArgs &args, int MB, int S, int grid, bool cooperative,
                                  hipStream_t s) {
-    const void *kern = is_bf16 ? pick_kernel<bf16>(MB, S) : pick_kernel<f16>(MB, S);
+    // column blocks of a LayerNorm-fused projection per round: as many as a member of a group has of the widest one
+    const int members = grid / 8 * args.xpg, blocks = 64 * S;
+    const int per = members > 0 ? (blocks + members - 1) / members : blocks;
+    const int CB = MB == 2 || per > 2 ? 4 : per;
+    const void *kern = is_bf16 ? pick_kernel<bf16>(MB, S, CB) : pick_kernel<f16>(MB, S, CB);
     if (!kern) return hipErrorInvalidValue;
-    const size_t lds = seq_persistent_lds_bytes(MB, args.T, args.D);
+    const size_t lds = seq_persistent_lds_bytes(MB, args.D);
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(seq_reset_kernel, dim3(512), dim3(256), 0, s, (uint4 *)args.ws,
+                       seq_persistent_ws_bytes(MB, 256 * S) / 16, args.sync);
     SeqArgs a = args;
     void *params[] = {&a};
     if (cooperative) return hipLaunchCooperativeKernel(kern, dim3(grid), dim3(P_THREADS), params, (unsigned)lds, s);

@@ -93,6 +93,7 @@ struct sjd_flow {
     int mask_nearest = 0;        // o of the masked-dependency probe (eq. 6); 0: plain causal attention
     int seq_path = 0;            // 0 automatic, 1 per-step launches (graph replay), 2 persistent kernel, 3 the same, plain launch
     int *psync = nullptr;        // synchronisation words of the persistent kernel (1024 ints)
+    void *seq_ws = nullptr;      // its activations
     int n_cus = 0, n_cus_device = 0, coop = 0;   // workgroups of the persistent kernel; CUs of the device
     hipEvent_t ev[SJD_MAX_BLOCKS + 1] = {};
     // profiling
@@ -670,13 +671,27 @@ int run_sequential_fast(sjd_flow *f, int j, const float *z, float *x, int batch,
     return SJD_OK;
 }
 
-// The persistent kernel covers: 16-bit modes, head size 64, W in {256, 512, 768, 1024}, MLP ratio 4, batch <= 256,
+// The persistent kernel covers: 16-bit modes, head size 64, W in {256, 512, 768, 1024}, MLP ratio 4, batch <= 256, token size up to 64,
 // a cooperative launch of one workgroup per CU, and per-layer caches below 4 GiB (32-bit offsets).
 bool persistent_ok(const sjd_flow *f, int batch) {
     const sjd_config &c = f->cfg;
     return frag_ok(f, batch) && f->coop && f->n_cus >= 8 && batch <= 256 && c.token_dim <= 64 && c.mlp_ratio == 4 && c.n_layers <= kSeqMaxLayers &&
            (size_t)c.max_batch * c.seq_len * c.width * 2 < ((size_t)1 << 32) &&
-           seq_persistent_lds_bytes(batch <= 128 ? 1 : 2, c.seq_len, c.token_dim) <= 160 * 1024;
+           seq_persistent_lds_bytes(batch <= 128 ? 1 : 2, c.token_dim) <= 160 * 1024;
+}
+
+// XCDs per group of the persistent kernel.  More of them spread a stage's weights over more CUs and read them from memory
+// fewer times, but exchanges between XCDs take longer (2.4 us against 1.5 to 2) and a group then has more rows to pass
+// round.  Microseconds a step with 8 / 4 / 2 / 1 XCDs per group: width 1024, 2 layers: one sample 43 / 46 / 50 / 73, 16 samples 54 / 52 / 61 /
+// 80, 64 samples - / - / 108 / 128; width 768, 2 layers, 32 samples - / 51 / 52 / 65; width 512, 4 layers: one sample 59 / 58 / 63 / 70, 16 samples
+// 78 / 73 / 70 / 73; width 256, 4 layers, 32 samples - / 70 / 62 / 57.  A group holds at most sixteen samples (one row block of the matrix
+// instruction) unless the batch leaves no choice.
+int seq_xcds_per_group(const sjd_flow *f, int batch) {
+    const int W = f->cfg.width;
+    int x = W <= 256 ? 1 : W <= 512 ? 2 : 4;
+    if (batch <= 4 && W > 256) x *= 2;
+    while (x > 1 && (batch * x + 7) / 8 > 16) x /= 2;
+    return x;
 }
 
 int run_sequential_persistent(sjd_flow *f, int j, const float *z, float *x, int batch, hipStream_t s) {
@@ -693,19 +708,19 @@ int run_sequential_persistent(sjd_flow *f, int j, const float *z, float *x, int 
     a.lnf_g = bw.lnf_g; a.lnf_b = bw.lnf_b; a.b_head = bw.b_head; a.f_head = bw.f_head;
     a.w_in = bw.w_in; a.b_in = bw.b_in; a.pos = bw.pos;
     a.z = z; a.x = x;
-    a.hs = f->h; a.qkv = f->qkv; a.o = f->o; a.ff = f->f; a.p = f->p;
+    a.ws = f->seq_ws;
+    a.xpg = seq_xcds_per_group(f, batch);
     a.kcache = f->kcache; a.vcache = f->vcache;
     a.kv_layer_stride = (size_t)c.max_batch * c.seq_len * c.width;
     a.B = batch; a.T = c.seq_len; a.D = c.token_dim; a.reversed = (c.reverse_mask >> j) & 1;
     a.sync = f->psync;
-    a.spin_max = 1 << 21;  // a poll takes ~0.5 us: about a second before a barrier gives up
+    a.spin_max = 1 << 20;  // a poll takes about 1 us: about a second before a wait gives up
     const double steps = c.seq_len - 1.0, W = c.width, R = c.mlp_ratio;
     const double wbytes = c.n_layers * (4.0 + 2.0 * R) * W * W * 2.0 + 2.0 * c.token_dim * W * 2.0;
     const double kvbytes = (double)c.n_layers * batch * (c.seq_len / 2.0) * W * 2.0 * 2.0;
     ProfScope ps(f, SJD_PROF_DECODE_FUSED, steps * 2.0 * batch * (c.n_layers * (4.0 + 2.0 * R) * W * W + 2.0 * c.token_dim * W) +
                                                steps * 4.0 * batch * (c.seq_len / 2.0) * W * c.n_layers,
                  steps * (wbytes + kvbytes), s);
-    HIP_TRY(hipMemsetAsync(f->psync, 0, 1024 * sizeof(int), s));
     hipError_t e = launch_seq_persistent(c.dtype == SJD_DTYPE_BF16, a, MB, c.width / 256, f->n_cus, f->seq_path != 3, s);
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -719,7 +734,7 @@ int run_sequential_persistent(sjd_flow *f, int j, const float *z, float *x, int 
     HIP_TRY(hipGetLastError());
     if (f->host_pin[0] != 0) {
         fail(SJD_EHIP, "persistent sequential kernel: %s",
-             f->host_pin[0] == 2 ? "fewer XCD groups than planned for" : "a group barrier timed out");
+             f->host_pin[0] == 2 ? "fewer XCD groups than planned for" : "a wait for other workgroups timed out");
         // every wave has left the kernel (bounded waits); z is untouched and x, the caches and the workspaces are
         // simply written again, so in automatic mode the caller runs the block by per-step launches instead
         return SJD_ELAUNCH_RETRY;
@@ -734,11 +749,10 @@ int run_sequential(sjd_flow *f, int j, const float *z, float *x, int batch, hipS
     if (f->mask_nearest == 0) {   // the masked probe takes the plain per-step path below in every mode
         if (f->seq_path >= 2 && !persistent_ok(f, batch))
             return fail(SJD_EINVAL, "the persistent sequential kernel does not cover this configuration");
-        // automatic choice: the persistent kernel, except for long sequences at the largest width, where its
-        // attention stage (two pairs at a time per CU) and the eightfold weight traffic lose to per-step
-        // launches (measured: T = 1024, W = 1024, 32 samples: 541 ms against 505 ms)
-        const bool prefer_steps = f->seq_path == 0 && f->cfg.seq_len > 512 && f->cfg.width >= 1024;
-        if (f->seq_path != 1 && !prefer_steps && persistent_ok(f, batch)) {
+        // automatic choice: the persistent kernel wherever it applies (microseconds a step against per-step launches: width
+        // 1024, 8 layers, 1024 tokens, 32 samples 284 against 340; 2 layers, 256 tokens, 256 samples 175 against 247; width 256,
+        // 4 layers, 512 tokens, one sample 55 against 93)
+        if (f->seq_path != 1 && persistent_ok(f, batch)) {
             const int rc = run_sequential_persistent(f, j, z, x, batch, s);
             if (rc != SJD_ELAUNCH_RETRY) return rc;
             if (f->seq_path != 0) return SJD_EHIP;      // the persistent kernel was asked for explicitly
@@ -817,6 +831,7 @@ int sjd_flow_create(const sjd_config *cfg, sjd_flow **out) {
     A((void **)&f->active[1], B * 4);
     A((void **)&f->trace, 2 * T * B * 4);
     A((void **)&f->psync, 1024 * sizeof(int));
+    if (frag_ok(f, 0)) A(&f->seq_ws, seq_persistent_ws_bytes(B <= 128 ? 1 : 2, (int)W));
     {
         hipDeviceProp_t prop;
         if (rc == SJD_OK && hipGetDeviceProperties(&prop, f->device) == hipSuccess) {
@@ -1250,12 +1265,6 @@ int sjd_op_attention_h16(int dtype, const void *qkv_dev, void *o_dev, int n_samp
     HIP_TRY(hipGetLastError());
     return SJD_OK;
 }
-
-#ifdef SJD_SEQ_TIMELINE
-extern "C" __attribute__((visibility("default"))) int sjd_debug_read_sync(sjd_flow *f, int *out1024) {
-    return hipMemcpy(out1024, f->psync, 1024 * sizeof(int), hipMemcpyDeviceToHost) == hipSuccess ? 0 : -1;
-}
-#endif
 
 int sjd_flow_set_projection_path(sjd_flow *f, int path) {
     if (!f) return fail(SJD_EINVAL, "null flow");

@@ -100,3 +100,53 @@ def test_persistent_kernel_gives_the_same_bits_with_fewer_workgroups(torch_cuda)
             f.set_sequential_cus(n)
             assert torch.equal(f.sequential_inverse_block(j, zd), ref), (j, n)
     f.close()
+
+
+def _flow(batch, tokens, dim, layers, width, seed):
+    import paper_2505_24791_amd as sjd
+    import torch
+    cfg = wl.FlowConfig("groups", n_blocks=1, n_layers=layers, width=width, n_heads=width // 64, seq_len=tokens,
+                        token_dim=dim, batch=batch, bf16=True)
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    f = sjd.Flow(cfg)
+    f.load_weights(blob)
+    return cfg, blob, f, torch.from_numpy(wl.make_latent(cfg, seed=seed)).cuda()
+
+
+@pytest.mark.parametrize("batch,tokens,dim,layers,width", [
+    (2, 12, 64, 1, 1024),      # eight XCDs per group, one column unit per member, the largest token size
+    (3, 300, 5, 2, 512),       # four; more than one batch of cached keys per key group
+    (33, 9, 12, 1, 768),       # two, seventeen rows would not fit: nine per group
+    (100, 17, 7, 1, 768),      # one; several rounds of column blocks
+    (130, 14, 48, 1, 1024),    # one, two row blocks per group, the last one nearly empty
+    (1, 600, 3, 1, 256),       # three batches of cached keys, most members without any work
+])
+def test_persistent_kernel_over_its_group_sizes(torch_cuda, orc32, batch, tokens, dim, layers, width):
+    print(f"case B {batch} T {tokens} D {dim} N {layers} W {width}", flush=True)
+    cfg, blob, f, z = _flow(batch, tokens, dim, layers, width, seed=45)
+    f.set_sequential_path(2)
+    x = f.sequential_inverse_block(0, z)
+    assert torch_cuda.equal(f.sequential_inverse_block(0, z), x)
+    one = f.sequential_inverse_block(0, z[-1:].contiguous())          # another group size, the same bits
+    assert torch_cuda.equal(one[0], x[-1])
+    f.set_sequential_path(1)
+    assert (f.sequential_inverse_block(0, z) - x).abs().max().item() <= 2 * TOL
+    for b in {0, batch - 1}:
+        ref = orc32.sequential_inverse_block(cfg, blob, 0, z[b].cpu().numpy())
+        assert np.abs(x[b].cpu().numpy() - ref).max() <= TOL, b
+    f.close()
+
+
+def test_persistent_kernel_passes_every_nan_pattern_on(torch_cuda):
+    """The kernel marks empty words by a NaN pattern: a sample that is full of exactly that pattern must neither stop the others
+    nor change them."""
+    torch = torch_cuda
+    _, _, f, z = _flow(11, 15, 6, 2, 512, seed=46)
+    f.set_sequential_path(2)
+    clean = f.sequential_inverse_block(0, z)
+    z[4].view(torch.int32).fill_(-1)
+    x = f.sequential_inverse_block(0, z)
+    assert torch.isnan(x[4]).all()
+    keep = [b for b in range(11) if b != 4]
+    assert torch.equal(x[keep], clean[keep])
+    f.close()
