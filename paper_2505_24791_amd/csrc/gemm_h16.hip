@@ -372,6 +372,148 @@ __global__ __launch_bounds__(256, 1) void gemm_h16_dma_kernel(const HT *__restri
     tile_epilogue<HT, MI, NI, BN, OutT, EPI>(acc, smem_raw, bias, resid, C, M, N, m0 + wm * 128, n0 + wn * 128, lane, wave);
 }
 
+// ------------------------------------------------------------------------------------------------
+// Small tiles, k-tiles of 64 in a ring of ST LDS stages filled by LDS-direct loads up to ST - 1 k-tiles ahead.  For
+// launches that do not fill the chip (one sample's rows, the late passes of a block, narrow flows) time is the latency of one
+// workgroup walking k: many small tiles, every load far ahead of its use, fragments of the next k-tile read under
+// the matrix instructions of this one.  Layout and swizzle of a stage, and the order of k, are those of the
+// kernel above: same bits.
+template <int N> __device__ __forceinline__ void wait_loads() {          // vmcnt(N) lgkmcnt(0)
+    __builtin_amdgcn_s_waitcnt((N & 15) | 0x70 | ((N >> 4) << 14));
+}
+template <int LPW, int R> __device__ __forceinline__ void wait_tiles(int r) {   // until at most r <= R k-tiles are under way
+    if constexpr (R == 0) wait_loads<0>();
+    else if (r >= R) wait_loads<R * LPW>();
+    else wait_tiles<LPW, R - 1>(r);
+}
+
+template <typename HT, int BM, int BN, int ST, typename OutT, int EPI>
+__global__ __launch_bounds__(256) void gemm_h16_ring_kernel(const HT *__restrict__ A, const HT *__restrict__ Bt,
+                                                            const float *__restrict__ bias, const float *resid, OutT *C,
+                                                            int M, int N, int K, int tiles_n, int n_tiles) {
+    typedef typename Half16<HT>::v8 v8;
+    constexpr int BK = 64, KSUB = BK / 16, MI = BM / 64, NI = BN / 64;
+    constexpr int LA = BM / 32, LB = BN / 32, LPW = LA + LB;   // 1 KB loads (8 rows x 128 bytes) per wave and k-tile
+    constexpr int STB = (BM + BN) * 128;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+
+    const int tile = xcd_tile(blockIdx.x, n_tiles);
+    if (tile >= n_tiles) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    const int tm = tile / tiles_n, tn = tile - tm * tiles_n;
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int KT = K / BK;
+
+    const int lr = lane >> 3, lc0 = (lane & 7) ^ ((lr >> 1) & 3);
+    const uint32_t row_bytes = (uint32_t)K * 2u;
+    uint32_t a_off[LA], b_off[LB];
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        const int blk = wave * LA + i;
+        int row = blk * 8 + lr;
+        row = row < M - 1 - m0 ? row : M - 1 - m0;             // rows past the end: re-read the last row, never stored
+        a_off[i] = (uint32_t)row * row_bytes + (uint32_t)((lc0 ^ (((blk >> 1) & 1) << 2)) * 16);
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        const int blk = wave * LB + i;
+        b_off[i] = (uint32_t)(blk * 8 + lr) * row_bytes + (uint32_t)((lc0 ^ (((blk >> 1) & 1) << 2)) * 16);
+    }
+    const char *a_base = reinterpret_cast<const char *>(A + (size_t)m0 * K);
+    const char *b_base = reinterpret_cast<const char *>(Bt + (size_t)n0 * K);   // Bt rows are padded up to the tile
+    const uint32_t lds0 = (uint32_t)(uintptr_t)SJD_LPTR(smem_raw);
+    // 64 lanes x 16 bytes from a wave-uniform base plus a 32-bit lane offset to 1 KB of LDS (see gemm_p8.hip)
+    auto dma = [&](const char *base, uint32_t off, uint32_t lds_addr) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     :: "s"(lds_addr), "v"(off), "s"(base) : "memory");
+    };
+    auto request = [&](int kt, int stage) {
+        const uint32_t st = lds0 + (uint32_t)(stage * STB);
+#pragma unroll
+        for (int i = 0; i < LA; ++i) dma(a_base + (size_t)kt * (BK * 2), a_off[i], st + (uint32_t)((wave * LA + i) * 1024));
+#pragma unroll
+        for (int i = 0; i < LB; ++i) dma(b_base + (size_t)kt * (BK * 2), b_off[i], st + (uint32_t)(BM * 128 + (wave * LB + i) * 1024));
+    };
+    struct Frags { v8 a[KSUB][MI], b[KSUB][NI]; };
+    const int swz = ((l32 >> 1) & 3) | (((l32 >> 4) & 1) << 2);
+    auto read = [&](int stage, Frags &f) {
+        const unsigned char *st = smem_raw + stage * STB;
+#pragma unroll
+        for (int ks = 0; ks < KSUB; ++ks) {
+            const int o = l32 * 128 + (((2 * ks + g) ^ swz) << 4);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) f.a[ks][i] = *reinterpret_cast<const v8 *>(st + (wm * MI + i) * 4096 + o);
+#pragma unroll
+            for (int j = 0; j < NI; ++j) f.b[ks][j] = *reinterpret_cast<const v8 *>(st + BM * 128 + (wn * NI + j) * 4096 + o);
+        }
+    };
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NI; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    auto multiply = [&](const Frags &f) {
+#pragma unroll
+        for (int ks = 0; ks < KSUB; ++ks)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NI; ++j) acc[i][j] = Half16<HT>::mfma(f.a[ks][i], f.b[ks][j], acc[i][j]);
+    };
+
+    Frags f0, f1;
+#pragma unroll
+    for (int t = 0; t < ST; ++t)
+        if (t < KT) request(t, t);
+    wait_tiles<LPW, ST - 1>(KT - 1);          // the first k-tile has landed
+    __builtin_amdgcn_s_barrier();
+    read(0, f0);
+    // k-tile kt: its fragments are on their way into `cur`.  Wait for them and for this wave's loads of k-tile kt + 1, then the
+    // barrier: k-tile kt + 1 is complete and nobody reads the stage of kt any more, so kt + ST is requested into it.
+    int stage = 0;
+    auto step = [&](int kt, Frags &cur, Frags &nxt) {
+        const int ns = stage + 1 == ST ? 0 : stage + 1;
+        if (kt + 1 < KT) {
+            wait_tiles<LPW, ST - 2>(KT - 2 - kt);
+            __builtin_amdgcn_s_barrier();
+            read(ns, nxt);
+            if (kt + ST < KT) request(kt + ST, stage);
+        }
+        multiply(cur);
+        stage = ns;
+    };
+    for (int kt = 0; kt < KT; kt += 2) {
+        step(kt, f0, f1);
+        if (kt + 1 < KT) step(kt + 1, f1, f0);
+    }
+    __builtin_amdgcn_s_waitcnt(0);            // all loads have landed and all reads are done before LDS is reused
+    __syncthreads();
+    tile_epilogue<HT, MI, NI, BN, OutT, EPI>(acc, smem_raw, bias, resid, C, M, N, m0 + wm * (BM / 2), n0 + wn * (BN / 2), lane, wave);
+}
+
+template <typename HT, int BM, int BN, int ST, typename OutT, int EPI>
+static void launch_ring(const HT *A, const HT *Bt, const float *bias, const float *resid, OutT *C, int M, int N, int K,
+                        hipStream_t s) {
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+    const int n_tiles = tiles_m * tiles_n;
+    const int grid = ((n_tiles + 7) / 8) * 8;
+    size_t smem = (size_t)ST * (BM + BN) * 128;
+    const size_t ep = (size_t)4 * 32 * (BN / 2 + 4) * sizeof(float);  // epilogue parking space
+    if (smem < ep) smem = ep;
+    auto kern = gemm_h16_ring_kernel<HT, BM, BN, ST, OutT, EPI>;
+    static std::atomic<bool> attr_set{false};   // callers may come from several host threads
+    if (!attr_set.load(std::memory_order_acquire)) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        attr_set.store(true, std::memory_order_release);
+    }
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(256), smem, s, A, Bt, bias, resid, C, M, N, K, tiles_n, n_tiles);
+}
+
 template <typename HT, typename OutT, int EPI>
 static void launch_dma(const HT *A, const HT *Bt, const float *bias, const float *resid, OutT *C, int M, int N, int K,
                        hipStream_t s) {
@@ -412,8 +554,8 @@ static void launch_tile(const HT *A, const HT *Bt, const float *bias, const floa
 //     (GELU: 648 vs 606; float32 residual with K = 1024: 610 vs 578) and for K <= 768;
 //   256x256x32 LDS-direct, one workgroup per CU: best main loop (K = 4096: 1025 vs 820) - used when
 //     the k-loop dominates.
-//   128x128x64 covers small problems.  Weight matrices are padded to 256 rows, so tiles never read
-//   past a matrix.
+//   64x64 and 64x128 rings, 128x128x64: launches that do not fill the chip (see below).  Weight matrices are padded to 256
+//   rows, so tiles never read past a matrix.
 template <typename HT, typename OutT, int EPI>
 static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float *resid, OutT *C, int M, int N, int K,
                       int kernel, hipStream_t s) {
@@ -426,9 +568,19 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
     if (kernel == 4 && p8_ok) return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
     const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
-    // the persistent kernel from one 256x256 tile per CU on (measured on the workloads' shapes: +15..30 % at
-    // K <= 1024, even at K = 4096; with fewer tiles the finer grain of the kernels below wins)
-    if (p8_ok && t256 >= 256) return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
+    const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64), t64x128 = (long)((M + 63) / 64) * ((N + 127) / 128);
+    constexpr long kCus = 256;
+    // Up to two 128x128 tiles per CU the finer grain wins, beyond that the persistent kernel (t128 = 384 / 564 at N = 1536, K = 512:
+    // 14.4 / 21.3 us against 16.3 / 17.5; t128 = 512 / 528 at K = 2048 / 4096: 47.6 / 113 against 50.5 / 84; at 8325 x 3072 x 1024 83 against 57).
+    if (p8_ok && t128 > 2 * kCus) return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
+    if (t128 <= 2 * kCus) {
+        // 64x64 while its tiles fit two per CU (256 x 512 x 2048: 25.1 us as 128x128 tiles, 13.0 as these; 2048 x 1024 x 1024:
+        // 16.9, 10.6, as 64x128 12.1), then 64x128 up to three per CU (4096 x 1024 x 4096: 55.6 as 128x128, 49.1, as 64x64 57.9;
+        // 2048 x 4096 x 1024, four per CU: 30.0 against 37.0).  Four LDS stages of 16 KB, three of 24 KB: two workgroups per CU, worth
+        // more than deeper rings (64x64 with eight stages: 51 instead of 30.6 us at 2048 x 1024 x 4096).
+        if (t64 <= 2 * kCus) return launch_ring<HT, 64, 64, 4, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+        if (t64x128 <= 3 * kCus) return launch_ring<HT, 64, 128, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+    }
     const bool deep = K >= 3072 || (EPI == EPI_BIAS && K >= 768 && N >= 768);
     // the LDS-direct kernel forms element offsets of A in 32 bits
     const bool dma_ok = (long long)M * K < (1ll << 32) && (long long)(N + 256) * K < (1ll << 32);

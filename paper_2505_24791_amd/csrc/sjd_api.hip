@@ -323,14 +323,17 @@ void conditioner_pass(sjd_flow *f, int j, const float *x, int n, const int32_t *
         ProfScope ps(f, SJD_PROF_OTHER, 2.0 * M * (double)D * W, (double)M * W * 4, s);
         launch_embed(x, bw.w_in, bw.b_in, bw.pos, f->h, M, D, W, RowMap{active, T, 0, T, rev}, s);
     }
-    // Width 512: LayerNorm + projection in one activation-stationary launch where that is faster: a
-    // workgroup of those kernels is 128 rows x 768..1024 columns of work, so below ~90 panels the tile
-    // kernels' finer grain wins (measured on configuration C2: QKV from 10240 rows on, MLP input from 12288)
+    // Width 512: LayerNorm + projection in one activation-stationary launch where that is faster.  A workgroup of those kernels
+    // is 128 rows x 768..1024 columns of work, two per panel of 128 rows: below ~90 panels the tile kernels' finer grain
+    // wins (QKV from 10240 rows on, MLP input from 12288), above 128 panels the last round of workgroups is nearly empty and the
+    // persistent kernel wins (a pass of 4 layers: 16384 rows 795 us against 831, 18432 rows 1123 against 937, 32768 rows 1596
+    // against 1432, 65536 rows 2912 against 2642).
     const bool panel_any = f->arena_panel && f->proj_path != 1 && gemm_panel_applicable(M, RW, W, 2) &&
                            gemm_panel_applicable(M, 3 * W, W, 2) && gemm_panel_applicable(M, W, W, 4);
-    const bool panel_qkv = panel_any && (f->proj_path == 2 || M >= 10240);
-    const bool panel_fc1 = panel_any && (f->proj_path == 2 || M >= 12288);
-    const bool stream_fc2 = panel_any && f->stream_ok && (f->proj_path == 2 || M >= 10240) && gemm_stream_applicable(M, W, RW);
+    const bool panel_one_round = M <= 16384;
+    const bool panel_qkv = panel_any && (f->proj_path == 2 || (M >= 10240 && panel_one_round));
+    const bool panel_fc1 = panel_any && (f->proj_path == 2 || (M >= 12288 && panel_one_round));
+    const bool stream_fc2 = panel_any && f->stream_ok && (f->proj_path == 2 || (M >= 10240 && panel_one_round)) && gemm_stream_applicable(M, W, RW);
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerW &lw = bw.layer[l];
         if (panel_qkv) ln_project_panel(f, f->h, lw.ln1_g, lw.ln1_b, lw.p_qkv, lw.b_qkv, f->qkv, M, 3 * W, EPI_BIAS, s);

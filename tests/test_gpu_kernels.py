@@ -67,3 +67,23 @@ def test_projection_rows_do_not_depend_on_their_neighbours(torch_cuda):
         full = sjd.op_linear_h16(ad, wd, bd, M, N, K, 0, kernel=kernel)
         part = sjd.op_linear_h16(ad[300:556].contiguous(), wd, bd, 256, N, K, 0, kernel=kernel)
         assert torch.equal(full[300:556], part)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 24, 64), (49, 96, 128), (64, 64, 192), (65, 65, 256),       # 64x64 ring: one k-tile, fewer k-tiles than stages, edges
+    (257, 500, 2048), (700, 1000, 320),                               # long k, an odd number of k-tiles
+    (4000, 1024, 256), (3001, 2300, 128),                             # 64x128 ring: two tiles per CU and more
+])
+def test_small_launches_give_the_tile_kernels_bits(torch_cuda, M, N, K):
+    """The automatic choice for launches that do not fill the chip walks k in the same order as the 128x128 kernel: same bits."""
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    for dtype in (torch.float16, torch.bfloat16):
+        a, _, wt, bias = _operands(torch, M, N, K, dtype, seed=M)
+        ad, wd, bd = a.cuda(), wt.cuda(), bias.cuda()
+        for epi in (0, 1):
+            assert torch.equal(sjd.op_linear_h16(ad, wd, bd, M, N, K, epi), sjd.op_linear_h16(ad, wd, bd, M, N, K, epi, kernel=3)), epi
+        r = [torch.arange(M * N, dtype=torch.float32).reshape(M, N).cuda() * 1e-3 for _ in range(2)]
+        for rd, kernel in zip(r, (0, 3)):
+            sjd.op_linear_h16(ad, wd, bd, M, N, K, 2, resid=rd, kernel=kernel)
+        assert torch.equal(r[0], r[1])
