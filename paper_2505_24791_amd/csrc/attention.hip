@@ -7,6 +7,7 @@
 //  * flash_attention_h16_kernel: whole-sequence causal attention for head size 64 on 16-bit data with
 //    MFMA; K and V tiles are staged in LDS, scores never leave registers (online softmax in float32), so
 //    there is no T x T buffer.
+//  * flash_attention_short_h16_kernel: the same for up to 256 tokens, all keys and values of a (sample, head) in LDS at once.
 //  * flash_attention_f32_kernel: the same in float32 on the float32 matrix instruction (float32 flows and
 //    the refined passes of 16-bit flows).
 #include "common.h"
@@ -161,11 +162,128 @@ __device__ __forceinline__ int fa_kswz(int key) { return ((key >> 1) & 3) | (((k
 // (the LDS bank-conflict counter reads zero on this kernel).
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
+// This lane's part of a transposing read (element offsets inside a V tile, for d < 32 and d >= 32): source row (4 g + j16 / 4) of the
+// 8-key group, the 8-byte piece (j16 % 4) of the 32 bytes that hold d = 32 db + 16 hh .. + 15, chunk slot swizzled by the row.
+__device__ __forceinline__ void fa_voff(int lane, int (&voff)[2]) {
+    const int g = lane >> 5, j16 = lane & 15, hh = (lane >> 4) & 1;
+#pragma unroll
+    for (int db = 0; db < 2; ++db) {
+        const int chunk = 4 * db + 2 * hh + ((j16 & 3) >> 1);
+        const int slot_v = chunk ^ (((j16 >> 3) & 1) << 2);
+        voff[db] = (4 * g + (j16 >> 2)) * FA_DH + slot_v * 8 + (j16 & 1) * 4;
+    }
+}
+
+// One step of 32 keys of a wave's 32 query rows q0 .. q0 + 31 (Kb, Vb: their rows in LDS, kb0 the first key): scores,
+// online softmax, second product.
+template <typename HT>
+__device__ __forceinline__ void fa_block(const HT *Kb, const HT *Vb, int kb0, int q0, int lane,
+                                         const typename Half16<HT>::v8 (&qf)[4], const int (&voff)[2], float scale_log2,
+                                         float &m_run, float &l_run, f32x16 (&oacc)[2]) {
+    typedef typename Half16<HT>::v8 v8;
+    typedef typename Half16<HT>::v4 v4;
+    const int l32 = lane & 31, g = lane >> 5, qrow = q0 + l32;
+    f32x16 sacc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const v8 kf = *reinterpret_cast<const v8 *>(&Kb[l32 * FA_KS + (((2 * c + g) ^ fa_kswz(l32)) << 3)]);
+        sacc = Half16<HT>::mfma(kf, qf[c], sacc);
+    }
+    // register v is key kb0 + 8 (v/4) + 4 g + v%4, query qrow; only blocks that reach the diagonal need
+    // the causal mask; scores stay unscaled, the softmax scale (times log2 e) enters through one fused
+    // multiply-add in front of the exponential
+    float mx = -INFINITY;
+    if (kb0 + 31 > q0) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int key = kb0 + 8 * (v >> 2) + 4 * g + (v & 3);
+            const float sv = key <= qrow ? sacc[v] : -INFINITY;
+            sacc[v] = sv;
+            mx = fmaxf(mx, sv);
+        }
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sacc[v]);
+    }
+    { float lo, hi; wave_halves(mx, lo, hi); mx = fmaxf(lo, hi) * scale_log2; }   // scale > 0: the maximum commutes with it
+    const float m_new = fmaxf(m_run, mx);
+    // rows past the end of the sequence may see no visible key; keep them finite
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    // a row whose maximum did not move has the factor exp2(0) = 1: when that holds for every row of the
+    // wave the rescaling is skipped, with the same bits
+    if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
+        const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
+        l_run *= corr;
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) oacc[db][v] *= corr;
+        m_run = m_new;
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sacc[v] = __builtin_amdgcn_exp2f(fmaf(sacc[v], scale_log2, -m_use));
+    // the row sum is taken over the probabilities as they enter the second product (rounded to 16 bits),
+    // two per instruction, in float32
+    float psum = 0.f;
+
+    // O^T += V^T P^T, 16 keys per instruction.  Slot e = 4 a + b of lane half g stands for key
+    // kb0 + 16 c2 + 8 a + 4 g + b in both operands.
+#pragma unroll
+    for (int c2 = 0; c2 < 2; ++c2) {
+        v8 pf;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) pf[e] = from_f32<HT>(sacc[8 * c2 + e]);
+        psum = Half16<HT>::add_all(pf, psum);
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+            union { i16x4 r; v4 h; } lo, hi;
+            const HT *vp = Vb + 16 * c2 * FA_DH + voff[db];
+            lo.r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(vp));
+            hi.r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(vp + 8 * FA_DH));
+            v8 vf;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { vf[e] = lo.h[e]; vf[4 + e] = hi.h[e]; }
+            oacc[db] = Half16<HT>::mfma(vf, pf, oacc[db]);
+        }
+    }
+    { float lo, hi; wave_halves(psum, lo, hi); l_run += lo + hi; }
+}
+
+// The wave's 32 finished rows: lane l32 + 32 g holds d = 32 db + 8 a + 4 g + 0..3 of row l32.  Two lanes' pieces of four make
+// sixteen contiguous bytes: a swap between the halves of the wave gives the lower lanes all of a, the upper ones all of a + 1, so
+// that a store covers 32 bytes of a row instead of 16 (each store touches 32 rows, and the cache counts its pieces: 63 -> 56.5 us at
+// 128 samples x 16 heads x 256 tokens, 107 -> 97 at 256 x 12).
+template <typename HT>
+__device__ __forceinline__ void fa_store(HT *orow, bool valid, int lane, float l_run, const f32x16 (&oacc)[2]) {
+    typedef typename Half16<HT>::v4 v4;
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const int g = lane >> 5;
+    const float inv = 1.0f / l_run;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int a = 0; a < 4; a += 2) {
+            u32x2 x[2];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                v4 ov;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) ov[b] = from_f32<HT>(oacc[db][4 * (a + q) + b] * inv);
+                x[q] = __builtin_bit_cast(u32x2, ov);
+            }
+            const auto s0 = __builtin_amdgcn_permlane32_swap(x[0].x, x[1].x, false, false);
+            const auto s1 = __builtin_amdgcn_permlane32_swap(x[0].y, x[1].y, false, false);
+            if (valid) *reinterpret_cast<u32x4 *>(orow + 32 * db + 8 * (a + g)) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+        }
+}
+
 template <typename HT>
 __global__ __launch_bounds__(256, 4) void flash_attention_h16_kernel(const HT *__restrict__ qkv, HT *__restrict__ o,
                                                                      int T, int H, int n_pairs, float scale_log2) {
     typedef typename Half16<HT>::v8 v8;
-    typedef typename Half16<HT>::v4 v4;
     __shared__ __attribute__((aligned(16))) HT Ks[2][FA_BK * FA_KS];
     __shared__ __attribute__((aligned(16))) HT Vs[2][FA_BK * FA_DH];
     const int W = H * FA_DH;
@@ -201,16 +319,8 @@ __global__ __launch_bounds__(256, 4) void flash_attention_h16_kernel(const HT *_
     // that were issued a moment before - and the prefetch is lost.
     asm volatile("" :: "v"(qf[0]), "v"(qf[1]), "v"(qf[2]), "v"(qf[3]));
 
-    // this lane's part of a transposing read: source row (4 g + j16 / 4) of the 8-key group, the 8-byte piece
-    // (j16 % 4) of the 32 bytes that hold d = 32 db + 16 hh .. + 15, chunk slot swizzled by the row
-    const int j16 = lane & 15, hh = (lane >> 4) & 1;
-    int voff[2];                                 // element offsets inside a V tile, for db = 0, 1
-#pragma unroll
-    for (int db = 0; db < 2; ++db) {
-        const int chunk = 4 * db + 2 * hh + ((j16 & 3) >> 1);
-        const int slot_v = chunk ^ (((j16 >> 3) & 1) << 2);
-        voff[db] = (4 * g + (j16 >> 2)) * FA_DH + slot_v * 8 + (j16 & 1) * 4;
-    }
+    int voff[2];
+    fa_voff(lane, voff);
 
     const int last_row = min(qt * FA_BQ + FA_BQ - 1, T - 1);
     const int n_kt = last_row / FA_BK + 1;
@@ -267,89 +377,65 @@ __global__ __launch_bounds__(256, 4) void flash_attention_h16_kernel(const HT *_
         for (int kb = 0; kb < 2; ++kb) {
             const int kb0 = key0 + 32 * kb;
             if (kb0 > q0 + 31) continue;
-            f32x16 sacc;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const v8 kf = *reinterpret_cast<const v8 *>(&Kt[(32 * kb + l32) * FA_KS + (((2 * c + g) ^ fa_kswz(l32)) << 3)]);
-                sacc = Half16<HT>::mfma(kf, qf[c], sacc);
-            }
-            // register v is key kb0 + 8 (v/4) + 4 g + v%4, query qrow; only blocks that reach the diagonal need
-            // the causal mask; scores stay unscaled, the softmax scale (times log2 e) enters through one fused
-            // multiply-add in front of the exponential
-            float mx = -INFINITY;
-            if (kb0 + 31 > q0) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int key = kb0 + 8 * (v >> 2) + 4 * g + (v & 3);
-                    const float sv = key <= qrow ? sacc[v] : -INFINITY;
-                    sacc[v] = sv;
-                    mx = fmaxf(mx, sv);
-                }
-            } else {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sacc[v]);
-            }
-            { float lo, hi; wave_halves(mx, lo, hi); mx = fmaxf(lo, hi) * scale_log2; }   // scale > 0: the maximum commutes with it
-            const float m_new = fmaxf(m_run, mx);
-            // rows past the end of the sequence may see no visible key; keep them finite
-            const float m_use = m_new == -INFINITY ? 0.f : m_new;
-            // a row whose maximum did not move has the factor exp2(0) = 1: when that holds for every row of the
-            // wave the rescaling is skipped, with the same bits
-            if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
-                const float corr = __builtin_amdgcn_exp2f(m_run - m_use);
-                l_run *= corr;
-#pragma unroll
-                for (int db = 0; db < 2; ++db)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) oacc[db][v] *= corr;
-                m_run = m_new;
-            }
-#pragma unroll
-            for (int v = 0; v < 16; ++v) sacc[v] = __builtin_amdgcn_exp2f(fmaf(sacc[v], scale_log2, -m_use));
-            // the row sum is taken over the probabilities as they enter the second product (rounded to 16 bits),
-            // two per instruction, in float32
-            float psum = 0.f;
-
-            // O^T += V^T P^T, 16 keys per instruction.  Slot e = 4 a + b of lane half g stands for key
-            // kb0 + 16 c2 + 8 a + 4 g + b in both operands.
-#pragma unroll
-            for (int c2 = 0; c2 < 2; ++c2) {
-                v8 pf;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) pf[e] = from_f32<HT>(sacc[8 * c2 + e]);
-                psum = Half16<HT>::add_all(pf, psum);
-#pragma unroll
-                for (int db = 0; db < 2; ++db) {
-                    union { i16x4 r; v4 h; } lo, hi;
-                    const HT *vp = Vt + (32 * kb + 16 * c2) * FA_DH + voff[db];
-                    lo.r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(vp));
-                    hi.r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(vp + 8 * FA_DH));
-                    v8 vf;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) { vf[e] = lo.h[e]; vf[4 + e] = hi.h[e]; }
-                    oacc[db] = Half16<HT>::mfma(vf, pf, oacc[db]);
-                }
-            }
-            { float lo, hi; wave_halves(psum, lo, hi); l_run += lo + hi; }
+            fa_block<HT>(Kt + 32 * kb * FA_KS, Vt + 32 * kb * FA_DH, kb0, q0, lane, qf, voff, scale_log2, m_run, l_run, oacc);
         }
         if (kt + 1 < n_kt) stage_tile(buf ^ 1);   // last read before the previous barrier
         __syncthreads();
     }
-    if (qrow < T) {
-        const float inv = 1.0f / l_run;
-        HT *orow = o + ((size_t)i * T + qrow) * W + h * FA_DH;
+    fa_store<HT>(o + ((size_t)i * T + qrow) * W + h * FA_DH, qrow < T, lane, l_run, oacc);
+}
+
+// Up to 256 tokens: one workgroup per (sample, head), a wave per 32 query rows, all keys and values in LDS at once (64 KB at
+// 256 tokens: two workgroups, 16 waves per CU), filled by LDS-direct loads.  With key tiles that pass by, a workgroup of 128
+// rows pays a barrier and a load latency for each of two to four tiles, half of them on the diagonal where most of its waves have nothing to do.
+// Here there is one barrier, and each wave then walks its own keys; wave w and w + 4 share a SIMD and take complementary
+// rows, so that the SIMDs have equal work.  Same steps in the same order: same bits.
+template <typename HT>
+__global__ __launch_bounds__(512, 4) void flash_attention_short_h16_kernel(const HT *__restrict__ qkv, HT *__restrict__ o, int T,
+                                                                         int H, float scale_log2) {
+    typedef typename Half16<HT>::v8 v8;
+    extern __shared__ __attribute__((aligned(16))) unsigned char fa_lds[];
+    const int nw = (int)blockDim.x >> 6;                         // 32 nw >= T
+    const int W = H * FA_DH, h = (int)blockIdx.x % H, i = (int)blockIdx.x / H;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l32 = lane & 31, g = lane >> 5;
+    const HT *base = qkv + (size_t)i * T * 3 * W + h * FA_DH;
+    HT *Ks = reinterpret_cast<HT *>(fa_lds), *Vs = Ks + nw * 32 * FA_DH;
+    // this wave loads keys and values 32 wave .. + 31, eight rows (1 KB) at a time: lane 8 r + c delivers the chunk of slot c
+    {
+        const uint32_t lds0 = (uint32_t)(uintptr_t)((__attribute__((address_space(3))) void *)fa_lds);
+        auto dma = [&](const HT *from, uint32_t off, uint32_t lds_addr) {
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         :: "s"(lds_addr), "v"(off), "s"(from) : "memory");
+        };
 #pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                v4 ov;
-#pragma unroll
-                for (int b = 0; b < 4; ++b) ov[b] = from_f32<HT>(oacc[db][4 * a + b] * inv);
-                *reinterpret_cast<v4 *>(orow + 32 * db + 8 * a + 4 * g) = ov;
-            }
+        for (int q = 0; q < 4; ++q) {
+            const int key = 32 * wave + 8 * q + (lane >> 3);
+            const uint32_t row = (uint32_t)(key < T ? key : T - 1) * (uint32_t)(3 * W) * 2u;   // rows past the end: masked
+            const uint32_t at = (uint32_t)(32 * wave + 8 * q) * (FA_DH * 2);
+            dma(base + W, row + (((lane & 7) ^ fa_kswz(key)) << 4), lds0 + at);
+            dma(base + 2 * W, row + (((lane & 7) ^ (((key >> 1) & 1) << 2)) << 4), lds0 + nw * 32 * FA_DH * 2 + at);
+        }
     }
+    const int blk = wave < 4 ? wave : nw - 1 - (wave - 4);
+    const int q0 = 32 * blk, qrow = q0 + l32;
+    const int qrow_c = qrow < T ? qrow : T - 1;
+    v8 qf[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) qf[c] = *reinterpret_cast<const v8 *>(base + (size_t)qrow_c * 3 * W + 16 * c + 8 * g);
+    f32x16 oacc[2];
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    int voff[2];
+    fa_voff(lane, voff);
+    __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0): this wave's rows have landed
+    __syncthreads();
+    for (int kb = 0; kb <= blk; ++kb)
+        fa_block<HT>(Ks + 32 * kb * FA_KS, Vs + 32 * kb * FA_DH, 32 * kb, q0, lane, qf, voff, scale_log2, m_run, l_run, oacc);
+    fa_store<HT>(o + ((size_t)i * T + qrow) * W + h * FA_DH, qrow < T, lane, l_run, oacc);
 }
 
 template <typename HT>
@@ -358,6 +444,16 @@ void launch_flash_attention_h16(const HT *qkv, HT *o, int n_samples, int T, int 
     const int n_qt = (T + FA_BQ - 1) / FA_BQ;
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)FA_DH);
     const int n_pairs = n_samples * H;
+    // Same bits either way.  Microseconds with the long kernel / this one: 128 samples x 16 heads, 256 tokens 56.5 / 52.5; 64 x 8 19.7 / 17.9;
+    // 16 x 16 12.1 / 9.8; 37 x 4, 225 tokens 10.6 / 8.5; 64 x 16, 200 tokens 29.5 / 25.9; 4 x 8, 49 tokens 4.2 / 3.7.  With twelve pairs per
+    // CU (256 x 12: 97 / 97, bfloat16 93 / 96) the long kernel's four workgroups per CU hide as much.
+    // (LDS-direct loads want their 16 bytes aligned; 32-bit row offsets hold for that many heads)
+    if (T <= 256 && n_pairs <= 2048 && ((uintptr_t)qkv & 15) == 0) {
+        const int nw = (T + 31) / 32;
+        const size_t lds = (size_t)nw * 32 * FA_DH * 2 * sizeof(HT);
+        hipLaunchKernelGGL(flash_attention_short_h16_kernel<HT>, dim3(n_pairs), dim3(64 * nw), lds, s, qkv, o, T, H, scale_log2);
+        return;
+    }
     const unsigned grid = (unsigned)((n_pairs + 7) / 8) * 8u * (unsigned)n_qt;
     hipLaunchKernelGGL(flash_attention_h16_kernel<HT>, dim3(grid), dim3(256), 0, s, qkv, o, T, H, n_pairs, scale_log2);
 }

@@ -572,8 +572,10 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
     constexpr long kCus = 256;
     // Up to two 128x128 tiles per CU the finer grain wins, beyond that the persistent kernel (t128 = 384 / 564 at N = 1536, K = 512:
     // 14.4 / 21.3 us against 16.3 / 17.5; t128 = 512 / 528 at K = 2048 / 4096: 47.6 / 113 against 50.5 / 84; at 8325 x 3072 x 1024 83 against 57).
-    if (p8_ok && t128 > 2 * kCus) return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
-    if (t128 <= 2 * kCus) {
+    // The LDS-direct loads of both want operands on 16-byte boundaries.
+    const bool aligned = (((uintptr_t)A | (uintptr_t)Bt) & 15) == 0;
+    if (p8_ok && (t256 >= kCus || (t128 > 2 * kCus && aligned))) return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
+    if (t128 <= 2 * kCus && aligned) {
         // 64x64 while its tiles fit two per CU (256 x 512 x 2048: 25.1 us as 128x128 tiles, 13.0 as these; 2048 x 1024 x 1024:
         // 16.9, 10.6, as 64x128 12.1), then 64x128 up to three per CU (4096 x 1024 x 4096: 55.6 as 128x128, 49.1, as 64x64 57.9;
         // 2048 x 4096 x 1024, four per CU: 30.0 against 37.0).  Four LDS stages of 16 KB, three of 24 KB: two workgroups per CU, worth

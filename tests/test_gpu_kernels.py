@@ -87,3 +87,21 @@ def test_small_launches_give_the_tile_kernels_bits(torch_cuda, M, N, K):
         for rd, kernel in zip(r, (0, 3)):
             sjd.op_linear_h16(ad, wd, bd, M, N, K, 2, resid=rd, kernel=kernel)
         assert torch.equal(r[0], r[1])
+
+
+@pytest.mark.parametrize("T", [1, 17, 32, 33, 96, 225, 256])
+def test_short_attention_matches_oracle_and_the_long_kernel(torch_cuda, orc64, T):
+    """Up to 256 tokens and 2048 (sample, head) pairs one workgroup takes a whole pair; with more pairs the kernel with passing key
+    tiles does, with the same bits."""
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    H, W, many = 3, 192, 700
+    for dtype, eps in ((torch.float16, 2.0 ** -11), (torch.bfloat16, 2.0 ** -8)):
+        g = torch.Generator().manual_seed(T)
+        qkv = torch.randn((many * T, 3 * W), generator=g).to(dtype)
+        few = sjd.op_attention_h16(qkv[:2 * T].cuda(), 2, T, H)
+        assert torch.equal(sjd.op_attention_h16(qkv.cuda(), many, T, H)[:2 * T], few)
+        q = qkv[T:2 * T].float().numpy()
+        ref = orc64.causal_attention(q[:, :W], q[:, W:2 * W], q[:, 2 * W:], H)
+        # probabilities are rounded to 16 bits before the second product: relative eps per term
+        assert np.abs(few[T:].float().cpu().numpy() - ref).max() <= 4 * eps * np.abs(q[:, 2 * W:]).max()
