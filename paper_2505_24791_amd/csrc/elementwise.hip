@@ -14,7 +14,8 @@ constexpr int EMB_ROWS = 16;
 __global__ __launch_bounds__(256) void embed_kernel(const float *__restrict__ x, const float *__restrict__ w_in,
                                                     const float *__restrict__ b_in, const float *__restrict__ pos,
                                                     float *__restrict__ h, int n_rows, int D, int W, RowMap map) {
-    extern __shared__ float xs[];   // [EMB_ROWS][D]
+    extern __shared__ __attribute__((aligned(16))) float xs[];   // [EMB_ROWS][DP]
+    const int DP = (D + 3) & ~3;    // rows on 16-byte boundaries
     __shared__ int prow[EMB_ROWS];
     const int m0 = blockIdx.x * EMB_ROWS;
     const int rows = n_rows - m0 < EMB_ROWS ? n_rows - m0 : EMB_ROWS;
@@ -30,7 +31,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const float *__restrict__ x,
             v = x[((size_t)b * map.T + tok) * D + d];
             if (d == 0) prow[r] = p;
         }
-        xs[e] = v;
+        xs[r * DP + d] = v;
     }
     __syncthreads();
     const int ncg = W >> 2;
@@ -40,11 +41,28 @@ __global__ __launch_bounds__(256) void embed_kernel(const float *__restrict__ x,
         f32x4 acc[EMB_ROWS / 2];
 #pragma unroll
         for (int r = 0; r < EMB_ROWS / 2; ++r) acc[r] = bias;
-        for (int d = 0; d < D; ++d) {
+        // Eight rows of w_in are requested before the first is used: one at a time, the loop is D round trips to L2.  The sums
+        // still run over d in index order.
+        int d = 0;
+        for (; d + 8 <= D; d += 8) {
+            f32x4 wv[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) wv[u] = *reinterpret_cast<const f32x4 *>(w_in + (size_t)(d + u) * W + w);
+#pragma unroll
+            for (int r = 0; r < EMB_ROWS / 2; ++r) {
+                const f32x4 *xp = reinterpret_cast<const f32x4 *>(xs + (r0 + r) * DP + d);
+                const f32x4 x0 = xp[0], x1 = xp[1];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[r][e] = fmaf(u < 4 ? x0[u & 3] : x1[u & 3], wv[u][e], acc[r][e]);
+            }
+        }
+        for (; d < D; ++d) {
             const f32x4 wv = *reinterpret_cast<const f32x4 *>(w_in + (size_t)d * W + w);
 #pragma unroll
             for (int r = 0; r < EMB_ROWS / 2; ++r) {
-                const float xv = xs[(r0 + r) * D + d];
+                const float xv = xs[(r0 + r) * DP + d];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) acc[r][e] = fmaf(xv, wv[e], acc[r][e]);
             }
@@ -64,7 +82,7 @@ __global__ __launch_bounds__(256) void embed_kernel(const float *__restrict__ x,
 void launch_embed(const float *x, const float *w_in, const float *b_in, const float *pos, float *h, int n_rows, int D,
                   int W, RowMap map, hipStream_t s) {
     if (n_rows <= 0) return;
-    hipLaunchKernelGGL(embed_kernel, dim3((n_rows + EMB_ROWS - 1) / EMB_ROWS), dim3(256), EMB_ROWS * D * sizeof(float), s, x,
+    hipLaunchKernelGGL(embed_kernel, dim3((n_rows + EMB_ROWS - 1) / EMB_ROWS), dim3(256), EMB_ROWS * ((D + 3) & ~3) * sizeof(float), s, x,
                        w_in, b_in, pos, h, n_rows, D, W, map);
 }
 
@@ -335,18 +353,33 @@ __global__ __launch_bounds__(256) void forward_epilogue_kernel(const float *__re
     const int n = T * D;
     const float *pr = p + (size_t)b * T * 2 * D;
     float acc = 0.f;
-    for (int e = threadIdx.x; e < n; e += 256) {
-        const int l = e / D, d = e - l * D;
-        const int tok = reversed ? T - 1 - l : l;
-        const size_t idx = ((size_t)b * T + tok) * D + d;
-        float v = x[idx];
-        if (l > 0) {
-            const float mu = pr[(size_t)(l - 1) * 2 * D + d];
-            const float al = pr[(size_t)(l - 1) * 2 * D + D + d];
-            v = (v - mu) * expf(-al);
-            acc += al;
+    // eight elements of a thread have their loads under way before the first is used; alpha is still summed in index order
+    constexpr int U = 8;
+    for (int e0 = threadIdx.x; e0 < n; e0 += 256 * U) {
+        float v[U], mu[U], al[U];
+        size_t idx[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + 256 * u;
+            if (e >= n) continue;
+            const int l = e / D, d = e - l * D;
+            idx[u] = ((size_t)b * T + (reversed ? T - 1 - l : l)) * D + d;
+            v[u] = x[idx[u]];
+            const float *pq = pr + (size_t)(l > 0 ? l - 1 : 0) * 2 * D + d;   // token 1 reads a row it does not use
+            mu[u] = pq[0];
+            al[u] = pq[D];
         }
-        y[idx] = v;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int e = e0 + 256 * u;
+            if (e >= n) continue;
+            float r = v[u];
+            if (e >= D) {
+                r = (r - mu[u]) * expf(-al[u]);
+                acc += al[u];
+            }
+            y[idx[u]] = r;
+        }
     }
     if (!logdet) return;
     acc = wave_sum(acc);
@@ -388,8 +421,9 @@ void launch_decode_epilogue(const float *p, const float *z, float *x, int B, int
 // ------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void split_params_kernel(const float *__restrict__ p, float *__restrict__ mu,
                                                            float *__restrict__ alpha, int T, int D, int reversed) {
+    // one element per thread (a workgroup per sample walked its T D elements one load latency after the other: 67 us at 3 x 1000 x 48)
     const int b = blockIdx.x;
-    for (int e = threadIdx.x; e < T * D; e += 256) {
+    for (int e = blockIdx.y * 256 + threadIdx.x; e < T * D; e += gridDim.y * 256) {
         const int l = e / D, d = e - l * D;
         const int tok = reversed ? T - 1 - l : l;
         const size_t idx = ((size_t)b * T + tok) * D + d;
@@ -405,7 +439,7 @@ __global__ __launch_bounds__(256) void split_params_kernel(const float *__restri
 
 void launch_split_params(const float *p, float *mu, float *alpha, int B, int T, int D, int reversed, hipStream_t s) {
     if (B <= 0) return;
-    hipLaunchKernelGGL(split_params_kernel, dim3(B), dim3(256), 0, s, p, mu, alpha, T, D, reversed);
+    hipLaunchKernelGGL(split_params_kernel, dim3(B, T * D < 256 * 1024 ? (T * D + 255) / 256 : 1024), dim3(256), 0, s, p, mu, alpha, T, D, reversed);
 }
 
 // ------------------------------------------------------------------------------------------------
