@@ -154,7 +154,7 @@ def main() -> int:
         del src, dst
         say("copy kernel done: 5 x 256 MiB read + 256 MiB written")
         cur = z
-        if args.seq_path in (2, 3) or (args.seq_path == 0 and not (cfg.seq_len > 512 and cfg.width >= 1024)):
+        if args.seq_path in (2, 3) or (args.seq_path == 0 and cfg.bf16):
             cur = flow.sequential_inverse_block(0, z)      # one dispatch: the persistent kernel
             say("block 0 (sequential, persistent kernel) done")
         else:
@@ -250,9 +250,10 @@ def main() -> int:
     piped = None
     pipe_cus = args.pipeline_cus
     if pipe_cus < 0:
-        # automatic: only where block 0 is a large share of a step and runs as the persistent kernel anyway
-        persistent_default = not (cfg.seq_len > 512 and cfg.width >= 1024)   # mirrors the library's automatic choice
-        pipe_cus = 128 if persistent_default and stats["block_ms"][0] >= 0.4 * sum(stats["block_ms"][:K]) else 0
+        # automatic: only where block 0 is a large share of a step and barely slows down on half of the CUs (not at the largest
+        # width with long sequences)
+        covered = not (cfg.seq_len > 512 and cfg.width >= 1024)
+        pipe_cus = 128 if covered and stats["block_ms"][0] >= 0.4 * sum(stats["block_ms"][:K]) else 0
     if pipe_cus and args.mode == "selective" and cfg.bf16 and K > 1:
         try:
             from paper_2505_24791_amd.pipeline import PipelinedSampler

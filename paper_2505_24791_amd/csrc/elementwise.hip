@@ -42,7 +42,8 @@ __global__ __launch_bounds__(256) void embed_kernel(const float *__restrict__ x,
 #pragma unroll
         for (int r = 0; r < EMB_ROWS / 2; ++r) acc[r] = bias;
         // Eight rows of w_in are requested before the first is used: one at a time, the loop is D round trips to L2.  The sums
-        // still run over d in index order.
+        // still run over d in index order.  3000 rows of width 768, D = 48: 42 -> 30 us; a large launch is bound by its multiply-adds
+        // (32768 rows of width 1024: 73 -> 72).
         int d = 0;
         for (; d + 8 <= D; d += 8) {
             f32x4 wv[8];
