@@ -105,3 +105,40 @@ def test_short_attention_matches_oracle_and_the_long_kernel(torch_cuda, orc64, T
         ref = orc64.causal_attention(q[:, :W], q[:, W:2 * W], q[:, 2 * W:], H)
         # probabilities are rounded to 16 bits before the second product: relative eps per term
         assert np.abs(few[T:].float().cpu().numpy() - ref).max() <= 4 * eps * np.abs(q[:, 2 * W:]).max()
+
+
+@pytest.mark.parametrize("dtype_name", ["float16", "bfloat16"])
+def test_gelu_epilogue_of_values_that_are_not_finite(torch_cuda, dtype_name):
+    """GELU in its erf form, 0.5 v (1 + erf(v / sqrt 2)): +inf stays +inf, -inf and NaN give NaN, large finite values stay
+    themselves.  The values come in through the bias (the product is zero) and, in bfloat16, through a sum that overflows
+    float32."""
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    dtype = getattr(torch, dtype_name)
+    inf, nan, N = float("inf"), float("nan"), 512
+    special = torch.tensor([inf, -inf, nan, 3.0e38, -3.0e38, 6.0e4, -6.0e4, 15.5, 16.5, -16.5, 0.0, 1.0])
+    bias = torch.cat([special, torch.linspace(-8, 8, N - len(special))])
+    ref = 0.5 * bias.double() * (1 + torch.erf(bias.double() / 2 ** 0.5))
+    eps = 2.0 ** -11 if dtype_name == "float16" else 2.0 ** -8
+    runs = []
+    for M, K in ((70, 128), (4200, 512), (70, 512)):
+        a, wt = torch.zeros((M, K), dtype=dtype).cuda(), torch.zeros((N, K), dtype=dtype).cuda()
+        runs += [(f"kernel {k}, {M} rows", sjd.op_linear_h16(a, wt, bias.cuda(), M, N, K, 1, kernel=k)) for k in range(5)]
+        if K == 512:
+            one = torch.ones(K).cuda()
+            runs.append((f"panel, {M} rows", sjd.op_panel_linear_h16(a.float(), wt, bias.cuda(), M, N, 1, ln_g=one, ln_b=one)))
+    for what, c in runs:
+        c = c.cpu().double()
+        for i, v in enumerate(special):
+            want = ref[i].to(dtype).double()         # 3e38 is past the largest half
+            assert torch.equal(torch.isnan(c[:, i]), torch.isnan(want).expand(len(c))), (what, v)
+            if not torch.isnan(want):
+                got = c[:, i]
+                assert (got == want).all() or ((got - want).abs() <= eps * abs(want) + 1e-7).all(), (what, v, want, got[0])
+        rest = slice(len(special), None)
+        assert (c[:, rest] - ref[rest]).abs().max() <= eps * 8 + 1e-6, what
+    if dtype_name == "bfloat16":
+        a, wt = torch.full((70, 128), 3.0e38, dtype=dtype).cuda(), torch.ones((N, 128), dtype=dtype).cuda()
+        for k in range(5):
+            c = sjd.op_linear_h16(a, wt, torch.zeros(N).cuda(), 70, N, 128, 1, kernel=k)
+            assert torch.isinf(c).all() and (c > 0).all(), k
