@@ -559,12 +559,16 @@ static void launch_tile(const HT *A, const HT *Bt, const float *bias, const floa
 template <typename HT, typename OutT, int EPI>
 static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float *resid, OutT *C, int M, int N, int K,
                       int kernel, hipStream_t s) {
-    if (kernel == 1) return launch_tile<HT, 256, 128, 32, 2, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
-    if (kernel == 2 && (long long)M * K < (1ll << 32) && (long long)(N + 256) * K < (1ll << 32))
-        return launch_dma<HT, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
-    if (kernel == 3) return launch_tile<HT, 128, 128, 64, 1, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+    // LDS-direct loads move 16 bytes per lane: the ring, the persistent and the 256x256 kernel want both operands on 16-byte
+    // boundaries.  The register-staged kernels take operands that lie anywhere.
+    const bool aligned = (((uintptr_t)A | (uintptr_t)Bt) & 15) == 0;
+    // the 256x256 kernel forms element offsets of A in 32 bits
+    const bool dma_ok = aligned && (long long)M * K < (1ll << 32) && (long long)(N + 256) * K < (1ll << 32);
     // the persistent kernel updates the residual stream in place: resid, when used, must be C
-    const bool p8_ok = gemm_p8_applicable(M, N, K) && (EPI != EPI_BIAS_RESIDUAL || (const void *)resid == (const void *)C);
+    const bool p8_ok = aligned && gemm_p8_applicable(M, N, K) && (EPI != EPI_BIAS_RESIDUAL || (const void *)resid == (const void *)C);
+    if (kernel == 1) return launch_tile<HT, 256, 128, 32, 2, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+    if (kernel == 2 && dma_ok) return launch_dma<HT, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+    if (kernel == 3) return launch_tile<HT, 128, 128, 64, 1, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
     if (kernel == 4 && p8_ok) return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
     const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
@@ -572,9 +576,7 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
     constexpr long kCus = 256;
     // Up to two 128x128 tiles per CU the finer grain wins, beyond that the persistent kernel (t128 = 384 / 564 at N = 1536, K = 512:
     // 14.4 / 21.3 us against 16.3 / 17.5; t128 = 512 / 528 at K = 2048 / 4096: 47.6 / 113 against 50.5 / 84; at 8325 x 3072 x 1024 83 against 57).
-    // The LDS-direct loads of both want operands on 16-byte boundaries.
-    const bool aligned = (((uintptr_t)A | (uintptr_t)Bt) & 15) == 0;
-    if (p8_ok && (t256 >= kCus || (t128 > 2 * kCus && aligned))) return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
+    if (p8_ok && (t256 >= kCus || t128 > 2 * kCus)) return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
     if (t128 <= 2 * kCus && aligned) {
         // 64x64 while its tiles fit two per CU (256 x 512 x 2048: 25.1 us as 128x128 tiles, 13.0 as these; 2048 x 1024 x 1024:
         // 16.9, 10.6, as 64x128 12.1), then 64x128 up to three per CU (4096 x 1024 x 4096: 55.6 as 128x128, 49.1, as 64x64 57.9;
@@ -584,8 +586,6 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
         if (t64x128 <= 3 * kCus) return launch_ring<HT, 64, 128, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
     }
     const bool deep = K >= 3072 || (EPI == EPI_BIAS && K >= 768 && N >= 768);
-    // the LDS-direct kernel forms element offsets of A in 32 bits
-    const bool dma_ok = (long long)M * K < (1ll << 32) && (long long)(N + 256) * K < (1ll << 32);
     if (deep && dma_ok && M >= 256 && N >= 256 && t256 >= 256) launch_dma<HT, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
     // measured: below ~3500 tiles of 128x128 the smaller tile wins (finer tail, shorter prologue per tile)
     else if (N >= 128 && M >= 256 && t128 >= 3584) launch_tile<HT, 256, 128, 32, 2, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);

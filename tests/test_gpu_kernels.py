@@ -142,3 +142,41 @@ def test_gelu_epilogue_of_values_that_are_not_finite(torch_cuda, dtype_name):
         for k in range(5):
             c = sjd.op_linear_h16(a, wt, torch.zeros(N).cuda(), 70, N, 128, 1, kernel=k)
             assert torch.isinf(c).all() and (c > 0).all(), k
+
+
+def _moved(torch, t, elements):
+    """A contiguous copy of t that starts `elements` past a 16-byte boundary."""
+    buf = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)
+    assert buf.data_ptr() % 16 == 0
+    v = buf[elements:elements + t.numel()].view(t.shape)
+    v.copy_(t)
+    return v
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (70, 256, 128), (3001, 1900, 128),          # the shapes of the two rings
+    (5000, 2048, 256),                           # of the persistent kernel with less than a tile per CU
+    (16640, 1024, 128), (16640, 1000, 3072),     # of the persistent and the 256x256 kernel
+])
+def test_operands_off_16_byte_boundaries(torch_cuda, M, N, K):
+    """Operands may start anywhere: the kernels whose loads want 16-byte boundaries leave them to those that do not, also when
+    they are asked for by number.  Same bits as from aligned operands."""
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    a, _, wt, bias = _operands(torch, M, N, K, torch.float16, seed=N)
+    ad, wd, bd = a.cuda(), wt.cuda(), bias.cuda()
+    ref = sjd.op_linear_h16(ad, wd, bd, M, N, K, 0, kernel=3)
+    for ea, ew in ((4, 0), (0, 4), (2, 6)):
+        am, wm = _moved(torch, ad, ea), _moved(torch, wd, ew)
+        assert (am.data_ptr() | wm.data_ptr()) % 16 != 0
+        for kernel in range(5):
+            assert torch.equal(sjd.op_linear_h16(am, wm, bd, M, N, K, 0, kernel=kernel), ref), (ea, ew, kernel)
+
+
+@pytest.mark.parametrize("T", [40, 256, 300])
+def test_attention_input_off_16_byte_boundaries(torch_cuda, T):
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    qkv = torch.randn((2 * T, 3 * 128), generator=torch.Generator().manual_seed(T)).half().cuda()
+    ref = sjd.op_attention_h16(qkv, 2, T, 2)
+    assert torch.equal(sjd.op_attention_h16(_moved(torch, qkv, 4), 2, T, 2), ref)
