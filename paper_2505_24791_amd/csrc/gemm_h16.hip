@@ -574,9 +574,14 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
     const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
     const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64), t64x128 = (long)((M + 63) / 64) * ((N + 127) / 128);
     constexpr long kCus = 256;
-    // Up to two 128x128 tiles per CU the finer grain wins, beyond that the persistent kernel (t128 = 384 / 564 at N = 1536, K = 512:
-    // 14.4 / 21.3 us against 16.3 / 17.5; t128 = 512 / 528 at K = 2048 / 4096: 47.6 / 113 against 50.5 / 84; at 8325 x 3072 x 1024 83 against 57).
-    if (p8_ok && (t256 >= kCus || t128 > 2 * kCus)) return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
+    // Up to two 128x128 tiles per CU the finer grain wins; beyond that the persistent kernel, if it has a tile for every CU or is
+    // through in one round.  It deals whole row panels to the XCDs, so with fewer tiles than CUs some XCDs may still have more
+    // than their CUs take at once, and the second round costs as much as the first.  Microseconds as 128x128 tiles / persistent, one round:
+    // 8690 x 1024 x 4096 118 / 84, 3321 x 3840 x 1280 56 / 39, 8690 x 1024 x 256 20.0 / 18.3; two: 5372 x 3072 x 768 45 / 51,
+    // 2053 x 5120 x 1280 50 / 68, 4576 x 3072 x 1024 48 / 50, 2829 x 4608 x 1536 70 / 69.
+    const long p8_per_xcd = ((M + 255) / 256 + 7) / 8 * (long)((N + 255) / 256);
+    if (p8_ok && (t256 >= kCus || (t128 > 2 * kCus && p8_per_xcd <= kCus / 8)))
+        return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
     if (t128 <= 2 * kCus && aligned) {
         // 64x64 while its tiles fit two per CU (256 x 512 x 2048: 25.1 us as 128x128 tiles, 13.0 as these; 2048 x 1024 x 1024:
         // 16.9, 10.6, as 64x128 12.1), then 64x128 up to three per CU (4096 x 1024 x 4096: 55.6 as 128x128, 49.1, as 64x64 57.9;

@@ -89,6 +89,31 @@ def test_small_launches_give_the_tile_kernels_bits(torch_cuda, M, N, K):
         assert torch.equal(r[0], r[1])
 
 
+def _tiles(M, N, bm, bn):
+    return -(-M // bm) * -(-N // bn)
+
+
+@pytest.mark.parametrize("M,N,K,one_round", [
+    (8690, 1024, 128, True), (4500, 3072, 128, False),      # 5 row panels x 4 column tiles on an XCD, 3 x 12
+    (2049, 4096, 192, True), (2049, 4352, 192, False),      # 2 x 16: exactly a round of 32 CUs, 2 x 17: one tile more
+])
+def test_middling_launches_give_the_tile_kernels_bits(torch_cuda, M, N, K, one_round):
+    """More than two 128x128 tiles per CU, but no 256x256 tile for every CU: the persistent kernel where no XCD gets more tiles than it
+    has CUs, else 128x128 tiles.  Same bits on both sides."""
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    assert _tiles(M, N, 128, 128) > 512 and _tiles(M, N, 256, 256) < 256
+    assert (-(-_tiles(M, 1, 256, 1) // 8) * (N // 256) <= 32) == one_round
+    a, _, wt, bias = _operands(torch, M, N, K, torch.float16, seed=N)
+    ad, wd, bd = a.cuda(), wt.cuda(), bias.cuda()
+    for epi in (0, 1):
+        assert torch.equal(sjd.op_linear_h16(ad, wd, bd, M, N, K, epi), sjd.op_linear_h16(ad, wd, bd, M, N, K, epi, kernel=3)), epi
+    r = [torch.zeros((M, N)).cuda() for _ in range(2)]
+    for rd, kernel in zip(r, (0, 3)):
+        sjd.op_linear_h16(ad, wd, bd, M, N, K, 2, resid=rd, kernel=kernel)
+    assert torch.equal(r[0], r[1])
+
+
 @pytest.mark.parametrize("T", [1, 17, 32, 33, 96, 225, 256])
 def test_short_attention_matches_oracle_and_the_long_kernel(torch_cuda, orc64, T):
     """Up to 256 tokens and 2048 (sample, head) pairs one workgroup takes a whole pair; with more pairs the kernel with passing key
