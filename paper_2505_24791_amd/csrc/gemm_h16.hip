@@ -588,7 +588,13 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
         // 2048 x 4096 x 1024, four per CU: 30.0 against 37.0).  Four LDS stages of 16 KB, three of 24 KB: two workgroups per CU, worth
         // more than deeper rings (64x64 with eight stages: 51 instead of 30.6 us at 2048 x 1024 x 4096).
         if (t64 <= 2 * kCus) return launch_ring<HT, 64, 64, 4, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
-        if (t64x128 <= 3 * kCus) return launch_ring<HT, 64, 128, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+        // Not where its second round has nothing to hide behind (2000 x 2560 x 64: 7.1 us as 128x128 tiles, 7.9), and not where the
+        // rows under way on an XCD are few against a large weight: tiles of half the height read it twice as often, and it no longer
+        // stays in the XCD's L2 (128x128 / these: 1400 x 2560 x 2048 26.9 / 24.8, 851 x 4096 x 1024 18.7 / 17.9, 400 x 5120 x 512 10.9 / 10.3;
+        // 587 x 3840 x 1280 18.0 / 20.5, 512 x 5120 x 768 13.3 / 15.6, 962 x 6144 x 1536 36 / 49, 512 x 8192 x 1024 17 / 23).
+        const long nk = (long)N * K;
+        const bool weight_ok = N <= 2560 || nk <= (N <= 4096 ? 4l << 20 : 5l << 19);
+        if (t64x128 <= (K >= 256 ? 3 : 2) * kCus && weight_ok) return launch_ring<HT, 64, 128, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
     }
     const bool deep = K >= 3072 || (EPI == EPI_BIAS && K >= 768 && N >= 768);
     if (deep && dma_ok && M >= 256 && N >= 256 && t256 >= 256) launch_dma<HT, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);

@@ -69,15 +69,29 @@ def test_projection_rows_do_not_depend_on_their_neighbours(torch_cuda):
         assert torch.equal(full[300:556], part)
 
 
-@pytest.mark.parametrize("M,N,K", [
-    (1, 24, 64), (49, 96, 128), (64, 64, 192), (65, 65, 256),       # 64x64 ring: one k-tile, fewer k-tiles than stages, edges
-    (257, 500, 2048), (700, 1000, 320),                               # long k, an odd number of k-tiles
-    (4000, 1024, 256), (3001, 2300, 128),                             # 64x128 ring: two tiles per CU and more
+def _tiles(M, N, bm, bn):
+    return -(-M // bm) * -(-N // bn)
+
+
+@pytest.mark.parametrize("M,N,K,tile", [
+    # 64x64 ring: one k-tile, fewer k-tiles than stages, edges, long k, an odd number of k-tiles
+    (1, 24, 64, "64x64"), (49, 96, 128, "64x64"), (64, 64, 192, "64x64"), (65, 65, 256, "64x64"),
+    (257, 500, 2048, "64x64"), (700, 1000, 320, "64x64"),
+    # 64x128 ring of three stages: fewer k-tiles than stages, edges on both sides, one 96-column tile (a head), two tiles per CU and more
+    (4000, 1024, 256, "64x128"), (1990, 1900, 64, "64x128"), (1990, 1900, 128, "64x128"), (32700, 96, 1024, "64x128"),
+    (3001, 1900, 320, "64x128"), (900, 4000, 1024, "64x128"),
+    # more tiles than that, or a second round too short for it, or a weight too large
+    (3001, 2300, 128, "128x128"), (3001, 1900, 192, "128x128"), (500, 5000, 576, "128x128"), (700, 3800, 1280, "128x128"),
 ])
-def test_small_launches_give_the_tile_kernels_bits(torch_cuda, M, N, K):
+def test_small_launches_give_the_tile_kernels_bits(torch_cuda, M, N, K, tile):
     """The automatic choice for launches that do not fill the chip walks k in the same order as the 128x128 kernel: same bits."""
     import paper_2505_24791_amd as sjd
     torch = torch_cuda
+    # the choice, restated
+    t6 = _tiles(M, N, 64, 128)
+    assert _tiles(M, N, 128, 128) <= 512
+    small = t6 <= (768 if K >= 256 else 512) and (N <= 2560 or N * K <= (4 << 20 if N <= 4096 else 5 << 19))
+    assert tile == ("64x64" if _tiles(M, N, 64, 64) <= 512 else "64x128" if small else "128x128")
     for dtype in (torch.float16, torch.bfloat16):
         a, _, wt, bias = _operands(torch, M, N, K, dtype, seed=M)
         ad, wd, bd = a.cuda(), wt.cuda(), bias.cuda()
@@ -87,10 +101,6 @@ def test_small_launches_give_the_tile_kernels_bits(torch_cuda, M, N, K):
         for rd, kernel in zip(r, (0, 3)):
             sjd.op_linear_h16(ad, wd, bd, M, N, K, 2, resid=rd, kernel=kernel)
         assert torch.equal(r[0], r[1])
-
-
-def _tiles(M, N, bm, bn):
-    return -(-M // bm) * -(-N // bn)
 
 
 @pytest.mark.parametrize("M,N,K,one_round", [
