@@ -3,7 +3,7 @@
 //
 // A step of the sequential inverse is a chain of 5 N dependent skinny products on a handful of rows; launched
 // one by one every link costs a kernel boundary plus a cold start.  Here the chain runs inside one cooperative
-// launch of one workgroup per CU.  The workgroups of `xpg` neighbouring XCDs (1, 2, 4 or 8) form a group; each
+// launch of one workgroup per CU.  The workgroups of `xpg` neighbouring XCDs (1, 2, 4 or 8; seq_groups.h) form a group; each
 // group takes an equal share of the samples and carries them through the whole block on its own.  Inside a group
 // every product is split by output columns over the members, attention by (sample, head) pairs.
 //
@@ -30,6 +30,7 @@
 // combined by the parallel formula for variances; 16x16x32 MFMA with K split over the 8 waves of a workgroup and partial sums
 // added in wave order; float32 residual stream.  A row's result does not depend on which group or member computes it.
 #include "common.h"
+#include "seq_groups.h"
 
 namespace sjd {
 
@@ -525,29 +526,17 @@ __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
             if (++it > a.spin_max) { ok = 0; break; }
             __builtin_amdgcn_s_sleep(2);
         }
-        int count[8], present = 0, rank = 0;
-        for (int g = 0; g < 8; ++g) {
-            count[g] = __hip_atomic_load(&a.sync[g], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-            if (g == xcc) rank = present;
-            present += count[g] > 0 ? 1 : 0;
-        }
-        const int gidx = rank / a.xpg;
-        int n = 0, before = 0, seen = 0;             // members of the group; those on its lower XCDs
-        for (int g = 0; g < 8; ++g) {
-            if (count[g] > 0) {
-                if (seen / a.xpg == gidx) { n += count[g]; if (g < xcc) before += count[g]; }
-                ++seen;
-            }
-        }
+        int count[8];
+        for (int g = 0; g < 8; ++g) count[g] = __hip_atomic_load(&a.sync[g], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
+        const SeqGroup grp = seq_group_of(count, xcc, a.xpg, a.B, RW_ROWS);
         if (!ok) __hip_atomic_store(c.status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sh[0] = ok; sh[1] = before + slot; sh[2] = n; sh[3] = (present + a.xpg - 1) / a.xpg; sh[4] = gidx; sh[7] = 0;
+        sh[0] = ok; sh[1] = grp.before + slot; sh[2] = grp.members; sh[3] = grp.per; sh[4] = grp.index; sh[7] = 0;
     }
     __syncthreads();
     if (!sh[0]) return;
     c.slot = sh[1]; c.n = sh[2];
-    const int groups = sh[3], gidx = sh[4];
-    const int per = (a.B + groups - 1) / groups;  // samples per group
-    if (per > RW_ROWS) {                           // fewer groups than the host planned for
+    const int per = sh[3], gidx = sh[4];           // samples per group
+    if (per > RW_ROWS) {                           // too few XCDs for the batch
         if (c.tid == 0) __hip_atomic_store(c.status, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }

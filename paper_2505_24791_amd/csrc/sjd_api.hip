@@ -737,7 +737,7 @@ int run_sequential_persistent(sjd_flow *f, int j, const float *z, float *x, int 
     HIP_TRY(hipGetLastError());
     if (f->host_pin[0] != 0) {
         fail(SJD_EHIP, "persistent sequential kernel: %s",
-             f->host_pin[0] == 2 ? "fewer XCD groups than planned for" : "a wait for other workgroups timed out");
+             f->host_pin[0] == 2 ? "too few XCDs for the batch" : "a wait for other workgroups timed out");
         // every wave has left the kernel (bounded waits); z is untouched and x, the caches and the workspaces are
         // simply written again, so in automatic mode the caller runs the block by per-step launches instead
         return SJD_ELAUNCH_RETRY;
