@@ -590,38 +590,48 @@ void fast_step(sjd_flow *f, int j, const float *z, float *x, int B, bool frag, h
     }
 }
 
-// The same step in float32 (decode_f32.hip): LayerNorm inside the projections where the width is covered.
+// The same step in float32: projections on the kernels of decode_f32.hip, LayerNorm inside where the width is covered.  Those read the
+// weights once per 32 rows; flows created for very many samples take the whole-sequence kernels.  Microseconds a step, 2 layers, 24
+// tokens, step kernels / whole-sequence kernels, full batch: width 1024, 256 samples 444 / 387, 768 1203 / 560, 1024 1579 / 639; width 512,
+// 512 samples 219 / 232, 1536 523 / 354, 4096 1258 / 702; width 128, 1024 samples 103 / 117, 4096 252 / 160; four samples: width 1024 99 / 364,
+// width 128 46 / 92.  The flow's largest batch decides, not the call's, so that a sample gives the same bits in any batch; as calls
+// with few samples would rather have the step kernels, the line lies at three to four times the crossing.
+bool tall_f32(const sjd_config &c) { return (size_t)c.max_batch * c.width > 768 * 1024; }
+
 void fast_step_f32(sjd_flow *f, int j, const float *z, float *x, int B, hipStream_t s) {
     const sjd_config &c = f->cfg;
     const int T = c.seq_len, W = c.width, D = c.token_dim, H = c.n_heads, RW = c.mlp_ratio * c.width;
     const int rev = (c.reverse_mask >> j) & 1;
     const BlockW &bw = f->block[j];
     float *a = (float *)f->a, *qkv = (float *)f->qkv, *o = (float *)f->o, *ff = (float *)f->f;
-    const bool ln_in = skinny_f32_ln_ok(W);
+    const bool tall = tall_f32(c), ln_in = !tall && skinny_f32_ln_ok(W);
     auto bytes = [&](int N, int K, double outs) { return 4.0 * ((double)K * N + (double)B * K + outs * B * N); };
-    auto ln_project = [&](int fam, const float *g, const float *be, const float *w, const float *bias, float *out, int N, Epi epi) {
+    // ldb: floats between rows of w (N, but for the head matrix of the whole-sequence kernels)
+    auto ln_project = [&](int fam, const float *g, const float *be, const float *w, int ldb, const float *bias, float *out, int N, Epi epi) {
         ProfScope ps(f, fam, 2.0 * B * (double)N * W, bytes(N, W, 1), s);
         if (!ln_in) launch_layernorm<float>(f->h, g, be, a, B, W, s);
-        launch_skinny_f32(ln_in ? f->h : a, ln_in ? g : nullptr, be, w, bias, nullptr, out, B, N, W, epi, s);
+        if (tall) launch_gemm_f32(a, w, ldb, bias, nullptr, out, B, N, W, epi, s);
+        else launch_skinny_f32(ln_in ? f->h : a, ln_in ? g : nullptr, be, w, bias, nullptr, out, B, N, W, epi, s);
     };
     auto resid_project = [&](const float *in, const float *w, const float *bias, int K) {
         ProfScope ps(f, SJD_PROF_DECODE_RESID, 2.0 * B * (double)K * W, bytes(W, K, 2), s);
-        launch_skinny_f32(in, nullptr, nullptr, w, bias, f->h, f->h, B, W, K, EPI_BIAS_RESIDUAL, s);
+        if (tall) launch_gemm_f32(in, w, W, bias, f->h, f->h, B, W, K, EPI_BIAS_RESIDUAL, s);
+        else launch_skinny_f32(in, nullptr, nullptr, w, bias, f->h, f->h, B, W, K, EPI_BIAS_RESIDUAL, s);
     };
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerW &lw = bw.layer[l];
         const size_t layer_off = (size_t)l * c.max_batch * T * W;
-        ln_project(SJD_PROF_DECODE_GEMM, lw.ln1_g, lw.ln1_b, lw.w_qkv, lw.b_qkv, qkv, 3 * W, EPI_BIAS);
+        ln_project(SJD_PROF_DECODE_GEMM, lw.ln1_g, lw.ln1_b, lw.w_qkv, 3 * W, lw.b_qkv, qkv, 3 * W, EPI_BIAS);
         {
             ProfScope ps(f, SJD_PROF_DECODE_ATTN, 4.0 * B * (T / 2.0) * W, 4.0 * B * (2.0 * (T / 2.0) * W + 4.0 * W), s);
             launch_decode_attention_f32(qkv, (float *)f->kcache + layer_off, (float *)f->vcache + layer_off, o, f->t_dev, B, T,
                                         H, W / H, s);
         }
         resid_project(o, lw.w_o, lw.b_o, W);
-        ln_project(SJD_PROF_DECODE_FC1, lw.ln2_g, lw.ln2_b, lw.w_fc1, lw.b_fc1, ff, RW, EPI_BIAS_GELU);
+        ln_project(SJD_PROF_DECODE_FC1, lw.ln2_g, lw.ln2_b, lw.w_fc1, RW, lw.b_fc1, ff, RW, EPI_BIAS_GELU);
         resid_project(ff, lw.w_fc2, lw.b_fc2, RW);
     }
-    ln_project(SJD_PROF_DECODE_HEAD, bw.lnf_g, bw.lnf_b, bw.w_head, bw.b_head, f->p, 2 * D, EPI_BIAS);
+    ln_project(SJD_PROF_DECODE_HEAD, bw.lnf_g, bw.lnf_b, tall ? bw.w_head4 : bw.w_head, head_ld(c), bw.b_head, f->p, 2 * D, EPI_BIAS);
     {
         ProfScope ps(f, SJD_PROF_EPILOGUE, 0.0, (double)B * (D * 16.0 + W * 4.0), s);
         launch_decode_advance(f->p, z, x, bw.w_in, bw.b_in, bw.pos, f->h, f->t_dev, f->ticket, B, T, D, W, rev, 0, false, s);

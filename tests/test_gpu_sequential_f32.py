@@ -1,6 +1,6 @@
 """Single-token steps of float32 flows against the CPU oracle: every width whose LayerNorm is part of a projection and
 one whose is not, every head size of the attention kernel, row counts around the 16-row blocks, head columns that no
-tile divides.  Needs an MI355X.  Tolerance: 1e-4 on the block's output (the float32 bound of this build)."""
+tile divides; flows created for so many samples that the whole-sequence projections take the steps.  Needs an MI355X.  Tolerance: 1e-4 on the block's output (the float32 bound of this build)."""
 import numpy as np
 import pytest
 
@@ -18,6 +18,8 @@ CASES = [
     (768, 12, 1, 9, 11, 40),
     (1024, 16, 1, 7, 48, 3),
     (48, 4, 1, 10, 4, 5),          # head size 12: the plain path
+    (256, 4, 1, 6, 5, 3073),       # max_batch * width above 768 K: whole-sequence projections, token size that pads the head matrix
+    (1024, 16, 1, 5, 8, 769),
 ]
 
 
