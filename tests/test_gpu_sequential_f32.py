@@ -1,6 +1,7 @@
 """Single-token steps of float32 flows against the CPU oracle: every width whose LayerNorm is part of a projection and
-one whose is not, every head size of the attention kernel, row counts around the 16-row blocks, head columns that no
-tile divides; flows created for so many samples that the whole-sequence projections take the steps.  Needs an MI355X.  Tolerance: 1e-4 on the block's output (the float32 bound of this build)."""
+one whose is not, every head size of the attention kernel below and above the keys it walks at a time, row counts around
+the 16-row blocks, head columns that no tile divides; flows made for so many samples that the whole-sequence projections
+take the steps.  Needs an MI355X.  Tolerance: 1e-4 on the block's output (the float32 bound of this build)."""
 import numpy as np
 import pytest
 
@@ -17,13 +18,18 @@ CASES = [
     (512, 4, 1, 20, 12, 33),       # head size 128
     (768, 12, 1, 9, 11, 40),
     (1024, 16, 1, 7, 48, 3),
+    # past the keys that the attention kernel walks at a time (256, 128, 64 and 32 at head sizes 16 to 128), with a remainder
+    (64, 4, 1, 270, 4, 2),
+    (64, 2, 1, 140, 3, 3),
+    (128, 2, 1, 133, 5, 2),
+    (256, 2, 1, 70, 4, 2),
     (48, 4, 1, 10, 4, 5),          # head size 12: the plain path
     (256, 4, 1, 6, 5, 3073),       # max_batch * width above 768 K: whole-sequence projections, token size that pads the head matrix
     (1024, 16, 1, 5, 8, 769),
 ]
 
 
-@pytest.mark.parametrize("W,H,N,T,D,B", CASES, ids=[f"w{c[0]}_dh{c[0] // c[1]}_b{c[5]}" for c in CASES])
+@pytest.mark.parametrize("W,H,N,T,D,B", CASES, ids=[f"w{c[0]}_dh{c[0] // c[1]}_t{c[3]}_b{c[5]}" for c in CASES])
 def test_float32_steps_match_oracle(orc32, W, H, N, T, D, B):
     import torch
     import paper_2505_24791_amd as sjd
