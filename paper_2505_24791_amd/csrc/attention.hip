@@ -1,9 +1,9 @@
 // Causal multi-head attention.
 //
 //  * attention_rows_kernel: one wave per (sample, head, query row), any head size and sequence
-//    length, float32, bf16 or f16 storage, float32 arithmetic.  It serves the float32 configuration's
-//    whole-sequence passes and, with a key/value cache, every single-token step of the sequential
-//    inverse (Sec. 3.5), where it is bound by reading the cached prefix from HBM.
+//    length, float32, bf16 or f16 storage, float32 arithmetic.  It serves whole-sequence passes of head sizes other than 64, the
+//    masked probe and, with a key/value cache, the single-token steps (Sec. 3.5) that neither the step kernels (decode.hip,
+//    decode_f32.hip) nor the persistent kernel cover.
 //  * flash_attention_h16_kernel: whole-sequence causal attention for head size 64 on 16-bit data with
 //    MFMA; K and V tiles are staged in LDS, scores never leave registers (online softmax in float32), so
 //    there is no T x T buffer.

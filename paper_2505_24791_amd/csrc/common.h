@@ -309,7 +309,7 @@ struct SeqLayer {
 constexpr int kSeqMaxLayers = 32;
 struct SeqArgs {
     SeqLayer layers[kSeqMaxLayers];  // in the kernel-argument segment: read with scalar loads, no pointer chasing
-    int n_layers, ratio;
+    int n_layers;
     const float *lnf_g, *lnf_b, *b_head;
     const void *f_head;
     const float *w_in, *b_in, *pos;
@@ -320,13 +320,14 @@ struct SeqArgs {
     size_t kv_layer_stride;  // elements between layers
     int B, T, D, reversed;
     int xpg;               // XCDs per group (1, 2, 4 or 8)
-    int *sync;             // [0..7] members per XCD, [8] arrivals, [9] status
+    int *sync;             // kSeqSyncWords: [0..7] members per XCD, [8] arrivals, [9] status
     int spin_max;
 };
 // Bytes per (row, column of width W) of the workspace: stream 4 + 3 slots of float32, qkv, attention output and MLP hidden
 // (3 + 1 + 4 widths) 3 slots of 16 bits; rows for 8 groups of 16 MB.
 constexpr uint32_t kSeqWsBytesPerElem = 4 * 4 + 3 * 4 + 3 * 2 * (3 + 1 + 4);
 inline size_t seq_persistent_ws_bytes(int MB, int W) { return (size_t)8 * 16 * MB * W * kSeqWsBytesPerElem; }
+constexpr int kSeqSyncWords = 16;
 size_t seq_persistent_lds_bytes(int MB, int D);
 // One workgroup of 512 threads per CU (grid = number of CUs), as a cooperative launch or a plain one.  W = 256 S.
 hipError_t launch_seq_persistent(bool is_bf16, const SeqArgs &args, int MB, int S, int grid, bool cooperative,

@@ -1,6 +1,8 @@
 // Single-token steps of the sequential inverse (eq. 5 with the key/value cache of Sec. 3.5) in float32: the float32
 // counterparts of the step kernels in decode.hip.  A step handles one position of every sample, so a projection
 // has as many rows as there are samples, and what it costs is the time until its weights have arrived.
+// Rows of activations, LayerNorm parameters and caches start on 16-byte boundaries (blocks of the blob are aligned, widths here are
+// multiples of 16); rows of a weight matrix are read by columns and may start anywhere.
 #include "common.h"
 
 namespace sjd {
@@ -10,10 +12,6 @@ namespace {
 // 16x16x4 float32 matrix instruction: lane (r = lane % 16, kg = lane / 16) feeds A[row r][k kg] and B[k kg][col r];
 // accumulator register v of that lane is row 4 kg + v, column r.
 __device__ __forceinline__ f32x4v mfma4(float a, float b, f32x4v c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-
-// four consecutive floats of a row whose start need not be 16-byte aligned (weights are used where they lie in
-// the blob, whose tensors are only 4-byte aligned from the second block on)
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int S32_NW = 8;     // waves per workgroup; they split k
 
@@ -72,7 +70,7 @@ __global__ __launch_bounds__(64 * S32_NW) void skinny_f32_kernel(const float *__
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
-            for (int i = 0; i < MB; ++i) xr[i][s] = *reinterpret_cast<const f32x4u *>(ap[i] + 16 * (s0 + s));
+            for (int i = 0; i < MB; ++i) xr[i][s] = *reinterpret_cast<const f32x4 *>(ap[i] + 16 * (s0 + s));
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
@@ -80,8 +78,8 @@ __global__ __launch_bounds__(64 * S32_NW) void skinny_f32_kernel(const float *__
         f32x4 gr[S], br[S];
 #pragma unroll
         for (int s = 0; s < S; ++s) {
-            gr[s] = *reinterpret_cast<const f32x4u *>(g + 16 * (s0 + s) + 4 * kg);
-            br[s] = *reinterpret_cast<const f32x4u *>(be + 16 * (s0 + s) + 4 * kg);
+            gr[s] = *reinterpret_cast<const f32x4 *>(g + 16 * (s0 + s) + 4 * kg);
+            br[s] = *reinterpret_cast<const f32x4 *>(be + 16 * (s0 + s) + 4 * kg);
         }
         float mean[MB], rstd[MB];
 #pragma unroll
@@ -130,7 +128,7 @@ __global__ __launch_bounds__(64 * S32_NW) void skinny_f32_kernel(const float *__
 #pragma unroll
                 for (int e = 0; e < 4; ++e) w[u][e] = bp[(size_t)(16 * (s + u) + e) * N];
 #pragma unroll
-                for (int i = 0; i < MB; ++i) a[u][i] = *reinterpret_cast<const f32x4u *>(ap[i] + 16 * (s + u));
+                for (int i = 0; i < MB; ++i) a[u][i] = *reinterpret_cast<const f32x4 *>(ap[i] + 16 * (s + u));
             }
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -149,7 +147,7 @@ __global__ __launch_bounds__(64 * S32_NW) void skinny_f32_kernel(const float *__
 #pragma unroll
                 for (int e = 0; e < 4; ++e) w[u][e] = bp[(size_t)(16 * su + e) * N];
 #pragma unroll
-                for (int i = 0; i < MB; ++i) a[u][i] = *reinterpret_cast<const f32x4u *>(ap[i] + 16 * su);
+                for (int i = 0; i < MB; ++i) a[u][i] = *reinterpret_cast<const f32x4 *>(ap[i] + 16 * su);
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u)

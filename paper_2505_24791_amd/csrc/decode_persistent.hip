@@ -658,7 +658,7 @@ __global__ __launch_bounds__(256) void seq_reset_kernel(uint4 *ws, size_t n16, i
     for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += (size_t)gridDim.x * 256)
         ws[i] = uint4{kEmpty, kEmpty, kEmpty, kEmpty};
     if (blockIdx.x == 0)
-        for (int i = threadIdx.x; i < 1024; i += 256) sync[i] = 0;
+        for (int i = threadIdx.x; i < kSeqSyncWords; i += 256) sync[i] = 0;
 }
 
 }  // namespace

@@ -3,8 +3,9 @@
 // Both operands are K-contiguous (the weights are stored transposed at load time), which is the
 // shape v_mfma_f32_32x32x16_{bf16,f16} wants: every lane feeds 8 consecutive k of one row.  A workgroup
 // of four waves (2 x 2) owns a BM x BN tile; a wave owns (BM/2) x (BN/2) as 32x32 MFMA blocks.
-// K is walked in index order through LDS.  Two main loops: one stages tiles through registers into
-// two padded LDS buffers; the other fills four LDS stages with LDS-direct loads (see below).
+// K is walked in index order through LDS.  Three main loops: one stages tiles through registers into
+// two padded LDS buffers; one fills four LDS stages of 256x256 tiles with LDS-direct loads; one keeps small tiles in a
+// ring of LDS-direct stages (see below).
 // No split-K and no atomics: an output row depends only on its own row of A, so results are
 // independent of which other rows share the tile or the batch.
 #include "common.h"

@@ -44,7 +44,6 @@ typedef __amdgpu_buffer_rsrc_t rsrc_t;
 typedef int i32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-#define SJD_Q_GPTR(p) ((const __attribute__((address_space(1))) void *)(p))
 #define SJD_Q_LPTR(p) ((__attribute__((address_space(3))) void *)(p))
 
 template <typename HT, typename OutT, int EPI>

@@ -92,7 +92,7 @@ struct sjd_flow {
     int use_graphs = 1;
     int mask_nearest = 0;        // o of the masked-dependency probe (eq. 6); 0: plain causal attention
     int seq_path = 0;            // 0 automatic, 1 per-step launches (graph replay), 2 persistent kernel, 3 the same, plain launch
-    int *psync = nullptr;        // synchronisation words of the persistent kernel (1024 ints)
+    int *psync = nullptr;        // synchronisation words of the persistent kernel (kSeqSyncWords ints)
     void *seq_ws = nullptr;      // its activations
     int n_cus = 0, n_cus_device = 0, coop = 0;   // workgroups of the persistent kernel; CUs of the device
     hipEvent_t ev[SJD_MAX_BLOCKS + 1] = {};
@@ -712,7 +712,7 @@ int run_sequential_persistent(sjd_flow *f, int j, const float *z, float *x, int 
     const BlockW &bw = f->block[j];
     const int MB = batch <= 128 ? 1 : 2;
     SeqArgs a{};
-    a.n_layers = c.n_layers; a.ratio = c.mlp_ratio;
+    a.n_layers = c.n_layers;
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerW &lw = bw.layer[l];
         a.layers[l] = SeqLayer{lw.ln1_g, lw.ln1_b, lw.b_qkv, lw.b_o, lw.ln2_g, lw.ln2_b, lw.b_fc1, lw.b_fc2,
@@ -762,9 +762,11 @@ int run_sequential(sjd_flow *f, int j, const float *z, float *x, int batch, hipS
     if (f->mask_nearest == 0) {   // the masked probe takes the plain per-step path below in every mode
         if (f->seq_path >= 2 && !persistent_ok(f, batch))
             return fail(SJD_EINVAL, "the persistent sequential kernel does not cover this configuration");
-        // automatic choice: the persistent kernel wherever it applies (microseconds a step against per-step launches: width
-        // 1024, 8 layers, 1024 tokens, 32 samples 284 against 340; 2 layers, 256 tokens, 256 samples 175 against 247; width 256,
-        // 4 layers, 512 tokens, one sample 55 against 93)
+        // automatic choice: the persistent kernel wherever it applies.  Microseconds a step against per-step launches, 2 layers:
+        //   width 1024, 1 / 16 / 32 / 64 / 128 / 256 samples:  600 tokens 47 56 70 91 145 235 against 83 87 89 130 196 309; 1024 tokens
+        //   50 61 79 110 183 311 against 88 93 98 149 236 385; 2048 tokens 58 73 104 157 276 against 102 108 118 194 332; 4096 tokens, 16 to 128
+        //   96 150 248 456 against 138 160 286 527;  width 512, 64 and 128 samples: 1024 tokens 61 87 against 93 124, 4096 tokens 132 219
+        //   against 155 257;  width 256, 64 and 256 samples: 1024 tokens 38 79 against 76 107, 4096 tokens 66 194 against 121 225.
         if (f->seq_path != 1 && persistent_ok(f, batch)) {
             const int rc = run_sequential_persistent(f, j, z, x, batch, s);
             if (rc != SJD_ELAUNCH_RETRY) return rc;
@@ -816,7 +818,7 @@ int sjd_flow_create(const sjd_config *cfg, sjd_flow **out) {
     f->cfg = c;
     f->device = dev;
     const size_t T = c.seq_len, W = c.width, D = c.token_dim, R = c.mlp_ratio, B = c.max_batch, N = c.n_layers;
-    const size_t M = B * T > 512 ? B * T : 512, ab = act_bytes(f);  // the single-token paths work on up to 8 x 32 rows; the persistent kernel keeps two copies of its residual stream
+    const size_t M = B * T > 512 ? B * T : 512, ab = act_bytes(f);  // the 16-bit step kernels work on up to 256 rows in groups of up to 64
     int rc = SJD_OK;
     auto A = [&](void **p, size_t n) { if (rc == SJD_OK) rc = dev_alloc(f, p, n); };
     A((void **)&f->blob, (size_t)c.n_blocks * block_stride(c) * sizeof(float));
@@ -843,7 +845,7 @@ int sjd_flow_create(const sjd_config *cfg, sjd_flow **out) {
     A((void **)&f->active[0], B * 4);
     A((void **)&f->active[1], B * 4);
     A((void **)&f->trace, 2 * T * B * 4);
-    A((void **)&f->psync, 1024 * sizeof(int));
+    A((void **)&f->psync, kSeqSyncWords * sizeof(int));
     if (frag_ok(f, 0)) A(&f->seq_ws, seq_persistent_ws_bytes(B <= 128 ? 1 : 2, (int)W));
     {
         hipDeviceProp_t prop;
