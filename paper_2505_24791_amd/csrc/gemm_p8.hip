@@ -21,10 +21,12 @@
 // Measured (us per launch, k-tiles of 32 in four stages -> this; IEEE half, bias / GELU / float32 residual epilogue):
 //   32768 x 3072 x 1024 bias 197 -> 178, 32768 x 4096 x 1024 GELU 300 -> 278, 32768 x 1024 x 1024 residual 101 -> 85,
 //   32768 x 1024 x 4096 residual 281 -> 246, 65536 x 768 x 3072 residual 337 -> 297.
-// What bounds it: power.  The matrix pipe is busy 71 % of the cycles of the K = 4096 launch at a clock of 1.55 GHz; a
-// loop of nothing but these instructions on random operands runs at 1.64 GHz (1.72 PFLOP/s).  Taking out the waits
-// and the barrier gains 4 %, and four waves of 128 x 128 (a third fewer LDS reads) take as long with more idle cycles
-// at a higher clock.
+// What bounds it: no single unit.  Power allows a loop of nothing but these instructions on random operands 1.64 GHz (1.72 PFLOP/s);
+// at about that clock the matrix pipe is busy 69 % of the cycles at N = 3072, K = 1024 (bias), 66 % at N = 1024, K = 4096 (residual), 56 %
+// at N = 4096, K = 1024 (GELU) and 39 % at N = K = 1024 (residual).  The rest is the operand stream into LDS (8 to 9 TB/s out of
+// L2; waves wait for data or the barrier 30 to 49 % of their time) and the epilogues, which nothing hides: at the bias launch's rate the GELU
+// launch would take 240 us of its 276 and the last one 60 of 94.  Taking out the waits and the barrier gains 4 %, and four waves of 128
+// x 128 (a third fewer LDS reads) take as long with more idle cycles at a higher clock.
 #include "common.h"
 #include <atomic>
 
