@@ -772,7 +772,8 @@ int run_sequential(sjd_flow *f, int j, const float *z, float *x, int batch, hipS
             if (rc != SJD_ELAUNCH_RETRY) return rc;
             if (f->seq_path != 0) return SJD_EHIP;      // the persistent kernel was asked for explicitly
         }
-        if (fast_decode_ok(f) || fast_decode_f32_ok(f)) return run_sequential_fast(f, j, z, x, batch, s);
+        // a single token takes no step: float32 flows copy it below (5 us; with the embedding of a next token that is not there 9)
+        if (fast_decode_ok(f) || (T > 1 && fast_decode_f32_ok(f))) return run_sequential_fast(f, j, z, x, batch, s);
     }
     launch_decode_epilogue(f->p, z, x, batch, T, D, -1, rev, s);  // x_1 = y_1
     for (int t = 0; t + 1 < T; ++t) decode_step(f, j, z, x, batch, t, s);

@@ -18,6 +18,7 @@ CASES = [
     (512, 4, 1, 20, 12, 33),       # head size 128
     (768, 12, 1, 9, 11, 40),
     (1024, 16, 1, 7, 48, 3),
+    (128, 4, 1, 1, 5, 3),          # one token: copied
     # past the keys that the attention kernel walks at a time (256, 128, 64 and 32 at head sizes 16 to 128), with a remainder
     (64, 4, 1, 270, 4, 2),
     (64, 2, 1, 140, 3, 3),
