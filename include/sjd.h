@@ -263,10 +263,10 @@ SJD_API int sjd_flow_set_mask_nearest(sjd_flow *flow, int o);
  * 0 automatic (the persistent kernel where it applies, else per-step launches), 1 per-step launches
  * replayed as a graph, 2 the persistent kernel (SJD_EINVAL at the call if the configuration is outside
  * what it covers: head size 64, W in {256, 512, 768, 1024}, MLP ratio 4, batch <= 256, token size <= 64, at most 32
- * layers, a layer's key cache below 4 GiB), 3 the persistent kernel started with an ordinary launch instead of a cooperative one (for tools that cannot follow
- * cooperative launches; needs an otherwise idle device, and reports SJD_EHIP instead of waiting
- * forever if its workgroups do not all become resident).  All compute eq. 5 with the
- * key/value cache of Sec. 3.5; they differ in how the T-1 dependent steps are scheduled on the GPU. */
+ * layers, a layer's key cache below 4 GiB), 3 the persistent kernel started with an ordinary launch instead of
+ * a cooperative one (for tools that cannot follow cooperative launches; needs an otherwise idle device, and
+ * reports SJD_EHIP instead of waiting forever if its workgroups do not all become resident).  All compute eq. 5
+ * with the key/value cache of Sec. 3.5; they differ in how the T-1 dependent steps are scheduled on the GPU. */
 SJD_API int sjd_flow_set_sequential_path(sjd_flow *flow, int path);
 
 /* Number of workgroups of the persistent sequential kernel: 0 (the default) = one per CU of the device,
