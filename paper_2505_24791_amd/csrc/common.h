@@ -320,6 +320,8 @@ struct SeqArgs {
     size_t kv_layer_stride;  // elements between layers
     int B, T, D, reversed;
     int xpg;               // XCDs per group (1, 2, 4 or 8)
+    int kv_stream;         // 1: cached rows are loaded with the streaming hint
+    int kv_ahead;          // 1: the first cached rows of a pair are requested into LDS between the stages before (one row block only)
     int *sync;             // kSeqSyncWords: [0..7] members per XCD, [8] arrivals, [9] status
     int spin_max;
 };

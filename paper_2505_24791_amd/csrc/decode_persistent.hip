@@ -31,6 +31,7 @@
 // added in wave order; float32 residual stream.  A row's result does not depend on which group or member computes it.
 #include "common.h"
 #include "seq_groups.h"
+#include <type_traits>
 
 namespace sjd {
 
@@ -53,8 +54,8 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void *p, uint32_t bytes) {
 __device__ __forceinline__ i32x4 ld16(rsrc_t rs, uint32_t byte_off) {
     return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, 16));
 }
-// the same for rows of the key/value cache, with the streaming hint on top: a row is read once per step and
-// the cache is far larger than any cache level, so it should not displace the weights, which every step reads again
+// the same for rows of a key/value cache too large for the memory-side cache, with the streaming hint on top: a row is read once per
+// step and should not displace the weights, which every step reads again
 __device__ __forceinline__ i32x4 ld16_stream(rsrc_t rs, uint32_t byte_off) {
     return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, 16 | 2));
 }
@@ -79,6 +80,15 @@ __device__ __forceinline__ float sum_rows(float x) {   // lanes that agree in bi
     x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
     const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+}
+// a lane of the lower half gets a's sum over both halves, one of the upper half b's; the same for even and odd rows of sixteen
+__device__ __forceinline__ float add_halves32(float a, float b) {
+    const auto v = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(v[0]) + __uint_as_float(v[1]);
+}
+__device__ __forceinline__ float add_halves16(float a, float b) {
+    const auto v = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(v[0]) + __uint_as_float(v[1]);
 }
 __device__ __forceinline__ float max_rows(float x) {
     const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -105,6 +115,7 @@ struct Ctx {
     int row0, nrows;    // first sample of the group, samples of the group
     int cw;             // columns of a unit of the residual projections (4, 8 or 16)
     int spin_max;
+    bool kv_stream;     // cached rows are loaded with the streaming hint
     int *status;
     LdsInt *bad;        // a wait of this workgroup gave up
 };
@@ -153,17 +164,24 @@ __device__ __forceinline__ void poll16(const Ctx &c, rsrc_t rs, OFF off, i32x4 (
 // matrix operand and rows the second, so a lane ends up with four consecutive columns of one row.
 // 16-bit results go to out_off (fragment-major; the member's part at empty_off is emptied); with LOCAL the float32
 // result goes to the workgroup's own buffer (row-major [16 MB][N], row 0 = the group's first row) and the member takes every block.
-template <typename HT, int MB, int S, int CB, int EPI, bool LOCAL>
+// A member without a share of a stage still requests its part of the cached rows: behind the same wait and barrier as in the stage.
+template <class AHEAD> __device__ __forceinline__ void idle_ahead(AHEAD ahead) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    __syncthreads();
+    ahead();
+}
+
+template <typename HT, int MB, int S, int CB, int EPI, bool LOCAL, class AHEAD>
 __device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t ws, uint32_t in_off, const float *__restrict__ g,
                                               const float *__restrict__ be, const HT *__restrict__ Wt,
                                               const float *__restrict__ bias, uint32_t out_off, uint32_t empty_off,
-                                              float *local, int N, f32x4v *red, float2 *stat) {
+                                              float *local, int N, f32x4v *red, float2 *stat, AHEAD ahead) {
     typedef typename Half16<HT>::v8 v8;
     typedef typename Half16<HT>::v4 v4;
     constexpr int W = 256 * S, KS = 8 * S;
     const int nbt = (N + 15) >> 4;
     const int slot = LOCAL ? 0 : c_in.slot, n = LOCAL ? 1 : c_in.n;
-    if (slot >= nbt) return;
+    if (slot >= nbt) { idle_ahead(ahead); return; }
     const Ctx c = local_ctx(c_in);
     const int k0 = c.wave * 32 * S + c.kg * 8;
     v8 w[CB][S];
@@ -228,6 +246,7 @@ __device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t ws, uint32
         if (c.kg == 0) stat[c.wave * (MB * 16) + i * 16 + c.r] = float2{mw, m2};
     }
     __syncthreads();
+    ahead();
     v8 fa[MB][S];
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
@@ -304,14 +323,14 @@ __device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t ws, uint32
 // A (at a_off) 16-bit fragment-major, the streams float32 fragment-major.  A unit is cw columns: with many members a 16-column
 // block is shared out among two or four of them (the lanes of the other columns repeat theirs), so that every
 // member pulls an equal, small piece of the weights; unit u belongs to member u % n.
-template <typename HT, int MB, int S, int KMUL>
+template <typename HT, int MB, int S, int KMUL, class AHEAD>
 __device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t ws, uint32_t a_off, const HT *__restrict__ Wt,
                                                  const float *__restrict__ bias, uint32_t in_off, uint32_t out_off,
-                                                 uint32_t empty_off, f32x4v *red) {
+                                                 uint32_t empty_off, f32x4v *red, AHEAD ahead) {
     typedef typename Half16<HT>::v8 v8;
     constexpr int W = 256 * S, KSN = W / 32, KSA = 8 * S * KMUL, KSW = S * KMUL;
     const int nu = W / c_in.cw;
-    if (c_in.slot >= nu) return;
+    if (c_in.slot >= nu) { idle_ahead(ahead); return; }
     const Ctx c = local_ctx(c_in);
     const int cmask = c.cw - 1;
     v8 w[KSW];
@@ -352,6 +371,7 @@ __device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t ws, uin
             red[(c.wave * MB + i) * 64 + c.lane] = acc;
         }
         __syncthreads();
+        if (u == c.slot) ahead();
         if (finish) {
             f32x4v t = red[c.wave * 64 + c.lane];
 #pragma unroll
@@ -372,13 +392,57 @@ __device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t ws, uin
 // exchange, the four waves through LDS).  The partition of the keys and the order of the sums depend on t only.
 // Cached rows do not depend on the current step: the first batch is requested before the poll for q, k, v, and each
 // next batch (of this pair or the next) as soon as the registers of the current one have been used.
+// What bounds it: memory and the load path of a CU (64 bytes a clock) where the prefix is long, else the serial chain behind the last
+// score: groups hand on the half of their sums that they do not keep, and a wave finishes a pair, one element a lane.  Microseconds a step, with
+// eight lanes finishing 64 elements, three exchanges a sum and loads issued for rows past the prefix -> now: width 512, 4 layers, one sample 57.5 ->
+// 55.6; width 256, 6 layers, 37 samples 81.5 -> 77.5; width 768, 8 layers, 256 samples 445 -> 420; width 1024, 8 layers, 32 samples of
+// 1024 tokens 282 -> 270.
+//
+// AHEAD: the first 32 P_LU keys of a member's first two pairs come out of LDS: while the other four stages of a layer exchange
+// their results the memory that holds the cache is idle, and what it costs to stream the cached rows of a long prefix is its bandwidth.
+// They are requested by LDS-direct loads between those stages (kv_ahead), each thread the pieces that it reads itself, so the order
+// "requested, waited for by the next poll, read" needs no barrier.  The registers then hold the P_AU rows that follow: batch 0 is
+// rows 0..P_LU-1 from LDS and the others from registers, and the first P_LU registers are a batch further.
+// Same bits.  Microseconds a step without -> with: width 1024, 8 layers, 19 samples of 777 tokens 225 -> 216, 32 of 1024 270 -> 258.
 constexpr int P_NSUB = 2;
 constexpr int P_AU = 8;  // cache rows per thread and batch
+constexpr int P_LU = 5;  // of batch 0 of the first pairs: rows in LDS (what it has left of 160 KB at token size 64)
+constexpr int P_AHEAD_BYTES = 2 * P_LU * P_THREADS * 16;
+constexpr int P_AHEAD_STEPS[5] = {0, 3, 5, 8, 10};   // loads per thread after each of the four stages: K rows 0..P_LU-1, then V rows
+static_assert(P_AHEAD_STEPS[4] == 2 * P_LU, "every row is requested");
 
-template <typename HT, int MB, int S>
+// Part `part` (0..3) of the rows that the attention of a layer finds in LDS, for position t.  A row is requested at the
+// earliest behind the barrier of the stage that follows the attention which wrote it, and the writer has waited for its store by then.
+template <int S>
+__device__ __forceinline__ void kv_ahead(const Ctx &c_in, int part, const void *kc, const void *vc, int t, int T, uint32_t lds0) {
+    constexpr int W = 256 * S, H = W / 64;
+    const Ctx c = local_ctx(c_in);
+    const int sub = c.wave >> 2, stid = c.tid & 255, dc = stid & 7, sg = stid >> 3;
+    const int pi = c.slot + sub * c.n;
+    if (t <= 0 || pi >= c.nrows * H) return;
+    const int row = pi / H, h = pi - row * H;
+    const uint32_t base = (uint32_t)(((size_t)(c.row0 + row) * T) * W + h * 64 + dc * 8) * 2u;
+#pragma unroll
+    for (int i = 0; i < 2 * P_LU; ++i) {
+        if (i < P_AHEAD_STEPS[part] || i >= P_AHEAD_STEPS[part + 1]) continue;
+        const int u = i < P_LU ? i : i - P_LU;
+        if (32 * u >= t) continue;
+        const int s = sg + 32 * u;
+        const uint32_t off = base + (uint32_t)(s < t ? s : t - 1) * (W * 2u);    // past the end: a row that is there, its score is masked
+        const uint32_t dst = lds0 + (uint32_t)(i * P_THREADS + c.wave * 64) * 16u;
+        const void *src = i < P_LU ? kc : vc;
+        // 64 lanes x 16 bytes from (scalar base + lane offset) to 1 KB of LDS at M0, past this CU's vector cache; nothing else here uses M0
+        if (c.kv_stream)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 sc1 nt" :: "s"(dst), "v"(off), "s"(src) : "memory");
+        else
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 sc1" :: "s"(dst), "v"(off), "s"(src) : "memory");
+    }
+}
+
+template <typename HT, int MB, int S, bool AHEAD>
 __device__ __forceinline__ void attention_stage(const Ctx &c_in, rsrc_t ws, uint32_t qkv_off, HT *kc, HT *vc, rsrc_t kc_rs,
                                                 rsrc_t vc_rs, uint32_t out_off, uint32_t empty_off, int t, int T,
-                                                float *opart, float2 *wst, int &par) {
+                                                float *opart, float2 *wst, int &par, const i32x4 *ahead) {
     typedef typename Half16<HT>::v8 v8;
     constexpr int W = 256 * S, H = W / 64, KS3 = 3 * W / 32;
     const int npairs = c_in.nrows * H;
@@ -389,18 +453,29 @@ __device__ __forceinline__ void attention_stage(const Ctx &c_in, rsrc_t ws, uint
     const int mine = (npairs - c.slot + c.n - 1) / c.n;    // pairs of this member
     const int nb = (t + 32 * P_AU - 1) / (32 * P_AU);      // batches of cached keys
     auto pair_of = [&](int k0) { return c.slot + (k0 + sub) * c.n; };
-    auto rows = [&](rsrc_t rs, int k0, int jb, i32x4 (&v)[P_AU]) {
+    auto rows = [&](rsrc_t rs, int k0, int jb, int u0, int u1, i32x4 (&v)[P_AU]) {   // rows u0 <= u < u1 of batch jb
         const bool valid = k0 + sub < mine;
         const int pi = valid ? pair_of(k0) : 0, row = pi / H, h = pi - row * H;
         const uint32_t base = (uint32_t)(((size_t)(c.row0 + row) * T) * W + h * 64 + dc * 8) * 2u;
+        auto all = [&](auto load) {
 #pragma unroll
-        for (int u = 0; u < P_AU; ++u) {
-            const int s = sg + 32 * (jb * P_AU + u);
-            v[u] = ld16_stream(rs, where(valid && s < t, base + (uint32_t)s * (W * 2u)));
-        }
+            for (int u = 0; u < P_AU; ++u) {
+                if (u < u0 || u >= u1) continue;
+                const int s0 = 32 * (jb * P_AU + u), s = s0 + sg;
+                // a load takes its time at the cache also where there is nothing to read
+                if (s0 < t) v[u] = load(rs, where(valid && s < t, base + (uint32_t)s * (W * 2u))); else v[u] = i32x4{0, 0, 0, 0};
+            }
+        };
+        if (c.kv_stream) all([](rsrc_t r, uint32_t off) { return ld16_stream(r, off); });
+        else all([](rsrc_t r, uint32_t off) { return ld16(r, off); });
     };
     i32x4 kk[P_AU], vv[P_AU];
-    if (nb > 0) { rows(kc_rs, 0, 0, kk); rows(vc_rs, 0, 0, vv); }
+    if (nb > 0) {
+        if constexpr (AHEAD) {
+            rows(kc_rs, 0, 0, P_LU, P_AU, kk); rows(vc_rs, 0, 0, P_LU, P_AU, vv);
+            rows(kc_rs, 0, 1, 0, P_LU, kk); rows(vc_rs, 0, 1, 0, P_LU, vv);
+        } else { rows(kc_rs, 0, 0, 0, P_AU, kk); rows(vc_rs, 0, 0, 0, P_AU, vv); }
+    }
     __builtin_amdgcn_sched_barrier(0);
     for (int k0 = 0; k0 < mine; k0 += P_NSUB) {
         const bool valid = (k0 + sub) < mine;
@@ -423,18 +498,19 @@ __device__ __forceinline__ void attention_stage(const Ctx &c_in, rsrc_t ws, uint
         float m = sg == 0 ? df : -INFINITY, l = sg == 0 ? 1.f : 0.f, acc[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] = sg == 0 ? (float)vf[e] : 0.f;
-        for (int jb = 0; jb < nb; ++jb) {
+        auto batch = [&](auto from_lds, int jb) {
+            constexpr int LU = decltype(from_lds)::value ? P_LU : 0;
             const bool more = jb + 1 < nb;
             const int nk0 = more ? k0 : k0 + P_NSUB, njb = more ? jb + 1 : 0;
             const bool next = more || nk0 < mine;
             float d[P_AU], mn = m;
 #pragma unroll
             for (int u = 0; u < P_AU; ++u) {
-                d[u] = score(__builtin_bit_cast(v8, kk[u]));
+                d[u] = score(__builtin_bit_cast(v8, u < LU ? ahead[u * P_THREADS + c.tid] : kk[u]));
                 if (sg + 32 * (jb * P_AU + u) >= t) d[u] = -INFINITY;
                 mn = fmaxf(mn, d[u]);
             }
-            if (next) rows(kc_rs, nk0, njb, kk);
+            if (next) { if (LU && more) rows(kc_rs, nk0, njb, P_LU, P_AU, kk); else rows(kc_rs, nk0, njb, 0, P_AU, kk); }
             const float mu = mn == -INFINITY ? 0.f : mn;       // a key group may not have any key yet
             const float corr = __builtin_amdgcn_exp2f(m - mu);
             m = mn;
@@ -444,58 +520,65 @@ __device__ __forceinline__ void attention_stage(const Ctx &c_in, rsrc_t ws, uint
 #pragma unroll
             for (int u = 0; u < P_AU; ++u) {
                 const float p = __builtin_amdgcn_exp2f(d[u] - mu);
-                const v8 v8v = __builtin_bit_cast(v8, vv[u]);
+                i32x4 vr = vv[u];
+                if (u < LU) { if (32 * u < t) vr = ahead[(P_LU + u) * P_THREADS + c.tid]; else vr = i32x4{0, 0, 0, 0}; }   // not requested: LDS may hold NaNs
+                const v8 v8v = __builtin_bit_cast(v8, vr);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) acc[e] = fmaf(p, (float)v8v[e], acc[e]);
                 l += p;
             }
-            if (next) rows(vc_rs, nk0, njb, vv);
+            if (next) { if (LU && more) rows(vc_rs, nk0, njb, P_LU, P_AU, vv); else rows(vc_rs, nk0, njb, 0, P_AU, vv); }
+        };
+        int jb = 0;
+        if constexpr (AHEAD) {
+            if (k0 == 0 && nb > 0) { batch(std::true_type{}, 0); jb = 1; }
         }
+        for (; jb < nb; ++jb) batch(std::false_type{}, jb);
         // the 8 key groups of a wave (lanes differing in bits 3..5), then the pair's four waves in order
         const float mw = max_rows(fmaxf(m, dpp<0x128>(m)));    // 0x128: rotated by eight within sixteen lanes
         const float f = __builtin_amdgcn_exp2f(m - (mw == -INFINITY ? 0.f : mw));
-        auto over_groups = [&](float x) { x *= f; return sum_rows(x + dpp<0x128>(x)); };
-        l = over_groups(l);
+        l *= f;
+        l = sum_rows(l + dpp<0x128>(l));
+        // eight sums over eight groups: at each level a lane passes on the half of the values that it does not keep, and ends up with
+        // elements e0 and e0 + 1 of its chunk
+        float x4[4], x2[2];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = over_groups(acc[e]);
+        for (int e = 0; e < 4; ++e) x4[e] = add_halves32(acc[e] * f, acc[e + 4] * f);
+#pragma unroll
+        for (int e = 0; e < 2; ++e) { x2[e] = add_halves16(x4[e], x4[e + 2]); x2[e] += dpp<0x128>(x2[e]); }
+        const int e0 = 4 * (c.lane >> 5) + 2 * ((c.lane >> 4) & 1);
         // With few pairs per member there is hardly ever a next one under way here, and the compiler should know: it would
         // wait at the start of the next stage, behind the stores of this one.
         if (MB == 1) __builtin_amdgcn_s_waitcnt(0x0F70);
         float *op = opart + par * (P_NW * 64);
         float2 *wp = wst + par * P_NW;
         par ^= 1;                                  // the other half may still be read by a slower wave
-        if (c.lane < 8) {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) op[c.wave * 64 + c.lane * 8 + e] = acc[e];
-            if (c.lane == 0) wp[c.wave] = float2{mw, l};
-        }
+        if ((c.lane & 8) == 0) *reinterpret_cast<float2 *>(&op[c.wave * 64 + dc * 8 + e0]) = float2{x2[0], x2[1]};
+        if (c.lane == 0) wp[c.wave] = float2{mw, l};
         __syncthreads();
-        if (valid && stid < 8) {
+        if (valid && stid < 64) {                  // one wave a pair, one element a lane
             const int w0 = 4 * sub;
             const float mm = fmaxf(fmaxf(wp[w0].x, wp[w0 + 1].x), fmaxf(wp[w0 + 2].x, wp[w0 + 3].x));
-            float fw[4], den = 0.f;
+            float den = 0.f, sum = 0.f;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) { fw[q] = __builtin_amdgcn_exp2f(wp[w0 + q].x - mm); den += wp[w0 + q].y * fw[q]; }
-            v8 ov;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int d = stid * 8 + e;
-                float s = 0.f;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) s += op[(w0 + q) * 64 + d] * fw[q];
-                ov[e] = from_f32<HT>(s / den);
+            for (int q = 0; q < 4; ++q) {
+                const float fw = __builtin_amdgcn_exp2f(wp[w0 + q].x - mm);
+                den += wp[w0 + q].y * fw;
+                sum += op[(w0 + q) * 64 + stid] * fw;
             }
-            i32x4 four = __builtin_bit_cast(i32x4, ov);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) four[v] = flagged(four[v]);
-            const uint32_t eo = (uint32_t)frag_off(wsrow, h * 64 + stid * 8, W / 32) * 2u;
-            st16(ws, out_off + eo, four);
-            st16(ws, empty_off + eo, i32x4{-1, -1, -1, -1});
+            const float val = sum / den, other = dpp<0xB1>(val);       // the neighbour's element: two to a word
+            typedef HT v2 __attribute__((ext_vector_type(2)));
+            if ((stid & 1) == 0) {
+                const int two = __builtin_bit_cast(int, v2{from_f32<HT>(val), from_f32<HT>(other)});
+                const uint32_t eo = (uint32_t)frag_off(wsrow, h * 64 + stid, W / 32) * 2u;
+                st4(ws, out_off + eo, flagged(two));
+                st4(ws, empty_off + eo, -1);
+            }
         }
     }
 }
 
-template <typename HT, int MB, int S, int CB>
+template <typename HT, int MB, int S, int CB, bool AHEAD>
 __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
     constexpr int W = 256 * S, RW_ROWS = 16 * MB, CBH = S <= 2 ? 2 : 4;
     constexpr int CBM = CB > CBH ? CB : CBH;
@@ -509,9 +592,12 @@ __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
     float *xs = opart + 2 * P_NW * 64;                                        // [16*MB][D]
     float *wemb = xs + RW_ROWS * a.D;                                         // [P_EB][D + 1][16]: w_in slice, then b_in
     float *pl = wemb + (size_t)P_EB * (a.D + 1) * 16;                         // [16*MB][2D]: this step's [mu | alpha] of the group's rows
+    i32x4 *kv = reinterpret_cast<i32x4 *>(pl + (size_t)RW_ROWS * 2 * a.D);    // [2 P_LU][512]: cached rows for the next attention
+    const uint32_t kv_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)kv;
 
     Ctx c;
     c.tid = threadIdx.x; c.lane = c.tid & 63; c.wave = c.tid >> 6; c.r = c.lane & 15; c.kg = c.lane >> 4;
+    c.kv_stream = a.kv_stream != 0;
     c.status = a.sync + 9; c.spin_max = a.spin_max; c.bad = (LdsInt *)&sh[7];
 
     // ---- groups: the workgroups of xpg XCDs, found from the hardware's XCC id
@@ -633,20 +719,33 @@ __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
             const rsrc_t kc_rs = make_rsrc(kc, (uint32_t)(a.kv_layer_stride * 2u));
             const rsrc_t vc_rs = make_rsrc(vc, (uint32_t)(a.kv_layer_stride * 2u));
             const int e3 = s3 == 0 ? 2 : s3 - 1;                // slot of the use before this one
+            // cached rows for the next attention: part 3 (behind the QKV projection) for this layer's, parts 0 to 2 for that of the next
+            // layer or of the next step's first
+            auto ahead = [&](int part) {
+                return [&, part]() { (void)part;
+                    if constexpr (AHEAD) {
+                        const int next = part == 3 ? ly : ly + 1;
+                        const bool wrap = next == a.n_layers;
+                        const size_t off = wrap ? 0 : (size_t)next * a.kv_layer_stride;
+                        kv_ahead<S>(c, part, reinterpret_cast<const HT *>(a.kcache) + off, reinterpret_cast<const HT *>(a.vcache) + off,
+                                    wrap ? l + 1 : l, T, kv_lds);
+                    }
+                };
+            };
             ln_gemm_stage<HT, MB, S, CB, EPI_BIAS, false>(c, ws, off_h(hq), lw.ln1_g, lw.ln1_b, (const HT *)lw.f_qkv, lw.b_qkv,
-                                                               off_q(s3), off_q(e3), nullptr, 3 * W, red, stat);
-            attention_stage<HT, MB, S>(c, ws, off_q(s3), kc, vc, kc_rs, vc_rs, off_o(s3), off_o(e3), l, T, opart, wst, par);
-            gemm_resid_stage<HT, MB, S, 1>(c, ws, off_o(s3), (const HT *)lw.f_o, lw.b_o, off_h(hq), off_a(s3), off_a(e3), red2);
+                                                               off_q(s3), off_q(e3), nullptr, 3 * W, red, stat, ahead(3));
+            attention_stage<HT, MB, S, AHEAD>(c, ws, off_q(s3), kc, vc, kc_rs, vc_rs, off_o(s3), off_o(e3), l, T, opart, wst, par, kv);
+            gemm_resid_stage<HT, MB, S, 1>(c, ws, off_o(s3), (const HT *)lw.f_o, lw.b_o, off_h(hq), off_a(s3), off_a(e3), red2, ahead(0));
             ln_gemm_stage<HT, MB, S, CB, EPI_BIAS_GELU, false>(c, ws, off_a(s3), lw.ln2_g, lw.ln2_b, (const HT *)lw.f_fc1, lw.b_fc1,
-                                                                    off_f(s3), off_f(e3), nullptr, 4 * W, red, stat);
-            gemm_resid_stage<HT, MB, S, 4>(c, ws, off_f(s3), (const HT *)lw.f_fc2, lw.b_fc2, off_a(s3), off_h(hq + 1), off_h(hq + 3), red2);
+                                                                    off_f(s3), off_f(e3), nullptr, 4 * W, red, stat, ahead(1));
+            gemm_resid_stage<HT, MB, S, 4>(c, ws, off_f(s3), (const HT *)lw.f_fc2, lw.b_fc2, off_a(s3), off_h(hq + 1), off_h(hq + 3), red2, ahead(2));
             ++hq;
             s3 = s3 == 2 ? 0 : s3 + 1;
         }
         // ---- head: every member computes all of [mu | alpha] for the group's rows (a few column blocks)
         // into its own LDS, so that x_l and the next embedding follow without another exchange
         ln_gemm_stage<HT, MB, S, CBH, EPI_BIAS, true>(c, ws, off_h(hq), a.lnf_g, a.lnf_b, (const HT *)a.f_head, a.b_head, 0, 0,
-                                                           pl, 2 * D, red, stat);
+                                                           pl, 2 * D, red, stat, []() {});
         ++hq;
         __syncthreads();
         if (*c.bad) return;
@@ -663,18 +762,22 @@ __global__ __launch_bounds__(256) void seq_reset_kernel(uint4 *ws, size_t n16, i
 
 }  // namespace
 
-size_t seq_persistent_lds_bytes(int MB, int D) {
-    const size_t need = (size_t)P_NW * 4 * MB * 64 * 16 + (size_t)P_NW * MB * 64 * 16 + (size_t)P_NW * MB * 16 * 8 + 2 * P_NW * 8 +
+static size_t seq_lds_bytes(int MB, int D, bool ahead) {
+    const size_t need = (ahead ? P_AHEAD_BYTES : 0) + (size_t)P_NW * 4 * MB * 64 * 16 + (size_t)P_NW * MB * 64 * 16 + (size_t)P_NW * MB * 16 * 8 + 2 * P_NW * 8 +
                         (size_t)2 * P_NW * 64 * 4 + (size_t)16 * MB * D * 4 + (size_t)P_EB * (D + 1) * 16 * 4 + (size_t)16 * MB * 2 * D * 4;
     const size_t one_per_cu = 84 * 1024;  // more than half of a CU's LDS: exactly one workgroup per CU
     return ((need < one_per_cu ? one_per_cu : need) + 255) & ~(size_t)255;
 }
 
+size_t seq_persistent_lds_bytes(int MB, int D) { return seq_lds_bytes(MB, D, MB == 1); }
+
 template <typename HT>
-static const void *pick_kernel(int MB, int S, int CB) {
-#define SJD_PK(MBv, Sv, CBv) if (MB == MBv && S == Sv && CB == CBv) return reinterpret_cast<const void *>(&seq_persistent_kernel<HT, MBv, Sv, CBv>);
-#define SJD_PS(Sv) SJD_PK(1, Sv, 1) SJD_PK(1, Sv, 2) SJD_PK(1, Sv, 4) SJD_PK(2, Sv, 4)
-    SJD_PS(1) SJD_PS(2) SJD_PS(3) SJD_PS(4)
+static const void *pick_kernel(int MB, int S, int CB, bool ahead) {
+#define SJD_PK(MBv, Sv, CBv, AHv) if (MB == MBv && S == Sv && CB == CBv && ahead == AHv) return reinterpret_cast<const void *>(&seq_persistent_kernel<HT, MBv, Sv, CBv, AHv>);
+#define SJD_PS(Sv) SJD_PK(1, Sv, 1, false) SJD_PK(1, Sv, 2, false) SJD_PK(1, Sv, 4, false) SJD_PK(2, Sv, 4, false)
+#define SJD_PA(Sv) SJD_PK(1, Sv, 1, true) SJD_PK(1, Sv, 2, true) SJD_PK(1, Sv, 4, true)
+    SJD_PS(1) SJD_PS(2) SJD_PS(3) SJD_PS(4) SJD_PA(2) SJD_PA(3) SJD_PA(4)
+#undef SJD_PA
 #undef SJD_PS
 #undef SJD_PK
     return nullptr;
@@ -686,9 +789,10 @@ hipError_t launch_seq_persistent(bool is_bf16, const SeqArgs &args, int MB, int 
     const int members = grid / 8 * args.xpg, blocks = 64 * S;
     const int per = members > 0 ? (blocks + members - 1) / members : blocks;
     const int CB = MB == 2 || per > 2 ? 4 : per;
-    const void *kern = is_bf16 ? pick_kernel<bf16>(MB, S, CB) : pick_kernel<f16>(MB, S, CB);
+    const bool ahead = args.kv_ahead && MB == 1 && S >= 2;   // two row blocks leave no room for it
+    const void *kern = is_bf16 ? pick_kernel<bf16>(MB, S, CB, ahead) : pick_kernel<f16>(MB, S, CB, ahead);
     if (!kern) return hipErrorInvalidValue;
-    const size_t lds = seq_persistent_lds_bytes(MB, args.D);
+    const size_t lds = seq_lds_bytes(MB, args.D, ahead);
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(seq_reset_kernel, dim3(512), dim3(256), 0, s, (uint4 *)args.ws,

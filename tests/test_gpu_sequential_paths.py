@@ -137,6 +137,26 @@ def test_persistent_kernel_over_its_group_sizes(torch_cuda, orc32, batch, tokens
     f.close()
 
 
+@pytest.mark.parametrize("batch,tokens,dim,layers,width", [
+    (32, 290, 64, 1, 512),     # one layer, the largest token size; the prefix ends inside, at and behind the rows kept in LDS
+    (40, 256, 5, 2, 512),      # the shortest sequences, members with one and with two pairs
+    (16, 513, 12, 2, 1024),    # three batches of cached keys, every member one pair
+    (23, 520, 3, 1, 768),      # more than two pairs for some members
+])
+def test_cached_rows_through_lds_give_the_same_bits(torch_cuda, batch, tokens, dim, layers, width):
+    """A batch that fills the chip takes the first cached rows of a pair out of LDS, a single sample out of registers."""
+    print(f"case B {batch} T {tokens} D {dim} N {layers} W {width}", flush=True)
+    _, _, f, z = _flow(batch, tokens, dim, layers, width, seed=47)
+    f.set_sequential_path(2)
+    x = f.sequential_inverse_block(0, z)
+    assert torch_cuda.isfinite(x).all()
+    for b in (0, batch // 2, batch - 1):
+        assert torch_cuda.equal(f.sequential_inverse_block(0, z[b:b + 1].contiguous())[0], x[b]), b
+    f.set_sequential_path(1)
+    assert (f.sequential_inverse_block(0, z) - x).abs().max().item() <= 2 * TOL
+    f.close()
+
+
 def test_persistent_kernel_passes_every_nan_pattern_on(torch_cuda):
     """The kernel marks empty words by a NaN pattern: a sample that is full of exactly that pattern must neither stop the others
     nor change them."""
