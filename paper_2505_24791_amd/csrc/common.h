@@ -335,6 +335,23 @@ size_t seq_persistent_lds_bytes(int MB, int D);
 hipError_t launch_seq_persistent(bool is_bf16, const SeqArgs &args, int MB, int S, int grid, bool cooperative,
                                  hipStream_t s);
 
+// The sequential inverse of a narrow float32 flow's block in one launch, a workgroup per sample (decode_f32_block.hip).
+struct SeqF32Layer {
+    const float *ln1_g, *ln1_b, *w_qkv, *b_qkv, *w_o, *b_o, *ln2_g, *ln2_b, *w_fc1, *b_fc1, *w_fc2, *b_fc2;
+};
+struct SeqF32Args {
+    SeqF32Layer layers[kSeqMaxLayers];
+    int n_layers;
+    const float *lnf_g, *lnf_b, *w_head, *b_head;   // w_head: rows head_ld floats apart, on 16-byte boundaries
+    int head_ld;
+    const float *w_in, *b_in, *pos, *z;
+    float *x, *kcache, *vcache;                     // caches [layer][max_batch][T][W]
+    size_t kv_layer_stride;
+    int T, D, dh, reversed;
+};
+bool seq_block_f32_ok(int W, int dh, int mlp_ratio, int n_layers);
+void launch_seq_block_f32(const SeqF32Args &args, int W, int B, hipStream_t s);
+
 void launch_jacobi_trace(const float *x, const float *x_ref, JacobiState st, float *delta_out, float *err_out, int B,
                          int T, int D, hipStream_t s);
 void launch_forward_epilogue(const float *p, const float *x, float *y, float *logdet, int B, int T, int D, int reversed,

@@ -50,3 +50,37 @@ def test_float32_steps_match_oracle(orc32, W, H, N, T, D, B):
         ref = np.stack([orc32.sequential_inverse_block(cfg, blob, j, z[b]) for b in pick])
         assert np.abs(x.cpu().numpy()[pick] - ref).max() <= 1e-4
     f.close()
+
+
+@pytest.mark.parametrize("W,H,N,T,D,B", [
+    (64, 4, 3, 70, 3, 2),          # more keys than are walked at a time (64), head size 16
+    (64, 1, 1, 257, 5, 2),         # several batches of cached keys, head size 64
+    (128, 8, 2, 130, 16, 5),       # the same at 32 keys at a time
+    (128, 1, 1, 34, 2, 3),         # head size 128
+    (128, 4, 1, 3, 1024, 2),       # the largest token size
+    (128, 2, 1, 4, 511, 2),        # an odd one: the head matrix is padded
+    (128, 4, 2, 9, 16, 300),       # more samples than CUs
+])
+def test_narrow_block_in_one_launch(orc32, W, H, N, T, D, B):
+    """Widths 64 and 128: the whole block in one launch and, on request, per-step launches."""
+    import torch
+    import paper_2505_24791_amd as sjd
+    cfg = wl.FlowConfig("seq_f32", n_blocks=2, n_layers=N, width=W, n_heads=H, seq_len=T, token_dim=D, batch=B, bf16=False)
+    print(cfg, flush=True)
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    z = wl.make_latent(cfg, seed=19)
+    zd = torch.from_numpy(z).cuda()
+    f = sjd.Flow(cfg)
+    f.load_weights(blob)
+    for j in range(2):
+        f.set_sequential_path(0)
+        x = f.sequential_inverse_block(j, zd)
+        assert torch.equal(f.sequential_inverse_block(j, zd), x)
+        assert torch.equal(f.sequential_inverse_block(j, zd[-1:].contiguous())[0], x[-1])
+        f.set_sequential_path(1)
+        steps = f.sequential_inverse_block(j, zd)
+        for b in (0, B - 1):
+            ref = orc32.sequential_inverse_block(cfg, blob, j, z[b])
+            assert np.abs(x[b].cpu().numpy() - ref).max() <= 1e-4
+            assert np.abs(steps[b].cpu().numpy() - ref).max() <= 1e-4
+    f.close()
