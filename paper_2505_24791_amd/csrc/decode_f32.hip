@@ -1,5 +1,5 @@
 // Single-token steps of the sequential inverse (eq. 5 with the key/value cache of Sec. 3.5) in float32: the float32
-// counterparts of the step kernels in decode.hip.  A step handles one position of every sample, so a projection
+// counterparts of the step kernels in decode.hip.  The projections also serve whole-sequence passes of few rows.  A step handles one position of every sample, so a projection
 // has as many rows as there are samples, and what it costs is the time until its weights have arrived.
 // Rows of activations, LayerNorm parameters and caches start on 16-byte boundaries (blocks of the blob are aligned, widths here are
 // multiples of 16); rows of a weight matrix are read by columns and may start anywhere.

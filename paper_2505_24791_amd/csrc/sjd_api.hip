@@ -311,6 +311,21 @@ void attention_step(sjd_flow *f, int l, int B, int t, hipStream_t s) {
                                 (AT *)f->o, B, c.seq_len, t, c.n_heads, c.width / c.n_heads, f->mask_nearest, s);
 }
 
+// Float32 passes of few rows: LayerNorm + projection, or projection + residual, on the kernels of the single-token steps, which split k
+// over the waves of a workgroup; the whole-sequence kernel has a few tiles then, each with a wave or two per SIMD walking all of k, behind a
+// LayerNorm launch.  A conditioner of 2 layers, us, whole-sequence / step kernels: width 128, 196 rows 158 / 113, 1200 rows 169 / 141, 4096 rows 231 /
+// 243; width 256, 256 rows 212 / 142, 800 rows 195 / 167, 1600 rows 228 / 231; width 512, 256 rows 286 / 196, 600 rows 297 / 290, 800 rows 318 / 343;
+// width 1024, 128 rows 425 / 295, 196 rows 451 / 459.  The largest pass of the flow decides, not this one's rows: a row gives the same bits in any batch.
+bool short_f32(const sjd_config &c) {
+    return c.dtype == SJD_DTYPE_F32 && skinny_f32_ln_ok(c.width) && (size_t)c.max_batch * c.seq_len * c.width <= 192 * 1024;
+}
+void project_short_f32(sjd_flow *f, int fam, const float *A, const float *g, const float *be, const float *w, const float *bias, float *C,
+                       int M, int N, int K, Epi epi, hipStream_t s) {
+    const double outs = epi == EPI_BIAS_RESIDUAL ? 2.0 : 1.0;
+    ProfScope ps(f, fam, 2.0 * M * (double)N * K, 4.0 * ((double)M * K + (double)K * N + outs * M * N + N), s);
+    launch_skinny_f32(A, g, be, w, bias, epi == EPI_BIAS_RESIDUAL ? C : nullptr, C, M, N, K, epi, s);
+}
+
 // Whole-sequence conditioner pass on `n` samples listed in `active` (device, nullable = identity).
 // Leaves the head output in f->p: [n*T, 2D], row r of a sample = parameters of position r+1.
 void conditioner_pass(sjd_flow *f, int j, const float *x, int n, const int32_t *active, hipStream_t s) {
@@ -334,9 +349,11 @@ void conditioner_pass(sjd_flow *f, int j, const float *x, int n, const int32_t *
     const bool panel_qkv = panel_any && (f->proj_path == 2 || (M >= 10240 && panel_one_round));
     const bool panel_fc1 = panel_any && (f->proj_path == 2 || (M >= 12288 && panel_one_round));
     const bool stream_fc2 = panel_any && f->stream_ok && (f->proj_path == 2 || (M >= 10240 && panel_one_round)) && gemm_stream_applicable(M, W, RW);
+    const bool few = short_f32(c);
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerW &lw = bw.layer[l];
-        if (panel_qkv) ln_project_panel(f, f->h, lw.ln1_g, lw.ln1_b, lw.p_qkv, lw.b_qkv, f->qkv, M, 3 * W, EPI_BIAS, s);
+        if (few) project_short_f32(f, SJD_PROF_GEMM, f->h, lw.ln1_g, lw.ln1_b, lw.w_qkv, lw.b_qkv, (float *)f->qkv, M, 3 * W, W, EPI_BIAS, s);
+        else if (panel_qkv) ln_project_panel(f, f->h, lw.ln1_g, lw.ln1_b, lw.p_qkv, lw.b_qkv, f->qkv, M, 3 * W, EPI_BIAS, s);
         else {
             layernorm(f, f->h, lw.ln1_g, lw.ln1_b, f->a, M, s);
             project(f, SJD_PROF_GEMM, f->a, lw.w_qkv, lw.t_qkv, lw.b_qkv, f->qkv, M, 3 * W, W, EPI_BIAS, false, s);
@@ -348,18 +365,25 @@ void conditioner_pass(sjd_flow *f, int j, const float *x, int n, const int32_t *
             else if (c.dtype == SJD_DTYPE_F16) attention_full<f16>(f->qkv, f->o, n, T, W, H, f->mask_nearest, s);
             else attention_full<float>(f->qkv, f->o, n, T, W, H, f->mask_nearest, s);
         }
-        if (panel_qkv) project_panel_resid(f, f->o, lw.p_o, lw.b_o, f->h, M, W, s);
+        if (few) project_short_f32(f, SJD_PROF_GEMM_RESID, (float *)f->o, nullptr, nullptr, lw.w_o, lw.b_o, f->h, M, W, W, EPI_BIAS_RESIDUAL, s);
+        else if (panel_qkv) project_panel_resid(f, f->o, lw.p_o, lw.b_o, f->h, M, W, s);
         else project(f, SJD_PROF_GEMM_RESID, f->o, lw.w_o, lw.t_o, lw.b_o, f->h, M, W, W, EPI_BIAS_RESIDUAL, true, s);
-        if (panel_fc1) ln_project_panel(f, f->h, lw.ln2_g, lw.ln2_b, lw.p_fc1, lw.b_fc1, f->f, M, RW, EPI_BIAS_GELU, s);
+        if (few) project_short_f32(f, SJD_PROF_GEMM_FC1, f->h, lw.ln2_g, lw.ln2_b, lw.w_fc1, lw.b_fc1, (float *)f->f, M, RW, W, EPI_BIAS_GELU, s);
+        else if (panel_fc1) ln_project_panel(f, f->h, lw.ln2_g, lw.ln2_b, lw.p_fc1, lw.b_fc1, f->f, M, RW, EPI_BIAS_GELU, s);
         else {
             layernorm(f, f->h, lw.ln2_g, lw.ln2_b, f->a, M, s);
             project(f, SJD_PROF_GEMM_FC1, f->a, lw.w_fc1, lw.t_fc1, lw.b_fc1, f->f, M, RW, W, EPI_BIAS_GELU, false, s);
         }
-        if (stream_fc2) {
+        if (few) project_short_f32(f, SJD_PROF_GEMM_RESID, (float *)f->f, nullptr, nullptr, lw.w_fc2, lw.b_fc2, f->h, M, W, RW, EPI_BIAS_RESIDUAL, s);
+        else if (stream_fc2) {
             ProfScope ps(f, SJD_PROF_GEMM_RESID, 2.0 * M * (double)W * RW, (double)M * RW * 2.0 + (double)RW * W * 2.0 + (double)M * W * 8.0 + W * 4.0, s);
             if (c.dtype == SJD_DTYPE_BF16) launch_gemm_stream_resid<bf16>((const bf16 *)f->f, (const bf16 *)lw.p_fc2, lw.b_fc2, f->h, M, W, RW, s);
             else launch_gemm_stream_resid<f16>((const f16 *)f->f, (const f16 *)lw.p_fc2, lw.b_fc2, f->h, M, W, RW, s);
         } else project(f, SJD_PROF_GEMM_RESID, f->f, lw.w_fc2, lw.t_fc2, lw.b_fc2, f->h, M, W, RW, EPI_BIAS_RESIDUAL, true, s);
+    }
+    if (few) {
+        project_short_f32(f, SJD_PROF_GEMM_HEAD, f->h, bw.lnf_g, bw.lnf_b, bw.w_head, bw.b_head, f->p, M, 2 * D, W, EPI_BIAS, s);
+        return;
     }
     layernorm(f, f->h, bw.lnf_g, bw.lnf_b, f->a, M, s);
     project(f, SJD_PROF_GEMM_HEAD, f->a, bw.w_head4, bw.t_head, bw.b_head, f->p, M, 2 * D, W, EPI_BIAS, true, s, head_ld(c));

@@ -41,3 +41,29 @@ def test_float32_conditioner_matches_oracle(orc32, W, H, T, D, B):
             assert np.abs(mu[b].cpu().numpy() - rmu).max() <= 1e-4
             assert np.abs(al[b].cpu().numpy() - ral).max() <= 1e-4
     f.close()
+
+
+@pytest.mark.parametrize("W,H,T,D,B", [
+    (128, 4, 96, 16, 16),          # rows * width on the line below which the step kernels take a pass
+    (128, 4, 97, 16, 16),          # and past it
+    (256, 4, 15, 5, 3),            # 45 rows, the last block of sixteen with thirteen
+    (768, 12, 17, 33, 1),
+    (1024, 16, 24, 48, 8),
+], ids=lambda v: str(v))
+def test_passes_of_few_rows_match_oracle(orc32, W, H, T, D, B):
+    import torch
+    import paper_2505_24791_amd as sjd
+    cfg = wl.FlowConfig("few_f32", n_blocks=2, n_layers=2, width=W, n_heads=H, seq_len=T, token_dim=D, batch=B, bf16=False)
+    print(cfg, flush=True)
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    x = wl.make_latent(cfg, seed=29)
+    f = sjd.Flow(cfg)
+    f.load_weights(blob)
+    mu, al = f.conditioner(1, torch.from_numpy(x).cuda())
+    one_mu, one_al = f.conditioner(1, torch.from_numpy(x[-1:].copy()).cuda())         # one row block or two: the same bits
+    assert torch.equal(one_mu[0], mu[-1]) and torch.equal(one_al[0], al[-1])
+    for b in (0, B - 1):
+        rmu, ral = orc32.cond(cfg, blob, 1, x[b][::-1])
+        assert np.abs(mu[b].cpu().numpy() - rmu[::-1]).max() <= 1e-4
+        assert np.abs(al[b].cpu().numpy() - ral[::-1]).max() <= 1e-4
+    f.close()
