@@ -4,10 +4,11 @@
 // At widths 64 and 128 a step has next to no work in it (1.6 MB of weights at width 128 and 2 layers), and as a chain of 5 N + 2 launches
 // (decode_f32.hip) it costs 3 us a link.  Inside a workgroup a link is a barrier.  What bounds it: the load path of a CU (every workgroup
 // pulls the block's weights out of its L2 once per step, 6 us a layer at width 128), and the ten barriers of a layer with a trip to LDS each
-// (6 us).  So a product's weights are requested as soon as the registers of the one before are free, ahead of the barriers between them.
+// (5 us; eight waves: sixteen halve the work of each but take 29 us a step where this takes 24).  So a product's weights are requested as soon
+// as the registers of the one before are free, ahead of the barriers between them, and small parameters ahead of those: loads come back in order.
 // The samples share nothing: no co-residency is needed, more samples than CUs run in rounds, and a sample gives the same bits in any batch.
-// Microseconds a step, per-step launches -> this: width 128, 2 layers, 4 samples of 49 tokens 45 -> 29, 256 samples 62 -> 30, 256 of 256
-// tokens 70 -> 35, 4 of 1000 tokens 53 -> 36; 8 layers, 4 samples 141 -> 108; width 64, 4 layers, 32 samples 103 -> 30.
+// Microseconds a step, per-step launches -> this: width 128, 2 layers, 4 samples of 49 tokens 45 -> 24, 256 samples 63 -> 25, 256 of 256
+// tokens 70 -> 31, 4 of 1000 tokens 54 -> 36; 8 layers, 4 samples 142 -> 93; width 64, 4 layers, 32 samples 104 -> 24.
 //
 // A product y[n] = sum_k x[k] w[k][n]: thread (slice, group) takes four columns and an equal run of k, the partial sums of a column
 // meet in LDS and are added in order of k.  Attention: W / 4 lanes hold a key of all heads (four values each, dh / 4 lanes a head), the key
@@ -18,7 +19,7 @@ namespace sjd {
 
 namespace {
 
-constexpr int SB_T = 1024;       // threads
+constexpr int SB_T = 512;        // threads
 
 // Sums over lanes without the LDS unit, whose exchanges take a hundred clocks each: DPP inside a row of sixteen lanes, swaps across rows.
 template <int CTRL> __device__ __forceinline__ float sb_dpp(float x) {
@@ -135,28 +136,66 @@ __global__ __launch_bounds__(SB_T) void seq_block_f32_kernel(SeqF32Args a) {
     int hs = 1;                                 // and its slices
     while (2 * hs * g4 <= SB_T && 2 * hs <= W) hs *= 2;
 
+    // the first rows of this thread's part of the embedding and head matrices stay in registers for all steps
+    constexpr int ES = SB_T / W, EK = 8, HK = 4;
+    const int kp = W / hs;
+    float we[EK];
+    f32x4 wh[HK];
+#pragma unroll
+    for (int i = 0; i < EK; ++i) {
+        const int d = (int)threadIdx.x / W + i * ES;
+        we[i] = a.w_in[(uint32_t)((d < D ? d : 0) * W + threadIdx.x % W)];
+    }
+    {
+        const int s = (int)threadIdx.x / g4, c = (int)threadIdx.x - s * g4;
+#pragma unroll
+        for (int i = 0; i < HK; ++i)
+            wh[i] = *reinterpret_cast<const f32x4 *>(a.w_head + (uint32_t)((s < hs && i < kp ? s * kp + i : 0) * a.head_ld + 4 * c));
+    }
     SbStream<W> stream;
-    float z = threadIdx.x < D ? a.z[(b * T + (a.reversed ? T - 1 : 0)) * D + threadIdx.x] : 0.f;
+    constexpr int ZP = 1024 / SB_T;             // token sizes up to 1024: latent values a step ahead
+    float z[ZP];
+#pragma unroll
+    for (int i = 0; i < ZP; ++i) {
+        const int d = (int)threadIdx.x + i * SB_T;
+        z[i] = d < D ? a.z[(b * T + (a.reversed ? T - 1 : 0)) * D + d] : 0.f;
+    }
     for (int l = 0; l < T; ++l) {
         // copies that the optimiser cannot see through: addresses are worked out where they are used instead of being kept for all steps
         int tid = threadIdx.x;
         asm volatile("" : "+v"(tid));
         const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         const size_t tok = a.reversed ? T - 1 - l : l;
-        if (tid < D) {                              // token sizes up to SB_T
-            const size_t idx = (b * T + tok) * D + tid;
-            float v = z;
-            if (l > 0) v = fmaf(v, expf(p[D + tid]), p[tid]);
-            a.x[idx] = v;
-            xs[tid] = v;
-            if (l + 1 < T) z = a.z[a.reversed ? idx - D : idx + D];
+#pragma unroll
+        for (int i = 0; i < ZP; ++i) {
+            const int d = tid + i * SB_T;
+            if (d < D) {
+                const size_t idx = (b * T + tok) * D + d;
+                float v = z[i];
+                if (l > 0) v = fmaf(v, expf(p[D + d]), p[d]);
+                a.x[idx] = v;
+                xs[d] = v;
+                if (l + 1 < T) z[i] = a.z[a.reversed ? idx - D : idx + D];
+            }
         }
         if (l == T - 1) break;
         __syncthreads();
-        {   // embedding: D split over SB_T / W slices
+        {   // embedding: D split over ES slices
             const int c = tid % W, s = tid / W;
             float t = 0.f;
-            for (int d = s; d < D; d += SB_T / W) t = fmaf(xs[d], a.w_in[(size_t)d * W + c], t);
+#pragma unroll
+            for (int i = 0; i < EK; ++i) {
+                const int d = s + i * ES;
+                if (d < D) t = fmaf(xs[d], we[i], t);
+            }
+            for (int d0 = s + EK * ES; d0 < D; d0 += 8 * ES) {      // eight loads at a time
+                float w[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) w[i] = a.w_in[(uint32_t)((d0 + i * ES < D ? d0 + i * ES : d0) * W + c)];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    if (d0 + i * ES < D) t = fmaf(xs[d0 + i * ES], w[i], t);
+            }
             part[s * W + c] = t;
         }
         for (int ly = 0; ly < a.n_layers; ++ly) {
@@ -308,14 +347,23 @@ __global__ __launch_bounds__(SB_T) void seq_block_f32_kernel(SeqF32Args a) {
         __syncthreads();
         // ---- head: [mu | alpha] of position l + 1
         {
-            const int s = tid / g4, c = tid - s * g4, kp = W / hs;
+            const int s = tid / g4, c = tid - s * g4;
             if (s < hs) {
                 f32x4 t = {0.f, 0.f, 0.f, 0.f};
-                for (int k = s * kp; k < (s + 1) * kp; ++k) {
+                auto take = [&](int k, f32x4 w) {
                     const float v = xn[k];
-                    const f32x4 w = *reinterpret_cast<const f32x4 *>(a.w_head + (size_t)k * a.head_ld + 4 * c);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) t[e] = fmaf(v, w[e], t[e]);
+                };
+#pragma unroll
+                for (int i = 0; i < HK; ++i)
+                    if (i < kp) take(s * kp + i, wh[i]);
+                for (int k0 = HK; k0 < kp; k0 += HK) {              // kp is a power of two, HK loads at a time
+                    f32x4 w[HK];
+#pragma unroll
+                    for (int i = 0; i < HK; ++i) w[i] = *reinterpret_cast<const f32x4 *>(a.w_head + (uint32_t)((s * kp + k0 + i) * a.head_ld + 4 * c));
+#pragma unroll
+                    for (int i = 0; i < HK; ++i) take(s * kp + k0 + i, w[i]);
                 }
                 *reinterpret_cast<f32x4 *>(part + (s * g4 + c) * 4) = t;
             }

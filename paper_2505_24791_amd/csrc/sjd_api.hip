@@ -709,7 +709,7 @@ int run_sequential_fast(sjd_flow *f, int j, const float *z, float *x, int batch,
 }
 
 // Narrow float32 flows: the whole block in one launch, a workgroup per sample.  Samples beyond the CUs run in further rounds: width 128, 2 layers,
-// 257 samples 58 us a step against 63 with per-step launches, 1024 samples 117 against 100.  As in tall_f32, the flow's largest batch decides.
+// 257 samples 48 us a step against 63 with per-step launches, 1024 samples 117 (of 1024 threads) against 100.  As in tall_f32, the flow's largest batch decides.
 bool block_f32_ok(const sjd_flow *f) {
     const sjd_config &c = f->cfg;
     return fast_decode_f32_ok(f) && c.max_batch <= 2 * f->n_cus_device && seq_block_f32_ok(c.width, c.width / c.n_heads, c.mlp_ratio, c.n_layers);
