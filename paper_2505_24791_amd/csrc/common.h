@@ -187,6 +187,12 @@ bool gemm_p8_applicable(int M, int N, int K);
 template <typename HT, typename OutT>
 void launch_gemm_p8(const HT *A, const HT *Bt, const float *bias, OutT *C, int M, int N, int K, Epi epi, hipStream_t s);
 
+// MLP-input projection with GELU for launches that fill the chip (gemm_duo.hip): C[M,N] (16-bit) = gelu(A[M,K] * W + bias), W in the
+// fragment order of the 32x32x16 instruction (launch_weights_to_frag32 from the transposed [N, K] copy); bit-identical to launch_gemm_h16.
+bool gemm_duo_applicable(int M, int N, int K);
+template <typename HT>
+void launch_gemm_duo_gelu(const HT *A, const HT *Wf, const float *bias, HT *C, int M, int N, int K, hipStream_t s);
+
 // Activation-stationary projections for K = 512 (gemm_panel.hip).  Wf: the weight in the fragment order of
 // the 32x32x16 instruction (launch_weights_to_panel_frag from the transposed [N, 512] copy; N % 256 == 0).
 //   launch_ln_gemm_panel:    C[M,N] (16-bit) = epi(LayerNorm(H[M,512]; g, b) * W + bias), epi = EPI_BIAS or EPI_BIAS_GELU

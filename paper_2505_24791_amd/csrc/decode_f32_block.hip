@@ -121,7 +121,7 @@ template <int W> struct SbStream {
 
 template <int W>
 __global__ __launch_bounds__(SB_T) void seq_block_f32_kernel(SeqF32Args a) {
-    constexpr int C = W / 4, KG = SB_T / C, GW = 64 / C, NWV = SB_T / 64;   // lanes of a key, keys at a time, keys per wave, waves
+    constexpr int C = W / 4, KG = SB_T / C, NWV = SB_T / 64;   // lanes of a key, keys at a time, waves
     constexpr int U = 4;                                                    // keys in flight per thread
     __shared__ __attribute__((aligned(16))) float part[SB_T * 4];
     __shared__ __attribute__((aligned(16))) float xn[W], qkv[3 * W], o[W], ff[4 * W];

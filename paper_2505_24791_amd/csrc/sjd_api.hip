@@ -42,7 +42,7 @@ struct LayerW {
     const float *w_qkv, *w_o, *w_fc1, *w_fc2;      // float32 [in, out] (views into the device blob)
     void *t_qkv, *t_o, *t_fc1, *t_fc2;             // 16-bit transposed [out (padded), in]
     void *f_qkv, *f_o, *f_fc1, *f_fc2;             // 16-bit fragment-major copies for single-token steps
-    void *p_qkv = nullptr, *p_o = nullptr, *p_fc1 = nullptr, *p_fc2 = nullptr;   // 32x32x16 fragment order for the panel / streaming kernels (W = 512)
+    void *p_qkv = nullptr, *p_o = nullptr, *p_fc1 = nullptr, *p_fc2 = nullptr;   // 32x32x16 fragment order: panel / streaming kernels (W = 512), MLP input of large launches (p_fc1)
 };
 struct BlockW {
     const float *w_in, *b_in, *pos, *lnf_g, *lnf_b, *w_head, *b_head;
@@ -67,6 +67,7 @@ struct sjd_flow {
     float *head4 = nullptr;      // padded head matrices (token sizes that are odd)
     void *arena = nullptr;       // transposed 16-bit matrices
     void *arena_frag = nullptr;  // the same matrices in fragment-major order (sequential fast path)
+    void *arena_fc1 = nullptr;   // MLP-input matrices in the order of gemm_duo.hip (flows without arena_panel, which holds them too)
     void *arena_panel = nullptr; // QKV, attention-output and MLP-input matrices in the panel kernels' order
     int proj_path = 0;           // 0 automatic, 1 tile kernels only, 2 panel kernels wherever they apply
     bool stream_ok = false;      // the streaming MLP-output kernel reproduced the tile kernel's bits at load time
@@ -134,6 +135,12 @@ constexpr size_t kNPad = 256;  // transposed weights are padded to this many row
 // the panel projection kernels cover 16-bit flows of width 512 whose matrices have multiples of 256 columns
 bool panel_ok(const sjd_config &c) {
     return c.dtype != SJD_DTYPE_F32 && c.width == 512 && ((size_t)c.mlp_ratio * c.width) % 256 == 0;
+}
+
+// MLP-input matrices in fragment order for the flows whose largest pass is one for gemm_duo.hip
+bool duo_ok(const sjd_config &c) {
+    return c.dtype != SJD_DTYPE_F32 && !panel_ok(c) && (long long)c.mlp_ratio * c.width < (1 << 20) &&
+           gemm_duo_applicable(c.max_batch * c.seq_len, c.mlp_ratio * c.width, c.width);
 }
 
 size_t arena_elems_per_block(const sjd_config &c) {
@@ -280,6 +287,14 @@ void ln_project_panel(sjd_flow *f, const float *H, const float *g, const float *
     else launch_ln_gemm_panel<f16>(H, g, b, (const f16 *)wf, bias, (f16 *)C, M, N, epi, s);
 }
 
+// C = gelu(A W + bias) on the kernel with two workgroups per CU
+void project_duo_gelu(sjd_flow *f, const void *A, const void *wf, const float *bias, void *C, int M, int N, hipStream_t s) {
+    const int W = f->cfg.width;
+    ProfScope ps(f, SJD_PROF_GEMM_FC1, 2.0 * M * (double)N * W, (double)M * W * 2.0 + (double)W * N * 2.0 + (double)M * N * 2.0 + N * 4.0, s);
+    if (f->cfg.dtype == SJD_DTYPE_BF16) launch_gemm_duo_gelu<bf16>((const bf16 *)A, (const bf16 *)wf, bias, (bf16 *)C, M, N, W, s);
+    else launch_gemm_duo_gelu<f16>((const f16 *)A, (const f16 *)wf, bias, (f16 *)C, M, N, W, s);
+}
+
 // H += A W + bias on the panel kernel
 void project_panel_resid(sjd_flow *f, const void *A, const void *wf, const float *bias, float *H, int M, int N,
                          hipStream_t s) {
@@ -339,15 +354,16 @@ void conditioner_pass(sjd_flow *f, int j, const float *x, int n, const int32_t *
         launch_embed(x, bw.w_in, bw.b_in, bw.pos, f->h, M, D, W, RowMap{active, T, 0, T, rev}, s);
     }
     // Width 512: LayerNorm + projection in one activation-stationary launch where that is faster.  A workgroup of those kernels
-    // is 128 rows x 768..1024 columns of work, two per panel of 128 rows: below ~90 panels the tile kernels' finer grain
-    // wins (QKV from 10240 rows on, MLP input from 12288), above 128 panels the last round of workgroups is nearly empty and the
+    // is 128 rows x 768..1024 columns of work, two per panel of 128 rows: below ~90 panels (10240 rows) the tile kernels' finer grain
+    // wins, above 128 panels the last round of workgroups is nearly empty and the
     // persistent kernel wins (a pass of 4 layers: 16384 rows 795 us against 831, 18432 rows 1123 against 937, 32768 rows 1596
     // against 1432, 65536 rows 2912 against 2642).
     const bool panel_any = f->arena_panel && f->proj_path != 1 && gemm_panel_applicable(M, RW, W, 2) &&
                            gemm_panel_applicable(M, 3 * W, W, 2) && gemm_panel_applicable(M, W, W, 4);
     const bool panel_one_round = M <= 16384;
     const bool panel_qkv = panel_any && (f->proj_path == 2 || (M >= 10240 && panel_one_round));
-    const bool panel_fc1 = panel_any && (f->proj_path == 2 || (M >= 12288 && panel_one_round));
+    const bool panel_fc1 = panel_any && f->proj_path == 2;
+    const bool duo_fc1 = c.dtype != SJD_DTYPE_F32 && f->proj_path == 0 && bw.layer[0].p_fc1 && gemm_duo_applicable(M, RW, W);
     const bool stream_fc2 = panel_any && f->stream_ok && (f->proj_path == 2 || (M >= 10240 && panel_one_round)) && gemm_stream_applicable(M, W, RW);
     const bool few = short_f32(c);
     for (int l = 0; l < c.n_layers; ++l) {
@@ -372,7 +388,8 @@ void conditioner_pass(sjd_flow *f, int j, const float *x, int n, const int32_t *
         else if (panel_fc1) ln_project_panel(f, f->h, lw.ln2_g, lw.ln2_b, lw.p_fc1, lw.b_fc1, f->f, M, RW, EPI_BIAS_GELU, s);
         else {
             layernorm(f, f->h, lw.ln2_g, lw.ln2_b, f->a, M, s);
-            project(f, SJD_PROF_GEMM_FC1, f->a, lw.w_fc1, lw.t_fc1, lw.b_fc1, f->f, M, RW, W, EPI_BIAS_GELU, false, s);
+            if (duo_fc1) project_duo_gelu(f, f->a, lw.p_fc1, lw.b_fc1, f->f, M, RW, s);
+            else project(f, SJD_PROF_GEMM_FC1, f->a, lw.w_fc1, lw.t_fc1, lw.b_fc1, f->f, M, RW, W, EPI_BIAS_GELU, false, s);
         }
         if (few) project_short_f32(f, SJD_PROF_GEMM_RESID, (float *)f->f, nullptr, nullptr, lw.w_fc2, lw.b_fc2, f->h, M, W, RW, EPI_BIAS_RESIDUAL, s);
         else if (stream_fc2) {
@@ -890,6 +907,7 @@ int sjd_flow_create(const sjd_config *cfg, sjd_flow **out) {
     if (c.dtype != SJD_DTYPE_F32) A(&f->arena, (size_t)c.n_blocks * arena_elems_per_block(c) * 2);
     if (fast_decode_ok(f)) A(&f->arena_frag, (size_t)c.n_blocks * arena_elems_per_block(c) * 2);
     if (panel_ok(c)) A(&f->arena_panel, (size_t)c.n_blocks * c.n_layers * (3 * W + W + 2 * R * W) * W * 2);
+    if (duo_ok(c)) A(&f->arena_fc1, (size_t)c.n_blocks * c.n_layers * R * W * W * 2);
     A((void **)&f->h, M * W * 4);
     A((void **)&f->p, M * 2 * D * 4);
     A(&f->a, M * W * ab);
@@ -1021,6 +1039,11 @@ int sjd_flow_load_weights(sjd_flow *f, const void *host_blob, size_t nbytes) {
             lw.p_qkv = prep_panel(lw.t_qkv, 3 * W);
             lw.p_o = prep_panel(lw.t_o, W);
             lw.p_fc1 = prep_panel(lw.t_fc1, R * W);
+            if (f->arena_fc1) {
+                lw.p_fc1 = (char *)f->arena_fc1 + ((size_t)j * c.n_layers + l) * R * W * W * 2;
+                if (dt == SJD_DTYPE_BF16) launch_weights_to_frag32<bf16>((const bf16 *)lw.t_fc1, (bf16 *)lw.p_fc1, (int)(R * W), (int)W, 0);
+                else launch_weights_to_frag32<f16>((const f16 *)lw.t_fc1, (f16 *)lw.p_fc1, (int)(R * W), (int)W, 0);
+            }
             if (f->arena_panel) {                       // MLP output: [W, R W] transposed -> fragment order, k = R W
                 lw.p_fc2 = arp;
                 if (dt == SJD_DTYPE_BF16) launch_weights_to_frag32<bf16>((const bf16 *)lw.t_fc2, (bf16 *)arp, (int)W, (int)(R * W), 0);
