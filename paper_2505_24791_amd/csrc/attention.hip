@@ -63,7 +63,17 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(const QT *__restric
         float dot = 0.f;
         if (s < n_cached) {
             const KVT *kr = kb + (int64_t)s * kv_stride;
-            for (int d = 0; d < dh; ++d) dot = fmaf(qs[d], to_f32<KVT>(kr[d]), dot);
+            int d = 0;
+            if constexpr (sizeof(KVT) == 4) {       // sixteen bytes a load (they need not start on sixteen)
+                typedef float f32x4a __attribute__((ext_vector_type(4), aligned(4)));
+#pragma unroll 4
+                for (; d + 4 <= dh; d += 4) {
+                    const f32x4a k4 = *reinterpret_cast<const f32x4a *>(kr + d);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) dot = fmaf(qs[d + e], k4[e], dot);
+                }
+            }
+            for (; d < dh; ++d) dot = fmaf(qs[d], to_f32<KVT>(kr[d]), dot);
         } else {
             for (int d = 0; d < dh; ++d) dot = fmaf(qs[d], to_f32<QT>(kf[d]), dot);
         }
@@ -82,11 +92,27 @@ __global__ __launch_bounds__(256) void attention_rows_kernel(const QT *__restric
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_s_waitcnt(0xc07f);
     const float inv = n_keys > 0 ? 1.0f / den : 0.f;
-    for (int d = lane; d < dh; d += 64) {
+    // Values, eight rows requested at a time.  For float32 heads of 32, 16, ... the wave splits into 64 / dh groups of keys, added in order at the end.
+    const int G = sizeof(KVT) == 4 && dh <= 32 && (dh & (dh - 1)) == 0 ? 64 / dh : 1;
+    for (int d0 = 0; d0 < dh; d0 += 64) {
+        const int grp = G > 1 ? lane / dh : 0, d = G > 1 ? lane - grp * dh : d0 + lane;
+        const bool live = grp < G && d < dh;
         float acc = 0.f;
-        for (int s = 0; s < n_cached; ++s) acc = fmaf(sc[s], to_f32<KVT>(vb[(int64_t)s * kv_stride + d]), acc);
-        if (n_cached < n_keys) acc = fmaf(sc[n_cached], to_f32<QT>(vf[d]), acc);
-        o[qrow * o_stride + h * dh + d] = from_f32<QT>(acc * inv);
+        if (live) {
+            int s = grp;
+            for (; s + 7 * G < n_cached; s += 8 * G) {
+                float vv[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) vv[u] = to_f32<KVT>(vb[(int64_t)(s + u * G) * kv_stride + d]);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc = fmaf(sc[s + u * G], vv[u], acc);
+            }
+            for (; s < n_cached; s += G) acc = fmaf(sc[s], to_f32<KVT>(vb[(int64_t)s * kv_stride + d]), acc);
+            if (grp == 0 && n_cached < n_keys) acc = fmaf(sc[n_cached], to_f32<QT>(vf[d]), acc);
+        }
+        float sum = acc;
+        for (int g = 1; g < G; ++g) sum += __shfl(acc, (g * dh + lane) & 63, 64);      // of use to the lanes of group 0
+        if (live && grp == 0) o[qrow * o_stride + h * dh + d] = from_f32<QT>(sum * inv);
     }
 }
 

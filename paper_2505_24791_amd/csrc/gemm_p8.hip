@@ -21,12 +21,12 @@
 // Measured (us per launch, k-tiles of 32 in four stages -> this; IEEE half, bias / GELU / float32 residual epilogue):
 //   32768 x 3072 x 1024 bias 197 -> 178, 32768 x 4096 x 1024 GELU 300 -> 278, 32768 x 1024 x 1024 residual 101 -> 85,
 //   32768 x 1024 x 4096 residual 281 -> 246, 65536 x 768 x 3072 residual 337 -> 297.
-// What bounds it: no single unit.  Power allows a loop of nothing but these instructions on random operands 1.64 GHz (1.72 PFLOP/s);
-// at about that clock the matrix pipe is busy 69 % of the cycles at N = 3072, K = 1024 (bias), 66 % at N = 1024, K = 4096 (residual), 56 %
-// at N = 4096, K = 1024 (GELU) and 39 % at N = K = 1024 (residual).  The rest is the operand stream into LDS (8 to 9 TB/s out of
-// L2; waves wait for data or the barrier 30 to 49 % of their time) and the epilogues, which nothing hides: at the bias launch's rate the GELU
-// launch would take 240 us of its 276 and the last one 60 of 94.  Taking out the waits and the barrier gains 4 %, and four waves of 128
-// x 128 (a third fewer LDS reads) take as long with more idle cycles at a higher clock.
+// What bounds it: power, then the epilogues.  Without its epilogue the kernel runs at 1.25 to 1.30 PFLOP/s on random operands at all of
+// these shapes (1.7 on a zero left operand), and so do variants with the weights from L2 instead of LDS, with two workgroups of four waves, and with the waits
+// taken out; four waves of 128 x 128 (a third fewer LDS reads) take as long with more idle cycles at a higher clock.  On top come the epilogues: bias 16 us
+// of the first shape, a float32 residual 30 of the third and fourth (all CUs read and write 256 KB each at once; starting them staggered, and residual loads
+// one to three groups ahead, gained nothing), GELU 63 of the second, 54 of them vector ALU: launches with GELU that fill the chip go to gemm_duo.hip, which
+// runs it beside the matrix instructions.
 #include "common.h"
 #include <atomic>
 

@@ -67,3 +67,23 @@ def test_passes_of_few_rows_match_oracle(orc32, W, H, T, D, B):
         assert np.abs(mu[b].cpu().numpy() - rmu[::-1]).max() <= 1e-4
         assert np.abs(al[b].cpu().numpy() - ral[::-1]).max() <= 1e-4
     f.close()
+
+
+@pytest.mark.parametrize("W,H,T,B", [(64, 16, 1, 2), (64, 16, 130, 2), (64, 8, 65, 3), (64, 4, 33, 2), (128, 4, 17, 2), (128, 4, 150, 2), (96, 8, 70, 2)],
+                         ids=lambda v: str(v))
+def test_rowwise_attention_of_small_heads(orc32, W, H, T, B):
+    """Heads of 4 to 32 (the wave splits into groups of keys) and of 12 (it does not), keys below, at and past the groups' eight rows."""
+    import torch
+    import paper_2505_24791_amd as sjd
+    cfg = wl.FlowConfig("att_f32", n_blocks=1, n_layers=2, width=W, n_heads=H, seq_len=T, token_dim=5, batch=B, bf16=False)
+    print(cfg, flush=True)
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    x = wl.make_latent(cfg, seed=37)
+    f = sjd.Flow(cfg)
+    f.load_weights(blob)
+    mu, al = f.conditioner(0, torch.from_numpy(x).cuda())
+    for b in range(B):
+        rmu, ral = orc32.cond(cfg, blob, 0, x[b])
+        assert np.abs(mu[b].cpu().numpy() - rmu).max() <= 1e-4
+        assert np.abs(al[b].cpu().numpy() - ral).max() <= 1e-4
+    f.close()
