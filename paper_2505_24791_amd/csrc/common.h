@@ -189,7 +189,7 @@ void launch_gemm_p8(const HT *A, const HT *Bt, const float *bias, OutT *C, int M
 
 // MLP-input projection with GELU for launches that fill the chip (gemm_duo.hip): C[M,N] (16-bit) = gelu(A[M,K] * W + bias), W in the
 // fragment order of the 32x32x16 instruction (launch_weights_to_frag32 from the transposed [N, K] copy); bit-identical to launch_gemm_h16.
-bool gemm_duo_applicable(int M, int N, int K);
+// For launches that gemm_duo_applicable() (gemm_rules.h) admits.
 template <typename HT>
 void launch_gemm_duo_gelu(const HT *A, const HT *Wf, const float *bias, HT *C, int M, int N, int K, hipStream_t s);
 

@@ -16,6 +16,7 @@
 // Measured, us, gemm_p8.hip -> this: 32768 x 4096 x 1024 276 -> 257, 16384 x 4096 x 1024 143 -> 133, 65536 x 3072 x 768 340 -> 301, 8192 x 3072 x 768
 // 55 -> 45, 32768 x 2048 x 512 91 -> 83.  The other epilogues gain nothing or lose (float32 residual at k = 4096: 246 -> 257).
 #include "common.h"
+#include "gemm_rules.h"
 #include <atomic>
 #include <type_traits>
 
@@ -23,7 +24,7 @@ namespace sjd {
 
 namespace {
 
-constexpr int U_BM = 128, U_BN = 256;
+constexpr int U_BM = kDuoRows, U_BN = kDuoCols;
 constexpr int U_CB = 4;                       // column tiles per column block of the tile order
 constexpr int U_UNITS = 4, U_UNIT = 16 * 1024;  // units of the LDS ring: A of one k-tile, 128 rows x 128 B
 constexpr int U_PARK = 16 * 1024;
@@ -224,13 +225,6 @@ __global__ __launch_bounds__(256, 2) void gemm_h16_duo_kernel(const HT *__restri
 }
 
 }  // namespace
-
-// From 256 tiles on (one per CU) this is as fast as the smaller tiles of gemm_h16.hip or faster: 2048 x 4096 x 1024 30 -> 27 us, 4096 x 2048 x 512
-// 19.0 -> 18.5, 8192 x 1024 x 256 14.5 -> 13.6; below, 1024 x 3072 x 768 (96 tiles) 14.6 -> 16.2, 1024 x 2048 x 512 (64) 8 -> 13.
-bool gemm_duo_applicable(int M, int N, int K) {
-    return N >= 256 && N % 256 == 0 && K >= 256 && K % 128 == 0 && (long long)N * K * 2 < (1ll << 31) && (long long)N * 2 * 128 < (1ll << 31) &&
-           (long long)((M + U_BM - 1) / U_BM) * (N / U_BN) >= 256 && (long long)((M + U_BM - 1) / U_BM) * (N / U_BN) < (1ll << 30);
-}
 
 template <typename HT>
 void launch_gemm_duo_gelu(const HT *A, const HT *Wf, const float *bias, HT *C, int M, int N, int K, hipStream_t s) {

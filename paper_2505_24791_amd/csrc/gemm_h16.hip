@@ -9,6 +9,7 @@
 // No split-K and no atomics: an output row depends only on its own row of A, so results are
 // independent of which other rows share the tile or the batch.
 #include "common.h"
+#include "gemm_rules.h"
 #include <atomic>
 
 namespace sjd {
@@ -580,8 +581,7 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
     // than their CUs take at once, and the second round costs as much as the first.  Microseconds as 128x128 tiles / persistent, one round:
     // 8690 x 1024 x 4096 118 / 84, 3321 x 3840 x 1280 56 / 39, 8690 x 1024 x 256 20.0 / 18.3; two: 5372 x 3072 x 768 45 / 51,
     // 2053 x 5120 x 1280 50 / 68, 4576 x 3072 x 1024 48 / 50, 2829 x 4608 x 1536 70 / 69.
-    const long p8_per_xcd = ((M + 255) / 256 + 7) / 8 * (long)((N + 255) / 256);
-    if (p8_ok && (t256 >= kCus || (t128 > 2 * kCus && p8_per_xcd <= kCus / 8)))
+    if (p8_ok && (t256 >= kCus || (t128 > 2 * kCus && gemm_p8_one_round(M, N))))
         return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
     if (t128 <= 2 * kCus && aligned) {
         // 64x64 while its tiles fit two per CU (256 x 512 x 2048: 25.1 us as 128x128 tiles, 13.0 as these; 2048 x 1024 x 1024:

@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "common.h"
+#include "gemm_rules.h"
 
 using namespace sjd;
 
