@@ -789,7 +789,7 @@ hipError_t launch_seq_persistent(bool is_bf16, const SeqArgs &args, int MB, int 
     const int members = grid / 8 * args.xpg, blocks = 64 * S;
     const int per = members > 0 ? (blocks + members - 1) / members : blocks;
     const int CB = MB == 2 || per > 2 ? 4 : per;
-    const bool ahead = args.kv_ahead && MB == 1 && S >= 2;   // two row blocks leave no room for it
+    const bool ahead = args.kv_ahead != 0;
     const void *kern = is_bf16 ? pick_kernel<bf16>(MB, S, CB, ahead) : pick_kernel<f16>(MB, S, CB, ahead);
     if (!kern) return hipErrorInvalidValue;
     const size_t lds = seq_lds_bytes(MB, args.D, ahead);

@@ -44,4 +44,20 @@ SJD_HOST_DEVICE inline SeqGroup seq_group_of(const int (&count)[8], int xcc, int
     return g;
 }
 
+// Whether the first cached rows of a member's first two pairs are requested into LDS between the stages before the attention
+// (decode_persistent.hip): one row block per group (two leave no room), widths from 512 on (narrower ones have no such kernel), the busiest members
+// with a second pair, and a prefix long beside the weights that those stages load.  The requests cost every member, and a member with one
+// pair waits for one set of cached rows at most.  Microseconds a step without -> with, busiest group's pairs / members:
+//   width 512, 4 layers, 256 tokens: 64/64 64.0 -> 66.8, 72/64 69.7 -> 71.4, 80/64 72.0 -> 72.8, 88/64 74.5 -> 74.7, 96/64 76.1 -> 75.1, 128/64 79.9 -> 77.8, 256/64
+//     99.1 -> 97.3; 1024 tokens: 64/64 78.0 -> 81.4, 88/64 99.7 -> 97.4, 128/64 116 -> 109; 192 tokens: 128/64 78.1 -> 76.6, 200/64 90.1 -> 90.9, 256/64 95.5 -> 95.2;
+//   width 768, 8 layers: 513 tokens: 132/128 150.1 -> 152.6, 156/128 162.3 -> 164.9; 600: 144/128 166.5 -> 166.9, 168/128 174.7 -> 174.3, 192/64 229.0 -> 229.1, 384/64
+//     370 -> 367; 777: 144/128 177.5 -> 177.2, 168/128 186.0 -> 184.0, 120/128 159.9 -> 162.8;
+//   width 1024, 8 layers: 513 tokens: 128/128 176.2 -> 180.4, 144/128 193.4 -> 190.6, 256/128 221 -> 211, 256/32 310 -> 310; 256 tokens: 256/32 264 -> 272, 512/32
+//     408 -> 415; 777: 160/128 222.3 -> 215.2.
+inline bool seq_rows_ahead(int B, int heads, int width, int T, int n_cus, int xpg) {
+    if (B > 128 || width < 512 || T < (width <= 512 ? 256 : width <= 768 ? 600 : 513)) return false;
+    const int groups = 8 / xpg, members = n_cus / groups, pairs = (B + groups - 1) / groups * heads;
+    return width <= 512 ? 8 * pairs >= 11 * members : pairs > members;
+}
+
 }  // namespace sjd

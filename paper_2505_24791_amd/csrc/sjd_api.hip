@@ -16,6 +16,7 @@
 
 #include "common.h"
 #include "gemm_rules.h"
+#include "seq_groups.h"
 
 using namespace sjd;
 
@@ -806,11 +807,7 @@ int run_sequential_persistent(sjd_flow *f, int j, const float *z, float *x, int 
     // samples (159 MB) 100 -> 104, 64 samples of 1024 tokens (293 MB) 118 -> 118; width 1024, 8 layers, 8 samples of 1024 tokens (338 MB)
     // 202 -> 196, 32 samples (738 MB) 298 -> 283.
     a.kv_stream = wbytes + kvbytes > 256e6;
-    // Cached rows through LDS between the stages pay where streaming them is what an attention stage costs: every member has a pair, and the
-    // prefix is long beside the weights that those stages load.  Without -> with: width 512, 4 layers, 64 / 128 samples of 256 tokens 79.4 -> 78.0 /
-    // 103 -> 99, 64 of 1024 117 -> 111; width 1024, 32 samples of 600 tokens (4 layers) 117 -> 112; outside the rule: width 1024, 8
-    // layers, 64 samples of 256 tokens 259 -> 272, 8 of 1024 185 -> 189, width 512, 16 samples of 1024 75.0 -> 76.7, 100 of 128 89 -> 92.
-    a.kv_ahead = batch * c.n_heads >= f->n_cus && c.seq_len >= (c.width <= 512 ? 256 : 513);
+    a.kv_ahead = seq_rows_ahead(batch, c.n_heads, c.width, c.seq_len, f->n_cus, a.xpg);
     ProfScope ps(f, SJD_PROF_DECODE_FUSED, steps * 2.0 * batch * (c.n_layers * (4.0 + 2.0 * R) * W * W + 2.0 * c.token_dim * W) +
                                                steps * 4.0 * batch * (c.seq_len / 2.0) * W * c.n_layers,
                  steps * (wbytes + kvbytes), s);

@@ -138,10 +138,15 @@ def test_persistent_kernel_over_its_group_sizes(torch_cuda, orc32, batch, tokens
 
 
 @pytest.mark.parametrize("batch,tokens,dim,layers,width", [
-    (32, 290, 64, 1, 512),     # one layer, the largest token size; the prefix ends inside, at and behind the rows kept in LDS
-    (40, 256, 5, 2, 512),      # the shortest sequences, members with one and with two pairs
-    (16, 513, 12, 2, 1024),    # three batches of cached keys, every member one pair
-    (23, 520, 3, 1, 768),      # more than two pairs for some members
+    (32, 290, 64, 1, 512),     # one pair for every member: from registers
+    (40, 256, 5, 2, 512),      # a second pair for a quarter of them: the same
+    (16, 513, 12, 2, 1024),    # two batches of cached keys, every member one pair
+    (23, 520, 3, 1, 768),      # a prefix that is short beside the weights
+    (44, 290, 64, 1, 512),     # through LDS: one layer, the largest token size; the prefix ends inside, at and behind the rows kept there
+    (41, 256, 5, 2, 512),      # the shortest sequences, the fewest pairs, members with one and with two
+    (17, 520, 12, 2, 1024),    # three batches of cached keys
+    (21, 601, 3, 1, 768),      # the last group has a sample less
+    (100, 257, 7, 1, 512),     # more than two pairs a member
 ])
 def test_cached_rows_through_lds_give_the_same_bits(torch_cuda, batch, tokens, dim, layers, width):
     """A batch that fills the chip takes the first cached rows of a pair out of LDS, a single sample out of registers."""
