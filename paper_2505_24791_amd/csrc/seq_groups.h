@@ -44,6 +44,19 @@ SJD_HOST_DEVICE inline SeqGroup seq_group_of(const int (&count)[8], int xcc, int
     return g;
 }
 
+// XCDs per group of the persistent kernel.  More of them spread a stage's weights over more CUs and read them from memory
+// fewer times, but exchanges between XCDs take longer (2.4 us against 1.5 to 2) and a group then has more rows to pass
+// round.  Microseconds a step with 8 / 4 / 2 / 1 XCDs per group: width 1024, 2 layers: one sample 43 / 46 / 50 / 73, 16 samples 54 / 52 / 61 /
+// 80, 64 samples - / - / 108 / 128; width 768, 2 layers, 32 samples - / 51 / 52 / 65; width 512, 4 layers: one sample 59 / 58 / 63 / 70, 16 samples
+// 78 / 73 / 70 / 73; width 256, 4 layers, 32 samples - / 70 / 62 / 57.  A group holds at most sixteen samples (one row block of the matrix
+// instruction) unless the batch leaves no choice.
+inline int seq_xcds_per_group(int W, int batch) {
+    int x = W <= 256 ? 1 : W <= 512 ? 2 : 4;
+    if (batch <= 4 && W > 256) x *= 2;
+    while (x > 1 && (batch * x + 7) / 8 > 16) x /= 2;
+    return x;
+}
+
 // Whether the first cached rows of a member's first two pairs are requested into LDS between the stages before the attention
 // (decode_persistent.hip): one row block per group (two leave no room), widths from 512 on (narrower ones have no such kernel), the busiest members
 // with a second pair, and a prefix long beside the weights that those stages load.  The requests cost every member, and a member with one

@@ -764,20 +764,6 @@ bool persistent_ok(const sjd_flow *f, int batch) {
            seq_persistent_lds_bytes(batch <= 128 ? 1 : 2, c.token_dim) <= 160 * 1024;
 }
 
-// XCDs per group of the persistent kernel.  More of them spread a stage's weights over more CUs and read them from memory
-// fewer times, but exchanges between XCDs take longer (2.4 us against 1.5 to 2) and a group then has more rows to pass
-// round.  Microseconds a step with 8 / 4 / 2 / 1 XCDs per group: width 1024, 2 layers: one sample 43 / 46 / 50 / 73, 16 samples 54 / 52 / 61 /
-// 80, 64 samples - / - / 108 / 128; width 768, 2 layers, 32 samples - / 51 / 52 / 65; width 512, 4 layers: one sample 59 / 58 / 63 / 70, 16 samples
-// 78 / 73 / 70 / 73; width 256, 4 layers, 32 samples - / 70 / 62 / 57.  A group holds at most sixteen samples (one row block of the matrix
-// instruction) unless the batch leaves no choice.
-int seq_xcds_per_group(const sjd_flow *f, int batch) {
-    const int W = f->cfg.width;
-    int x = W <= 256 ? 1 : W <= 512 ? 2 : 4;
-    if (batch <= 4 && W > 256) x *= 2;
-    while (x > 1 && (batch * x + 7) / 8 > 16) x /= 2;
-    return x;
-}
-
 int run_sequential_persistent(sjd_flow *f, int j, const float *z, float *x, int batch, hipStream_t s) {
     const sjd_config &c = f->cfg;
     const BlockW &bw = f->block[j];
@@ -793,7 +779,7 @@ int run_sequential_persistent(sjd_flow *f, int j, const float *z, float *x, int 
     a.w_in = bw.w_in; a.b_in = bw.b_in; a.pos = bw.pos;
     a.z = z; a.x = x;
     a.ws = f->seq_ws;
-    a.xpg = seq_xcds_per_group(f, batch);
+    a.xpg = seq_xcds_per_group(c.width, batch);
     a.kcache = f->kcache; a.vcache = f->vcache;
     a.kv_layer_stride = (size_t)c.max_batch * c.seq_len * c.width;
     a.B = batch; a.T = c.seq_len; a.D = c.token_dim; a.reversed = (c.reverse_mask >> j) & 1;

@@ -59,7 +59,12 @@ def test_passes_of_few_rows_match_oracle(orc32, W, H, T, D, B):
     x = wl.make_latent(cfg, seed=29)
     f = sjd.Flow(cfg)
     f.load_weights(blob)
+    f.profile_enable(range(sjd.PROF_FAMILIES))
     mu, al = f.conditioner(1, torch.from_numpy(x).cuda())
+    prof = f.profile_read()
+    f.profile_enable([])
+    few = B * T * W <= 192 * 1024
+    assert prof["other"]["launches"] == (1 if few else 6)          # the embedding, and LayerNorm where it is a launch of its own
     one_mu, one_al = f.conditioner(1, torch.from_numpy(x[-1:].copy()).cuda())         # one row block or two: the same bits
     assert torch.equal(one_mu[0], mu[-1]) and torch.equal(one_al[0], al[-1])
     for b in (0, B - 1):

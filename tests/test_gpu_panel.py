@@ -152,8 +152,8 @@ def test_flow_gives_the_same_bits_on_both_projection_paths(torch_cuda, dtype_nam
 
 def test_headline_workload_takes_the_panel_kernels_and_gives_the_same_bits(torch_cuda):
     """Configuration C2 at its full batch (16384 rows per pass: the launch configuration that bench.py
-    times): the automatic choice is the activation-stationary / streaming kernels, and a Jacobi block gives
-    the bits and pass counts of the tile kernels."""
+    times): the automatic choice is the activation-stationary / streaming kernels (the MLP input on two workgroups per CU), and a
+    Jacobi block gives the bits and pass counts of the tile kernels."""
     import paper_2505_24791_amd as sjd
     import workloads as wl
     torch = torch_cuda

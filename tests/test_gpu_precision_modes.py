@@ -143,3 +143,40 @@ def test_max_norm_of_alg1_with_refinement_follows_the_oracle(c2):
         if abs(tr[rit - 1] - 1e-3) > 1e-5:
             assert abs(int(iters[b]) - rit) <= 1
     f.close()
+
+
+@pytest.mark.parametrize("W,H,T,B", [
+    (256, 4, 40, 6),
+    (512, 8, 64, 6),               # rows * width on the line below which the float32 step kernels take a pass
+    (512, 8, 65, 6),               # and past it
+], ids=lambda v: str(v))
+def test_refined_passes_of_few_rows_follow_the_oracle(orc32, W, H, T, B):
+    """Small 16-bit flows: with a bound that every sample is under, all passes after the first run in float32.  T passes then give the
+    sequential inverse of the float32 oracle to the float32 bound (1e-4): the first token is copied, and each pass makes one more exact."""
+    import torch
+    import paper_2505_24791_amd as sjd
+    cfg = wl.FlowConfig("few_refined", n_blocks=2, n_layers=2, width=W, n_heads=H, seq_len=T, token_dim=8, batch=B, bf16=True)
+    print(cfg, flush=True)
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    z = wl.make_latent(cfg, seed=41)
+    f = sjd.Flow(cfg)
+    f.load_weights(blob)
+    f.profile_enable(range(sjd.PROF_FAMILIES))
+    x, iters, passes, _ = f.jacobi_inverse_block(1, torch.from_numpy(z).cuda(), sjd.JacobiOpts(tau=0.0, refine_below=1e30))
+    prof = f.profile_read()
+    f.profile_enable([])
+    assert passes == T and (iters == T).all()
+    # the embedding and, where it is a launch of its own, LayerNorm: in the first pass, which runs on 16-bit operands, and past the line
+    few = B * T * W <= 192 * 1024
+    assert prof["other"]["launches"] == 6 + (T - 1) * (1 if few else 6)
+    for b in range(B):
+        ref = orc32.sequential_inverse_block(cfg, blob, 1, z[b])
+        assert np.abs(x[b].cpu().numpy() - ref).max() <= 1e-4, b
+    # and at the bound in use: the oracle's counts within one pass (a sample within 1 % of the threshold may take any)
+    x, iters, _, _ = f.jacobi_inverse_block(1, torch.from_numpy(z).cuda(), sjd.JacobiOpts(tau=1e-4, refine_below=1e-3))
+    for b in range(B):
+        rx, rit, tr = orc32.jacobi_inverse_block(cfg, blob, 1, z[b], 1e-4, want_trace=True)
+        assert np.abs(x[b].cpu().numpy() - rx).max() <= 2e-2
+        if abs(tr[rit - 1] - 1e-4) > 1e-6:
+            assert abs(int(iters[b]) - rit) <= 1, b
+    f.close()

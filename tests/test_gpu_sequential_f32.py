@@ -74,7 +74,11 @@ def test_narrow_block_in_one_launch(orc32, W, H, N, T, D, B):
     f.load_weights(blob)
     for j in range(2):
         f.set_sequential_path(0)
+        f.profile_enable(range(sjd.PROF_FAMILIES))
         x = f.sequential_inverse_block(j, zd)
+        prof = f.profile_read()
+        f.profile_enable([])
+        assert prof["decode_fused"]["launches"] == 1 and prof["decode_gemm"]["launches"] == 0
         assert torch.equal(f.sequential_inverse_block(j, zd), x)
         assert torch.equal(f.sequential_inverse_block(j, zd[-1:].contiguous())[0], x[-1])
         f.set_sequential_path(1)

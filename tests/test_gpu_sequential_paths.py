@@ -137,19 +137,22 @@ def test_persistent_kernel_over_its_group_sizes(torch_cuda, orc32, batch, tokens
     f.close()
 
 
-@pytest.mark.parametrize("batch,tokens,dim,layers,width", [
-    (32, 290, 64, 1, 512),     # one pair for every member: from registers
-    (40, 256, 5, 2, 512),      # a second pair for a quarter of them: the same
-    (16, 513, 12, 2, 1024),    # two batches of cached keys, every member one pair
-    (23, 520, 3, 1, 768),      # a prefix that is short beside the weights
-    (44, 290, 64, 1, 512),     # through LDS: one layer, the largest token size; the prefix ends inside, at and behind the rows kept there
-    (41, 256, 5, 2, 512),      # the shortest sequences, the fewest pairs, members with one and with two
-    (17, 520, 12, 2, 1024),    # three batches of cached keys
-    (21, 601, 3, 1, 768),      # the last group has a sample less
-    (100, 257, 7, 1, 512),     # more than two pairs a member
+@pytest.mark.parametrize("batch,tokens,dim,layers,width,through_lds", [
+    (32, 290, 64, 1, 512, False),      # one pair for every member
+    (40, 256, 5, 2, 512, False),       # a second pair for a quarter of them
+    (16, 513, 12, 2, 1024, False),     # two batches of cached keys, every member one pair
+    (23, 520, 3, 1, 768, False),       # a prefix that is short beside the weights
+    (44, 290, 64, 1, 512, True),       # one layer, the largest token size; the prefix ends inside, at and behind the rows kept in LDS
+    (41, 256, 5, 2, 512, True),        # the shortest sequences, the fewest pairs, members with one and with two
+    (17, 520, 12, 2, 1024, True),      # three batches of cached keys
+    (21, 601, 3, 1, 768, True),        # the last group has a sample less
+    (100, 257, 7, 1, 512, True),       # more than two pairs a member
 ])
-def test_cached_rows_through_lds_give_the_same_bits(torch_cuda, batch, tokens, dim, layers, width):
+def test_cached_rows_through_lds_give_the_same_bits(torch_cuda, launch_rules, batch, tokens, dim, layers, width, through_lds):
     """A batch that fills the chip takes the first cached rows of a pair out of LDS, a single sample out of registers."""
+    n_cus = torch_cuda.cuda.get_device_properties(0).multi_processor_count
+    for b, lds in ((batch, through_lds), (1, False)):
+        assert bool(launch_rules.rows_ahead(b, width // 64, width, tokens, n_cus, launch_rules.xcds_per_group(width, b))) == lds
     print(f"case B {batch} T {tokens} D {dim} N {layers} W {width}", flush=True)
     _, _, f, z = _flow(batch, tokens, dim, layers, width, seed=47)
     f.set_sequential_path(2)

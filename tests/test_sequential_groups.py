@@ -1,6 +1,5 @@
 """Group formation of the persistent sequential kernel (csrc/seq_groups.h), compiled for the host: on any set of XCDs every sample
 belongs to exactly one group that can hold it, and the members of a group are numbered without gaps."""
-import ctypes
 import os
 import shutil
 import subprocess
@@ -60,23 +59,10 @@ def test_every_sample_has_a_group_on_any_set_of_xcds(tmp_path):
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout
 
 
-ROWS_AHEAD = r"""
-#include "seq_groups.h"
-extern "C" int rows_ahead(int B, int heads, int width, int T, int n_cus, int xpg) { return sjd::seq_rows_ahead(B, heads, width, T, n_cus, xpg); }
-"""
-
-
-def test_cached_rows_go_ahead_only_where_members_have_a_second_pair(tmp_path):
+def test_cached_rows_go_ahead_only_where_members_have_a_second_pair(launch_rules):
     """Requests between the stages cost every member; they pay where the busiest members have more than one pair (width 512, 32 samples of 256
     tokens, one pair each: 64.0 us a step without, 66.8 with; width 1024, 16 samples of 777 tokens: 188, 192)."""
-    gxx = shutil.which("g++")
-    assert gxx, "g++ is part of the image"
-    src = tmp_path / "ahead.cpp"
-    src.write_text(ROWS_AHEAD)
-    lib = str(tmp_path / "ahead.so")
-    subprocess.run([gxx, "-O1", "-std=c++17", "-Wall", "-Wextra", "-Werror", "-shared", "-fPIC",
-                    "-I", os.path.join(ROOT, "paper_2505_24791_amd", "csrc"), str(src), "-o", lib], check=True)
-    ahead = ctypes.CDLL(lib).rows_ahead
+    ahead = launch_rules.rows_ahead
     # width 512, two XCDs a group: 64 members share the pairs of a quarter of the batch
     assert [b for b in range(1, 129) if ahead(b, 8, 512, 256, 256, 2)] == list(range(41, 129))
     assert not ahead(64, 8, 512, 255, 256, 2)
