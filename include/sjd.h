@@ -246,10 +246,11 @@ SJD_API int sjd_op_panel_linear_h16_noalloc(int dtype, const void *a_dev, const 
 SJD_API int sjd_op_attention_h16(int dtype, const void *qkv_dev, void *o_dev, int n_samples, int T, int H,
                                  void *hip_stream);
 
-/* Which kernels the whole-sequence passes of a 16-bit flow use for their projections: 0 automatic (the
- * activation-stationary kernels for width 512 from 2048 rows on, the tile kernels otherwise), 1 tile
- * kernels with separate LayerNorm launches everywhere, 2 activation-stationary kernels for every row count
- * (SJD_EINVAL unless the flow is 16-bit with width 512).  The two give the same bits. */
+/* Which kernels the whole-sequence passes of a 16-bit flow use for their projections: 0 automatic (by shape: tile
+ * and persistent kernels; the MLP input of large passes on the one with two workgroups per CU; for width 512 between
+ * 10240 and 16384 rows the activation-stationary kernels for all but the MLP input), 1 tile and persistent kernels
+ * with separate LayerNorm launches everywhere, 2 activation-stationary kernels for every row count
+ * (SJD_EINVAL unless the flow is 16-bit with width 512).  All give the same bits. */
 SJD_API int sjd_flow_set_projection_path(sjd_flow *flow, int path);
 
 /* The masked-dependency probe of Sec. 3.2, eq. 6: with o > 0 every attention of the conditioner ignores

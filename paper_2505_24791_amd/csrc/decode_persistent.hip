@@ -159,11 +159,6 @@ __device__ __forceinline__ void poll16(const Ctx &c, rsrc_t rs, OFF off, i32x4 (
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
 }
 
-// C[:, blocks of this member] = epi(LayerNorm(stream) * Wt^T + bias) for the group's rows, K = W = 256 S.  The stream
-// (at in_off) is float32 fragment-major, Wt fragment-major; 16-column block cb belongs to member cb % n, CB blocks a round.  Weights are the first
-// matrix operand and rows the second, so a lane ends up with four consecutive columns of one row.
-// 16-bit results go to out_off (fragment-major; the member's part at empty_off is emptied); with LOCAL the float32
-// result goes to the workgroup's own buffer (row-major [16 MB][N], row 0 = the group's first row) and the member takes every block.
 // A member without a share of a stage still requests its part of the cached rows: behind the same wait and barrier as in the stage.
 template <class AHEAD> __device__ __forceinline__ void idle_ahead(AHEAD ahead) {
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
@@ -171,6 +166,11 @@ template <class AHEAD> __device__ __forceinline__ void idle_ahead(AHEAD ahead) {
     ahead();
 }
 
+// C[:, blocks of this member] = epi(LayerNorm(stream) * Wt^T + bias) for the group's rows, K = W = 256 S.  The stream
+// (at in_off) is float32 fragment-major, Wt fragment-major; 16-column block cb belongs to member cb % n, CB blocks a round.  Weights are the first
+// matrix operand and rows the second, so a lane ends up with four consecutive columns of one row.
+// 16-bit results go to out_off (fragment-major; the member's part at empty_off is emptied); with LOCAL the float32
+// result goes to the workgroup's own buffer (row-major [16 MB][N], row 0 = the group's first row) and the member takes every block.
 template <typename HT, int MB, int S, int CB, int EPI, bool LOCAL, class AHEAD>
 __device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t ws, uint32_t in_off, const float *__restrict__ g,
                                               const float *__restrict__ be, const HT *__restrict__ Wt,

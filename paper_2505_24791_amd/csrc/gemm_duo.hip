@@ -5,7 +5,9 @@
 // issue slots a value, 54 us of vector ALU in that launch, which the persistent kernel of gemm_p8.hip cannot run beside matrix instructions,
 // for its one workgroup per CU has all of its accumulators in the epilogue at once.  Here a CU holds two independent workgroups, a 128 x
 // 256 tile and 80 KB of LDS each, so that one works on its epilogue while the other multiplies.  They start in step; the second half of a tile's k
-// runs at a higher wave priority, so that of two the one that is ahead finishes first and they fall out of step within a tile or two.
+// and its epilogue run at a higher wave priority, so that of two the one that is ahead finishes first and they fall out of step within a tile or
+// two.  (Priority lowered before the epilogue: 13659 x 4096 x 1024 114.4 -> 112.7 us, 18139 x 3072 x 768 92.0 -> 90.8, 26587 x 3072 x 768 129.1 -> 131.3, 27355 x
+// 2048 x 512 70.3 -> 71.3.)
 //   * four waves per workgroup, one per SIMD, 128 x 64 of the tile each (128 accumulator registers);
 //   * A through LDS: k-tiles of 64 (whole cache lines) in a ring of four 16 KB units filled by LDS-direct loads three k-tiles ahead, one
 //     barrier per k-tile; swizzled as in gemm_p8.hip;
@@ -13,8 +15,9 @@
 //     ahead: a smaller tile needs more operand bytes per product, and LDS could not deliver both;
 //   * both request streams run on into the workgroup's next tile; the epilogue parks accumulators in 16 KB of LDS of its own.
 // k is walked in index order with the same instruction: results are bit-identical to the other 16-bit kernels.
-// Measured, us, gemm_p8.hip -> this: 32768 x 4096 x 1024 276 -> 257, 16384 x 4096 x 1024 143 -> 133, 65536 x 3072 x 768 340 -> 301, 8192 x 3072 x 768
-// 55 -> 45, 32768 x 2048 x 512 91 -> 83.  The other epilogues gain nothing or lose (float32 residual at k = 4096: 246 -> 257).
+// Measured alone, us, gemm_p8.hip -> this: 32768 x 4096 x 1024 276 -> 257, 16384 x 4096 x 1024 143 -> 133, 65536 x 3072 x 768 340 -> 301, 8192 x 3072 x 768
+// 55 -> 45, 32768 x 2048 x 512 91 -> 83; inside the passes of the largest flows 1.5 to 2 %.  The other epilogues gain nothing or lose (float32 residual at k
+// = 4096: 246 -> 257).
 #include "common.h"
 #include "gemm_rules.h"
 #include <atomic>

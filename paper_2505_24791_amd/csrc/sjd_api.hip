@@ -333,6 +333,7 @@ void attention_step(sjd_flow *f, int l, int B, int t, hipStream_t s) {
 // LayerNorm launch.  A conditioner of 2 layers, us, whole-sequence / step kernels: width 128, 196 rows 158 / 113, 1200 rows 169 / 141, 4096 rows 231 /
 // 243; width 256, 256 rows 212 / 142, 800 rows 195 / 167, 1600 rows 228 / 231; width 512, 256 rows 286 / 196, 600 rows 297 / 290, 800 rows 318 / 343;
 // width 1024, 128 rows 425 / 295, 196 rows 451 / 459.  The largest pass of the flow decides, not this one's rows: a row gives the same bits in any batch.
+// The float32 passes of small 16-bit flows (refine_below) take the same rule: conditioner_pass_f32 runs this pass with the float32 weights.
 bool short_f32(const sjd_config &c) {
     return c.dtype == SJD_DTYPE_F32 && skinny_f32_ln_ok(c.width) && (size_t)c.max_batch * c.seq_len * c.width <= 192 * 1024;
 }
@@ -355,11 +356,11 @@ void conditioner_pass(sjd_flow *f, int j, const float *x, int n, const int32_t *
         ProfScope ps(f, SJD_PROF_OTHER, 2.0 * M * (double)D * W, (double)M * W * 4, s);
         launch_embed(x, bw.w_in, bw.b_in, bw.pos, f->h, M, D, W, RowMap{active, T, 0, T, rev}, s);
     }
-    // Width 512: LayerNorm + projection in one activation-stationary launch where that is faster.  A workgroup of those kernels
-    // is 128 rows x 768..1024 columns of work, two per panel of 128 rows: below ~90 panels (10240 rows) the tile kernels' finer grain
-    // wins, above 128 panels the last round of workgroups is nearly empty and the
-    // persistent kernel wins (a pass of 4 layers: 16384 rows 795 us against 831, 18432 rows 1123 against 937, 32768 rows 1596
-    // against 1432, 65536 rows 2912 against 2642).
+    // Width 512: LayerNorm + QKV, the attention output and the MLP output on the activation-stationary kernels, a workgroup of which is 128 rows x 768..1024
+    // columns of work: above 16384 rows (128 panels) their last round is nearly empty.  A pass of 4 layers, us, tile kernels / these: 8192 rows
+    // 490 / 511, 8448 579 / 538, 9984 598 / 567, 10240 601 / 571, 12288 692 / 636, 16384 797 / 737, 17408 861 / 942, 20480 931 / 1013.  The lower line was
+    // drawn while the MLP input was a panel launch as well; without it these kernels win from 8448 rows on.  The MLP input takes the panel kernel only
+    // where it is asked for (12288 rows 663 against 638 with gemm_duo.hip, 16384 rows 749 against 737).
     const bool panel_any = f->arena_panel && f->proj_path != 1 && gemm_panel_applicable(M, RW, W, 2) &&
                            gemm_panel_applicable(M, 3 * W, W, 2) && gemm_panel_applicable(M, W, W, 4);
     const bool panel_one_round = M <= 16384;
@@ -727,8 +728,10 @@ int run_sequential_fast(sjd_flow *f, int j, const float *z, float *x, int batch,
     return SJD_OK;
 }
 
-// Narrow float32 flows: the whole block in one launch, a workgroup per sample.  Samples beyond the CUs run in further rounds: width 128, 2 layers,
-// 257 samples 48 us a step against 63 with per-step launches, 1024 samples 117 (of 1024 threads) against 100.  As in tall_f32, the flow's largest batch decides.
+// Narrow float32 flows: the whole block in one launch, a workgroup per sample.  Samples beyond the CUs run in further rounds.  Microseconds a step,
+// per-step launches -> this, 2 layers: width 128, 256 tokens, one sample 44 -> 26, 257 samples 72 -> 59, 512 88 -> 64, 600 96 -> 91, 1024 133 -> 127; 4096 tokens, one
+// sample 81 -> 75, 128 samples 150 -> 116; 32 layers of 2048 tokens, one sample 978 -> 746; width 64, 256 tokens, 512 samples 79 -> 21, 1024 99 -> 37: faster at every
+// length and depth, and past two samples per CU by little at width 128.  As in tall_f32, the flow's largest batch decides.
 bool block_f32_ok(const sjd_flow *f) {
     const sjd_config &c = f->cfg;
     return fast_decode_f32_ok(f) && c.max_batch <= 2 * f->n_cus_device && seq_block_f32_ok(c.width, c.width / c.n_heads, c.mlp_ratio, c.n_layers);
