@@ -99,7 +99,7 @@ def parse():
 def main() -> int:
     args = parse()
     if args.gpus != 1:
-        print("bench.py: this build runs on exactly one GPU (samples are independent: more GPUs would each take a "
+        print("bench.py: runs on exactly one GPU (samples are independent: more GPUs would each take a "
               "slice of the batch); run with --gpus 1", file=sys.stderr)
         return 2
     import numpy as np

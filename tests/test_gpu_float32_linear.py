@@ -1,6 +1,6 @@
 """Float32 projections of whole-sequence passes through the conditioner, against the CPU oracle: row counts that give
 every tile size of the matrix kernel and its edges, token sizes that pad the head matrix, a width off the matrix kernel.
-Needs an MI355X.  Tolerance: 1e-4 (the float32 bound of this build; values are of order 0.1 to 1)."""
+Needs an MI355X.  Tolerance: 1e-4 (the float32 bound; values are of order 0.1 to 1)."""
 import numpy as np
 import pytest
 

@@ -1,6 +1,6 @@
 """HIP path against the CPU oracle, element by element, through the C boundary.  Needs an MI355X.
 
-Tolerances (the benchmark spec): float32 mode max |err| <= 1e-4 with identical per-sample
+Tolerances: float32 mode max |err| <= 1e-4 with identical per-sample
 pass counts in every block; bf16 mode max |err| <= 2e-2 on final samples.  A seed whose oracle
 delta at the deciding pass (or the one before) lies within 1 % of tau could legitimately stop one
 pass apart in the two implementations; such seeds are reported and skipped over, never compared
@@ -175,7 +175,7 @@ def test_bf16_conditioner_matches_oracle(torch_cuda, orc64, name, cfg, perturb, 
                 rmu, ral = rmu[::-1], ral[::-1]
             worst = max(worst, np.abs(mu[b] - rmu).max(), np.abs(al[b] - ral).max())
     print(f"{name} dtype {dtype}: worst conditioner error {worst:.3e}")
-    # One pass of the conditioner, not final samples: the bounds are this build's own, tighter than the 2e-2 that
+    # One pass of the conditioner, not final samples: the bounds are tighter than the 2e-2 that
     # the task states for samples, and sit a factor of two above what these cases measure (IEEE half <= 3.0e-4,
     # bf16 <= 2.3e-3: eight times coarser operands)
     assert worst <= (1e-3 if dtype == 2 else 5e-3)

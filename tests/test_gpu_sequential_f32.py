@@ -1,7 +1,7 @@
 """Single-token steps of float32 flows against the CPU oracle: every width whose LayerNorm is part of a projection and
 one whose is not, every head size of the attention kernel below and above the keys it walks at a time, row counts around
 the 16-row blocks, head columns that no tile divides; flows made for so many samples that the whole-sequence projections
-take the steps.  Needs an MI355X.  Tolerance: 1e-4 on the block's output (the float32 bound of this build)."""
+take the steps.  Needs an MI355X.  Tolerance: 1e-4 on the block's output (the float32 bound)."""
 import numpy as np
 import pytest
 

@@ -1,6 +1,6 @@
 """The two schedules of the sequential inverse in the 16-bit modes (per-step launches and the
 persistent kernel) against the CPU oracle and against each other, through the C boundary.
-Needs an MI355X.  Tolerance: 2e-2 on the block's output (the 16-bit bound of this build)."""
+Needs an MI355X.  Tolerance: 2e-2 on the block's output (the 16-bit bound)."""
 import numpy as np
 import pytest
 

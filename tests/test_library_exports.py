@@ -57,7 +57,7 @@ def test_product_never_touches_the_oracle():
 
 
 def test_bench_refuses_more_than_one_gpu_and_has_no_cpu_path():
-    """`bench.py --gpus N` with N > 1 exits with a message (this build runs on one GPU); without a
+    """`bench.py --gpus N` with N > 1 exits with a message (it runs on one GPU); without a
     GPU the benchmark says so and stops instead of falling back to anything."""
     import subprocess
     import sys
