@@ -10,10 +10,11 @@
 // What bounds it is the latency of a link: what one member writes all others need next.  There is no barrier: a
 // buffer is filled with a word that no result has (kEmpty, a NaN pattern) before it is used, and a reader simply
 // loads its operands again until no word of them is empty.  Every 32-bit word is its own flag, so the order in
-// which words arrive does not matter; stores and loads carry the sc1 scope bit (agent scope), which is coherent
-// between XCDs as well.  All-gather of 16 to 64 KB among 256 workgroups that way: 2.4 to 2.7 us, against a counter barrier
-// (0.9 to 2 us inside one XCD) followed by the loads (another 1 to 2 us); and as a group may span XCDs, few samples
-// still use the whole chip and the block's weights are read from memory once per group instead of once per XCD.
+// which words arrive does not matter.  A group of several XCDs stores and loads with the sc1 scope bit (agent scope), which is coherent
+// between XCDs: past the L2 of either side, to the memory behind it and back; a group of one XCD exchanges through its L2 (kLoadBits).  All-gather
+// of 2 to 64 KB, a round of a loop of nothing else: 2.2 to 2.8 us among 64 to 256 workgroups; among the 32 of one XCD 1.7 to 3.4 with the scope bit, 1.3
+// to 1.6 through the L2.  Microseconds a step, scope bit -> L2: width 256, 6 layers, 37 samples 77.7 -> 59.6; 4 layers, 128 samples 70.9 -> 45.6; width
+// 512, 4 layers, 128 samples 97.8 -> 80.2; width 768, 8 layers, 256 samples 421 -> 400.
 //
 // Life of a buffer.  Results rotate through three slots (the residual stream after the MLP and the embedding: four).
 // A member that has written slot q of a buffer empties what it had written in slot q-1 (stream: q-2), and every
@@ -50,7 +51,16 @@ typedef __amdgpu_buffer_rsrc_t rsrc_t;
 __device__ __forceinline__ rsrc_t make_rsrc(const void *p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
 }
-// 16-byte loads with the sc1 scope bit: never served by this CU's vector cache
+// Cache bits of the exchanged words (bit 1 nt, bit 4 sc1).  ONE: the group is one XCD and the words meet in its L2.  Plain stores go
+// through the vector cache to the L2.  A load with the nt bit misses the vector cache also where the line is there, and leaves no line behind (12.3
+// million loads of lines that the CU had loaded before another CU of the XCD stored to them: none stale after nt loads, nor with nt after plain
+// loads; plain and sc0 loads all stale), so each attempt of a wait reads the L2.  Else agent scope.
+template <bool ONE> constexpr int kLoadBits = ONE ? 2 : 16;
+template <bool ONE> constexpr int kStoreBits = ONE ? 0 : 16;
+template <bool ONE> __device__ __forceinline__ i32x4 ld16x(rsrc_t rs, uint32_t byte_off) {
+    return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, kLoadBits<ONE>));
+}
+// 16-byte loads of cached rows with the sc1 scope bit: never served by this CU's vector cache
 __device__ __forceinline__ i32x4 ld16(rsrc_t rs, uint32_t byte_off) {
     return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, 16));
 }
@@ -102,9 +112,9 @@ __device__ __forceinline__ int flagged(float v) {
     return (int)(w == kEmpty ? 0x7FC00000u : w);
 }
 __device__ __forceinline__ int flagged(int two_halves) { return two_halves == -1 ? 0x7FFF7FFF : two_halves; }
-__device__ __forceinline__ void st16(rsrc_t rs, uint32_t byte_off, i32x4 v) { __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)byte_off, 0, 16); }
-__device__ __forceinline__ void st8(rsrc_t rs, uint32_t byte_off, i32x2 v) { __builtin_amdgcn_raw_buffer_store_b64(v, rs, (int)byte_off, 0, 16); }
-__device__ __forceinline__ void st4(rsrc_t rs, uint32_t byte_off, int v) { __builtin_amdgcn_raw_buffer_store_b32(v, rs, (int)byte_off, 0, 16); }
+template <bool ONE> __device__ __forceinline__ void st16(rsrc_t rs, uint32_t byte_off, i32x4 v) { __builtin_amdgcn_raw_buffer_store_b128(v, rs, (int)byte_off, 0, kStoreBits<ONE>); }
+template <bool ONE> __device__ __forceinline__ void st8(rsrc_t rs, uint32_t byte_off, i32x2 v) { __builtin_amdgcn_raw_buffer_store_b64(v, rs, (int)byte_off, 0, kStoreBits<ONE>); }
+template <bool ONE> __device__ __forceinline__ void st4(rsrc_t rs, uint32_t byte_off, int v) { __builtin_amdgcn_raw_buffer_store_b32(v, rs, (int)byte_off, 0, kStoreBits<ONE>); }
 
 typedef __attribute__((address_space(3))) int LdsInt;   // LDS, not the generic address space: no flat accesses
 
@@ -136,13 +146,13 @@ __device__ __forceinline__ Ctx local_ctx(const Ctx &c) {
 // Load N pieces of 16 bytes until no word of them is empty.  Afterwards everything this wave has stored or requested so
 // far is complete (the wait is free: the operands requested before the poll are needed next).  Reloading only the pieces that
 // were missing, or pausing between attempts, was slower or made no difference.
-template <int N, class OFF>
+template <bool ONE, int N, class OFF>
 __device__ __forceinline__ void poll16(const Ctx &c, rsrc_t rs, OFF off, i32x4 (&v)[N]) {
     int it = 0;
     while (true) {
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int u = 0; u < N; ++u) v[u] = ld16(rs, off(u));
+        for (int u = 0; u < N; ++u) v[u] = ld16x<ONE>(rs, off(u));
         uint32_t m = 0;
 #pragma unroll
         for (int u = 0; u < N; ++u)
@@ -171,7 +181,7 @@ template <class AHEAD> __device__ __forceinline__ void idle_ahead(AHEAD ahead) {
 // matrix operand and rows the second, so a lane ends up with four consecutive columns of one row.
 // 16-bit results go to out_off (fragment-major; the member's part at empty_off is emptied); with LOCAL the float32
 // result goes to the workgroup's own buffer (row-major [16 MB][N], row 0 = the group's first row) and the member takes every block.
-template <typename HT, int MB, int S, int CB, int EPI, bool LOCAL, class AHEAD>
+template <typename HT, int MB, int S, int CB, int EPI, bool LOCAL, bool ONE, class AHEAD>
 __device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t ws, uint32_t in_off, const float *__restrict__ g,
                                               const float *__restrict__ be, const HT *__restrict__ Wt,
                                               const float *__restrict__ bias, uint32_t out_off, uint32_t empty_off,
@@ -220,7 +230,7 @@ __device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t ws, uint32
     fetch_bias(slot);
     __builtin_amdgcn_sched_barrier(0);
     i32x4 raw[MB * S * 2];
-    poll16(c, ws, [&](int u) {
+    poll16<ONE>(c, ws, [&](int u) {
         const int i = u / (2 * S), s = (u >> 1) % S;
         const uint32_t off = in_off + (uint32_t)((((c.rb0 + i) * KS + c.wave * S + s) * 64 + c.lane) * 8) * 4u + (u & 1) * 16u;
         return where(i * 16 + c.r < c.nrows, off);
@@ -311,8 +321,8 @@ __device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t ws, uint32
                 if (row < c.nrows) {
                     const i32x2 two = __builtin_bit_cast(i32x2, h);
                     const uint32_t eo = (uint32_t)frag_off(c.rb0 * 16 + row, col, N >> 5) * 2u;
-                    st8(ws, out_off + eo, i32x2{flagged(two.x), flagged(two.y)});
-                    st8(ws, empty_off + eo, i32x2{-1, -1});
+                    st8<ONE>(ws, out_off + eo, i32x2{flagged(two.x), flagged(two.y)});
+                    st8<ONE>(ws, empty_off + eo, i32x2{-1, -1});
                 }
             }
         }
@@ -323,7 +333,7 @@ __device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t ws, uint32
 // A (at a_off) 16-bit fragment-major, the streams float32 fragment-major.  A unit is cw columns: with many members a 16-column
 // block is shared out among two or four of them (the lanes of the other columns repeat theirs), so that every
 // member pulls an equal, small piece of the weights; unit u belongs to member u % n.
-template <typename HT, int MB, int S, int KMUL, class AHEAD>
+template <typename HT, int MB, int S, int KMUL, bool ONE, class AHEAD>
 __device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t ws, uint32_t a_off, const HT *__restrict__ Wt,
                                                  const float *__restrict__ bias, uint32_t in_off, uint32_t out_off,
                                                  uint32_t empty_off, f32x4v *red, AHEAD ahead) {
@@ -350,7 +360,7 @@ __device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t ws, uin
     fetch(c.slot);
     __builtin_amdgcn_sched_barrier(0);
     i32x4 raw[MB * KSW + 1];                    // the activation, and the stream values of the first unit
-    poll16(c, ws, [&](int u) {
+    poll16<ONE>(c, ws, [&](int u) {
         if (u == MB * KSW) return where(finish, in_off + eo);
         const int i = u / KSW, k = u % KSW;
         const uint32_t off = a_off + (uint32_t)((((c.rb0 + i) * KSA + c.wave * KSW + k) * 64 + c.lane) * 8) * 2u;
@@ -361,7 +371,7 @@ __device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t ws, uin
         if (u != c.slot) {
             __syncthreads();                    // the previous unit's partial sums have been read
             fetch(u);
-            poll16(c, ws, [&](int) { return where(finish, in_off + eo); }, rv);
+            poll16<ONE>(c, ws, [&](int) { return where(finish, in_off + eo); }, rv);
         }
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
@@ -379,8 +389,8 @@ __device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t ws, uin
             i32x4 out;
 #pragma unroll
             for (int v = 0; v < 4; ++v) out[v] = flagged((t[v] + bv[v]) + __int_as_float(rv[0][v]));
-            st16(ws, out_off + eo, out);
-            st16(ws, empty_off + eo, i32x4{-1, -1, -1, -1});
+            st16<ONE>(ws, out_off + eo, out);
+            st16<ONE>(ws, empty_off + eo, i32x4{-1, -1, -1, -1});
         }
     }
 }
@@ -439,7 +449,7 @@ __device__ __forceinline__ void kv_ahead(const Ctx &c_in, int part, const void *
     }
 }
 
-template <typename HT, int MB, int S, bool AHEAD>
+template <typename HT, int MB, int S, bool AHEAD, bool ONE>
 __device__ __forceinline__ void attention_stage(const Ctx &c_in, rsrc_t ws, uint32_t qkv_off, HT *kc, HT *vc, rsrc_t kc_rs,
                                                 rsrc_t vc_rs, uint32_t out_off, uint32_t empty_off, int t, int T,
                                                 float *opart, float2 *wst, int &par, const i32x4 *ahead) {
@@ -483,7 +493,7 @@ __device__ __forceinline__ void attention_stage(const Ctx &c_in, rsrc_t ws, uint
         const int row = pi / H, h = pi - row * H;
         const int wsrow = c.rb0 * 16 + row;
         i32x4 fresh[3];
-        poll16(c, ws, [&](int part) {
+        poll16<ONE>(c, ws, [&](int part) {
             return where(valid, qkv_off + (uint32_t)frag_off(wsrow, part * W + h * 64 + dc * 8, KS3) * 2u);
         }, fresh);
         const v8 q8 = __builtin_bit_cast(v8, fresh[0]), kf = __builtin_bit_cast(v8, fresh[1]), vf = __builtin_bit_cast(v8, fresh[2]);
@@ -571,14 +581,14 @@ __device__ __forceinline__ void attention_stage(const Ctx &c_in, rsrc_t ws, uint
             if ((stid & 1) == 0) {
                 const int two = __builtin_bit_cast(int, v2{from_f32<HT>(val), from_f32<HT>(other)});
                 const uint32_t eo = (uint32_t)frag_off(wsrow, h * 64 + stid, W / 32) * 2u;
-                st4(ws, out_off + eo, flagged(two));
-                st4(ws, empty_off + eo, -1);
+                st4<ONE>(ws, out_off + eo, flagged(two));
+                st4<ONE>(ws, empty_off + eo, -1);
             }
         }
     }
 }
 
-template <typename HT, int MB, int S, int CB, bool AHEAD>
+template <typename HT, int MB, int S, int CB, bool AHEAD, bool ONE>
 __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
     constexpr int W = 256 * S, RW_ROWS = 16 * MB, CBH = S <= 2 ? 2 : 4;
     constexpr int CBM = CB > CBH ? CB : CBH;
@@ -706,8 +716,8 @@ __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
                         for (int d = 0; d < D; ++d) acc = fmaf(xs[er * D + d], a.w_in[(size_t)d * W + col], acc);
                     }
                     const uint32_t eo = (uint32_t)frag_off(c.rb0 * 16 + er, col, W / 32) * 4u;
-                    st4(ws, off_h(hq) + eo, flagged(acc));
-                    st4(ws, off_h(hq + 2) + eo, -1);            // slot of use hq - 2
+                    st4<ONE>(ws, off_h(hq) + eo, flagged(acc));
+                    st4<ONE>(ws, off_h(hq + 2) + eo, -1);            // slot of use hq - 2
                     if (bi == 0 && l + 1 < T) pos0 = a.pos[(size_t)(l + 1) * W + col];
                 }
             }
@@ -732,19 +742,19 @@ __global__ __launch_bounds__(P_THREADS) void seq_persistent_kernel(SeqArgs a) {
                     }
                 };
             };
-            ln_gemm_stage<HT, MB, S, CB, EPI_BIAS, false>(c, ws, off_h(hq), lw.ln1_g, lw.ln1_b, (const HT *)lw.f_qkv, lw.b_qkv,
+            ln_gemm_stage<HT, MB, S, CB, EPI_BIAS, false, ONE>(c, ws, off_h(hq), lw.ln1_g, lw.ln1_b, (const HT *)lw.f_qkv, lw.b_qkv,
                                                                off_q(s3), off_q(e3), nullptr, 3 * W, red, stat, ahead(3));
-            attention_stage<HT, MB, S, AHEAD>(c, ws, off_q(s3), kc, vc, kc_rs, vc_rs, off_o(s3), off_o(e3), l, T, opart, wst, par, kv);
-            gemm_resid_stage<HT, MB, S, 1>(c, ws, off_o(s3), (const HT *)lw.f_o, lw.b_o, off_h(hq), off_a(s3), off_a(e3), red2, ahead(0));
-            ln_gemm_stage<HT, MB, S, CB, EPI_BIAS_GELU, false>(c, ws, off_a(s3), lw.ln2_g, lw.ln2_b, (const HT *)lw.f_fc1, lw.b_fc1,
+            attention_stage<HT, MB, S, AHEAD, ONE>(c, ws, off_q(s3), kc, vc, kc_rs, vc_rs, off_o(s3), off_o(e3), l, T, opart, wst, par, kv);
+            gemm_resid_stage<HT, MB, S, 1, ONE>(c, ws, off_o(s3), (const HT *)lw.f_o, lw.b_o, off_h(hq), off_a(s3), off_a(e3), red2, ahead(0));
+            ln_gemm_stage<HT, MB, S, CB, EPI_BIAS_GELU, false, ONE>(c, ws, off_a(s3), lw.ln2_g, lw.ln2_b, (const HT *)lw.f_fc1, lw.b_fc1,
                                                                     off_f(s3), off_f(e3), nullptr, 4 * W, red, stat, ahead(1));
-            gemm_resid_stage<HT, MB, S, 4>(c, ws, off_f(s3), (const HT *)lw.f_fc2, lw.b_fc2, off_a(s3), off_h(hq + 1), off_h(hq + 3), red2, ahead(2));
+            gemm_resid_stage<HT, MB, S, 4, ONE>(c, ws, off_f(s3), (const HT *)lw.f_fc2, lw.b_fc2, off_a(s3), off_h(hq + 1), off_h(hq + 3), red2, ahead(2));
             ++hq;
             s3 = s3 == 2 ? 0 : s3 + 1;
         }
         // ---- head: every member computes all of [mu | alpha] for the group's rows (a few column blocks)
         // into its own LDS, so that x_l and the next embedding follow without another exchange
-        ln_gemm_stage<HT, MB, S, CBH, EPI_BIAS, true>(c, ws, off_h(hq), a.lnf_g, a.lnf_b, (const HT *)a.f_head, a.b_head, 0, 0,
+        ln_gemm_stage<HT, MB, S, CBH, EPI_BIAS, true, ONE>(c, ws, off_h(hq), a.lnf_g, a.lnf_b, (const HT *)a.f_head, a.b_head, 0, 0,
                                                            pl, 2 * D, red, stat, []() {});
         ++hq;
         __syncthreads();
@@ -772,13 +782,19 @@ static size_t seq_lds_bytes(int MB, int D, bool ahead) {
 size_t seq_persistent_lds_bytes(int MB, int D) { return seq_lds_bytes(MB, D, MB == 1); }
 
 template <typename HT>
-static const void *pick_kernel(int MB, int S, int CB, bool ahead) {
-#define SJD_PK(MBv, Sv, CBv, AHv) if (MB == MBv && S == Sv && CB == CBv && ahead == AHv) return reinterpret_cast<const void *>(&seq_persistent_kernel<HT, MBv, Sv, CBv, AHv>);
-#define SJD_PS(Sv) SJD_PK(1, Sv, 1, false) SJD_PK(1, Sv, 2, false) SJD_PK(1, Sv, 4, false) SJD_PK(2, Sv, 4, false)
-#define SJD_PA(Sv) SJD_PK(1, Sv, 1, true) SJD_PK(1, Sv, 2, true) SJD_PK(1, Sv, 4, true)
-    SJD_PS(1) SJD_PS(2) SJD_PS(3) SJD_PS(4) SJD_PA(2) SJD_PA(3) SJD_PA(4)
-#undef SJD_PA
-#undef SJD_PS
+static const void *pick_kernel(int MB, int S, int CB, bool ahead, bool one) {
+#define SJD_PK(MBv, Sv, CBv, AHv, ONEv) if (MB == MBv && S == Sv && CB == CBv && ahead == AHv && one == ONEv) return reinterpret_cast<const void *>(&seq_persistent_kernel<HT, MBv, Sv, CBv, AHv, ONEv>);
+    // one XCD per group: a member has two column blocks of the MLP input or more
+#define SJD_ONE(Sv) SJD_PK(1, Sv, 4, false, true) SJD_PK(2, Sv, 4, false, true)
+#define SJD_ANY(Sv) SJD_PK(1, Sv, 1, false, false) SJD_PK(1, Sv, 2, false, false) SJD_PK(1, Sv, 4, false, false)
+    SJD_PK(1, 1, 2, false, true)
+    SJD_ONE(1) SJD_ONE(2) SJD_ONE(3) SJD_ONE(4) SJD_ANY(1) SJD_ANY(2) SJD_ANY(3) SJD_ANY(4)
+    SJD_PK(1, 2, 4, true, true) SJD_PK(1, 3, 4, true, true) SJD_PK(1, 4, 4, true, true)
+    SJD_PK(1, 2, 1, true, false) SJD_PK(1, 2, 2, true, false) SJD_PK(1, 2, 4, true, false)
+    SJD_PK(1, 3, 1, true, false) SJD_PK(1, 3, 2, true, false) SJD_PK(1, 3, 4, true, false)
+    SJD_PK(1, 4, 1, true, false) SJD_PK(1, 4, 2, true, false) SJD_PK(1, 4, 4, true, false)
+#undef SJD_ANY
+#undef SJD_ONE
 #undef SJD_PK
     return nullptr;
 }
@@ -788,9 +804,10 @@ hipError_t launch_seq_persistent(bool is_bf16, const SeqArgs &args, int MB, int 
     // column blocks of a LayerNorm-fused projection per round: as many as a member of a group has of the widest one
     const int members = grid / 8 * args.xpg, blocks = 64 * S;
     const int per = members > 0 ? (blocks + members - 1) / members : blocks;
-    const int CB = MB == 2 || per > 2 ? 4 : per;
+    const bool one = args.xpg == 1;
+    const int CB = MB == 2 || per > 2 ? 4 : one && per < 2 ? 2 : per;
     const bool ahead = args.kv_ahead != 0;
-    const void *kern = is_bf16 ? pick_kernel<bf16>(MB, S, CB, ahead) : pick_kernel<f16>(MB, S, CB, ahead);
+    const void *kern = is_bf16 ? pick_kernel<bf16>(MB, S, CB, ahead, one) : pick_kernel<f16>(MB, S, CB, ahead, one);
     if (!kern) return hipErrorInvalidValue;
     const size_t lds = seq_lds_bytes(MB, args.D, ahead);
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -45,14 +45,16 @@ SJD_HOST_DEVICE inline SeqGroup seq_group_of(const int (&count)[8], int xcc, int
 }
 
 // XCDs per group of the persistent kernel.  More of them spread a stage's weights over more CUs and read them from memory
-// fewer times, but exchanges between XCDs take longer (2.4 us against 1.5 to 2) and a group then has more rows to pass
-// round.  Microseconds a step with 8 / 4 / 2 / 1 XCDs per group: width 1024, 2 layers: one sample 43 / 46 / 50 / 73, 16 samples 54 / 52 / 61 /
-// 80, 64 samples - / - / 108 / 128; width 768, 2 layers, 32 samples - / 51 / 52 / 65; width 512, 4 layers: one sample 59 / 58 / 63 / 70, 16 samples
-// 78 / 73 / 70 / 73; width 256, 4 layers, 32 samples - / 70 / 62 / 57.  A group holds at most sixteen samples (one row block of the matrix
+// fewer times, but only a group of one XCD exchanges through its L2 (0.8 us an exchange against 1.6 to 2), and a larger group has more
+// rows to pass round.  Microseconds a step with 8 / 4 / 2 / 1 XCDs per group: width 512, 4 layers, 256 tokens: one sample 55.8 / 55.9 / 56.4 / 57.9, 4
+// samples 59.7 / 57.4 / 57.3 / 58.3, 16 66.5 / 64.2 / 62.4 / 59.3, 64 - / - / 77.2 / 63.1; 8 layers, 1024 tokens, 64 samples - / - / 213 / 193; width 256, 6
+// layers, 37 samples - / - / 92 / 60; width 768, 8 layers, one sample 117 / 118 / 139 / 187, 32 samples - / 151 / 170 / 201; width 1024, 8 layers: 19 samples of 777
+// tokens - / 214 / 244 / 310, 32 of 1024 - / 255 / 287 / 352; 2 layers, one sample 37 / 40 / 45 / 67: from width 768 on one XCD takes longer to pull all
+// weights through its L2 than the exchanges of several cost.  A group holds at most sixteen samples (one row block of the matrix
 // instruction) unless the batch leaves no choice.
 inline int seq_xcds_per_group(int W, int batch) {
-    int x = W <= 256 ? 1 : W <= 512 ? 2 : 4;
-    if (batch <= 4 && W > 256) x *= 2;
+    int x = W <= 512 ? 1 : 4;
+    if (batch <= 4 && W > 256) x = W <= 512 ? 4 : 8;
     while (x > 1 && (batch * x + 7) / 8 > 16) x /= 2;
     return x;
 }
