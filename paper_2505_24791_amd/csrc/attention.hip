@@ -503,7 +503,7 @@ constexpr int FB_BQ = 128, FB_BK = 64, FB_DH = 64;
 __device__ __forceinline__ int fb_kswz(int key) { return (key & 7) | (((key >> 4) & 1) << 3); }
 
 __global__ __launch_bounds__(256, 2) void flash_attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ o,
-                                                                  int T, int H, int n_pairs, float scale_log2) {
+                                                                  const float *__restrict__ sk, int T, int H, int n_pairs, float scale_log2) {
     __shared__ __attribute__((aligned(16))) float Ks[FB_BK * FB_DH];
     __shared__ __attribute__((aligned(16))) float Vs[FB_BK * FB_DH];
     const int W = H * FB_DH;
@@ -645,18 +645,20 @@ __global__ __launch_bounds__(256, 2) void flash_attention_f32_kernel(const float
                 f32x4 ov;
 #pragma unroll
                 for (int b = 0; b < 4; ++b) ov[b] = oacc[db][4 * a + b] * inv;
-                *reinterpret_cast<f32x4 *>(orow + 32 * db + 8 * a + 4 * g) = ov;
+                const int col = 32 * db + 8 * a + 4 * g;
+                if (sk) store_split4(orow, 0, col, W, ov, *reinterpret_cast<const f32x4 *>(sk + h * FB_DH + col));
+                else *reinterpret_cast<f32x4 *>(orow + col) = ov;
             }
     }
 }
 
-void launch_flash_attention_f32(const float *qkv, float *o, int n_samples, int T, int H, hipStream_t s) {
+void launch_flash_attention_f32(const float *qkv, float *o, const float *sk, int n_samples, int T, int H, hipStream_t s) {
     if (n_samples <= 0) return;
     const int n_qt = (T + FB_BQ - 1) / FB_BQ;
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)FB_DH);
     const int n_pairs = n_samples * H;
     const unsigned grid = (unsigned)((n_pairs + 7) / 8) * 8u * (unsigned)n_qt;
-    hipLaunchKernelGGL(flash_attention_f32_kernel, dim3(grid), dim3(256), 0, s, qkv, o, T, H, n_pairs, scale_log2);
+    hipLaunchKernelGGL(flash_attention_f32_kernel, dim3(grid), dim3(256), 0, s, qkv, o, sk, T, H, n_pairs, scale_log2);
 }
 
 

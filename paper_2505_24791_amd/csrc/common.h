@@ -140,6 +140,34 @@ __device__ __forceinline__ float gelu_erf_h16(float v) {
     return keep_f32(fmaf(-t, __builtin_amdgcn_exp2f(p), fmaxf(v, 0.f)));
 }
 
+// Split rows (gemm_split.hip): a row of W values, W % 16 == 0, takes the 4 W bytes of its float32 values; sixteen consecutive
+// values are 64 bytes, sixteen halves hi, then sixteen lo, value * s = hi + lo with a power of two s.
+__device__ __forceinline__ void store_split4(void *base, size_t row, int col, int W, f32x4 v, f32x4 s) {
+    f16x4 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float t = v[e] * s[e];
+        hi[e] = (f16)t;
+        lo[e] = (f16)(t - (float)hi[e]);
+    }
+    char *p = (char *)base + (row * W + (col & ~15)) * 4 + (col & 15) * 2;
+    *reinterpret_cast<f16x4 *>(p) = hi;
+    *reinterpret_cast<f16x4 *>(p + 32) = lo;
+}
+
+// eight columns, in 16-byte stores
+__device__ __forceinline__ void store_split8(void *base, size_t row, int col, int W, const float (&v)[8]) {   // values with their scales
+    f16x8 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        hi[e] = (f16)v[e];
+        lo[e] = (f16)(v[e] - (float)hi[e]);
+    }
+    char *p = (char *)base + (row * W + (col & ~15)) * 4 + (col & 15) * 2;
+    *reinterpret_cast<f16x8 *>(p) = hi;
+    *reinterpret_cast<f16x8 *>(p + 32) = lo;
+}
+
 // Row -> (sample, token) mapping shared by the embedding and the epilogues.  A whole-sequence pass
 // runs on `rows_per_sample = T` rows per active sample; a single-token step on one row per sample.
 struct RowMap {
@@ -170,6 +198,21 @@ void launch_layernorm(const float *x, const float *g, const float *b, OutT *y, i
 // float32 projection: C[M,N] = epi(A[M,K] * B[K,N] + bias), rows of B ldb floats apart; A and B 16-byte aligned
 void launch_gemm_f32(const float *A, const float *B, int ldb, const float *bias, const float *resid, float *C, int M, int N,
                      int K, Epi epi, hipStream_t s);
+
+// The same on split operands (gemm_split.hip), K % 32 == 0: A [M, K] split rows with the scales its producer was given (one
+// power of two per k), the weights as launch_split_weights leaves them.  EPI_BIAS and EPI_BIAS_RESIDUAL (C is the residual,
+// in place) give float32; EPI_BIAS_GELU gives split rows with the scales sk [N], N % 32 == 0.
+struct SplitW { const void *wt; const float *cs; };   // [N][K] split rows; [N] what takes the scales out of a sum again
+void launch_gemm_split(const void *A, const SplitW &w, const float *bias, const float *sk, float *C, int M, int N, int K, Epi epi,
+                       hipStream_t s);
+void launch_layernorm_split(const float *x, const float *g, const float *b, const float *sk, void *y, int n_rows, int W, hipStream_t s);
+void launch_split_rows(float *x, const float *sk, int rows, int W, hipStream_t s);   // float32 rows to split rows in place
+// Scales of LayerNorm's output, and of a projection of it ([K, N], rows ldw floats apart); weights with the scales sk of their k.  *bad is set where a
+// bound is not finite or above 2^60: the float32 instruction then.
+void launch_ln_scales(const float *g, const float *be, float *sk, int K, int32_t *bad, hipStream_t s);
+void launch_ln_projection_scales(const float *w, int ldw, const float *g, const float *be, const float *b, float *sk, int K, int N,
+                                 int32_t *bad, hipStream_t s);
+void launch_split_weights(const float *w, int ldw, const float *sk, void *Wt, float *cs, int K, int N, int32_t *bad, hipStream_t s);
 
 // 16-bit MFMA projection (HT = bf16 or f16): C[M,N] = epi(A[M,K] * Bt[N,K]^T + bias); Bt holds the
 // weight transposed, K contiguous, with at least round_up(N, 256) rows (zero filled).  K % 64 == 0.
@@ -235,7 +278,8 @@ void launch_decode_attention(const AT *qkv, AT *kcache, AT *vcache, AT *o, int B
 template <typename HT>
 void launch_flash_attention_h16(const HT *qkv, HT *o, int n_samples, int T, int H, hipStream_t s);
 // the same in float32 (float32 matrix instruction), head size 64
-void launch_flash_attention_f32(const float *qkv, float *o, int n_samples, int T, int H, hipStream_t s);
+// (sk: o as split rows with these scales)
+void launch_flash_attention_f32(const float *qkv, float *o, const float *sk, int n_samples, int T, int H, hipStream_t s);
 
 // Skinny 16-bit projection for single-token steps (M <= 256 rows, K % 32 == 0); same contract as
 // launch_gemm_h16.

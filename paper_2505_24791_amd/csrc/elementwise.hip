@@ -2,6 +2,7 @@
 // epilogue (affine update + difference reduction + convergence, Alg. 1), the sequential-step
 // epilogue (eq. 5 for one token), active-list compaction, and weight preparation.
 #include "common.h"
+#include <type_traits>
 
 namespace sjd {
 
@@ -89,10 +90,11 @@ void launch_embed(const float *x, const float *w_in, const float *b_in, const fl
 
 // ------------------------------------------------------------------------------------------------
 // LayerNorm: one wave per row, two-pass statistics in float32 (mean, then centred variance).
+struct split32 { float v; };   // OutT of split rows, with scales sk (store_split4)
 template <typename OutT>
 __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict__ x, const float *__restrict__ g,
-                                                        const float *__restrict__ b, OutT *__restrict__ y, int n_rows,
-                                                        int W) {
+                                                        const float *__restrict__ b, OutT *__restrict__ y, const float *__restrict__ sk,
+                                                        int n_rows, int W) {
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     if (row >= n_rows) return;
@@ -104,7 +106,18 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict_
     for (int i = lane; i < W; i += 64) { float d = xr[i] - mean; v = fmaf(d, d, v); }
     const float rstd = 1.0f / sqrtf(wave_sum(v) / (float)W + 1e-5f);
     OutT *yr = y + (size_t)row * W;
-    for (int i = lane; i < W; i += 64) yr[i] = from_f32<OutT>(keep_f32((xr[i] - mean) * rstd * g[i] + b[i]));
+    for (int i = lane; i < W; i += 64) {
+        const float o = keep_f32((xr[i] - mean) * rstd * g[i] + b[i]);
+        if constexpr (std::is_same<OutT, split32>::value) {
+            const float t = o * sk[i];
+            const f16 hi = (f16)t;
+            f16 *p = reinterpret_cast<f16 *>(yr + (i & ~15)) + (i & 15);
+            p[0] = hi;
+            p[16] = (f16)(t - (float)hi);
+        } else {
+            yr[i] = from_f32<OutT>(o);
+        }
+    }
 }
 
 // The same for widths that are multiples of 256: the row is read once, 16 bytes per lane and load,
@@ -112,7 +125,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict_
 template <typename OutT, int V>
 __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *__restrict__ x, const float *__restrict__ g,
                                                             const float *__restrict__ b, OutT *__restrict__ y,
-                                                            int n_rows) {
+                                                            const float *__restrict__ sk, int n_rows) {
     constexpr int W = 256 * V;
     const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
@@ -139,7 +152,9 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *__restr
         f32x4 o;
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[e] = keep_f32((v[k][e] - mean) * rstd * g4[e] + b4[e]);
-        if constexpr (sizeof(OutT) == 4) {
+        if constexpr (std::is_same<OutT, split32>::value) {
+            store_split4(yr, 0, (k * 64 + lane) * 4, W, o, reinterpret_cast<const f32x4 *>(sk)[k * 64 + lane]);
+        } else if constexpr (sizeof(OutT) == 4) {
             reinterpret_cast<f32x4 *>(yr)[k * 64 + lane] = o;
         } else {
             typename Half16<OutT>::v4 h4;
@@ -151,16 +166,23 @@ __global__ __launch_bounds__(256) void layernorm_vec_kernel(const float *__restr
 }
 
 template <typename OutT>
-void launch_layernorm(const float *x, const float *g, const float *b, OutT *y, int n_rows, int W, hipStream_t s) {
+static void launch_ln(const float *x, const float *g, const float *b, OutT *y, const float *sk, int n_rows, int W, hipStream_t s) {
     if (n_rows <= 0) return;
     const dim3 grid((n_rows + 3) / 4), block(256);
     switch (W) {
-    case 256: hipLaunchKernelGGL((layernorm_vec_kernel<OutT, 1>), grid, block, 0, s, x, g, b, y, n_rows); break;
-    case 512: hipLaunchKernelGGL((layernorm_vec_kernel<OutT, 2>), grid, block, 0, s, x, g, b, y, n_rows); break;
-    case 768: hipLaunchKernelGGL((layernorm_vec_kernel<OutT, 3>), grid, block, 0, s, x, g, b, y, n_rows); break;
-    case 1024: hipLaunchKernelGGL((layernorm_vec_kernel<OutT, 4>), grid, block, 0, s, x, g, b, y, n_rows); break;
-    default: hipLaunchKernelGGL(layernorm_kernel<OutT>, grid, block, 0, s, x, g, b, y, n_rows, W); break;
+    case 256: hipLaunchKernelGGL((layernorm_vec_kernel<OutT, 1>), grid, block, 0, s, x, g, b, y, sk, n_rows); break;
+    case 512: hipLaunchKernelGGL((layernorm_vec_kernel<OutT, 2>), grid, block, 0, s, x, g, b, y, sk, n_rows); break;
+    case 768: hipLaunchKernelGGL((layernorm_vec_kernel<OutT, 3>), grid, block, 0, s, x, g, b, y, sk, n_rows); break;
+    case 1024: hipLaunchKernelGGL((layernorm_vec_kernel<OutT, 4>), grid, block, 0, s, x, g, b, y, sk, n_rows); break;
+    default: hipLaunchKernelGGL(layernorm_kernel<OutT>, grid, block, 0, s, x, g, b, y, sk, n_rows, W); break;
     }
+}
+template <typename OutT>
+void launch_layernorm(const float *x, const float *g, const float *b, OutT *y, int n_rows, int W, hipStream_t s) {
+    launch_ln<OutT>(x, g, b, y, nullptr, n_rows, W, s);
+}
+void launch_layernorm_split(const float *x, const float *g, const float *b, const float *sk, void *y, int n_rows, int W, hipStream_t s) {
+    launch_ln<split32>(x, g, b, (split32 *)y, sk, n_rows, W, s);
 }
 template void launch_layernorm<float>(const float *, const float *, const float *, float *, int, int, hipStream_t);
 template void launch_layernorm<bf16>(const float *, const float *, const float *, bf16 *, int, int, hipStream_t);

@@ -45,11 +45,15 @@ struct LayerW {
     void *t_qkv, *t_o, *t_fc1, *t_fc2;             // 16-bit transposed [out (padded), in]
     void *f_qkv, *f_o, *f_fc1, *f_fc2;             // 16-bit fragment-major copies for single-token steps
     void *p_qkv = nullptr, *p_o = nullptr, *p_fc1 = nullptr, *p_fc2 = nullptr;   // 32x32x16 fragment order: panel / streaming kernels (W = 512), MLP input of large launches (p_fc1)
+    SplitW s_qkv{}, s_o{}, s_fc1{}, s_fc2{};       // split float32 copies (gemm_split.hip)
+    const float *k_ln1 = nullptr, *k_v = nullptr, *k_ln2 = nullptr, *k_f = nullptr;   // scales of their left operands
 };
 struct BlockW {
     const float *w_in, *b_in, *pos, *lnf_g, *lnf_b, *w_head, *b_head;
     const float *w_head4;        // w_head with rows padded to a multiple of four floats (w_head itself where they are)
     void *t_head, *f_head;
+    SplitW s_head{};
+    const float *k_lnf = nullptr;
     std::vector<LayerW> layer;
 };
 
@@ -71,6 +75,9 @@ struct sjd_flow {
     void *arena_frag = nullptr;  // the same matrices in fragment-major order (sequential fast path)
     void *arena_fc1 = nullptr;   // MLP-input matrices in the order of gemm_duo.hip (flows without arena_panel, which holds them too)
     void *arena_panel = nullptr; // QKV, attention-output and MLP-input matrices in the panel kernels' order
+    void *arena_split = nullptr; // float32 matrices as sums of two halves, and their scales
+    int32_t *split_bad = nullptr;
+    int split = 0;               // float32 passes on split operands: 0 not prepared, 1 yes, 2 no (a bound of the weights is not finite, no memory)
     int proj_path = 0;           // 0 automatic, 1 tile kernels only, 2 panel kernels wherever they apply
     bool stream_ok = false;      // the streaming MLP-output kernel reproduced the tile kernel's bits at load time
     std::vector<BlockW> block;
@@ -306,18 +313,19 @@ void project_panel_resid(sjd_flow *f, const void *A, const void *wf, const float
     else launch_gemm_panel_resid<f16>((const f16 *)A, (const f16 *)wf, bias, H, M, N, s);
 }
 
-// whole-sequence causal attention on the fused qkv buffer [n*T, 3W] -> o [n*T, W]
+// whole-sequence causal attention on the fused qkv buffer [n*T, 3W] -> o [n*T, W] (sk, float32 only: as split rows)
 template <typename AT>
-void attention_full(const void *qkv, void *o, int n, int T, int W, int H, int mask_o, hipStream_t s) {
+void attention_full(const void *qkv, void *o, int n, int T, int W, int H, int mask_o, hipStream_t s, const float *sk = nullptr) {
     const AT *q = (const AT *)qkv;
     if constexpr (sizeof(AT) == 2) {
         if (W / H == 64 && mask_o == 0) { launch_flash_attention_h16<AT>(q, (AT *)o, n, T, H, s); return; }
     } else {
-        if (W / H == 64 && mask_o == 0) { launch_flash_attention_f32(q, (float *)o, n, T, H, s); return; }
+        if (W / H == 64 && mask_o == 0) { launch_flash_attention_f32(q, (float *)o, sk, n, T, H, s); return; }
     }
     // the masked probe (a diagnostic) takes the row-wise kernel in every mode
     launch_attention_rows<AT, AT>(q, 3 * W, q + W, q + 2 * W, 3 * W, (int64_t)T * 3 * W, (AT *)o, W, n, T, 0, H, W / H,
                                   mask_o, s);
+    if (sk) launch_split_rows((float *)o, sk, n * T, W, s);
 }
 
 template <typename AT>
@@ -342,6 +350,95 @@ void project_short_f32(sjd_flow *f, int fam, const float *A, const float *g, con
     const double outs = epi == EPI_BIAS_RESIDUAL ? 2.0 : 1.0;
     ProfScope ps(f, fam, 2.0 * M * (double)N * K, 4.0 * ((double)M * K + (double)K * N + outs * M * N + N), s);
     launch_skinny_f32(A, g, be, w, bias, epi == EPI_BIAS_RESIDUAL ? C : nullptr, C, M, N, K, epi, s);
+}
+
+// Float32 passes on split operands: LayerNorm, attention and the MLP input leave theirs split.
+bool split_applicable(sjd_config c) {
+    c.dtype = SJD_DTYPE_F32;
+    return c.width % 32 == 0 && !short_f32(c);
+}
+
+int prepare_split(sjd_flow *f, hipStream_t s) {
+    const sjd_config &c = f->cfg;
+    f->split = 2;
+    if (!split_applicable(c)) return SJD_OK;
+    const size_t W = c.width, R = c.mlp_ratio, D2 = 2 * (size_t)c.token_dim, N = c.n_layers;
+    // floats: matrices, a scale per column, a scale per k of the left operands (LayerNorm's, all of QKV, the MLP's)
+    const size_t per_block = N * ((4 + 2 * R) * W * W + (4 + R + 1) * W + (2 + 3 + R) * W) + D2 * W + round_up(D2, 64) + W;
+    if (!f->arena_split) {
+        const size_t bytes = ((size_t)c.n_blocks * per_block + 64) * 4;
+        if (hipMalloc(&f->arena_split, bytes) != hipSuccess) {       // the float32 instruction needs no memory of its own
+            (void)hipGetLastError();
+            f->arena_split = nullptr;
+            return SJD_OK;
+        }
+        f->allocs.push_back(f->arena_split);
+        f->bytes += bytes;
+        f->split_bad = (int32_t *)f->arena_split + (size_t)c.n_blocks * per_block;
+    }
+    HIP_TRY(hipMemsetAsync(f->split_bad, 0, sizeof(int32_t), s));
+    float *p = (float *)f->arena_split;
+    auto take = [&](size_t n) { float *q = p; p += n; return q; };
+    auto split = [&](const float *w, size_t K, size_t Nn, const float *sk, size_t ldw) {
+        float *wt = take(K * Nn), *cs = take(round_up(Nn, 4));
+        launch_split_weights(w, (int)ldw, sk, wt, cs, (int)K, (int)Nn, f->split_bad, s);
+        return SplitW{wt, cs};
+    };
+    for (int j = 0; j < c.n_blocks; ++j) {
+        BlockW &bw = f->block[j];
+        p = (float *)f->arena_split + (size_t)j * per_block;
+        for (LayerW &lw : bw.layer) {
+            float *k_ln1 = take(W), *k_qkv = take(3 * W), *k_ln2 = take(W), *k_f = take(R * W);
+            launch_ln_scales(lw.ln1_g, lw.ln1_b, k_ln1, (int)W, f->split_bad, s);
+            launch_ln_scales(lw.ln2_g, lw.ln2_b, k_ln2, (int)W, f->split_bad, s);
+            // attention averages rows of v, and |gelu(x)| <= |x|
+            launch_ln_projection_scales(lw.w_qkv, (int)(3 * W), lw.ln1_g, lw.ln1_b, lw.b_qkv, k_qkv, (int)W, (int)(3 * W), f->split_bad, s);
+            launch_ln_projection_scales(lw.w_fc1, (int)(R * W), lw.ln2_g, lw.ln2_b, lw.b_fc1, k_f, (int)W, (int)(R * W), f->split_bad, s);
+            lw.k_ln1 = k_ln1; lw.k_v = k_qkv + 2 * W; lw.k_ln2 = k_ln2; lw.k_f = k_f;
+            lw.s_qkv = split(lw.w_qkv, W, 3 * W, k_ln1, 3 * W);
+            lw.s_o = split(lw.w_o, W, W, lw.k_v, W);
+            lw.s_fc1 = split(lw.w_fc1, W, R * W, k_ln2, R * W);
+            lw.s_fc2 = split(lw.w_fc2, R * W, W, k_f, W);
+        }
+        float *k_lnf = take(W);
+        launch_ln_scales(bw.lnf_g, bw.lnf_b, k_lnf, (int)W, f->split_bad, s);
+        bw.k_lnf = k_lnf;
+        bw.s_head = split(bw.w_head, W, D2, k_lnf, D2);
+    }
+    int32_t bad = 0;
+    HIP_TRY(hipMemcpyAsync(&bad, f->split_bad, sizeof(bad), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(hipGetLastError());
+    f->split = bad ? 2 : 1;
+    return SJD_OK;
+}
+
+void conditioner_layers_split(sjd_flow *f, const BlockW &bw, int n, hipStream_t s) {
+    const sjd_config &c = f->cfg;
+    const int T = c.seq_len, W = c.width, D = c.token_dim, H = c.n_heads, RW = c.mlp_ratio * c.width, M = n * T;
+    auto ln = [&](const float *g, const float *b, const float *sk) {
+        ProfScope ps(f, SJD_PROF_OTHER, 0.0, (double)M * W * 8.0, s);
+        launch_layernorm_split(f->h, g, b, sk, f->a, M, W, s);
+    };
+    auto proj = [&](int fam, const void *A, const SplitW &w, const float *bias, const float *sk, void *C, int N, int K, Epi epi) {
+        const double outs = epi == EPI_BIAS_RESIDUAL ? 2.0 : 1.0;
+        ProfScope ps(f, fam, 2.0 * M * (double)N * K, 4.0 * ((double)M * K + (double)K * N + outs * M * N + N), s);
+        launch_gemm_split(A, w, bias, sk, (float *)C, M, N, K, epi, s);
+    };
+    for (const LayerW &lw : bw.layer) {
+        ln(lw.ln1_g, lw.ln1_b, lw.k_ln1);
+        proj(SJD_PROF_GEMM, f->a, lw.s_qkv, lw.b_qkv, nullptr, f->qkv, 3 * W, W, EPI_BIAS);
+        {
+            ProfScope ps(f, SJD_PROF_ATTENTION, 2.0 * n * (double)T * (T + 1) * W, (double)M * 4 * W * 4.0, s);
+            attention_full<float>(f->qkv, f->o, n, T, W, H, f->mask_nearest, s, lw.k_v);
+        }
+        proj(SJD_PROF_GEMM_RESID, f->o, lw.s_o, lw.b_o, nullptr, f->h, W, W, EPI_BIAS_RESIDUAL);
+        ln(lw.ln2_g, lw.ln2_b, lw.k_ln2);
+        proj(SJD_PROF_GEMM_FC1, f->a, lw.s_fc1, lw.b_fc1, lw.k_f, f->f, RW, W, EPI_BIAS_GELU);
+        proj(SJD_PROF_GEMM_RESID, f->f, lw.s_fc2, lw.b_fc2, nullptr, f->h, W, RW, EPI_BIAS_RESIDUAL);
+    }
+    ln(bw.lnf_g, bw.lnf_b, bw.k_lnf);
+    proj(SJD_PROF_GEMM_HEAD, f->a, bw.s_head, bw.b_head, nullptr, f->p, 2 * D, W, EPI_BIAS);
 }
 
 // Whole-sequence conditioner pass on `n` samples listed in `active` (device, nullable = identity).
@@ -369,6 +466,7 @@ void conditioner_pass(sjd_flow *f, int j, const float *x, int n, const int32_t *
     const bool duo_fc1 = c.dtype != SJD_DTYPE_F32 && f->proj_path == 0 && bw.layer[0].p_fc1 && gemm_duo_applicable(M, RW, W);
     const bool stream_fc2 = panel_any && f->stream_ok && (f->proj_path == 2 || (M >= 10240 && panel_one_round)) && gemm_stream_applicable(M, W, RW);
     const bool few = short_f32(c);
+    if (c.dtype == SJD_DTYPE_F32 && f->split == 1) { conditioner_layers_split(f, bw, n, s); return; }
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerW &lw = bw.layer[l];
         if (few) project_short_f32(f, SJD_PROF_GEMM, f->h, lw.ln1_g, lw.ln1_b, lw.w_qkv, lw.b_qkv, (float *)f->qkv, M, 3 * W, W, EPI_BIAS, s);
@@ -472,7 +570,8 @@ int check_opts(const sjd_jacobi_opts *o) {
 // With `trace` every pass also records each sample's delta and (x_ref given) the l2 distance of its
 // newest iterate to x_ref into f->trace.
 // Float32 workspaces for refined passes of a 16-bit flow: about 8192 rows at a time.
-int ensure_refine_workspace(sjd_flow *f) {
+int ensure_refine_workspace(sjd_flow *f, hipStream_t s) {
+    if (f->split == 0) { const int rc = prepare_split(f, s); if (rc) return rc; }
     if (f->r32_samples) return SJD_OK;
     const sjd_config &c = f->cfg;
     int n = 8192 / c.seq_len;
@@ -514,7 +613,7 @@ int run_jacobi(sjd_flow *f, int j, const float *z, float *x, int batch, const sj
     // refinement: a sample marked fine (its delta fell below opts->refine_below) runs in float32 from then on;
     // the compaction puts those samples at the end of the list
     const float refine = c.dtype != SJD_DTYPE_F32 ? opts->refine_below : 0.f;
-    if (refine > 0.f) { int rc = ensure_refine_workspace(f); if (rc) return rc; }
+    if (refine > 0.f) { int rc = ensure_refine_workspace(f, s); if (rc) return rc; }
     int n_live = batch, n_listed = batch, n_fine = 0, passes = 0;
     while (n_live > 0 && passes < cap) {
         // Alg. 1 starts every sample from the same iterate, x^0 = 0, and the conditioner sees nothing else: the
@@ -1054,6 +1153,11 @@ int sjd_flow_load_weights(sjd_flow *f, const void *host_blob, size_t nbytes) {
     }
     HIP_TRY(hipDeviceSynchronize());
     HIP_TRY(hipGetLastError());
+    f->split = 0;
+    if (dt == SJD_DTYPE_F32) {
+        int rc = prepare_split(f, 0);
+        if (rc) return rc;
+    }
     f->stream_ok = false;
     if (f->arena_panel) {
         int rc = stream_self_check(f);
@@ -1347,7 +1451,7 @@ int sjd_op_attention_h16(int dtype, const void *qkv_dev, void *o_dev, int n_samp
     if (n_samples < 1 || T < 1 || T > 4096 || H < 1 || H > 65535 || n_samples > 65535)
         return fail(SJD_EINVAL, "need 1 <= n_samples, H <= 65535 and 1 <= T <= 4096");
     hipStream_t s = (hipStream_t)hip_stream;
-    if (dtype == SJD_DTYPE_F32) launch_flash_attention_f32((const float *)qkv_dev, (float *)o_dev, n_samples, T, H, s);
+    if (dtype == SJD_DTYPE_F32) launch_flash_attention_f32((const float *)qkv_dev, (float *)o_dev, nullptr, n_samples, T, H, s);
     else if (dtype == SJD_DTYPE_BF16) launch_flash_attention_h16<bf16>((const bf16 *)qkv_dev, (bf16 *)o_dev, n_samples, T, H, s);
     else launch_flash_attention_h16<f16>((const f16 *)qkv_dev, (f16 *)o_dev, n_samples, T, H, s);
     HIP_TRY(hipStreamSynchronize(s));

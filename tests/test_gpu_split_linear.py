@@ -1,0 +1,101 @@
+"""Float32 passes on split operands, where they can go wrong: tile edges of every size, widths whose LayerNorm and attention are the general
+kernels, weights of very different scales, weights whose bounds the scales do not cover.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+def _flow(cfg, blob):
+    import paper_2505_24791_amd as sjd
+    f = sjd.Flow(cfg)
+    f.load_weights(blob)
+    return f
+
+
+def _tensors(cfg, blob):
+    out, off = {}, 0
+    for name, shape in wl.block_tensors(cfg):
+        n = int(np.prod(shape))
+        out[name] = blob[off:off + n].reshape(shape)
+        off += n
+    return out
+
+
+# Every operand is hi + lo to 2^-23, a sum of K products then to about 2^-23 sqrt(K) of its terms' size, as with float32 products; two layers of
+# some six such roundings each, relative to the result: 4e-6 (seen: 1.1e-6 at eight layers).
+@pytest.mark.parametrize("W,H,T,D,B", [
+    (512, 8, 129, 12, 3),           # 387 rows: 64x64 tiles, the last of three rows
+    (96, 8, 50, 5, 50),             # heads of 12, LayerNorm of any width
+    (128, 4, 49, 16, 33),           # heads of 32
+    (256, 4, 225, 12, 37),          # 8325 rows
+    (512, 8, 256, 33, 32),          # 128x128 and 128x64 tiles
+    (768, 12, 193, 3, 5),
+], ids=lambda v: str(v))
+def test_split_conditioner_against_64_bits(orc64, W, H, T, D, B):
+    import torch
+    cfg = wl.FlowConfig("split", n_blocks=1, n_layers=2, width=W, n_heads=H, seq_len=T, token_dim=D, batch=B, bf16=False)
+    print(cfg, flush=True)
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    x = wl.make_latent(cfg, seed=31)
+    f = _flow(cfg, blob)
+    mu, al = f.conditioner(0, torch.from_numpy(x).cuda())
+    one = f.conditioner(0, torch.from_numpy(x[-1:].copy()).cuda())                    # same bits in any tile size
+    assert torch.equal(one[0][0], mu[-1]) and torch.equal(one[1][0], al[-1])
+    for b in (0, B - 1):
+        for got, ref in zip((mu, al), orc64.cond(cfg, blob, 0, x[b])):
+            err = np.linalg.norm(got[b].cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+            assert err <= 4e-6
+    f.close()
+
+
+def test_powers_of_two_in_the_weights_change_nothing():
+    """LayerNorm's gains and shifts, the values' columns and the hidden units times powers of two that the next matrix takes back:
+    the scales follow them, and the results are the same bits."""
+    import torch
+    cfg = wl.FlowConfig("split", n_blocks=1, n_layers=1, width=256, n_heads=4, seq_len=100, token_dim=6, batch=9, bf16=False)
+    print(cfg, flush=True)
+    W = cfg.width
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    x = torch.from_numpy(wl.make_latent(cfg, seed=37)).cuda()
+    rng = np.random.default_rng(5)
+    two = lambda n: np.ldexp(np.float32(1), rng.integers(-12, 13, n)).astype(np.float32)
+    scaled = blob.copy()
+    t = _tensors(cfg, scaled)
+    for ln, nxt in (("l0.ln1", "l0.w_qkv"), ("l0.ln2", "l0.w_fc1"), ("lnf", "w_head")):
+        p = two(W)
+        t[ln + "_g"] *= p
+        t[ln + "_b"] *= p
+        t[nxt] /= p[:, None]
+    p = two(W)
+    t["l0.w_qkv"][:, 2 * W:] *= p
+    t["l0.b_qkv"][2 * W:] *= p
+    t["l0.w_o"] /= p[:, None]
+    f, g = _flow(cfg, blob), _flow(cfg, scaled)
+    for a, b in zip(f.conditioner(0, x), g.conditioner(0, x)):
+        assert torch.equal(a, b)
+    f.close()
+    g.close()
+
+
+@pytest.mark.parametrize("huge", [1e19, np.inf])
+def test_bounds_out_of_range_keep_the_float32_instruction(orc32, huge):
+    """A value column of 1e19 (above 2^60) that the output projection drops again, and a hidden unit's bias of -inf, whose GELU is not a number."""
+    import torch
+    cfg = wl.FlowConfig("split", n_blocks=1, n_layers=1, width=256, n_heads=4, seq_len=60, token_dim=6, batch=16, bf16=False)
+    print(cfg, flush=True)
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    t = _tensors(cfg, blob)
+    if np.isinf(huge):
+        t["l0.b_fc1"][7] = -huge
+    else:
+        t["l0.b_qkv"][2 * cfg.width + 5] = huge
+        t["l0.w_o"][5] = 0
+    x = wl.make_latent(cfg, seed=41)
+    f = _flow(cfg, blob)
+    mu, al = f.conditioner(0, torch.from_numpy(x).cuda())
+    for got, ref in zip((mu, al), orc32.cond(cfg, blob, 0, x[3])):
+        np.testing.assert_allclose(got[3].cpu().numpy(), ref, rtol=0, atol=1e-4, equal_nan=True)
+    f.close()
