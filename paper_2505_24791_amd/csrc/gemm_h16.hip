@@ -375,26 +375,22 @@ __global__ __launch_bounds__(256, 1) void gemm_h16_dma_kernel(const HT *__restri
 }
 
 // ------------------------------------------------------------------------------------------------
-// Small tiles, k-tiles of 64 in a ring of ST LDS stages filled by LDS-direct loads up to ST - 1 k-tiles ahead.  For
+// Tiles of up to 128x128, k-tiles of 64 in a ring of ST LDS stages filled by LDS-direct loads up to ST - 1 k-tiles ahead.  For
 // launches that do not fill the chip (one sample's rows, the late passes of a block, narrow flows) time is the latency of one
-// workgroup walking k: many small tiles, every load far ahead of its use, fragments of the next k-tile read under
-// the matrix instructions of this one.  Layout and swizzle of a stage, and the order of k, are those of the
-// kernel above: same bits.
+// workgroup walking k: every load far ahead of its use, the fragments of half a k-tile read under the matrix instructions of the half before, and
+// the loads spread between those instructions: requested together after the barrier they hold the wave up until the address unit has
+// taken them (64 bytes a clock), and all of a k-tile's fragments at once took so many registers that two copies of the accumulators were
+// kept and moved.  us, before / with both: 256 x 512 x 2048 12.6 / 8.8, 256 x 1024 x 4096 21.8 / 13.7, 3000 x 768 x 3072 30.4 / 25.1, 8192 x 1024 x 4096
+// 94.9 / 85.9.  Layout and swizzle of a stage, and the order of k, are those of the kernel above: same bits.
 template <int N> __device__ __forceinline__ void wait_loads() {          // vmcnt(N) lgkmcnt(0)
     __builtin_amdgcn_s_waitcnt((N & 15) | 0x70 | ((N >> 4) << 14));
 }
-template <int LPW, int R> __device__ __forceinline__ void wait_tiles(int r) {   // until at most r <= R k-tiles are under way
-    if constexpr (R == 0) wait_loads<0>();
-    else if (r >= R) wait_loads<R * LPW>();
-    else wait_tiles<LPW, R - 1>(r);
-}
-
 template <typename HT, int BM, int BN, int ST, typename OutT, int EPI>
 __global__ __launch_bounds__(256) void gemm_h16_ring_kernel(const HT *__restrict__ A, const HT *__restrict__ Bt,
                                                             const float *__restrict__ bias, const float *resid, OutT *C,
                                                             int M, int N, int K, int tiles_n, int n_tiles) {
     typedef typename Half16<HT>::v8 v8;
-    constexpr int BK = 64, KSUB = BK / 16, MI = BM / 64, NI = BN / 64;
+    constexpr int BK = 64, MI = BM / 64, NI = BN / 64;
     constexpr int LA = BM / 32, LB = BN / 32, LPW = LA + LB;   // 1 KB loads (8 rows x 128 bytes) per wave and k-tile
     constexpr int STB = (BM + BN) * 128;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -432,25 +428,26 @@ __global__ __launch_bounds__(256) void gemm_h16_ring_kernel(const HT *__restrict
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                      :: "s"(lds_addr), "v"(off), "s"(base) : "memory");
     };
-    auto request = [&](int kt, int stage) {
+    // load q (0 .. LPW - 1) of this wave for k-tile kt; past the end the last k-tile again, into a stage that is not read any more
+    auto request1 = [&](int kt, int stage, int q) {
         const uint32_t st = lds0 + (uint32_t)(stage * STB);
-#pragma unroll
-        for (int i = 0; i < LA; ++i) dma(a_base + (size_t)kt * (BK * 2), a_off[i], st + (uint32_t)((wave * LA + i) * 1024));
-#pragma unroll
-        for (int i = 0; i < LB; ++i) dma(b_base + (size_t)kt * (BK * 2), b_off[i], st + (uint32_t)(BM * 128 + (wave * LB + i) * 1024));
+        const size_t k = (size_t)(kt < KT ? kt : KT - 1) * (BK * 2);
+        if (q < LA) dma(a_base + k, a_off[q < LA ? q : 0], st + (uint32_t)((wave * LA + q) * 1024));
+        else dma(b_base + k, b_off[q < LA ? 0 : q - LA], st + (uint32_t)(BM * 128 + (wave * LB + q - LA) * 1024));
     };
-    struct Frags { v8 a[KSUB][MI], b[KSUB][NI]; };
+    struct Frags { v8 a[2][MI], b[2][NI]; };                   // two k-steps of 16: half a k-tile
     const int swz = ((l32 >> 1) & 3) | (((l32 >> 4) & 1) << 2);
-    auto read = [&](int stage, Frags &f) {
+    auto read = [&](Frags &f, int stage, int half) {
         const unsigned char *st = smem_raw + stage * STB;
 #pragma unroll
-        for (int ks = 0; ks < KSUB; ++ks) {
-            const int o = l32 * 128 + (((2 * ks + g) ^ swz) << 4);
+        for (int ks = 0; ks < 2; ++ks) {
+            const int o = l32 * 128 + (((2 * (2 * half + ks) + g) ^ swz) << 4);
 #pragma unroll
             for (int i = 0; i < MI; ++i) f.a[ks][i] = *reinterpret_cast<const v8 *>(st + (wm * MI + i) * 4096 + o);
 #pragma unroll
             for (int j = 0; j < NI; ++j) f.b[ks][j] = *reinterpret_cast<const v8 *>(st + BM * 128 + (wn * NI + j) * 4096 + o);
         }
+        __builtin_amdgcn_sched_barrier(0);
     };
     f32x16 acc[MI][NI];
 #pragma unroll
@@ -459,39 +456,55 @@ __global__ __launch_bounds__(256) void gemm_h16_ring_kernel(const HT *__restrict
         for (int j = 0; j < NI; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    auto multiply = [&](const Frags &f) {
+    // The products of half a k-tile, and between them loads q0 .. of k-tile kt: requested in one go they hold the wave up until the
+    // address unit has taken them all.
+    constexpr int HALF = LPW / 2, NM = 2 * MI * NI;
+    auto multiply = [&](const Frags &f, int kt, int stage, int q0) {
+        int m = 0;
 #pragma unroll
-        for (int ks = 0; ks < KSUB; ++ks)
+        for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
             for (int i = 0; i < MI; ++i)
 #pragma unroll
-                for (int j = 0; j < NI; ++j) acc[i][j] = Half16<HT>::mfma(f.a[ks][i], f.b[ks][j], acc[i][j]);
-    };
-
-    Frags f0, f1;
+                for (int j = 0; j < NI; ++j) {
+                    acc[i][j] = Half16<HT>::mfma(f.a[ks][i], f.b[ks][j], acc[i][j]);
+                    const int lo = m * HALF / NM, hi = (m + 1) * HALF / NM;
+                    if (hi > lo) {
+                        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < ST; ++t)
-        if (t < KT) request(t, t);
-    wait_tiles<LPW, ST - 1>(KT - 1);          // the first k-tile has landed
-    __builtin_amdgcn_s_barrier();
-    read(0, f0);
-    // k-tile kt: its fragments are on their way into `cur`.  Wait for them and for this wave's loads of k-tile kt + 1, then the
-    // barrier: k-tile kt + 1 is complete and nobody reads the stage of kt any more, so kt + ST is requested into it.
-    int stage = 0;
-    auto step = [&](int kt, Frags &cur, Frags &nxt) {
-        const int ns = stage + 1 == ST ? 0 : stage + 1;
-        if (kt + 1 < KT) {
-            wait_tiles<LPW, ST - 2>(KT - 2 - kt);
-            __builtin_amdgcn_s_barrier();
-            read(ns, nxt);
-            if (kt + ST < KT) request(kt + ST, stage);
-        }
-        multiply(cur);
-        stage = ns;
+                        for (int q = 0; q < HALF; ++q)
+                            if (q >= lo && q < hi) request1(kt, stage, q0 + q);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    ++m;
+                }
+        __builtin_amdgcn_sched_barrier(0);
     };
-    for (int kt = 0; kt < KT; kt += 2) {
-        step(kt, f0, f1);
-        if (kt + 1 < KT) step(kt + 1, f1, f0);
+    // this wave's part of the next k-tile has landed (younger ones may be on their way) and its reads of this one are done; then everyone's, and
+    // nobody reads this k-tile's stage any more
+    auto next_tile = [&]() {
+        wait_loads<(ST - 2) * LPW>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+#pragma unroll
+    for (int t = 0; t < ST - 1; ++t)
+#pragma unroll
+        for (int q = 0; q < LPW; ++q) request1(t, t, q);
+    next_tile();
+#pragma unroll
+    for (int q = 0; q < HALF; ++q) request1(ST - 1, ST - 1, q);
+    Frags f0, f1;
+    read(f0, 0, 0);
+    int stage = 0, prev = ST - 1;
+    for (int kt = 0; kt < KT; ++kt) {
+        read(f1, stage, 1);
+        multiply(f0, kt + ST - 1, prev, HALF);
+        next_tile();
+        prev = stage;
+        stage = stage + 1 == ST ? 0 : stage + 1;
+        read(f0, stage, 0);
+        multiply(f1, kt + ST, prev, 0);
     }
     __builtin_amdgcn_s_waitcnt(0);            // all loads have landed and all reads are done before LDS is reused
     __syncthreads();
@@ -556,7 +569,7 @@ static void launch_tile(const HT *A, const HT *Bt, const float *bias, const floa
 //     (GELU: 648 vs 606; float32 residual with K = 1024: 610 vs 578) and for K <= 768;
 //   256x256x32 LDS-direct, one workgroup per CU: best main loop (K = 4096: 1025 vs 820) - used when
 //     the k-loop dominates.
-//   64x64 and 64x128 rings, 128x128x64: launches that do not fill the chip (see below).  Weight matrices are padded to 256
+//   rings of 64x64 to 128x128 tiles: launches that do not fill the chip (see below).  Weight matrices are padded to 256
 //   rows, so tiles never read past a matrix.
 template <typename HT, typename OutT, int EPI>
 static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float *resid, OutT *C, int M, int N, int K,
@@ -574,28 +587,32 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
     if (kernel == 4 && p8_ok) return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
     const long t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
-    const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64), t64x128 = (long)((M + 63) / 64) * ((N + 127) / 128);
+    const long t64 = (long)((M + 63) / 64) * ((N + 63) / 64);
     constexpr long kCus = 256;
-    // Up to two 128x128 tiles per CU the finer grain wins; beyond that the persistent kernel, if it has a tile for every CU or is
-    // through in one round.  It deals whole row panels to the XCDs, so with fewer tiles than CUs some XCDs may still have more
-    // than their CUs take at once, and the second round costs as much as the first.  Microseconds as 128x128 tiles / persistent, one round:
-    // 8690 x 1024 x 4096 118 / 84, 3321 x 3840 x 1280 56 / 39, 8690 x 1024 x 256 20.0 / 18.3; two: 5372 x 3072 x 768 45 / 51,
-    // 2053 x 5120 x 1280 50 / 68, 4576 x 3072 x 1024 48 / 50, 2829 x 4608 x 1536 70 / 69.
+    // Up to two 128x128 tiles per CU the finer grain wins (8192 x 1024 x 4096: 85.9 us against 94.9); beyond that the persistent kernel, if it has a
+    // tile for every CU or is through in one round.  It deals whole row panels to the XCDs, so with fewer tiles than CUs some XCDs may still have more
+    // than their CUs take at once, and the second round costs as much as the first.  Microseconds as 128x128 rings / persistent, one round:
+    // 4096 x 2304 x 768 27.9 / 22.7, 3400 x 3072 x 1024 39.2 / 34.9, 6000 x 2304 x 768 31.9 / 25.9, 10000 x 3072 x 1024 83 / 61; two: 5372 x 3072 x 768 40 / 51,
+    // 2053 x 5120 x 1280 43 / 68, 4576 x 3072 x 1024 40 / 50, 2829 x 4608 x 1536 56 / 69.
     if (p8_ok && (t256 >= kCus || (t128 > 2 * kCus && gemm_p8_one_round(M, N))))
         return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
-    if (t128 <= 2 * kCus && aligned) {
-        // 64x64 while its tiles fit two per CU (256 x 512 x 2048: 25.1 us as 128x128 tiles, 13.0 as these; 2048 x 1024 x 1024:
-        // 16.9, 10.6, as 64x128 12.1), then 64x128 up to three per CU (4096 x 1024 x 4096: 55.6 as 128x128, 49.1, as 64x64 57.9;
-        // 2048 x 4096 x 1024, four per CU: 30.0 against 37.0).  Four LDS stages of 16 KB, three of 24 KB: two workgroups per CU, worth
-        // more than deeper rings (64x64 with eight stages: 51 instead of 30.6 us at 2048 x 1024 x 4096).
-        if (t64 <= 2 * kCus) return launch_ring<HT, 64, 64, 4, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
-        // Not where its second round has nothing to hide behind (2000 x 2560 x 64: 7.1 us as 128x128 tiles, 7.9), and not where the
-        // rows under way on an XCD are few against a large weight: tiles of half the height read it twice as often, and it no longer
-        // stays in the XCD's L2 (128x128 / these: 1400 x 2560 x 2048 26.9 / 24.8, 851 x 4096 x 1024 18.7 / 17.9, 400 x 5120 x 512 10.9 / 10.3;
-        // 587 x 3840 x 1280 18.0 / 20.5, 512 x 5120 x 768 13.3 / 15.6, 962 x 6144 x 1536 36 / 49, 512 x 8192 x 1024 17 / 23).
-        const long nk = (long)N * K;
-        const bool weight_ok = N <= 2560 || nk <= (N <= 4096 ? 4l << 20 : 5l << 19);
-        if (t64x128 <= (K >= 256 ? 3 : 2) * kCus && weight_ok) return launch_ring<HT, 64, 128, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+    if (aligned) {
+        // The smallest tile of which no CU has more than one (64x64: or few have; as two of them share a CU, long k hides that): 64x64 with four
+        // stages of 16 KB, or five where they are at work for long enough, 128x64 with four of 24 KB, 128x128 with three of 32 KB, or four for long
+        // k; beyond one 128x128 tile to a CU two workgroups with two stages (us, register-staged 128x128 / this: 5372 x 3072 x 768 45 / 40, 2829 x 4608 x
+        // 1536 70 / 56, 5000 x 3072 x 1024 51 / 42).  A tile of half the size reads more of both operands and runs at a lower rate, but for short k,
+        // where its fill is what counts.  us as 64x64 / 128x64 / 128x128, M x N x K, the weight from memory as a pass finds it: 256 x 512 x 2048 8.3 / 10.9 / 16.0;
+        // 600 x 1024 x 4096 17.3 / 25.1 / 34.7; 1500 x 768 x 3072 17.4 / 21.2 / 30.0; 1500 x 1024 x 1024 9.6 / 9.0 / 11.9; 3000 x 512 x 2048 14.4 / 12.7 / 17.3; 3000 x 1024
+        // x 4096 46.8 / 39.4 / 34.5; 1500 x 2304 x 768 14.7 / 12.6 / 11.4; 8192 x 512 x 2048 33.1 / 27.0 / 24.0; 8192 x 1024 x 4096 118 / 91 / 76; short: 3000 x 768 x 256
+        // 6.9 / 6.0 / 6.5, 8192 x 512 x 512 13.8 / 12.2 / 12.2.
+        const long t128x64 = (long)((M + 127) / 128) * ((N + 63) / 64);
+        if (t64 <= (K >= 2048 ? 5 * kCus / 4 : kCus) && K >= 1024) return launch_ring<HT, 64, 64, 5, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+        if (t64 <= (K < 512 ? 2 : 1) * kCus) return launch_ring<HT, 64, 64, 4, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+        if (t128x64 <= kCus && K >= 512) return launch_ring<HT, 128, 64, 4, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+        if (t128x64 <= 2 * kCus && K <= 512) return launch_ring<HT, 128, 64, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+        if (t128 <= kCus && K >= 2048) return launch_ring<HT, 128, 128, 4, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+        if (t128 <= kCus) return launch_ring<HT, 128, 128, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+        if (t128 < 3584) return launch_ring<HT, 128, 128, 2, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
     }
     const bool deep = K >= 3072 || (EPI == EPI_BIAS && K >= 768 && N >= 768);
     if (deep && dma_ok && M >= 256 && N >= 256 && t256 >= 256) launch_dma<HT, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);

@@ -3,8 +3,8 @@
 //
 // A float32 value times a power of two that puts it below 2^15 is hi + lo to 2^-23 of itself (hi the value rounded to a half, lo
 // what is left, rounded too); below 2^-16 of the bound the error stays at 2^-40 of it.  A product is then lo hi + hi lo + hi hi, exact in
-// the instruction's float32 accumulator; what is left out, lo lo, is below 2^-22 of the product.  See split_scales() for the
-// powers of two: they come from the weights alone and bound every value that any input can produce, so nothing overflows.
+// the instruction's float32 accumulator; what is left out, lo lo, is below 2^-22 of the product.  The powers of two
+// (scale_of) come from the weights alone and bound every value that any input can produce, so nothing overflows.
 //
 // What bounds it: a tile's walk over k-tiles at small sizes, then the address unit (64 bytes a clock into LDS, half of a 128x64 tile's time) and the power limit of
 // the matrix pipe.  A conditioner, us, float32 instruction -> this: 4 layers of width 512, 4096 rows 1208 -> 668; 4 of width 768, 3000 rows 2354 -> 1457; 6 of width

@@ -215,3 +215,28 @@ def test_attention_input_off_16_byte_boundaries(torch_cuda, T):
     qkv = torch.randn((2 * T, 3 * 128), generator=torch.Generator().manual_seed(T)).half().cuda()
     ref = sjd.op_attention_h16(qkv, 2, T, 2)
     assert torch.equal(sjd.op_attention_h16(_moved(torch, qkv, 4), 2, T, 2), ref)
+
+
+@pytest.mark.parametrize("M,N,K", [
+    (1, 10, 64), (130, 200, 192), (2100, 960, 256),        # 64x64, four stages: fewer k-tiles than stages, an odd number, two tiles to a CU
+    (33, 64, 1024), (1217, 960, 2112),                     # 64x64, five stages, more tiles than CUs
+    (1400, 768, 768), (1345, 1000, 576),                   # 128x64, four stages
+    (5000, 520, 64), (2945, 770, 512),                     # 128x64, three stages
+    (1500, 2300, 768), (1409, 2817, 1088),                 # 128x128, three stages
+    (2945, 770, 2048),                                     # 128x128, four stages
+    (4576, 3072, 1024), (2829, 4600, 128),                 # 128x128, two stages, more than two tiles to a CU
+])
+@pytest.mark.parametrize("dtype_name", ["float16", "bfloat16"])
+def test_every_ring_gives_the_tile_kernels_bits(torch_cuda, M, N, K, dtype_name):
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    print(M, N, K, dtype_name, flush=True)
+    a, _, wt, bias = _operands(torch, M, N, K, getattr(torch, dtype_name), seed=83)
+    ad, wd, bd = a.cuda(), wt.cuda(), bias.cuda()
+    for epi in (0, 1):
+        assert torch.equal(sjd.op_linear_h16(ad, wd, bd, M, N, K, epi), sjd.op_linear_h16(ad, wd, bd, M, N, K, epi, kernel=3))
+    r = torch.from_numpy(np.random.default_rng(7).standard_normal((M, N)).astype(np.float32)).cuda()
+    r0, r3 = r.clone(), r.clone()
+    sjd.op_linear_h16(ad, wd, bd, M, N, K, 2, resid=r0)
+    sjd.op_linear_h16(ad, wd, bd, M, N, K, 2, resid=r3, kernel=3)
+    assert torch.equal(r0, r3)
