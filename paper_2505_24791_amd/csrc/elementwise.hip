@@ -196,10 +196,59 @@ template void launch_layernorm<f16>(const float *, const float *, const float *,
 
 __device__ __forceinline__ float nan_max(float a, float d) { return (d > a || d != d) ? d : a; }
 
-__global__ __launch_bounds__(256) void jacobi_epilogue_kernel(const float *__restrict__ p, const float *__restrict__ z,
-                                                              float *__restrict__ x, JacobiState st, int T, int D,
-                                                              int reversed, float tau, int criterion, int cap,
-                                                              int shared_params, float refine_below) {
+// The flags of a sample, written by the workgroup that has its update and read by the last one of the pass, on whatever XCD it is: past the
+// caches of either.
+__device__ __forceinline__ int flag_load(const int32_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ void flag_set(int32_t *p) { __hip_atomic_store(p, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Rebuilds the list of samples that still iterate and counts them: first the samples that are not marked
+// fine, then the fine ones (their passes run in float32), each part in increasing order of the sample index.
+// With keep_all the list is left complete (finished samples go with the first part) and only the counts of
+// unfinished samples are produced.  One workgroup of 256 threads; list: the pass's samples.
+__device__ __forceinline__ void compact_active(const JacobiState &st, const int32_t *list, int n_listed, int keep_all) {
+    __shared__ int wave_keep[4], wave_live[4];
+    __shared__ int base_keep, base_live, base_fine;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (threadIdx.x == 0) { base_keep = 0; base_live = 0; base_fine = 0; }
+    __syncthreads();
+    for (int part = 0; part < 2; ++part) {
+        for (int start = 0; start < n_listed; start += 256) {
+            const int i = start + threadIdx.x;
+            int b = -1, live = 0, done = 0;
+            if (i < n_listed) {
+                b = list[i];
+                done = flag_load(&st.done[b]);
+                const int fine = !done && flag_load(&st.fine[b]);
+                live = !done && fine == part;
+            }
+            const int keep = live || (part == 0 && keep_all && i < n_listed && done);
+            const unsigned long long mk = __ballot(keep), ml = __ballot(live);
+            const int before = __popcll(mk & ((1ull << lane) - 1ull));
+            if (lane == 0) { wave_keep[wv] = __popcll(mk); wave_live[wv] = __popcll(ml); }
+            __syncthreads();
+            int off = base_keep;
+            for (int w = 0; w < wv; ++w) off += wave_keep[w];
+            if (keep) st.active_out[off + before] = b;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                const int lv = wave_live[0] + wave_live[1] + wave_live[2] + wave_live[3];
+                base_keep += wave_keep[0] + wave_keep[1] + wave_keep[2] + wave_keep[3];
+                base_live += lv;
+                if (part == 1) base_fine += lv;
+            }
+            __syncthreads();
+        }
+    }
+    // both counts in one word, straight to the host: it waits for the word
+    if (threadIdx.x == 0)
+        __hip_atomic_store(st.counts, (uint64_t)(uint32_t)base_live | ((uint64_t)(uint32_t)base_fine << 32), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// A sample's update: x <- z exp(alpha) + mu, its difference norm, and what follows from it.
+__device__ __forceinline__ void jacobi_update(const float *__restrict__ p, const float *__restrict__ z, float *__restrict__ x, const JacobiState &st,
+                                              int T, int D, int reversed, float tau, int criterion, int cap, int shared_params,
+                                              float refine_below) {
     __shared__ float part[4];
     const int i = blockIdx.x;
     const int b = st.active_in[i];
@@ -257,64 +306,39 @@ __global__ __launch_bounds__(256) void jacobi_epilogue_kernel(const float *__res
         st.iters[b] = it;
         st.delta[b] = delta;
         if (delta < tau || it >= cap) {
-            st.done[b] = 1;
+            flag_set(&st.done[b]);
             if (!(fabsf(delta) <= 3.0e38f)) *st.nonfinite = 1;
         }
-        if (delta < refine_below) st.fine[b] = 1;
+        if (delta < refine_below) flag_set(&st.fine[b]);
     }
 }
 
-// Rebuilds the list of samples that still iterate and counts them: first the samples that are not marked
-// fine, then the fine ones (their passes run in float32), each part in increasing order of the sample index.
-// With keep_all the list is left complete (finished samples go with the first part) and only the counts of
-// unfinished samples are produced.
-__global__ __launch_bounds__(256) void compact_active_kernel(JacobiState st, int n_listed, int keep_all) {
-    __shared__ int wave_keep[4], wave_live[4];
-    __shared__ int base_keep, base_live, base_fine;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    if (threadIdx.x == 0) { base_keep = 0; base_live = 0; base_fine = 0; }
-    __syncthreads();
-    for (int part = 0; part < 2; ++part) {
-        for (int start = 0; start < n_listed; start += 256) {
-            const int i = start + threadIdx.x;
-            int b = -1, live = 0;
-            if (i < n_listed) {
-                b = st.active_in[i];
-                const int alive = st.done[b] ? 0 : 1;
-                const int fine = alive && st.fine[b];
-                live = alive && fine == part;
-            }
-            const int keep = live || (part == 0 && keep_all && i < n_listed && st.done[b]);
-            const unsigned long long mk = __ballot(keep), ml = __ballot(live);
-            const int before = __popcll(mk & ((1ull << lane) - 1ull));
-            if (lane == 0) { wave_keep[wv] = __popcll(mk); wave_live[wv] = __popcll(ml); }
-            __syncthreads();
-            int off = base_keep;
-            for (int w = 0; w < wv; ++w) off += wave_keep[w];
-            if (keep) st.active_out[off + before] = b;
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                const int lv = wave_live[0] + wave_live[1] + wave_live[2] + wave_live[3];
-                base_keep += wave_keep[0] + wave_keep[1] + wave_keep[2] + wave_keep[3];
-                base_live += lv;
-                if (part == 1) base_fine += lv;
-            }
-            __syncthreads();
-        }
+// The last workgroup of a pass (of all its launches: n_listed samples together) rebuilds the list, so that no launch of its own and no copy stand
+// between a pass and the next one: a launch of one workgroup takes 4 us behind another, the copy of two counts 6, and the host's wait for
+// the stream 15.
+__global__ __launch_bounds__(256) void jacobi_epilogue_kernel(const float *__restrict__ p, const float *__restrict__ z,
+                                                              float *__restrict__ x, JacobiState st, int T, int D,
+                                                              int reversed, float tau, int criterion, int cap,
+                                                              int shared_params, float refine_below, const int32_t *list,
+                                                              int n_listed, int keep_all) {
+    __shared__ int last;
+    jacobi_update(p, z, x, st, T, D, reversed, tau, criterion, cap, shared_params, refine_below);
+    if (threadIdx.x == 0) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this sample's flags are where the last workgroup reads them
+        last = __hip_atomic_fetch_add(st.ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == (uint32_t)n_listed;
     }
-    if (threadIdx.x == 0) { st.n_active_out[0] = base_live; st.n_active_out[1] = base_fine; }
+    __syncthreads();
+    if (!last) return;
+    if (threadIdx.x == 0) *st.ticket = 0;
+    compact_active(st, list, n_listed, keep_all);
 }
 
 void launch_jacobi_update(const float *p, const float *z, float *x, JacobiState st, int n, int T, int D, int reversed,
-                          float tau, int criterion, int cap, int shared_params, float refine_below, hipStream_t s) {
+                          float tau, int criterion, int cap, int shared_params, float refine_below, const int32_t *list,
+                          int n_listed, int keep_all, hipStream_t s) {
     if (n <= 0) return;
     hipLaunchKernelGGL(jacobi_epilogue_kernel, dim3(n), dim3(256), 0, s, p, z, x, st, T, D, reversed, tau, criterion,
-                       cap, shared_params, refine_below);
-}
-
-void launch_jacobi_compact(JacobiState st, int n_listed, int keep_all, hipStream_t s) {
-    if (n_listed <= 0) return;
-    hipLaunchKernelGGL(compact_active_kernel, dim3(1), dim3(256), 0, s, st, n_listed, keep_all);
+                       cap, shared_params, refine_below, list, n_listed, keep_all);
 }
 
 __global__ __launch_bounds__(256) void jacobi_init_kernel(const float *__restrict__ z, float *__restrict__ x,
@@ -326,7 +350,7 @@ __global__ __launch_bounds__(256) void jacobi_init_kernel(const float *__restric
         for (int b = threadIdx.x; b < B; b += 256) {
             st.iters[b] = 0; st.done[b] = 0; st.fine[b] = 0; st.delta[b] = 0.f; st.active_in[b] = b; st.active_out[b] = b;
         }
-        if (threadIdx.x == 0) { st.n_active_out[0] = B; st.n_active_out[1] = 0; *st.nonfinite = 0; }
+        if (threadIdx.x == 0) { *st.ticket = 0; *st.nonfinite = 0; }
     }
 }
 

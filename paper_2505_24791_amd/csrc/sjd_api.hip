@@ -8,6 +8,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <chrono>
 #include <map>
 #include <mutex>
 #include <new>
@@ -93,7 +94,8 @@ struct sjd_flow {
     // on first use for r32_samples samples at a time
     void *r32_a = nullptr, *r32_qkv = nullptr, *r32_o = nullptr, *r32_f = nullptr;
     int r32_samples = 0;
-    int32_t *host_pin = nullptr;                // pinned: [0] n_active, [1] n_fine, [2] nonfinite, [3..] iters[B]
+    int32_t *host_pin = nullptr;                // pinned: [0] status of the persistent kernel, [2] nonfinite, [3..] iters[B]
+    uint64_t *host_counts = nullptr;            // pinned, written by the GPU: the counts of a Jacobi pass
     // sequential fast path: device step counter, ticket, capture stream, one graph per (block, batch)
     int32_t *t_dev = nullptr;
     uint32_t *ticket = nullptr;
@@ -597,6 +599,20 @@ void conditioner_pass_f32(sjd_flow *f, int j, const float *x, int n, const int32
     f->a = a; f->qkv = qkv; f->o = o; f->f = ff; f->arena_panel = panel;
 }
 
+// The counts of the pass just launched, from the word that its last workgroup stores.  Short passes are over soon, and waiting for the stream
+// instead costs 15 us of an idle GPU behind each; after a millisecond the stream is waited for, which also reports what went wrong.
+constexpr uint64_t kNoCounts = ~0ull;
+int wait_counts(sjd_flow *f, uint64_t *counts, hipStream_t s) {
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(1);
+    while ((*counts = __atomic_load_n(f->host_counts, __ATOMIC_ACQUIRE)) == kNoCounts && std::chrono::steady_clock::now() < until) {}
+    if (*counts != kNoCounts) return SJD_OK;
+    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(hipGetLastError());
+    *counts = __atomic_load_n(f->host_counts, __ATOMIC_ACQUIRE);
+    if (*counts == kNoCounts) return fail(SJD_EHIP, "a Jacobi pass ended without its counts");
+    return SJD_OK;
+}
+
 int run_jacobi(sjd_flow *f, int j, const float *z, float *x, int batch, const sjd_jacobi_opts *opts, int *passes_out,
                bool *nonfinite_out, hipStream_t s, bool trace = false, const float *x_ref = nullptr) {
     const sjd_config &c = f->cfg;
@@ -620,10 +636,12 @@ int run_jacobi(sjd_flow *f, int j, const float *z, float *x, int batch, const sj
         // parameters of the first pass are the same for all samples.  That pass therefore runs on the rows of one
         // sample (sample 0, still all zero) and its head output serves the whole batch - the same bits as running
         // it on every sample, since a row's result does not depend on which other rows are in the pass.
+        __atomic_store_n(f->host_counts, kNoCounts, __ATOMIC_RELEASE);   // the pass before has delivered its word
         const bool shared_first = passes == 0 && opts->init == 0 && n_listed > 1;
         auto update = [&](JacobiState part, int n, int shared) {
             ProfScope ps(f, SJD_PROF_EPILOGUE, 0.0, (double)n * T * D * 24.0, s);
-            launch_jacobi_update(f->p, z, x, part, n, T, D, rev, opts->tau, opts->criterion, cap, shared, refine, s);
+            launch_jacobi_update(f->p, z, x, part, n, T, D, rev, opts->tau, opts->criterion, cap, shared, refine, st.active_in, n_listed,
+                                 opts->drop_converged ? 0 : 1, s);
         };
         if (shared_first) {
             conditioner_pass(f, j, x, 1, nullptr, s);
@@ -642,23 +660,24 @@ int run_jacobi(sjd_flow *f, int j, const float *z, float *x, int batch, const sj
                 update(part, n, 0);
             }
         }
-        launch_jacobi_compact(st, n_listed, opts->drop_converged ? 0 : 1, s);
         if (trace)
             launch_jacobi_trace(x, x_ref, st, f->trace + (size_t)passes * batch,
                                 f->trace + ((size_t)T + passes) * batch, batch, T, D, s);
-        HIP_TRY(hipMemcpyAsync(f->host_pin, st.n_active_out, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        HIP_TRY(hipGetLastError());
-        n_live = f->host_pin[0];
-        n_fine = f->host_pin[1];
+        if (const hipError_t e = hipGetLastError(); e != hipSuccess) {
+            (void)hipStreamSynchronize(s);                            // what was launched may still store its word
+            return fail(SJD_EHIP, "a Jacobi pass could not be launched: %s", hipGetErrorString(e));
+        }
+        uint64_t counts = 0;
+        if (int rc = wait_counts(f, &counts, s)) return rc;
+        n_live = (int)(uint32_t)counts;
+        n_fine = (int)(counts >> 32);
         if (n_live < 0 || n_live > batch || n_fine < 0 || n_fine > n_live)
             return fail(SJD_EHIP, "active-sample counts %d, %d are out of range", n_live, n_fine);
         if (opts->drop_converged) n_listed = n_live;
         int32_t *t = st.active_in; st.active_in = st.active_out; st.active_out = t;
         ++passes;
     }
-    HIP_TRY(hipMemcpyAsync(f->host_pin + 2, st.nonfinite, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(f->host_pin + 3, st.iters, sizeof(int32_t) * batch, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(f->host_pin + 2, st.nonfinite, sizeof(int32_t) * (1 + (size_t)batch), hipMemcpyDeviceToHost, s));   // and the pass counts
     HIP_TRY(hipStreamSynchronize(s));
     *passes_out = passes;
     *nonfinite_out = f->host_pin[2] != 0;
@@ -1005,10 +1024,8 @@ int sjd_flow_create(const sjd_config *cfg, sjd_flow **out) {
     A((void **)&f->pp[0], M * D * 4);
     A((void **)&f->pp[1], M * D * 4);
     A((void **)&f->st.delta, B * 4);
-    A((void **)&f->st.iters, B * 4);
+    A((void **)&f->st.nonfinite, (B + 1) * 4);     // one copy takes both: the flag, then the pass counts
     A((void **)&f->st.done, B * 4);
-    A((void **)&f->st.nonfinite, 4);
-    A((void **)&f->st.n_active_out, 8);
     A((void **)&f->st.fine, B * 4);
     A((void **)&f->active[0], B * 4);
     A((void **)&f->active[1], B * 4);
@@ -1022,14 +1039,19 @@ int sjd_flow_create(const sjd_config *cfg, sjd_flow **out) {
             f->coop = prop.cooperativeLaunch;
         }
     }
-    f->st.ticket = nullptr;
     A((void **)&f->t_dev, 4);
-    A((void **)&f->ticket, 4);
-    if (rc == SJD_OK && hipMemset(f->ticket, 0, 4) != hipSuccess) rc = fail(SJD_EHIP, "hipMemset failed");
+    A((void **)&f->ticket, 8);                     // of the sequential steps, and of the Jacobi updates
+    if (rc == SJD_OK && hipMemset(f->ticket, 0, 8) != hipSuccess) rc = fail(SJD_EHIP, "hipMemset failed");
     if (rc == SJD_OK && hipStreamCreateWithFlags(&f->cap_stream, hipStreamNonBlocking) != hipSuccess)
         rc = fail(SJD_EHIP, "hipStreamCreate failed");
-    if (rc == SJD_OK && hipHostMalloc((void **)&f->host_pin, (B + 3) * sizeof(int32_t)) != hipSuccess)
+    if (rc == SJD_OK && (hipHostMalloc((void **)&f->host_pin, (B + 3) * sizeof(int32_t)) != hipSuccess ||
+                         hipHostMalloc((void **)&f->host_counts, 64, hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess ||
+                         hipHostGetDevicePointer((void **)&f->st.counts, f->host_counts, 0) != hipSuccess))
         rc = fail(SJD_ENOMEM, "pinned host allocation failed");
+    if (rc == SJD_OK) {
+        f->st.iters = f->st.nonfinite + 1;
+        f->st.ticket = f->ticket + 1;
+    }
     for (int i = 0; rc == SJD_OK && i <= c.n_blocks; ++i)
         if (hipEventCreate(&f->ev[i]) != hipSuccess) rc = fail(SJD_EHIP, "hipEventCreate failed");
     if (rc != SJD_OK) { sjd_flow_destroy(f); return rc; }
@@ -1044,6 +1066,7 @@ void sjd_flow_destroy(sjd_flow *f) {
     if (f->cap_stream) (void)hipStreamDestroy(f->cap_stream);
     for (void *p : f->allocs) (void)hipFree(p);
     if (f->host_pin) (void)hipHostFree(f->host_pin);
+    if (f->host_counts) (void)hipHostFree(f->host_counts);
     for (auto &e : f->ev) if (e) (void)hipEventDestroy(e);
     for (auto &sp : f->spans) { (void)hipEventDestroy(sp.a); (void)hipEventDestroy(sp.b); }
     for (auto &e : f->free_events) (void)hipEventDestroy(e);

@@ -289,3 +289,24 @@ def test_sample_stats_and_modes(torch_cuda, orc64):
                 assert st["block_iters"][j] == cfg.seq_len - 1 and np.all(iters[j] == cfg.seq_len - 1)
             assert st["block_ms"][j] > 0
     f.close()
+
+
+@pytest.mark.parametrize("drop", [1, 0])
+def test_lists_of_many_samples_and_several_launches(torch_cuda, drop):
+    """More samples than the compaction takes at once (256), a float32 part in two launches beside the half-precision one, samples that finish at
+    different passes: every sample ends as it does in a batch of its own, bit for bit."""
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    cfg = SMALL_H16.with_(n_blocks=1, n_layers=1, batch=601)
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    z = wl.make_latent(cfg) * np.linspace(0.02, 2.0, cfg.batch, dtype=np.float32)[:, None, None]
+    f = sjd.Flow(cfg)
+    f.load_weights(blob)
+    opts = sjd.JacobiOpts(tau=1e-4, refine_below=1e-3, drop_converged=drop)
+    x, it, passes = f.jacobi_inverse_block(0, _dev(torch, z), opts)[:3]
+    it = np.asarray(it)
+    assert passes == it.max() and len(np.unique(it)) >= 3
+    for pick in (slice(0, 1), slice(255, 258), slice(590, 601)):
+        xs, its, _ = f.jacobi_inverse_block(0, _dev(torch, z[pick]), opts)[:3]
+        assert torch.equal(xs, x[pick]) and np.array_equal(np.asarray(its), it[pick])
+    f.close()
