@@ -8,6 +8,7 @@
 //    MFMA; K and V tiles are staged in LDS, scores never leave registers (online softmax in float32), so
 //    there is no T x T buffer.
 //  * flash_attention_short_h16_kernel: the same for up to 256 tokens, all keys and values of a (sample, head) in LDS at once.
+//  * flash_attention_split_kernel: float32 attention on the half-precision instruction, operands as two halves (head size 64);
 //  * flash_attention_f32_kernel: the same in float32 on the float32 matrix instruction (float32 flows and
 //    the refined passes of 16-bit flows).
 #include "common.h"
@@ -503,7 +504,7 @@ constexpr int FB_BQ = 128, FB_BK = 64, FB_DH = 64;
 __device__ __forceinline__ int fb_kswz(int key) { return (key & 7) | (((key >> 4) & 1) << 3); }
 
 __global__ __launch_bounds__(256, 2) void flash_attention_f32_kernel(const float *__restrict__ qkv, float *__restrict__ o,
-                                                                  const float *__restrict__ sk, int T, int H, int n_pairs, float scale_log2) {
+                                                                  int T, int H, int n_pairs, float scale_log2) {
     __shared__ __attribute__((aligned(16))) float Ks[FB_BK * FB_DH];
     __shared__ __attribute__((aligned(16))) float Vs[FB_BK * FB_DH];
     const int W = H * FB_DH;
@@ -645,21 +646,194 @@ __global__ __launch_bounds__(256, 2) void flash_attention_f32_kernel(const float
                 f32x4 ov;
 #pragma unroll
                 for (int b = 0; b < 4; ++b) ov[b] = oacc[db][4 * a + b] * inv;
-                const int col = 32 * db + 8 * a + 4 * g;
-                if (sk) store_split4(orow, 0, col, W, ov, *reinterpret_cast<const f32x4 *>(sk + h * FB_DH + col));
-                else *reinterpret_cast<f32x4 *>(orow + col) = ov;
+                *reinterpret_cast<f32x4 *>(orow + 32 * db + 8 * a + 4 * g) = ov;
             }
     }
 }
 
-void launch_flash_attention_f32(const float *qkv, float *o, const float *sk, int n_samples, int T, int H, hipStream_t s) {
+void launch_flash_attention_f32(const float *qkv, float *o, int n_samples, int T, int H, hipStream_t s) {
     if (n_samples <= 0) return;
     const int n_qt = (T + FB_BQ - 1) / FB_BQ;
     const float scale_log2 = 1.4426950408889634f / sqrtf((float)FB_DH);
     const int n_pairs = n_samples * H;
     const unsigned grid = (unsigned)((n_pairs + 7) / 8) * 8u * (unsigned)n_qt;
-    hipLaunchKernelGGL(flash_attention_f32_kernel, dim3(grid), dim3(256), 0, s, qkv, o, sk, T, H, n_pairs, scale_log2);
+    hipLaunchKernelGGL(flash_attention_f32_kernel, dim3(grid), dim3(256), 0, s, qkv, o, T, H, n_pairs, scale_log2);
 }
 
+// ------------------------------------------------------------------------------------------------
+// The float32 attention on split rows (gemm_split.hip): queries, keys and values come as two halves each, hs[h] takes the scales of a head's queries and
+// keys out of a score, and a probability times 2^15 is split the same way.  Three products on the half-precision instruction (32 cycles each for
+// sixteen of d or keys) stand for eight on the float32 one (64 each for two).  The scheme is the 16-bit kernel's: S^T = K Q^T, O^T += V^T P^T, V
+// through the transposing LDS read; row sums, maximum and accumulators in float32.  The output keeps the scales of the values: it is
+// stored as split rows for the output projection, whose k they are.
+// A conditioner with the projections on split operands, us, float32 attention -> this: 4 layers of width 512, 16 x 256 tokens 668 -> 629; 4 of width 768, 3 x 1000 1457 ->
+// 1137; 6 of width 256, 37 x 225 986 -> 836; 3 of width 512, 1024 tokens 460 -> 347.  Its error against 64 bits is the same.  What bounds it: a wave's chain
+// of products, exponentials and the splitting of probabilities, two waves a SIMD.
+// LDS: keys [64][256 bytes] as they lie in memory, 16-byte chunk c of row `key` in slot c ^ fb_kswz(key); values as two planes, hi and lo, [64 keys][64 d], each as in
+// the 16-bit kernel.
+__global__ __launch_bounds__(256, 2) void flash_attention_split_kernel(const f16 *__restrict__ qkv, f16 *__restrict__ o, const float *__restrict__ hs,
+                                                                       int T, int H, int n_pairs, float scale_log2) {
+    __shared__ __attribute__((aligned(16))) f16 Ks[FB_BK * 2 * FB_DH];
+    __shared__ __attribute__((aligned(16))) f16 Vs[2][FB_BK * FB_DH];
+    const int W = H * FB_DH;
+    const int n_qt = (T + FB_BQ - 1) / FB_BQ;
+    const int slot = (int)blockIdx.x >> 3;         // the query tiles of one (sample, head) on one XCD
+    const int pair = (slot / n_qt) * 8 + ((int)blockIdx.x & 7);
+    if (pair >= n_pairs) return;
+    const int qt = n_qt - 1 - slot % n_qt;
+    const int h = pair % H, i = pair / H;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int l32 = lane & 31, g = lane >> 5;
+    const f16 *base = qkv + (size_t)i * T * 6 * W + h * 2 * FB_DH;   // rows of 6 W halves; a head: 128 of them
+    const int q0 = qt * FB_BQ + wave * 32;
+    const int qrow = q0 + l32;
+    const int qrow_c = qrow < T ? qrow : T - 1;
+    scale_log2 *= hs[h];
+
+    f16x8 qf[4][2];
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) qf[c][p] = *reinterpret_cast<const f16x8 *>(base + (size_t)qrow_c * 6 * W + 32 * c + 16 * p + 8 * g);
+    f32x16 oacc[2];
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) asm volatile("" :: "v"(qf[c][0]), "v"(qf[c][1]));   // in registers before the loop
+    int voff[2];
+    fa_voff(lane, voff);
+
+    const int last_row = min(qt * FB_BQ + FB_BQ - 1, T - 1);
+    const int n_kt = last_row / FB_BK + 1;
+    f16x8 kreg[4], vreg[4];
+    auto fetch_tile = [&](int kt_) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = tid + r * 256;
+            int krow = kt_ * FB_BK + (c >> 4);
+            krow = krow < T ? krow : T - 1;
+            const f16 *src = base + (size_t)krow * 6 * W + (c & 15) * 8;
+            kreg[r] = *reinterpret_cast<const f16x8 *>(src + 2 * W);
+            vreg[r] = *reinterpret_cast<const f16x8 *>(src + 4 * W);
+        }
+    };
+    fetch_tile(0);
+    for (int kt = 0; kt < n_kt; ++kt) {
+        const int key0 = kt * FB_BK;
+        __syncthreads();  // previous tile fully consumed
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int c = tid + r * 256;
+            const int key = c >> 4, ch = c & 15;   // chunk: sixteen of d (ch / 4), lo (ch / 2 % 2), eight of them (ch % 2)
+            *reinterpret_cast<f16x8 *>(&Ks[key * 2 * FB_DH + ((ch ^ fb_kswz(key)) << 3)]) = kreg[r];
+            *reinterpret_cast<f16x8 *>(&Vs[(ch >> 1) & 1][key * FB_DH + (((2 * (ch >> 2) + (ch & 1)) ^ (((key >> 1) & 1) << 2)) << 3)]) = vreg[r];
+        }
+        __syncthreads();
+        if (kt + 1 < n_kt) fetch_tile(kt + 1);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            const int kb0 = key0 + 32 * kb;
+            if (kb0 > q0 + 31) continue;           // entirely above this wave's rows
+            f32x16 sacc;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sacc[v] = 0.f;
+            const int key = 32 * kb + l32;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                f16x8 kf[2];
+#pragma unroll
+                for (int p = 0; p < 2; ++p) kf[p] = *reinterpret_cast<const f16x8 *>(&Ks[key * 2 * FB_DH + (((4 * c + 2 * p + g) ^ fb_kswz(key)) << 3)]);
+                sacc = Half16<f16>::mfma(kf[1], qf[c][0], sacc);
+                sacc = Half16<f16>::mfma(kf[0], qf[c][1], sacc);
+                sacc = Half16<f16>::mfma(kf[0], qf[c][0], sacc);
+            }
+            // register v is key kb0 + 8 (v/4) + 4 g + v%4, query qrow
+            float mx = -INFINITY;
+            if (kb0 + 31 > q0) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float sv = kb0 + 8 * (v >> 2) + 4 * g + (v & 3) <= qrow ? sacc[v] : -INFINITY;
+                    sacc[v] = sv;
+                    mx = fmaxf(mx, sv);
+                }
+            } else {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) mx = fmaxf(mx, sacc[v]);
+            }
+            { float lo, hi; wave_halves(mx, lo, hi); mx = fmaxf(lo, hi) * scale_log2; }
+            const float m_new = fmaxf(m_run, mx);
+            const float m_use = m_new == -INFINITY ? 0.f : m_new;   // rows past the end of the sequence stay finite
+            if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
+                const float corr = exp2f(m_run - m_use);
+                l_run *= corr;
+#pragma unroll
+                for (int db = 0; db < 2; ++db)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) oacc[db][v] *= corr;
+                m_run = m_new;
+            }
+            float psum = 0.f;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float pv = keep_f32(exp2f(fmaf(sacc[v], scale_log2, -m_use)) * 32768.f);
+                sacc[v] = pv;
+                psum += pv;
+            }
+            { float lo, hi; wave_halves(psum, lo, hi); l_run += lo + hi; }
+#pragma unroll
+            for (int c2 = 0; c2 < 2; ++c2) {
+                f16x8 pf[2];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const f16 hi = (f16)sacc[8 * c2 + e];
+                    pf[0][e] = hi;
+                    pf[1][e] = (f16)(sacc[8 * c2 + e] - (float)hi);
+                }
+#pragma unroll
+                for (int db = 0; db < 2; ++db) {
+                    f16x8 vf[2];
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        union { i16x4 r; f16x4 h; } lo, hi;
+                        const f16 *vp = &Vs[p][(32 * kb + 16 * c2) * FB_DH + voff[db]];
+                        lo.r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(vp));
+                        hi.r = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) i16x4 *)(vp + 8 * FB_DH));
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) { vf[p][e] = lo.h[e]; vf[p][4 + e] = hi.h[e]; }
+                    }
+                    oacc[db] = Half16<f16>::mfma(vf[1], pf[0], oacc[db]);
+                    oacc[db] = Half16<f16>::mfma(vf[0], pf[1], oacc[db]);
+                    oacc[db] = Half16<f16>::mfma(vf[0], pf[0], oacc[db]);
+                }
+            }
+        }
+    }
+    // O^T block db: register v is d = 32 db + 8 (v/4) + 4 g + v%4, query qrow
+    if (qrow < T) {
+        const float inv = 1.0f / l_run;
+        const f32x4 one = {1.f, 1.f, 1.f, 1.f};
+#pragma unroll
+        for (int db = 0; db < 2; ++db)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                f32x4 ov;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) ov[b] = oacc[db][4 * a + b] * inv;
+                store_split4(o, (size_t)i * T + qrow, h * FB_DH + 32 * db + 8 * a + 4 * g, W, ov, one);
+            }
+    }
+}
+
+void launch_flash_attention_split(const void *qkv, void *o, const float *hs, int n_samples, int T, int H, hipStream_t s) {
+    if (n_samples <= 0) return;
+    const int n_qt = (T + FB_BQ - 1) / FB_BQ;
+    const float scale_log2 = 1.4426950408889634f / sqrtf((float)FB_DH);
+    const int n_pairs = n_samples * H;
+    const unsigned grid = (unsigned)((n_pairs + 7) / 8) * 8u * (unsigned)n_qt;
+    hipLaunchKernelGGL(flash_attention_split_kernel, dim3(grid), dim3(256), 0, s, (const f16 *)qkv, (f16 *)o, hs, T, H, n_pairs, scale_log2);
+}
 
 }  // namespace sjd

@@ -146,7 +146,7 @@ __device__ __forceinline__ void store_split4(void *base, size_t row, int col, in
     f16x4 hi, lo;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        const float t = v[e] * s[e];
+        const float t = keep_f32(v[e] * s[e]);   // or hi may be rounded from the unrounded product, and lo be taken from another hi
         hi[e] = (f16)t;
         lo[e] = (f16)(t - (float)hi[e]);
     }
@@ -160,8 +160,9 @@ __device__ __forceinline__ void store_split8(void *base, size_t row, int col, in
     f16x8 hi, lo;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        hi[e] = (f16)v[e];
-        lo[e] = (f16)(v[e] - (float)hi[e]);
+        const float t = keep_f32(v[e]);
+        hi[e] = (f16)t;
+        lo[e] = (f16)(t - (float)hi[e]);
     }
     char *p = (char *)base + (row * W + (col & ~15)) * 4 + (col & 15) * 2;
     *reinterpret_cast<f16x8 *>(p) = hi;
@@ -200,8 +201,8 @@ void launch_gemm_f32(const float *A, const float *B, int ldb, const float *bias,
                      int K, Epi epi, hipStream_t s);
 
 // The same on split operands (gemm_split.hip), K % 32 == 0: A [M, K] split rows with the scales its producer was given (one
-// power of two per k), the weights as launch_split_weights leaves them.  EPI_BIAS and EPI_BIAS_RESIDUAL (C is the residual,
-// in place) give float32; EPI_BIAS_GELU gives split rows with the scales sk [N], N % 32 == 0.
+// power of two per k), the weights as launch_split_weights leaves them.  EPI_BIAS_RESIDUAL (C is the residual, in place) and EPI_BIAS
+// without sk give float32; EPI_BIAS_GELU and EPI_BIAS with sk give split rows with the scales sk [N], N % 32 == 0.
 struct SplitW { const void *wt; const float *cs; };   // [N][K] split rows; [N] what takes the scales out of a sum again
 void launch_gemm_split(const void *A, const SplitW &w, const float *bias, const float *sk, float *C, int M, int N, int K, Epi epi,
                        hipStream_t s);
@@ -212,6 +213,8 @@ void launch_split_rows(float *x, const float *sk, int rows, int W, hipStream_t s
 void launch_ln_scales(const float *g, const float *be, float *sk, int K, int32_t *bad, hipStream_t s);
 void launch_ln_projection_scales(const float *w, int ldw, const float *g, const float *be, const float *b, float *sk, int K, int N,
                                  int32_t *bad, hipStream_t s);
+// Heads of 64: the keys' scales (sk [3 W]) such that query times key has one scale 1 / hs[h] for all d of a head
+void launch_head_scales(float *sk, float *hs, int W, hipStream_t s);
 void launch_split_weights(const float *w, int ldw, const float *sk, void *Wt, float *cs, int K, int N, int32_t *bad, hipStream_t s);
 
 // 16-bit MFMA projection (HT = bf16 or f16): C[M,N] = epi(A[M,K] * Bt[N,K]^T + bias); Bt holds the
@@ -278,8 +281,9 @@ void launch_decode_attention(const AT *qkv, AT *kcache, AT *vcache, AT *o, int B
 template <typename HT>
 void launch_flash_attention_h16(const HT *qkv, HT *o, int n_samples, int T, int H, hipStream_t s);
 // the same in float32 (float32 matrix instruction), head size 64
-// (sk: o as split rows with these scales)
-void launch_flash_attention_f32(const float *qkv, float *o, const float *sk, int n_samples, int T, int H, hipStream_t s);
+void launch_flash_attention_f32(const float *qkv, float *o, int n_samples, int T, int H, hipStream_t s);
+// on split rows, in and out (attention.hip); hs [H] and the scales of the keys as launch_head_scales leaves them
+void launch_flash_attention_split(const void *qkv, void *o, const float *hs, int n_samples, int T, int H, hipStream_t s);
 
 // Skinny 16-bit projection for single-token steps (M <= 256 rows, K % 32 == 0); same contract as
 // launch_gemm_h16.

@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const float *__restrict_
     for (int i = lane; i < W; i += 64) {
         const float o = keep_f32((xr[i] - mean) * rstd * g[i] + b[i]);
         if constexpr (std::is_same<OutT, split32>::value) {
-            const float t = o * sk[i];
+            const float t = keep_f32(o * sk[i]);
             const f16 hi = (f16)t;
             f16 *p = reinterpret_cast<f16 *>(yr + (i & ~15)) + (i & 15);
             p[0] = hi;

@@ -256,8 +256,9 @@ void pick_gs(const void *A, const void *Wt, const float *cs, const float *bias, 
 }
 
 // ---- preparation of the weights -------------------------------------------------------------------
-// Largest exponent that a bound or a column may have: outside, the flow keeps to the float32 instruction
-constexpr int kMaxExp = 60;
+// The flow keeps to the float32 instruction above 2^60 (in scale_of); bounds below this share a scale, so that the product of two scales is a
+// float32 number
+constexpr int kMinExp = -40;
 
 // 2^(15 - e) with bound < 2^e; 1 where the bound is zero
 __device__ __forceinline__ float scale_of(float bound, int32_t *bad) {
@@ -265,7 +266,7 @@ __device__ __forceinline__ float scale_of(float bound, int32_t *bad) {
     if (bound == 0.f) return 1.f;
     int e;
     (void)frexpf(bound, &e);
-    if (e < -kMaxExp) e = -kMaxExp;
+    if (e < kMinExp) e = kMinExp;
     return ldexpf(1.f, 15 - e);
 }
 
@@ -300,6 +301,14 @@ __global__ __launch_bounds__(1024) void ln_projection_scales_kernel(const float 
     if (threadIdx.x < 64 && n < N) sk[n] = scale_of(1.02f * (sqrtf((float)K * q) + d + fabsf(b[n])), bad);
 }
 
+// A head's queries keep their scales; its keys get what makes the product of both the smallest that the 64 pairs of scales have
+__global__ __launch_bounds__(64) void head_scales_kernel(float *sk, float *hs, int W) {
+    const int c = blockIdx.x * 64 + threadIdx.x;
+    const float q = sk[c], both = -wave_max(-(q * sk[W + c]));
+    sk[W + c] = both / q;
+    if (threadIdx.x == 0) hs[blockIdx.x] = 1.f / both;
+}
+
 // Wt[n] = w[., n] / sk times the power of two that brings its largest value below 2^15; cs[n] the inverse of that power
 __global__ __launch_bounds__(1024) void split_weights_kernel(const float *__restrict__ w, int ldw, const float *__restrict__ sk,
                                                              f16 *__restrict__ Wt, float *__restrict__ cs, int K, int N, int32_t *bad) {
@@ -314,7 +323,7 @@ __global__ __launch_bounds__(1024) void split_weights_kernel(const float *__rest
         f16x8 hi, lo;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float t = value(k + e) * c;
+            const float t = keep_f32(value(k + e) * c);
             hi[e] = (f16)t;
             lo[e] = (f16)(t - (float)hi[e]);
         }
@@ -346,6 +355,9 @@ void launch_ln_projection_scales(const float *w, int ldw, const float *g, const 
                                  int32_t *bad, hipStream_t s) {
     hipLaunchKernelGGL(ln_projection_scales_kernel, dim3((N + 63) / 64), dim3(1024), 0, s, w, ldw, g, be, b, sk, K, N, bad);
 }
+void launch_head_scales(float *sk, float *hs, int W, hipStream_t s) {
+    hipLaunchKernelGGL(head_scales_kernel, dim3(W / 64), dim3(64), 0, s, sk, hs, W);
+}
 void launch_split_weights(const float *w, int ldw, const float *sk, void *Wt, float *cs, int K, int N, int32_t *bad, hipStream_t s) {
     hipLaunchKernelGGL(split_weights_kernel, dim3((N + 63) / 64), dim3(1024), 0, s, w, ldw, sk, (f16 *)Wt, cs, K, N, bad);
 }
@@ -357,7 +369,10 @@ void launch_split_rows(float *x, const float *sk, int rows, int W, hipStream_t s
 void launch_gemm_split(const void *A, const SplitW &w, const float *bias, const float *sk, float *C, int M, int N, int K, Epi epi, hipStream_t s) {
     if (M <= 0 || N <= 0) return;
     switch (epi) {
-    case EPI_BIAS: pick_gs<EPI_BIAS, false>(A, w.wt, w.cs, bias, nullptr, C, M, N, K, s); break;
+    case EPI_BIAS:
+        if (sk) pick_gs<EPI_BIAS, true>(A, w.wt, w.cs, bias, sk, C, M, N, K, s);
+        else pick_gs<EPI_BIAS, false>(A, w.wt, w.cs, bias, nullptr, C, M, N, K, s);
+        break;
     case EPI_BIAS_GELU: pick_gs<EPI_BIAS_GELU, true>(A, w.wt, w.cs, bias, sk, C, M, N, K, s); break;
     case EPI_BIAS_RESIDUAL: pick_gs<EPI_BIAS_RESIDUAL, false>(A, w.wt, w.cs, bias, nullptr, C, M, N, K, s); break;
     }

@@ -47,7 +47,7 @@ struct LayerW {
     void *f_qkv, *f_o, *f_fc1, *f_fc2;             // 16-bit fragment-major copies for single-token steps
     void *p_qkv = nullptr, *p_o = nullptr, *p_fc1 = nullptr, *p_fc2 = nullptr;   // 32x32x16 fragment order: panel / streaming kernels (W = 512), MLP input of large launches (p_fc1)
     SplitW s_qkv{}, s_o{}, s_fc1{}, s_fc2{};       // split float32 copies (gemm_split.hip)
-    const float *k_ln1 = nullptr, *k_v = nullptr, *k_ln2 = nullptr, *k_f = nullptr;   // scales of their left operands
+    const float *k_ln1 = nullptr, *k_qkv = nullptr, *k_v = nullptr, *hs = nullptr, *k_ln2 = nullptr, *k_f = nullptr;   // scales of their left operands (k_v) and of QKV; hs: of a head's scores
 };
 struct BlockW {
     const float *w_in, *b_in, *pos, *lnf_g, *lnf_b, *w_head, *b_head;
@@ -315,19 +315,18 @@ void project_panel_resid(sjd_flow *f, const void *A, const void *wf, const float
     else launch_gemm_panel_resid<f16>((const f16 *)A, (const f16 *)wf, bias, H, M, N, s);
 }
 
-// whole-sequence causal attention on the fused qkv buffer [n*T, 3W] -> o [n*T, W] (sk, float32 only: as split rows)
+// whole-sequence causal attention on the fused qkv buffer [n*T, 3W] -> o [n*T, W]
 template <typename AT>
-void attention_full(const void *qkv, void *o, int n, int T, int W, int H, int mask_o, hipStream_t s, const float *sk = nullptr) {
+void attention_full(const void *qkv, void *o, int n, int T, int W, int H, int mask_o, hipStream_t s) {
     const AT *q = (const AT *)qkv;
     if constexpr (sizeof(AT) == 2) {
         if (W / H == 64 && mask_o == 0) { launch_flash_attention_h16<AT>(q, (AT *)o, n, T, H, s); return; }
     } else {
-        if (W / H == 64 && mask_o == 0) { launch_flash_attention_f32(q, (float *)o, sk, n, T, H, s); return; }
+        if (W / H == 64 && mask_o == 0) { launch_flash_attention_f32(q, (float *)o, n, T, H, s); return; }
     }
     // the masked probe (a diagnostic) takes the row-wise kernel in every mode
     launch_attention_rows<AT, AT>(q, 3 * W, q + W, q + 2 * W, 3 * W, (int64_t)T * 3 * W, (AT *)o, W, n, T, 0, H, W / H,
                                   mask_o, s);
-    if (sk) launch_split_rows((float *)o, sk, n * T, W, s);
 }
 
 template <typename AT>
@@ -366,7 +365,7 @@ int prepare_split(sjd_flow *f, hipStream_t s) {
     if (!split_applicable(c)) return SJD_OK;
     const size_t W = c.width, R = c.mlp_ratio, D2 = 2 * (size_t)c.token_dim, N = c.n_layers;
     // floats: matrices, a scale per column, a scale per k of the left operands (LayerNorm's, all of QKV, the MLP's)
-    const size_t per_block = N * ((4 + 2 * R) * W * W + (4 + R + 1) * W + (2 + 3 + R) * W) + D2 * W + round_up(D2, 64) + W;
+    const size_t per_block = N * ((4 + 2 * R) * W * W + (4 + R + 1) * W + (2 + 3 + R) * W + W) + D2 * W + round_up(D2, 64) + W;
     if (!f->arena_split) {
         const size_t bytes = ((size_t)c.n_blocks * per_block + 64) * 4;
         if (hipMalloc(&f->arena_split, bytes) != hipSuccess) {       // the float32 instruction needs no memory of its own
@@ -396,6 +395,9 @@ int prepare_split(sjd_flow *f, hipStream_t s) {
             // attention averages rows of v, and |gelu(x)| <= |x|
             launch_ln_projection_scales(lw.w_qkv, (int)(3 * W), lw.ln1_g, lw.ln1_b, lw.b_qkv, k_qkv, (int)W, (int)(3 * W), f->split_bad, s);
             launch_ln_projection_scales(lw.w_fc1, (int)(R * W), lw.ln2_g, lw.ln2_b, lw.b_fc1, k_f, (int)W, (int)(R * W), f->split_bad, s);
+            float *hs = take(W);
+            if (W / c.n_heads == 64) launch_head_scales(k_qkv, hs, (int)W, s);
+            lw.k_qkv = k_qkv; lw.hs = hs;
             lw.k_ln1 = k_ln1; lw.k_v = k_qkv + 2 * W; lw.k_ln2 = k_ln2; lw.k_f = k_f;
             lw.s_qkv = split(lw.w_qkv, W, 3 * W, k_ln1, 3 * W);
             lw.s_o = split(lw.w_o, W, W, lw.k_v, W);
@@ -427,12 +429,17 @@ void conditioner_layers_split(sjd_flow *f, const BlockW &bw, int n, hipStream_t 
         ProfScope ps(f, fam, 2.0 * M * (double)N * K, 4.0 * ((double)M * K + (double)K * N + outs * M * N + N), s);
         launch_gemm_split(A, w, bias, sk, (float *)C, M, N, K, epi, s);
     };
+    const bool flash = W / H == 64 && f->mask_nearest == 0;
     for (const LayerW &lw : bw.layer) {
         ln(lw.ln1_g, lw.ln1_b, lw.k_ln1);
-        proj(SJD_PROF_GEMM, f->a, lw.s_qkv, lw.b_qkv, nullptr, f->qkv, 3 * W, W, EPI_BIAS);
+        proj(SJD_PROF_GEMM, f->a, lw.s_qkv, lw.b_qkv, flash ? lw.k_qkv : nullptr, f->qkv, 3 * W, W, EPI_BIAS);
         {
             ProfScope ps(f, SJD_PROF_ATTENTION, 2.0 * n * (double)T * (T + 1) * W, (double)M * 4 * W * 4.0, s);
-            attention_full<float>(f->qkv, f->o, n, T, W, H, f->mask_nearest, s, lw.k_v);
+            if (flash) launch_flash_attention_split(f->qkv, f->o, lw.hs, n, T, H, s);
+            else {
+                attention_full<float>(f->qkv, f->o, n, T, W, H, f->mask_nearest, s);
+                launch_split_rows((float *)f->o, lw.k_v, M, W, s);
+            }
         }
         proj(SJD_PROF_GEMM_RESID, f->o, lw.s_o, lw.b_o, nullptr, f->h, W, W, EPI_BIAS_RESIDUAL);
         ln(lw.ln2_g, lw.ln2_b, lw.k_ln2);
@@ -1474,7 +1481,7 @@ int sjd_op_attention_h16(int dtype, const void *qkv_dev, void *o_dev, int n_samp
     if (n_samples < 1 || T < 1 || T > 4096 || H < 1 || H > 65535 || n_samples > 65535)
         return fail(SJD_EINVAL, "need 1 <= n_samples, H <= 65535 and 1 <= T <= 4096");
     hipStream_t s = (hipStream_t)hip_stream;
-    if (dtype == SJD_DTYPE_F32) launch_flash_attention_f32((const float *)qkv_dev, (float *)o_dev, nullptr, n_samples, T, H, s);
+    if (dtype == SJD_DTYPE_F32) launch_flash_attention_f32((const float *)qkv_dev, (float *)o_dev, n_samples, T, H, s);
     else if (dtype == SJD_DTYPE_BF16) launch_flash_attention_h16<bf16>((const bf16 *)qkv_dev, (bf16 *)o_dev, n_samples, T, H, s);
     else launch_flash_attention_h16<f16>((const f16 *)qkv_dev, (f16 *)o_dev, n_samples, T, H, s);
     HIP_TRY(hipStreamSynchronize(s));

@@ -33,6 +33,8 @@ def _tensors(cfg, blob):
     (256, 4, 225, 12, 37),          # 8325 rows
     (512, 8, 256, 33, 32),          # 128x128 and 128x64 tiles
     (768, 12, 193, 3, 5),
+    (256, 4, 2, 12, 450),           # attention over two tokens, and over a last query tile of one row
+    (256, 4, 769, 7, 2),
 ], ids=lambda v: str(v))
 def test_split_conditioner_against_64_bits(orc64, W, H, T, D, B):
     import torch
@@ -52,7 +54,7 @@ def test_split_conditioner_against_64_bits(orc64, W, H, T, D, B):
 
 
 def test_powers_of_two_in_the_weights_change_nothing():
-    """LayerNorm's gains and shifts, the values' columns and the hidden units times powers of two that the next matrix takes back:
+    """LayerNorm's gains and shifts, the queries', the keys' and the values' columns times powers of two that the next matrix (or the keys) takes back:
     the scales follow them, and the results are the same bits."""
     import torch
     cfg = wl.FlowConfig("split", n_blocks=1, n_layers=1, width=256, n_heads=4, seq_len=100, token_dim=6, batch=9, bf16=False)
@@ -69,6 +71,11 @@ def test_powers_of_two_in_the_weights_change_nothing():
         t[ln + "_g"] *= p
         t[ln + "_b"] *= p
         t[nxt] /= p[:, None]
+    p = two(W)
+    t["l0.w_qkv"][:, :W] *= p
+    t["l0.b_qkv"][:W] *= p
+    t["l0.w_qkv"][:, W:2 * W] /= p
+    t["l0.b_qkv"][W:2 * W] /= p
     p = two(W)
     t["l0.w_qkv"][:, 2 * W:] *= p
     t["l0.b_qkv"][2 * W:] *= p
