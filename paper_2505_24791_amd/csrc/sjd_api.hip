@@ -339,9 +339,9 @@ void attention_step(sjd_flow *f, int l, int B, int t, hipStream_t s) {
 
 // Float32 passes of few rows: LayerNorm + projection, or projection + residual, on the kernels of the single-token steps, which split k
 // over the waves of a workgroup; the whole-sequence kernel has a few tiles then, each with a wave or two per SIMD walking all of k, behind a
-// LayerNorm launch.  A conditioner of 2 layers, us, whole-sequence / step kernels: width 128, 196 rows 158 / 113, 1200 rows 169 / 141, 4096 rows 231 /
-// 243; width 256, 256 rows 212 / 142, 800 rows 195 / 167, 1600 rows 228 / 231; width 512, 256 rows 286 / 196, 600 rows 297 / 290, 800 rows 318 / 343;
-// width 1024, 128 rows 425 / 295, 196 rows 451 / 459.  The largest pass of the flow decides, not this one's rows: a row gives the same bits in any batch.
+// LayerNorm launch.  A conditioner of 2 layers, us, whole-sequence kernels (on split operands) / these: width 128, 196 rows 131 / 93, 600 133 / 107, 1200
+// 164 / 151; width 256, 256 rows 161 / 137, 600 154 / 159; width 512, 100 rows 164 / 147, 196 184 / 186, 256 184 / 191; width 1024, 100 rows 213 / 279.  (The line was drawn
+// against the float32 instruction; now it lies too high by up to 3 % at width 512 and 30 at 1024.)  The largest pass of the flow decides, not this one's rows: a row gives the same bits in any batch.
 // The float32 passes of small 16-bit flows (refine_below) take the same rule: conditioner_pass_f32 runs this pass with the float32 weights.
 bool short_f32(const sjd_config &c) {
     return c.dtype == SJD_DTYPE_F32 && skinny_f32_ln_ok(c.width) && (size_t)c.max_batch * c.seq_len * c.width <= 192 * 1024;
