@@ -567,8 +567,8 @@ static void launch_tile(const HT *A, const HT *Bt, const float *bias, const floa
 //   256x128x32 staged through registers, two workgroups per CU: one workgroup's epilogue and barrier
 //     stalls hide behind the other's matrix instructions - best when the epilogue is a large share
 //     (GELU: 648 vs 606; float32 residual with K = 1024: 610 vs 578) and for K <= 768;
-//   256x256x32 LDS-direct, one workgroup per CU: best main loop (K = 4096: 1025 vs 820) - used when
-//     the k-loop dominates.
+//   256x256x32 LDS-direct, one workgroup per CU: best main loop (K = 4096: 1025 vs 820) - used where the k-loop dominates, the
+//     persistent kernel does not apply (N not a multiple of 256) and the last round of tiles is full enough (gemm_dma_before_ring).
 //   rings of 64x64 to 128x128 tiles: launches that do not fill the chip (see below).  Weight matrices are padded to 256
 //   rows, so tiles never read past a matrix.
 template <typename HT, typename OutT, int EPI>
@@ -596,6 +596,7 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
     // 2053 x 5120 x 1280 43 / 68, 4576 x 3072 x 1024 40 / 50, 2829 x 4608 x 1536 56 / 69.
     if (p8_ok && (t256 >= kCus || (t128 > 2 * kCus && gemm_p8_one_round(M, N))))
         return launch_gemm_p8<HT, OutT>(A, Bt, bias, C, M, N, K, (Epi)EPI, s);
+    const bool deep = K >= 3072 || (EPI == EPI_BIAS && K >= 768 && N >= 768);
     if (aligned) {
         // The smallest tile of which no CU has more than one (64x64: or few have; as two of them share a CU, long k hides that): 64x64 with four
         // stages of 16 KB, or five where they are at work for long enough, 128x64 with four of 24 KB, 128x128 with three of 32 KB, or four for long
@@ -612,10 +613,10 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
         if (t128x64 <= 2 * kCus && K <= 512) return launch_ring<HT, 128, 64, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
         if (t128 <= kCus && K >= 2048) return launch_ring<HT, 128, 128, 4, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
         if (t128 <= kCus) return launch_ring<HT, 128, 128, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
-        if (t128 < 3584) return launch_ring<HT, 128, 128, 2, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+        if (t128 < 3584 && !(deep && dma_ok && gemm_dma_before_ring(M, N, EPI == EPI_BIAS_GELU)))
+            return launch_ring<HT, 128, 128, 2, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
     }
-    const bool deep = K >= 3072 || (EPI == EPI_BIAS && K >= 768 && N >= 768);
-    if (deep && dma_ok && M >= 256 && N >= 256 && t256 >= 256) launch_dma<HT, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+    if (deep && dma_ok && M >= 256 && N >= 256 && t256 >= kCus) launch_dma<HT, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
     // measured: below ~3500 tiles of 128x128 the smaller tile wins (finer tail, shorter prologue per tile)
     else if (N >= 128 && M >= 256 && t128 >= 3584) launch_tile<HT, 256, 128, 32, 2, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
     else launch_tile<HT, 128, 128, 64, 1, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);

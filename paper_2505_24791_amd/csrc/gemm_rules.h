@@ -34,4 +34,20 @@ inline bool gemm_duo_applicable(int M, int N, int K) {
     return tiles_of_fullest_xcd(M, N, kDuoRows, kDuoCols) <= kCusPerXcd || !gemm_p8_one_round(M, N);
 }
 
+// Deep k-loops that the persistent kernel does not cover: one 256x256 tile to a CU (gemm_h16_dma_kernel) or two workgroups with 128x128
+// rings.  A full round of large tiles takes as long as 1.68 rounds of two small ones a CU (1.78 with GELU, which the ring's other workgroup hides):
+// 8192 x 2000 x 4096 117.3 us against 145.2, 8192 x 2000 x 1024 37.0 / 44.1, 32768 x 1000 x 4096 (two rounds) 244.7 / 306.7, its GELU 259 / 316.  A last
+// round that is partly empty takes half of one or more: 24000 x 600 x 4096 (1.1 rounds) 187.7 / 138.1, 24000 x 1000 x 4096 (1.5) 206.7 / 214.1, with GELU
+// 221.6 / 220.4, 24000 x 1100 x 4096 (1.8) 222.7 / 251.2, 12288 x 2688 x 896 (2.1) 87.5 / 77.1.  In a pass: MLP output of width 896, 32768 rows 240 / 273, of 960, 49152 rows
+// 378 / 463; QKV of 896, 16640 rows 100 / 111.
+inline bool gemm_dma_before_ring(int M, int N, bool gelu) {
+    const long long large = (((long long)M + 255) / 256) * (((long long)N + 255) / 256), small = (((long long)M + 127) / 128) * (((long long)N + 127) / 128);
+    if (M < 256 || N < 256 || large < kXcds * kCusPerXcd) return false;
+    auto rounds = [](double r, double started, double filled) {
+        const double whole = (double)(long long)r;
+        return whole + (r > whole ? started + filled * (r - whole) : 0.0);
+    };
+    return (gelu ? 1.78 : 1.68) * rounds(large / 256.0, 0.5, 0.45) < rounds(small / 512.0, 0.25, 0.75);
+}
+
 }  // namespace sjd

@@ -29,3 +29,15 @@ def test_launches_that_the_kernel_does_not_cover(launch_rules):
     assert launch_rules.duo(32768, 4096, 1024)
     for M, N, K in [(32768, 4096 + 128, 1024), (32768, 4096, 1024 + 64), (32768, 1024, 128), (32768, 1 << 20, 1024), (1, 4096, 1024)]:
         assert not launch_rules.duo(M, N, K), (M, N, K)
+
+
+def test_large_tiles_where_their_last_round_is_full(launch_rules):
+    """Deep k-loops with N not a multiple of 256: 256x256 tiles where they beat two 128x128 rings a CU (microseconds beside the rule)."""
+    dma = launch_rules.dma_before_ring
+    for m, n in ((8192, 2000), (32768, 1000), (24000, 2000), (24576, 1152), (8192, 3456), (12288, 3456), (32768, 896), (16640, 2688), (24000, 1100), (49152, 960)):
+        assert dma(m, n, 0), (m, n)
+    for m, n in ((24000, 600), (12288, 2688), (16640, 1000), (16640, 1100), (6000, 2688), (24576, 896)):
+        assert not dma(m, n, 0) and not dma(m, n, 1), (m, n)
+    assert dma(24000, 1000, 0) and not dma(24000, 1000, 1)         # one and a half rounds: GELU hides better beside the rings
+    assert not dma(255, 65536, 0) and not dma(65536, 255, 0) and not dma(4096, 3840, 0)
+    assert dma(4096, 4000, 0)                                       # one tile for every CU
