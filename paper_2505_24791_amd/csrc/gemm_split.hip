@@ -259,15 +259,24 @@ void pick_gs(const void *A, const void *Wt, const float *cs, const float *bias, 
 // The flow keeps to the float32 instruction above 2^60 (in scale_of); bounds below this share a scale, so that the product of two scales is a
 // float32 number
 constexpr int kMinExp = -40;
+// Scale of a channel that is zero for every input (a zero bound), above all others: it may stand beside any other scale, and where scales are
+// compared such a channel has no say.
+constexpr float kDead = 0x1p56f;
 
-// 2^(15 - e) with bound < 2^e; 1 where the bound is zero
+// 2^(15 - e) with bound < 2^e
 __device__ __forceinline__ float scale_of(float bound, int32_t *bad) {
     if (!(bound <= 0x1p60f)) { *bad = 1; return 1.f; }
-    if (bound == 0.f) return 1.f;
+    if (bound == 0.f) return kDead;
     int e;
     (void)frexpf(bound, &e);
     if (e < kMinExp) e = kMinExp;
     return ldexpf(1.f, 15 - e);
+}
+
+// |t| for a bound, t the product of a and b: zero only where one of them is
+__device__ __forceinline__ float some(float t, float a, float b) {
+    const float least = a != 0.f && b != 0.f ? 0x1p-120f : 0.f;
+    return fabsf(t) < least ? least : fabsf(t);          // what is not a number stays so
 }
 
 // A workgroup is 64 columns x 16 runs of k; what a column's runs found meets in LDS.
@@ -296,16 +305,20 @@ __global__ __launch_bounds__(1024) void ln_projection_scales_kernel(const float 
                                                                     float *__restrict__ sk, int K, int N, int32_t *bad) {
     __shared__ float part[16][64];
     const int n = blockIdx.x * 64 + (threadIdx.x & 63), nc = n < N ? n : N - 1;
-    const float q = over_k(K, part, true, [&](int k) { const float t = g[k] * w[(size_t)k * ldw + nc]; return t * t; });
-    const float d = over_k(K, part, true, [&](int k) { return fabsf(be[k] * w[(size_t)k * ldw + nc]); });
+    const float q = over_k(K, part, true, [&](int k) { const float v = w[(size_t)k * ldw + nc], t = g[k] * v; return some(t * t, g[k], v); });
+    const float d = over_k(K, part, true, [&](int k) { const float v = w[(size_t)k * ldw + nc]; return some(be[k] * v, be[k], v); });
     if (threadIdx.x < 64 && n < N) sk[n] = scale_of(1.02f * (sqrtf((float)K * q) + d + fabsf(b[n])), bad);
 }
 
-// A head's queries keep their scales; its keys get what makes the product of both the smallest that the 64 pairs of scales have
+// A head's queries keep their scales; its keys get what makes the product of both the smallest that the 64 pairs of scales have.  A pair with a
+// side that is zero adds nothing to a score: it keeps its scales.
 __global__ __launch_bounds__(64) void head_scales_kernel(float *sk, float *hs, int W) {
     const int c = blockIdx.x * 64 + threadIdx.x;
-    const float q = sk[c], both = -wave_max(-(q * sk[W + c]));
-    sk[W + c] = both / q;
+    const float q = sk[c], k = sk[W + c];
+    const bool live = q != kDead && k != kDead;
+    float both = -wave_max(live ? -(q * k) : -INFINITY);
+    if (both == INFINITY) both = 1.f;
+    if (live) sk[W + c] = both / q;
     if (threadIdx.x == 0) hs[blockIdx.x] = 1.f / both;
 }
 
@@ -314,7 +327,8 @@ __global__ __launch_bounds__(1024) void split_weights_kernel(const float *__rest
                                                              f16 *__restrict__ Wt, float *__restrict__ cs, int K, int N, int32_t *bad) {
     __shared__ float part[16][64];
     const int n = blockIdx.x * 64 + (threadIdx.x & 63), nc = n < N ? n : N - 1, r = threadIdx.x >> 6;
-    auto value = [&](int k) { return w[(size_t)k * ldw + nc] / sk[k]; };
+    // rows that only ever meet zeros count as zeros (where 0 times the weight is zero)
+    auto value = [&](int k) { const float v = w[(size_t)k * ldw + nc]; return sk[k] == kDead && fabsf(v) <= 0x1p120f ? 0.f : v / sk[k]; };
     float top = over_k(K, part, false, [&](int k) { const float t = fabsf(value(k)); return t <= 0x1p120f ? t : 0x1p120f; });
     const float c = scale_of(top, bad);
     if (n >= N) return;

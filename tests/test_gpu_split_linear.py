@@ -87,6 +87,53 @@ def test_powers_of_two_in_the_weights_change_nothing():
     g.close()
 
 
+# Channels that are zero for every input, among live ones whose queries are `spread` powers of two apart: the scales of the live ones are the smallest and
+# largest that a head has.  The values weigh so much that the attention's rounding is the result's; bound as above.
+@pytest.mark.parametrize("dead", ["query and key", "query", "key", "value", "hidden", "gain"])
+@pytest.mark.parametrize("std,spread", [(0.02, 0), (0.002, 0), (0.02, 12)])
+def test_dead_channels_take_no_bits_from_the_others(orc64, dead, std, spread):
+    import torch
+    cfg = wl.FlowConfig("split", n_blocks=1, n_layers=1, width=256, n_heads=4, seq_len=100, token_dim=6, batch=9, bf16=False)
+    print(cfg, dead, std, spread, flush=True)
+    W = cfg.width
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    x = wl.make_latent(cfg, seed=43)
+    t = _tensors(cfg, blob)
+    rng = np.random.default_rng(11)
+    for name in ("l0.w_qkv", "l0.w_fc1", "l0.b_qkv", "l0.b_fc1"):
+        t[name][...] *= np.float32(std / 0.02)
+    t["l0.w_qkv"][:, :W] *= np.float32(0.02 / std * 4)                     # scores of some size all the same
+    t["l0.w_o"][...] *= np.float32(0.02 / std * 50)
+    if spread:
+        p = np.ldexp(np.float32(1), -rng.integers(0, spread + 1, W)).astype(np.float32)
+        t["l0.w_qkv"][:, :W] *= p
+        t["l0.b_qkv"][:W] *= p
+    off = np.concatenate([h * 64 + rng.choice(64, 5, replace=False) for h in range(4)])
+    cols = {"query and key": [off, W + off], "query": [off], "key": [W + off], "value": [2 * W + off]}.get(dead, [])
+    for c in cols:
+        t["l0.w_qkv"][:, c] = 0
+        t["l0.b_qkv"][c] = 0
+    if dead == "hidden":
+        t["l0.w_fc1"][:, off] = 0
+        t["l0.b_fc1"][off] = 0
+        t["l0.w_fc1"][...] *= np.float32(2.0 ** -10)                       # the live ones' scales far above 1
+        t["l0.b_fc1"][...] *= np.float32(2.0 ** -10)
+        t["l0.w_fc2"][...] *= np.float32(2.0 ** 12)
+    if dead == "gain":
+        for ln, nxt in (("l0.ln1", "l0.w_qkv"), ("l0.ln2", "l0.w_fc1"), ("lnf", "w_head")):
+            for part in ("_g", "_b"):
+                t[ln + part][...] *= np.float32(2.0 ** -20)
+                t[ln + part][off] = 0
+            t[nxt][...] *= np.float32(2.0 ** 20)
+    f = _flow(cfg, blob)
+    mu, al = f.conditioner(0, torch.from_numpy(x).cuda())
+    for b in (0, 8):
+        for got, ref in zip((mu, al), orc64.cond(cfg, blob, 0, x[b])):
+            err = np.linalg.norm(got[b].cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+            assert err <= 4e-6
+    f.close()
+
+
 @pytest.mark.parametrize("huge", [1e19, np.inf])
 def test_bounds_out_of_range_keep_the_float32_instruction(orc32, huge):
     """A value column of 1e19 (above 2^60) that the output projection drops again, and a hidden unit's bias of -inf, whose GELU is not a number."""
