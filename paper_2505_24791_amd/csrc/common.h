@@ -209,7 +209,7 @@ void launch_gemm_split(const void *A, const SplitW &w, const float *bias, const 
 void launch_layernorm_split(const float *x, const float *g, const float *b, const float *sk, void *y, int n_rows, int W, hipStream_t s);
 void launch_split_rows(float *x, const float *sk, int rows, int W, hipStream_t s);   // float32 rows to split rows in place
 // Scales of LayerNorm's output, and of a projection of it ([K, N], rows ldw floats apart); weights with the scales sk of their k.  *bad is set where a
-// bound is not finite or above 2^60: the float32 instruction then.
+// bound is out of range: the float32 instruction then.
 void launch_ln_scales(const float *g, const float *be, float *sk, int K, int32_t *bad, hipStream_t s);
 void launch_ln_projection_scales(const float *w, int ldw, const float *g, const float *be, const float *b, float *sk, int K, int N,
                                  int32_t *bad, hipStream_t s);

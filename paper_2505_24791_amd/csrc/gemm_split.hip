@@ -256,20 +256,19 @@ void pick_gs(const void *A, const void *Wt, const float *cs, const float *bias, 
 }
 
 // ---- preparation of the weights -------------------------------------------------------------------
-// The flow keeps to the float32 instruction above 2^60 (in scale_of); bounds below this share a scale, so that the product of two scales is a
-// float32 number
-constexpr int kMinExp = -40;
+// Bounds that a scale follows: of what a pass stores, so that the product of two scales and a weight by one are float32 numbers, and of a column of weights,
+// whose scale only the sums meet.  Outside, zero aside, the flow keeps to the float32 instruction: a scale that stayed behind would cost bits.
+constexpr float kLeastBound = 0x1p-40f, kLeastColumn = 0x1p-100f, kLargestBound = 0x1p60f;
 // Scale of a channel that is zero for every input (a zero bound), above all others: it may stand beside any other scale, and where scales are
 // compared such a channel has no say.
 constexpr float kDead = 0x1p56f;
 
-// 2^(15 - e) with bound < 2^e
-__device__ __forceinline__ float scale_of(float bound, int32_t *bad) {
-    if (!(bound <= 0x1p60f)) { *bad = 1; return 1.f; }
+// 2^(15 - e) with 2^(e-1) <= bound < 2^e
+__device__ __forceinline__ float scale_of(float bound, float least, int32_t *bad) {
     if (bound == 0.f) return kDead;
+    if (!(bound >= least && bound <= kLargestBound)) { *bad = 1; return 1.f; }
     int e;
     (void)frexpf(bound, &e);
-    if (e < kMinExp) e = kMinExp;
     return ldexpf(1.f, 15 - e);
 }
 
@@ -284,6 +283,7 @@ template <class F>
 __device__ __forceinline__ float over_k(int K, float (&part)[16][64], bool add, F f) {
     const int cl = threadIdx.x & 63, r = threadIdx.x >> 6;
     float v = 0.f;
+#pragma unroll 8
     for (int k = r; k < K; k += 16) { const float t = f(k); v = add ? v + t : fmaxf(v, t); }
     __syncthreads();
     part[r][cl] = v;
@@ -296,7 +296,7 @@ __device__ __forceinline__ float over_k(int K, float (&part)[16][64], bool add, 
 // sk of LayerNorm's output: |x^ g + be| <= sqrt(K) |g| + |be|
 __global__ void ln_scales_kernel(const float *__restrict__ g, const float *__restrict__ be, float *__restrict__ sk, int K, int32_t *bad) {
     const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k < K) sk[k] = scale_of(1.02f * (sqrtf((float)K) * fabsf(g[k]) + fabsf(be[k])), bad);
+    if (k < K) sk[k] = scale_of(1.02f * (sqrtf((float)K) * fabsf(g[k]) + fabsf(be[k])), kLeastBound, bad);
 }
 
 // sk of what a projection of LayerNorm's output gives: |sum x^ g w + sum be w + b|, and the squares of x^ add up to K at most
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(1024) void ln_projection_scales_kernel(const float 
     const int n = blockIdx.x * 64 + (threadIdx.x & 63), nc = n < N ? n : N - 1;
     const float q = over_k(K, part, true, [&](int k) { const float v = w[(size_t)k * ldw + nc], t = g[k] * v; return some(t * t, g[k], v); });
     const float d = over_k(K, part, true, [&](int k) { const float v = w[(size_t)k * ldw + nc]; return some(be[k] * v, be[k], v); });
-    if (threadIdx.x < 64 && n < N) sk[n] = scale_of(1.02f * (sqrtf((float)K * q) + d + fabsf(b[n])), bad);
+    if (threadIdx.x < 64 && n < N) sk[n] = scale_of(1.02f * (sqrtf((float)K * q) + d + fabsf(b[n])), kLeastBound, bad);
 }
 
 // A head's queries keep their scales; its keys get what makes the product of both the smallest that the 64 pairs of scales have.  A pair with a
@@ -327,10 +327,14 @@ __global__ __launch_bounds__(1024) void split_weights_kernel(const float *__rest
                                                              f16 *__restrict__ Wt, float *__restrict__ cs, int K, int N, int32_t *bad) {
     __shared__ float part[16][64];
     const int n = blockIdx.x * 64 + (threadIdx.x & 63), nc = n < N ? n : N - 1, r = threadIdx.x >> 6;
-    // rows that only ever meet zeros count as zeros (where 0 times the weight is zero)
-    auto value = [&](int k) { const float v = w[(size_t)k * ldw + nc]; return sk[k] == kDead && fabsf(v) <= 0x1p120f ? 0.f : v / sk[k]; };
-    float top = over_k(K, part, false, [&](int k) { const float t = fabsf(value(k)); return t <= 0x1p120f ? t : 0x1p120f; });
-    const float c = scale_of(top, bad);
+    // w / sk; a weight that only ever meets zeros counts as zero (where 0 times it is zero)
+    auto value = [&](int k) {
+        const float v = w[(size_t)k * ldw + nc], s = sk[k];
+        if (s == kDead) return fabsf(v) <= 0x1p120f ? 0.f : v;
+        return v * __uint_as_float(0x7F000000u - __float_as_uint(s));        // s is a power of two
+    };
+    const float top = over_k(K, part, false, [&](int k) { const float t = fabsf(value(k)); return t <= 0x1p120f ? t : 0x1p120f; });
+    const float c = scale_of(top, kLeastColumn, bad);
     if (n >= N) return;
     if (r == 0) cs[n] = 1.f / c;
     for (int k = 8 * r; k < K; k += 128) {

@@ -78,7 +78,7 @@ struct sjd_flow {
     void *arena_panel = nullptr; // QKV, attention-output and MLP-input matrices in the panel kernels' order
     void *arena_split = nullptr; // float32 matrices as sums of two halves, and their scales
     int32_t *split_bad = nullptr;
-    int split = 0;               // float32 passes on split operands: 0 not prepared, 1 yes, 2 no (a bound of the weights is not finite, no memory)
+    int split = 0;               // float32 passes on split operands: 0 not prepared, 1 yes, 2 no (a bound of the weights is out of range, no memory)
     int proj_path = 0;           // 0 automatic, 1 tile kernels only, 2 panel kernels wherever they apply
     bool stream_ok = false;      // the streaming MLP-output kernel reproduced the tile kernel's bits at load time
     std::vector<BlockW> block;
