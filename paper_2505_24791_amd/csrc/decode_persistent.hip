@@ -10,11 +10,11 @@
 // What bounds it is the latency of a link: what one member writes all others need next.  There is no barrier: a
 // buffer is filled with a word that no result has (kEmpty, a NaN pattern) before it is used, and a reader simply
 // loads its operands again until no word of them is empty.  Every 32-bit word is its own flag, so the order in
-// which words arrive does not matter.  A group of several XCDs stores and loads with the sc1 scope bit (agent scope), which is coherent
-// between XCDs: past the L2 of either side, to the memory behind it and back; a group of one XCD exchanges through its L2 (kLoadBits).  All-gather
-// of 2 to 64 KB, a round of a loop of nothing else: 2.2 to 2.8 us among 64 to 256 workgroups; among the 32 of one XCD 1.7 to 3.4 with the scope bit, 1.3
-// to 1.6 through the L2.  Microseconds a step, scope bit -> L2: width 256, 6 layers, 37 samples 77.7 -> 59.6; 4 layers, 128 samples 70.9 -> 45.6; width
-// 512, 4 layers, 128 samples 97.8 -> 80.2; width 768, 8 layers, 256 samples 421 -> 400.
+// which words arrive does not matter.  Loads carry the sc1 scope bit (agent scope).  So do the stores of a group of several XCDs, which is coherent
+// between XCDs: past the L2 of either side, to the memory behind it and back (an all-gather of 2 to 64 KB, a round of a loop of nothing else: 2.2 to 2.8 us
+// among 64 to 256 workgroups); a group of one XCD stores to its L2, and the loads find the words there (kStoreBits).  Microseconds a step of
+// one-XCD groups, stores of agent scope -> to the L2: width 256, 6 layers, 37 samples 77.5 -> 57.1; 4 layers, 128 samples 70.6 -> 44.6; width 512, 4 layers, 64 samples
+// 81.1 -> 67.6, 128 97.0 -> 84.8; width 768, 8 layers, 256 samples 422 -> 396; width 1024, 4 layers, 200 samples 260 -> 251.
 //
 // Life of a buffer.  Results rotate through three slots (the residual stream after the MLP and the embedding: four).
 // A member that has written slot q of a buffer empties what it had written in slot q-1 (stream: q-2), and every
@@ -51,19 +51,14 @@ typedef __amdgpu_buffer_rsrc_t rsrc_t;
 __device__ __forceinline__ rsrc_t make_rsrc(const void *p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
 }
-// Cache bits of the exchanged words (bit 1 nt, bit 4 sc1).  ONE: the group is one XCD and the words meet in its L2.  Plain stores go
-// through the vector cache to the L2.  A load with the nt bit misses the vector cache also where the line is there, and leaves no line behind (12.3
-// million loads of lines that the CU had loaded before another CU of the XCD stored to them: none stale after nt loads, nor with nt after plain
-// loads; plain and sc0 loads all stale), so each attempt of a wait reads the L2.  Else agent scope.
-template <bool ONE> constexpr int kLoadBits = ONE ? 2 : 16;
-template <bool ONE> constexpr int kStoreBits = ONE ? 0 : 16;
-template <bool ONE> __device__ __forceinline__ i32x4 ld16x(rsrc_t rs, uint32_t byte_off) {
-    return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, kLoadBits<ONE>));
-}
-// 16-byte loads of cached rows with the sc1 scope bit: never served by this CU's vector cache
+// 16-byte loads of exchanged words and of cached rows, at agent scope (bit 4, sc1): never served by this CU's vector cache, so each attempt of
+// a wait sees what the L2 has.
 __device__ __forceinline__ i32x4 ld16(rsrc_t rs, uint32_t byte_off) {
     return __builtin_bit_cast(i32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, 16));
 }
+// Stores of exchanged words.  ONE: the group is one XCD, all of whose CUs share an L2; the vector cache writes through to it, so a plain store
+// is there once it is acknowledged, and loads that pass by the vector cache find it (a wave's own would have to).  Else agent scope.
+template <bool ONE> constexpr int kStoreBits = ONE ? 0 : 16;
 // the same for rows of a key/value cache too large for the memory-side cache, with the streaming hint on top: a row is read once per
 // step and should not displace the weights, which every step reads again
 __device__ __forceinline__ i32x4 ld16_stream(rsrc_t rs, uint32_t byte_off) {
@@ -146,13 +141,13 @@ __device__ __forceinline__ Ctx local_ctx(const Ctx &c) {
 // Load N pieces of 16 bytes until no word of them is empty.  Afterwards everything this wave has stored or requested so
 // far is complete (the wait is free: the operands requested before the poll are needed next).  Reloading only the pieces that
 // were missing, or pausing between attempts, was slower or made no difference.
-template <bool ONE, int N, class OFF>
+template <int N, class OFF>
 __device__ __forceinline__ void poll16(const Ctx &c, rsrc_t rs, OFF off, i32x4 (&v)[N]) {
     int it = 0;
     while (true) {
         asm volatile("" ::: "memory");
 #pragma unroll
-        for (int u = 0; u < N; ++u) v[u] = ld16x<ONE>(rs, off(u));
+        for (int u = 0; u < N; ++u) v[u] = ld16(rs, off(u));
         uint32_t m = 0;
 #pragma unroll
         for (int u = 0; u < N; ++u)
@@ -230,7 +225,7 @@ __device__ __forceinline__ void ln_gemm_stage(const Ctx &c_in, rsrc_t ws, uint32
     fetch_bias(slot);
     __builtin_amdgcn_sched_barrier(0);
     i32x4 raw[MB * S * 2];
-    poll16<ONE>(c, ws, [&](int u) {
+    poll16(c, ws, [&](int u) {
         const int i = u / (2 * S), s = (u >> 1) % S;
         const uint32_t off = in_off + (uint32_t)((((c.rb0 + i) * KS + c.wave * S + s) * 64 + c.lane) * 8) * 4u + (u & 1) * 16u;
         return where(i * 16 + c.r < c.nrows, off);
@@ -360,7 +355,7 @@ __device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t ws, uin
     fetch(c.slot);
     __builtin_amdgcn_sched_barrier(0);
     i32x4 raw[MB * KSW + 1];                    // the activation, and the stream values of the first unit
-    poll16<ONE>(c, ws, [&](int u) {
+    poll16(c, ws, [&](int u) {
         if (u == MB * KSW) return where(finish, in_off + eo);
         const int i = u / KSW, k = u % KSW;
         const uint32_t off = a_off + (uint32_t)((((c.rb0 + i) * KSA + c.wave * KSW + k) * 64 + c.lane) * 8) * 2u;
@@ -371,7 +366,7 @@ __device__ __forceinline__ void gemm_resid_stage(const Ctx &c_in, rsrc_t ws, uin
         if (u != c.slot) {
             __syncthreads();                    // the previous unit's partial sums have been read
             fetch(u);
-            poll16<ONE>(c, ws, [&](int) { return where(finish, in_off + eo); }, rv);
+            poll16(c, ws, [&](int) { return where(finish, in_off + eo); }, rv);
         }
 #pragma unroll
         for (int i = 0; i < MB; ++i) {
@@ -493,7 +488,7 @@ __device__ __forceinline__ void attention_stage(const Ctx &c_in, rsrc_t ws, uint
         const int row = pi / H, h = pi - row * H;
         const int wsrow = c.rb0 * 16 + row;
         i32x4 fresh[3];
-        poll16<ONE>(c, ws, [&](int part) {
+        poll16(c, ws, [&](int part) {
             return where(valid, qkv_off + (uint32_t)frag_off(wsrow, part * W + h * 64 + dc * 8, KS3) * 2u);
         }, fresh);
         const v8 q8 = __builtin_bit_cast(v8, fresh[0]), kf = __builtin_bit_cast(v8, fresh[1]), vf = __builtin_bit_cast(v8, fresh[2]);
