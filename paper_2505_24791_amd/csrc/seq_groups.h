@@ -44,16 +44,18 @@ SJD_HOST_DEVICE inline SeqGroup seq_group_of(const int (&count)[8], int xcc, int
     return g;
 }
 
-// XCDs per group of the persistent kernel.  More of them spread a stage's weights over more CUs and read them from memory
-// fewer times, but only a group of one XCD exchanges through its L2 (0.8 us an exchange against 1.6 to 2), and a larger group has more
-// rows to pass round.  Microseconds a step with 8 / 4 / 2 / 1 XCDs per group: width 512, 4 layers, 256 tokens: one sample 55.8 / 55.9 / 56.4 / 57.9, 4
-// samples 59.7 / 57.4 / 57.3 / 58.3, 16 66.5 / 64.2 / 62.4 / 59.3, 64 - / - / 77.2 / 63.1; 8 layers, 1024 tokens, 64 samples - / - / 213 / 193; width 256, 6
-// layers, 37 samples - / - / 92 / 60; width 768, 8 layers, one sample 117 / 118 / 139 / 187, 32 samples - / 151 / 170 / 201; width 1024, 8 layers: 19 samples of 777
-// tokens - / 214 / 244 / 310, 32 of 1024 - / 255 / 287 / 352; 2 layers, one sample 37 / 40 / 45 / 67: from width 768 on one XCD takes longer to pull all
-// weights through its L2 than the exchanges of several cost.  A group holds at most sixteen samples (one row block of the matrix
+// XCDs per group of the persistent kernel on n_cus workgroups.  More of them spread a stage's weights over more CUs and read them from memory
+// fewer times, but only a group of one XCD exchanges through its L2 (0.4 to 1.2 us less an exchange), and a larger group has more
+// rows to pass round.  Microseconds a step with 8 / 4 / 2 / 1 XCDs per group: width 512, 4 layers, 256 tokens: one sample 55.6 / 55.6 / 56.2 / 54.5, 4
+// samples 59.4 / 57.6 / 57.2 / 56.1, 16 66.3 / 64.0 / 62.0 / 56.9, 64 - / - / 77.1 / 62.5; 8 layers: one sample 104 / 104 / 108 / 106, 5 118 / 111 / 114 / 108; 64 of 1024 tokens
+// - / - / 213 / 194; width 256, 6 layers, 37 samples - / - / 92 / 57; width 768, 8 layers, 200 tokens: one sample 119 / 119 / 140 / 179, 32 samples - / 144 / 167 / 192; width
+// 1024, 8 layers, 19 samples - / 177 / 206 / 270; 2 layers, one sample 37 / 40 / 45 / 63: from width 768 on one XCD takes longer to pull all
+// weights through its L2 than the exchanges of several cost.  So it does at width 512 where a CU mask leaves an XCD fewer CUs; 4 layers, 256 tokens, 2 / 1 XCDs
+// per group: 224 CUs, 5, 16, 64 samples 63.1 / 66.2, 65.7 / 66.5, 88.2 / 86.0; 192: 62.3 / 66.2, 63.7 / 66.5, 82.9 / 85.4; 128: 59.0 / 72.1, 59.4 / 73.6, 82.4 / 93.7; 64 CUs, 64
+// samples 120 / 156; width 256 on 128 CUs 75 / 60.  A group holds at most sixteen samples (one row block of the matrix
 // instruction) unless the batch leaves no choice.
-inline int seq_xcds_per_group(int W, int batch) {
-    int x = W <= 512 ? 1 : 4;
+inline int seq_xcds_per_group(int W, int batch, int n_cus = 256) {
+    int x = W <= 256 || (W <= 512 && n_cus >= 256) ? 1 : W <= 512 ? 2 : 4;
     if (batch <= 4 && W > 256) x = W <= 512 ? 4 : 8;
     while (x > 1 && (batch * x + 7) / 8 > 16) x /= 2;
     return x;

@@ -907,7 +907,7 @@ int run_sequential_persistent(sjd_flow *f, int j, const float *z, float *x, int 
     a.w_in = bw.w_in; a.b_in = bw.b_in; a.pos = bw.pos;
     a.z = z; a.x = x;
     a.ws = f->seq_ws;
-    a.xpg = seq_xcds_per_group(c.width, batch);
+    a.xpg = seq_xcds_per_group(c.width, batch, f->n_cus);
     a.kcache = f->kcache; a.vcache = f->vcache;
     a.kv_layer_stride = (size_t)c.max_batch * c.seq_len * c.width;
     a.B = batch; a.T = c.seq_len; a.D = c.token_dim; a.reversed = (c.reverse_mask >> j) & 1;

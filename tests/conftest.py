@@ -35,6 +35,7 @@ int duo(int M, int N, int K) { return sjd::gemm_duo_applicable(M, N, K); }
 int dma_before_ring(int M, int N, int gelu) { return sjd::gemm_dma_before_ring(M, N, gelu != 0); }
 long long fullest(int M, int N, int rows, int cols) { return sjd::tiles_of_fullest_xcd(M, N, rows, cols); }
 int xcds_per_group(int W, int batch) { return sjd::seq_xcds_per_group(W, batch); }
+int xcds_per_group_on(int W, int batch, int n_cus) { return sjd::seq_xcds_per_group(W, batch, n_cus); }
 int rows_ahead(int B, int heads, int width, int T, int n_cus, int xpg) { return sjd::seq_rows_ahead(B, heads, width, T, n_cus, xpg); }
 }
 """

@@ -59,6 +59,20 @@ def test_every_sample_has_a_group_on_any_set_of_xcds(tmp_path):
     assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout
 
 
+def test_xcds_of_a_group_where_an_xcd_has_fewer_cus(launch_rules):
+    """Width 512: all CUs of an XCD pull a step's weights through its L2 fast enough for a group of its own, half of them do not (64 samples on 128
+    CUs: 82.4 us a step with two XCDs a group, 93.7 with one)."""
+    on = launch_rules.xcds_per_group_on
+    for n in (64, 128, 224):
+        assert [on(512, b, n) for b in (1, 4, 5, 64, 65, 256)] == [4, 4, 2, 2, 1, 1]
+        assert [on(256, b, n) for b in (1, 256)] == [1, 1]
+        assert [on(768, b, n) for b in (4, 5, 32, 64, 65)] == [8, 4, 4, 2, 1]
+    for w in (256, 512, 768, 1024):
+        for b in range(1, 257):
+            assert on(w, b, 256) == launch_rules.xcds_per_group(w, b)
+    assert [on(512, b, 256) for b in (4, 5, 64)] == [4, 1, 1]
+
+
 def test_cached_rows_go_ahead_only_where_members_have_a_second_pair(launch_rules):
     """Requests between the stages cost every member; they pay where the busiest members have more than one pair (width 512, 32 samples of 256
     tokens, one pair each: 64.0 us a step without, 66.8 with; width 1024, 16 samples of 777 tokens: 188, 192)."""
