@@ -779,15 +779,14 @@ size_t seq_persistent_lds_bytes(int MB, int D) { return seq_lds_bytes(MB, D, MB 
 template <typename HT>
 static const void *pick_kernel(int MB, int S, int CB, bool ahead, bool one) {
 #define SJD_PK(MBv, Sv, CBv, AHv, ONEv) if (MB == MBv && S == Sv && CB == CBv && ahead == AHv && one == ONEv) return reinterpret_cast<const void *>(&seq_persistent_kernel<HT, MBv, Sv, CBv, AHv, ONEv>);
-    // one XCD per group: a member has two column blocks of the MLP input or more
+    // one XCD per group: a member has two column blocks of the MLP input or more; width 256 knows no other groups
 #define SJD_ONE(Sv) SJD_PK(1, Sv, 4, false, true) SJD_PK(2, Sv, 4, false, true)
 #define SJD_ANY(Sv) SJD_PK(1, Sv, 1, false, false) SJD_PK(1, Sv, 2, false, false) SJD_PK(1, Sv, 4, false, false)
     SJD_PK(1, 1, 2, false, true)
-    SJD_ONE(1) SJD_ONE(2) SJD_ONE(3) SJD_ONE(4) SJD_ANY(1) SJD_ANY(2) SJD_ANY(3) SJD_ANY(4)
+    SJD_ONE(1) SJD_ONE(2) SJD_ONE(3) SJD_ONE(4) SJD_ANY(2) SJD_ANY(3) SJD_ANY(4)
+    // cached rows ahead: a member has a second pair, so its group is no larger than that leaves it two column blocks (width 512: four)
     SJD_PK(1, 2, 4, true, true) SJD_PK(1, 3, 4, true, true) SJD_PK(1, 4, 4, true, true)
-    SJD_PK(1, 2, 1, true, false) SJD_PK(1, 2, 2, true, false) SJD_PK(1, 2, 4, true, false)
-    SJD_PK(1, 3, 1, true, false) SJD_PK(1, 3, 2, true, false) SJD_PK(1, 3, 4, true, false)
-    SJD_PK(1, 4, 1, true, false) SJD_PK(1, 4, 2, true, false) SJD_PK(1, 4, 4, true, false)
+    SJD_PK(1, 2, 4, true, false) SJD_PK(1, 3, 2, true, false) SJD_PK(1, 3, 4, true, false) SJD_PK(1, 4, 2, true, false) SJD_PK(1, 4, 4, true, false)
 #undef SJD_ANY
 #undef SJD_ONE
 #undef SJD_PK

@@ -58,3 +58,20 @@ def test_only_groups_of_one_xcd_store_to_their_own_l2(kernels):
         assert len(stores) >= 10, name
         assert all(("sc1" in a) != one for _, a in stores), name
     assert seen == {True, False}
+
+
+def test_every_launch_has_a_kernel_and_every_kernel_a_launch(kernels, launch_rules):
+    """The variants (row blocks, width / 256, column blocks a round, cached rows ahead, one XCD) that the launch rules ask for, on any number of
+    workgroups that can be set."""
+    asked = set()
+    for S in (1, 2, 3, 4):
+        for n_cus in range(32, 257, 32):
+            for batch in range(1, 257):
+                xpg = launch_rules.xcds_per_group_on(256 * S, batch, n_cus)
+                mb, per = 1 if batch <= 128 else 2, -(-64 * S // (n_cus // 8 * xpg))
+                cb = 4 if mb == 2 or per > 2 else 2 if xpg == 1 and per < 2 else per      # as in launch_seq_persistent
+                for tokens in (2, 256, 513, 600, 1024, 4096):
+                    asked.add((mb, S, cb, launch_rules.rows_ahead(batch, 4 * S, 256 * S, tokens, n_cus, xpg), int(xpg == 1)))
+    for mangled in ("DF16b", "DF16_"):
+        built = {tuple(map(int, re.search(r"Li(\d)ELi(\d)ELi(\d)ELb([01])ELb([01])EE", k).groups())) for k in kernels if mangled in k}
+        assert built == asked
