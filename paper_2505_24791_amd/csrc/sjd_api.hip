@@ -580,18 +580,18 @@ int check_opts(const sjd_jacobi_opts *o) {
 // newest iterate to x_ref into f->trace.
 // Float32 workspaces for refined passes of a 16-bit flow: about 8192 rows at a time.
 int ensure_refine_workspace(sjd_flow *f, hipStream_t s) {
-    if (f->split == 0) { const int rc = prepare_split(f, s); if (rc) return rc; }
-    if (f->r32_samples) return SJD_OK;
     const sjd_config &c = f->cfg;
-    int n = 8192 / c.seq_len;
-    n = n < 1 ? 1 : (n > c.max_batch ? c.max_batch : n);
-    const size_t M = (size_t)n * c.seq_len, W = c.width, R = c.mlp_ratio;
-    int rc;
-    if ((rc = dev_alloc(f, &f->r32_a, M * W * 4)) || (rc = dev_alloc(f, &f->r32_qkv, M * 3 * W * 4)) ||
-        (rc = dev_alloc(f, &f->r32_o, M * W * 4)) || (rc = dev_alloc(f, &f->r32_f, M * R * W * 4)))
-        return rc;
-    f->r32_samples = n;
-    return SJD_OK;
+    if (!f->r32_samples) {
+        int n = 8192 / c.seq_len;
+        n = n < 1 ? 1 : (n > c.max_batch ? c.max_batch : n);
+        const size_t M = (size_t)n * c.seq_len, W = c.width, R = c.mlp_ratio;
+        int rc;
+        if ((rc = dev_alloc(f, &f->r32_a, M * W * 4)) || (rc = dev_alloc(f, &f->r32_qkv, M * 3 * W * 4)) ||
+            (rc = dev_alloc(f, &f->r32_o, M * W * 4)) || (rc = dev_alloc(f, &f->r32_f, M * R * W * 4)))
+            return rc;
+        f->r32_samples = n;
+    }
+    return f->split == 0 ? prepare_split(f, s) : SJD_OK;    // last: it can do without its memory
 }
 
 // A whole-sequence conditioner pass of a 16-bit flow in float32 arithmetic: the float32 weights of the blob, the

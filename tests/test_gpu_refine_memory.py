@@ -1,0 +1,78 @@
+"""Refined passes of 16-bit flows where memory is short, and after the weights are loaded again.  Needs an MI355X."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+CFG = wl.FlowConfig("refined", n_blocks=2, n_layers=4, width=512, n_heads=8, seq_len=256, token_dim=6, batch=32, bf16=True)
+OPTS = dict(tau=1e-4, refine_below=1e-3)
+WORKSPACES = 8192 * 9 * CFG.width * 4                                                      # 32 samples, 9 rows of the width each
+SPLIT = CFG.n_blocks * CFG.n_layers * 12 * CFG.width ** 2 * 4                              # the float32 matrices once more
+
+
+@pytest.fixture
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the GPU"
+    return torch
+
+
+def _flow(seed):
+    import paper_2505_24791_amd as sjd
+    f = sjd.Flow(CFG)
+    f.load_weights(wl.make_weights(CFG, 1000 * seed, perturb_affine=True))
+    return f
+
+
+def _fill(torch, leave):
+    """Tensors that take the device's free memory but for `leave` bytes."""
+    torch.cuda.empty_cache()
+    held = []
+    while (spare := torch.cuda.mem_get_info()[0] - leave) >= 4 << 20:
+        held.append(torch.empty(min(spare, 16 << 30) >> 21 << 21, dtype=torch.uint8, device="cuda"))
+    return held
+
+
+def test_refined_passes_where_only_their_workspaces_fit(torch_cuda):
+    """Split operands are an option, the float32 workspaces are not: with room for the workspaces and not for both, the passes run on
+    the float32 instruction.  Two runs of the same passes in float32 arithmetic: as near as their thresholds (1e-4, mean) leave them."""
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    z = torch.from_numpy(wl.make_latent(CFG, seed=5)).cuda()
+    f = _flow(1)
+    ref, ref_it, _, _ = f.jacobi_inverse_block(1, z, sjd.JacobiOpts(**OPTS))
+    f.close()
+    f = _flow(1)
+    small = f.jacobi_inverse_block(1, z, sjd.JacobiOpts(tau=1e-2))[0]                      # kernels loaded, nothing refined
+    held = _fill(torch, WORKSPACES + SPLIT // 2)
+    free, before = torch.cuda.mem_get_info()[0], f.device_bytes
+    print(f"free {free >> 20} MiB, workspaces {WORKSPACES >> 20}, split weights {SPLIT >> 20}", flush=True)
+    assert max(WORKSPACES, SPLIT) < free < WORKSPACES + SPLIT
+    try:
+        x, it, _, _ = f.jacobi_inverse_block(1, z, sjd.JacobiOpts(**OPTS))
+        x = x.clone()
+        assert f.device_bytes - before == WORKSPACES
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    assert np.abs(it.astype(int) - ref_it.astype(int)).max() <= 1
+    assert (x - ref).abs().max().item() <= 3e-3
+    assert torch.equal(f.jacobi_inverse_block(1, z, sjd.JacobiOpts(tau=1e-2))[0], small)
+    f.close()
+
+
+def test_refined_passes_follow_weights_that_are_loaded_again(torch_cuda):
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    z = torch.from_numpy(wl.make_latent(CFG, seed=5)).cuda()
+    opts = sjd.JacobiOpts(**OPTS)
+    f, g = _flow(1), _flow(2)
+    first = f.jacobi_inverse_block(1, z, opts)[0]
+    held = f.device_bytes
+    f.load_weights(wl.make_weights(CFG, 2000, perturb_affine=True))
+    again = f.jacobi_inverse_block(1, z, opts)[0]
+    assert torch.equal(again, g.jacobi_inverse_block(1, z, opts)[0])
+    assert not torch.equal(again, first) and f.device_bytes == held
+    f.close()
+    g.close()
