@@ -123,7 +123,11 @@ size_t act_bytes(const sjd_flow *f) { return f->cfg.dtype == SJD_DTYPE_F32 ? 4 :
 int dev_alloc(sjd_flow *f, void **out, size_t nbytes) {
     if (nbytes == 0) nbytes = 256;
     hipError_t e = hipMalloc(out, nbytes);
-    if (e != hipSuccess) return fail(SJD_ENOMEM, "hipMalloc of %zu bytes failed: %s", nbytes, hipGetErrorString(e));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();       // reported here, not by the next call's launches
+        *out = nullptr;
+        return fail(SJD_ENOMEM, "hipMalloc of %zu bytes failed: %s", nbytes, hipGetErrorString(e));
+    }
     f->allocs.push_back(*out);
     f->bytes += nbytes;
     return SJD_OK;
@@ -585,9 +589,9 @@ int ensure_refine_workspace(sjd_flow *f, hipStream_t s) {
         int n = 8192 / c.seq_len;
         n = n < 1 ? 1 : (n > c.max_batch ? c.max_batch : n);
         const size_t M = (size_t)n * c.seq_len, W = c.width, R = c.mlp_ratio;
-        int rc;
-        if ((rc = dev_alloc(f, &f->r32_a, M * W * 4)) || (rc = dev_alloc(f, &f->r32_qkv, M * 3 * W * 4)) ||
-            (rc = dev_alloc(f, &f->r32_o, M * W * 4)) || (rc = dev_alloc(f, &f->r32_f, M * R * W * 4)))
+        int rc;      // what an earlier call got before its allocation failed stays
+        if ((!f->r32_a && (rc = dev_alloc(f, &f->r32_a, M * W * 4))) || (!f->r32_qkv && (rc = dev_alloc(f, &f->r32_qkv, M * 3 * W * 4))) ||
+            (!f->r32_o && (rc = dev_alloc(f, &f->r32_o, M * W * 4))) || (!f->r32_f && (rc = dev_alloc(f, &f->r32_f, M * R * W * 4))))
             return rc;
         f->r32_samples = n;
     }

@@ -62,6 +62,27 @@ def test_refined_passes_where_only_their_workspaces_fit(torch_cuda):
     f.close()
 
 
+def test_refused_for_memory_and_asked_again(torch_cuda):
+    import paper_2505_24791_amd as sjd
+    torch = torch_cuda
+    z = torch.from_numpy(wl.make_latent(CFG, seed=5)).cuda()
+    f = _flow(1)
+    small = f.jacobi_inverse_block(1, z, sjd.JacobiOpts(tau=1e-2))[0]
+    held = _fill(torch, WORKSPACES // 2)
+    try:
+        with pytest.raises(RuntimeError, match="hipMalloc"):
+            f.jacobi_inverse_block(1, z, sjd.JacobiOpts(**OPTS))
+        assert torch.equal(f.jacobi_inverse_block(1, z, sjd.JacobiOpts(tau=1e-2))[0], small)
+    finally:
+        del held
+        torch.cuda.empty_cache()
+    x = f.jacobi_inverse_block(1, z, sjd.JacobiOpts(**OPTS))[0]
+    f.close()
+    g = _flow(1)
+    assert torch.equal(g.jacobi_inverse_block(1, z, sjd.JacobiOpts(**OPTS))[0], x)
+    g.close()
+
+
 def test_refined_passes_follow_weights_that_are_loaded_again(torch_cuda):
     import paper_2505_24791_amd as sjd
     torch = torch_cuda
