@@ -219,7 +219,7 @@ def test_attention_input_off_16_byte_boundaries(torch_cuda, T):
 
 @pytest.mark.parametrize("M,N,K", [
     (1, 10, 64), (130, 200, 192), (2100, 960, 256),        # 64x64, four stages: fewer k-tiles than stages, an odd number, two tiles to a CU
-    (33, 64, 1024), (1217, 960, 2112),                     # 64x64, five stages, more tiles than CUs
+    (33, 64, 1024), (1217, 960, 2112),                     # 64x64, five stages, and with a few tiles more than CUs 128x64
     (1400, 768, 768), (1345, 1000, 576),                   # 128x64, four stages
     (5000, 520, 64), (2945, 770, 512),                     # 128x64, three stages
     (1500, 2300, 768), (1409, 2817, 1088),                 # 128x128, three stages
