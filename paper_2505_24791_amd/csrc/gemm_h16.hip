@@ -601,18 +601,22 @@ static void pick_tile(const HT *A, const HT *Bt, const float *bias, const float 
         // The smallest tile of which no CU has more than one: 64x64 with four stages of 16 KB, or five where they are at work for long enough (with a few
         // CUs that have two, us as 64x64 / 128x64: 566 x 1920 x 3840 28.8 / 22.6, 1014 x 1280 x 5120 35.5 / 28.8, 1142 x 1024 x 2048 15.8 / 13.6), 128x64 with four of
         // 24 KB, 128x128 with three of 32 KB, or four for long k; beyond one 128x128 tile to a CU two workgroups with two stages (us, register-staged
-        // 128x128 / this: 5372 x 3072 x 768 45 / 40, 2829 x 4608 x 1536 70 / 56, 5000 x 3072 x 1024 51 / 42).  A tile of half the size reads more of both operands and runs at a lower rate, but for short k,
+        // 128x128 / this: 5372 x 3072 x 768 45 / 40, 2829 x 4608 x 1536 70 / 56, 5000 x 3072 x 1024 51 / 42), or with three of 64x128 while no CU has more than two of
+        // those, where 128x128 would leave most CUs one tile and a few two (128x128 / this: 5429 x 768 x 3072 44.8 / 37.6, 3233 x 1280 x 1280 24.1 / 20.7, 1300 x 3072 x
+        // 1024 18.5 / 15.6), but not for a large weight that tiles of half the height read twice as often (1300 x 3072 x 3072 40.8 / 43.5, 1050 x 3840 x 3840 50.9 /
+        // 64.9).  A tile of half the size reads more of both operands and runs at a lower rate, but for short k,
         // where its fill is what counts.  us as 64x64 / 128x64 / 128x128, M x N x K, the weight from memory as a pass finds it: 256 x 512 x 2048 8.3 / 10.9 / 16.0;
         // 600 x 1024 x 4096 17.3 / 25.1 / 34.7; 1500 x 1024 x 1024 9.6 / 9.0 / 11.9; 3000 x 512 x 2048 14.4 / 12.7 / 17.3; 3000 x 1024
         // x 4096 46.8 / 39.4 / 34.5; 1500 x 2304 x 768 14.7 / 12.6 / 11.4; 8192 x 512 x 2048 33.1 / 27.0 / 24.0; 8192 x 1024 x 4096 118 / 91 / 76; short: 3000 x 768 x 256
         // 6.9 / 6.0 / 6.5, 8192 x 512 x 512 13.8 / 12.2 / 12.2.
-        const long t128x64 = (long)((M + 127) / 128) * ((N + 63) / 64);
+        const long t128x64 = (long)((M + 127) / 128) * ((N + 63) / 64), t64x128 = (long)((M + 63) / 64) * ((N + 127) / 128);
         if (t64 <= kCus && K >= 1024) return launch_ring<HT, 64, 64, 5, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
         if (t64 <= (K < 512 ? 2 : 1) * kCus) return launch_ring<HT, 64, 64, 4, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
         if (t128x64 <= kCus && K >= 512) return launch_ring<HT, 128, 64, 4, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
         if (t128x64 <= 2 * kCus && K <= 512) return launch_ring<HT, 128, 64, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
         if (t128 <= kCus && K >= 2048) return launch_ring<HT, 128, 128, 4, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
         if (t128 <= kCus) return launch_ring<HT, 128, 128, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
+        if (t64x128 <= 2 * kCus && (N <= 2560 || (N <= 4096 && (long)N * K <= 4l << 20))) return launch_ring<HT, 64, 128, 3, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
         if (t128 < 3584 && !(deep && dma_ok && gemm_dma_before_ring(M, N, EPI == EPI_BIAS_GELU)))
             return launch_ring<HT, 128, 128, 2, OutT, EPI>(A, Bt, bias, resid, C, M, N, K, s);
     }

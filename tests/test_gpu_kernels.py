@@ -225,6 +225,7 @@ def test_attention_input_off_16_byte_boundaries(torch_cuda, T):
     (1500, 2300, 768), (1409, 2817, 1088),                 # 128x128, three stages
     (2945, 770, 2048),                                     # 128x128, four stages
     (4576, 3072, 1024), (2829, 4600, 128),                 # 128x128, two stages, more than two tiles to a CU
+    (5429, 766, 128), (1050, 3800, 1024),                  # 64x128, three stages: one more row block of 128 than one a CU
     (8100, 1930, 3072),                                    # deep, a 256x256 tile for every CU
 ])
 @pytest.mark.parametrize("dtype_name", ["float16", "bfloat16"])
