@@ -18,9 +18,10 @@
  * key/value cache and all workspaces, sized at creation for max_batch.
  *
  * Streams.  `hip_stream` is a hipStream_t passed as void* (NULL = the default stream).  All work
- * is enqueued on it.  Calls that run Jacobi decoding read one integer per pass back to the host
- * (the number of samples still iterating) and therefore synchronise that stream; all calls
- * return with their outputs complete.  One handle must not be used from two threads at once.
+ * is enqueued on it.  Calls that run Jacobi decoding need a number per pass on the host (the samples
+ * still iterating): the calling thread waits for each pass, polling pinned memory for up to a
+ * millisecond (one core busy), then blocked on the stream.  All calls return with their outputs
+ * complete.  One handle must not be used from two threads at once.
  *
  * Errors.  Every int-returning call gives SJD_OK (0) or a negative code; nothing throws or aborts
  * across this boundary.  sjd_last_error() returns a thread-local description of the last failure.
@@ -47,7 +48,12 @@ extern "C" {
 
 #define SJD_MAX_BLOCKS 32
 
-#define SJD_DTYPE_F32 0  /* everything float32 (correctness configuration) */
+#define SJD_DTYPE_F32 0  /* float32 results: weights, state, residual stream and accumulators are float32.  In whole-sequence passes of
+                            more than a few rows (widths that are multiples of 32) the operands of a projection, and of the attention
+                            of head size 64, are sums of two IEEE halves with power-of-two scales from the weights: to 2^-23 of a
+                            value, 2^-40 of its bound for tiny ones.  Against 64 bits the results are no further off than float32
+                            products (0.6 to 0.85 of their 2-norm error).  The matrices in that form take as much device
+                            memory again as the float32 ones; without it, or with bounds outside 2^-40 .. 2^60, float32 products. */
 #define SJD_DTYPE_BF16 1 /* bf16 weights, matrix operands, stored activations and KV cache; float32 state
                             (x, mu, alpha), residual stream, LayerNorm statistics, softmax, accumulators, delta */
 #define SJD_DTYPE_F16 2  /* as SJD_DTYPE_BF16 but every 16-bit operand is IEEE half: three more mantissa bits
@@ -90,7 +96,8 @@ typedef struct {
                                1e-3 (bf16): with tau under that floor, set this a few times above it (1e-3 for half)
                                and the pass counts follow exact arithmetic again.  Per sample, so a sample's result
                                still does not depend on the batch.  The first use allocates float32 workspaces for
-                               about 8192 rows in the handle. */
+                               about 8192 rows in the handle, and what SJD_DTYPE_F32 says of its matrices, if there is
+                               room for them. */
 } sjd_jacobi_opts;
 
 typedef struct {

@@ -468,9 +468,9 @@ void conditioner_pass(sjd_flow *f, int j, const float *x, int n, const int32_t *
     }
     // Width 512: LayerNorm + QKV, the attention output and the MLP output on the activation-stationary kernels, a workgroup of which is 128 rows x 768..1024
     // columns of work: above 16384 rows (128 panels) their last round is nearly empty.  A pass of 4 layers, us, tile kernels / these: 8192 rows
-    // 490 / 511, 8448 579 / 538, 9984 598 / 567, 10240 601 / 571, 12288 692 / 636, 16384 797 / 737, 17408 861 / 942, 20480 931 / 1013.  The lower line was
-    // drawn while the MLP input was a panel launch as well; without it these kernels win from 8448 rows on.  The MLP input takes the panel kernel only
-    // where it is asked for (12288 rows 663 against 638 with gemm_duo.hip, 16384 rows 749 against 737).
+    // 468 / 484, 8448 527 / 513, 9984 547 / 539, 10240 550 / 542, 10496 571 / 630, 10752 576 / 638, 11008 599 / 564, 12288 627 / 593, 16384 729 / 710, 16896 794 / 898, 20480
+    // 883 / 963.  (The lower line could lie at 8448 rows; with 81 to 85 panels they lose.)  The MLP input takes the panel kernel only
+    // where it is asked for (12288 rows 627 against 590 with gemm_duo.hip, 16384 rows 714 against 708).
     const bool panel_any = f->arena_panel && f->proj_path != 1 && gemm_panel_applicable(M, RW, W, 2) &&
                            gemm_panel_applicable(M, 3 * W, W, 2) && gemm_panel_applicable(M, W, W, 4);
     const bool panel_one_round = M <= 16384;
@@ -598,8 +598,8 @@ int ensure_refine_workspace(sjd_flow *f, hipStream_t s) {
     return f->split == 0 ? prepare_split(f, s) : SJD_OK;    // last: it can do without its memory
 }
 
-// A whole-sequence conditioner pass of a 16-bit flow in float32 arithmetic: the float32 weights of the blob, the
-// float32 kernels, float32 activations in the refinement workspaces.  n <= f->r32_samples.
+// A whole-sequence conditioner pass of a 16-bit flow as a float32 flow does it: from the float32 weights of the blob, on split operands where
+// those are prepared, activations in the refinement workspaces.  n <= f->r32_samples.
 void conditioner_pass_f32(sjd_flow *f, int j, const float *x, int n, const int32_t *active, hipStream_t s) {
     const int dtype = f->cfg.dtype;
     void *a = f->a, *qkv = f->qkv, *o = f->o, *ff = f->f, *panel = f->arena_panel;

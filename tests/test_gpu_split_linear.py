@@ -134,6 +134,34 @@ def test_dead_channels_take_no_bits_from_the_others(orc64, dead, std, spread):
     f.close()
 
 
+@pytest.mark.parametrize("kept", [64, 8, 1])
+def test_scales_of_a_head_far_apart(orc64, kept):
+    """All but `kept` channels of a head have queries and keys of 2^-20 to 1 of the others', each by itself: a score is what the large ones make it, and
+    the common scale of the products must leave those their bits.  Bound as above."""
+    import torch
+    cfg = wl.FlowConfig("split", n_blocks=1, n_layers=1, width=256, n_heads=4, seq_len=100, token_dim=6, batch=9, bf16=False)
+    print(cfg, kept, flush=True)
+    W = cfg.width
+    blob = wl.make_weights(cfg, perturb_affine=True)
+    x = wl.make_latent(cfg, seed=47)
+    t = _tensors(cfg, blob)
+    rng = np.random.default_rng(13)
+    p = np.ldexp(np.float32(1), -rng.integers(0, 21, 2 * W)).astype(np.float32)
+    large = np.concatenate([h * 64 + rng.choice(64, kept, replace=False) for h in range(4)])
+    p[large], p[W + large] = 8, 2
+    t["l0.w_qkv"][:, :2 * W] *= p
+    t["l0.b_qkv"][:2 * W] *= p
+    t["l0.w_o"][...] *= np.float32(50)
+    f = _flow(cfg, blob)
+    mu, al = f.conditioner(0, torch.from_numpy(x).cuda())
+    for b in (0, 8):
+        for got, ref in zip((mu, al), orc64.cond(cfg, blob, 0, x[b])):
+            err = np.linalg.norm(got[b].cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+            print(f"{err:.1e}", flush=True)
+            assert err <= 4e-6
+    f.close()
+
+
 def _out_of_range(kind, t, W):
     """Weights with a bound outside 2^-40 .. 2^60 on which split operands would go wrong."""
     if kind == "tiny value":      # a value column far below the others that the output projection brings back: its scale would leave it a few bits
