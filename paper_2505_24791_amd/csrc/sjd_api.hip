@@ -1,6 +1,6 @@
 // Host side of the library: the handle, weight loading, and the entry points declared in sjd.h.
 // Every arithmetic step runs in the HIP kernels of this directory; the host only sequences
-// launches and reads one integer per Jacobi pass (the number of samples still iterating).
+// launches and waits for one word per Jacobi pass (how many samples still iterate).
 #include "../../include/sjd.h"
 
 #include <math.h>

@@ -1,7 +1,7 @@
 """Two batches in flight on one GPU: the sequential block of batch i+1 beside the Jacobi blocks of batch i.
 
 The sequential inverse of the first block is a chain of T-1 dependent steps whose time is set by
-latencies, not by the number of CUs it runs on (configuration C2: 21.4 ms on 256 CUs, 22.2 ms on
+latencies more than by the number of CUs it runs on (configuration C2: 17.2 ms on 256 CUs, 21.0 ms on
 128); the Jacobi blocks are throughput work.  Run one after the other, each leaves most of the chip
 idle or waiting for half of the time.  Here the two kinds of work run on two streams restricted to
 disjoint sets of CUs (a CU mask with the same number of CUs on every XCD), on two flows that hold
